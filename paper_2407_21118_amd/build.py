@@ -29,7 +29,8 @@ BUILD_DIR = os.path.join(HERE, "_build")
 
 def sources():
     """(source file, extra flags) of every translation unit."""
-    return [(os.path.join(CSRC, "api.hip"), VGPR_FORM), (os.path.join(CSRC, "encode_gemm.hip"), [])]
+    vgpr = ["score_forms.hip", "score_forms_lowbit.hip", "score16_forms.hip", "score16_shared_forms.hip", "pv.hip", "api.hip"]
+    return [(os.path.join(CSRC, f), VGPR_FORM) for f in vgpr] + [(os.path.join(CSRC, "encode_gemm.hip"), [])]
 
 
 def _run(procs, verbose):

@@ -2,12 +2,12 @@
 // launch geometry, workspace carving.  No device memory is allocated here.
 
 #include "encode_quant.hip"
+#include "launch.h"
 #include "rope_fold.hip"
 #include "score.hip"
 #include "score16.hip"
 #include "score8.hip"
 #include "combine.hip"
-#include "pv.hip"
 #include "qk.hip"
 #include "probe.hip"
 
@@ -429,161 +429,12 @@ int allow_lds(K kernel, size_t bytes) {
                              (int)bytes) == hipSuccess ? PALU_OK : PALU_ERR_HIP;
 }
 
-using ScoreFn = void (*)(ScoreArgs);
-// waves8: four heads as 8 half-head wavefronts (two per SIMD) instead of 4 whole-head ones.
-template <typename T, bool I4, int NKS>
-ScoreFn score_fn_g(int lg, bool waves8) {
-  if constexpr (NKS > 16) {
-    return score_kernel<T, NKS, 2, 1, 4, I4>;
-  } else {
-    if (waves8) {
-      if constexpr (NKS <= 8) { if (lg == 2) return score_kernel<T, NKS, 2, 4, 8, I4>; }
-      if (lg == 1) return score_kernel<T, NKS, 2, 2, 8, I4>;
-      return score_kernel<T, NKS, 2, 1, 8, I4>;
-    }
-    if constexpr (NKS <= 8) { if (lg == 2) return score_kernel<T, NKS, 4, 4, 4, I4>; }
-    if (lg == 1) return score_kernel<T, NKS, 4, 2, 4, I4>;
-    return score_kernel<T, NKS, 4, 1, 4, I4>;
-  }
-}
-template <typename T, bool I4>
-ScoreFn score_fn_t(int rc, int lg, bool w8) {
-  switch (rc) {
-    case 0: return score_fn_g<T, I4, 2>(lg, w8);
-    case 1: return score_fn_g<T, I4, 4>(lg, w8);
-    case 2: return score_fn_g<T, I4, 6>(lg, w8);
-    case 3: return score_fn_g<T, I4, 8>(lg, w8);
-    case 4: return score_fn_g<T, I4, 10>(lg, w8);
-    case 5: return score_fn_g<T, I4, 12>(lg, w8);
-    case 6: return score_fn_g<T, I4, 14>(lg, w8);
-    case 7: return score_fn_g<T, I4, 16>(lg, w8);
-    case 8: return score_fn_g<T, I4, 18>(lg, w8);
-    case 9: return score_fn_g<T, I4, 20>(lg, w8);
-    case 10: return score_fn_g<T, I4, 22>(lg, w8);
-    case 11: return score_fn_g<T, I4, 24>(lg, w8);
-    case 12: return score_fn_g<T, I4, 26>(lg, w8);
-    case 13: return score_fn_g<T, I4, 28>(lg, w8);
-    case 14: return score_fn_g<T, I4, 30>(lg, w8);
-    default: return score_fn_g<T, I4, 32>(lg, w8);
-  }
-}
-ScoreFn score_fn(int act, bool i4, int cls_id, bool w8) {
-  const int rc = cls_id / 3, lg = cls_id % 3;
-  if (i4) return score_fn_t<F16, true>(rc, lg, w8);
-  return act == PALU_F16 ? score_fn_t<F16, false>(rc, lg, w8) : score_fn_t<BF16, false>(rc, lg, w8);
-}
-
-// unquantized latents, ranks 64 .. 256, one query per head: one whole head per wavefront (score16.hip)
-template <typename T, int NK>
-ScoreFn score16_fn_g(int lg) {
-  if constexpr (NK <= 2) { if (lg == 2) return score16_kernel<T, NK, 4>; }
-  if constexpr (NK <= 4) { if (lg >= 1) return score16_kernel<T, NK, 2>; }
-  return score16_kernel<T, NK, 1>;
-}
-template <int NK>
-ScoreFn score8_fn_g(int lg) {
-  if constexpr (NK <= 2) { if (lg == 2) return score8_kernel<NK, 4>; }
-  if constexpr (NK <= 4) { if (lg >= 1) return score8_kernel<NK, 2>; }
-  return score8_kernel<NK, 1>;
-}
-ScoreFn score8_fn(int rc, int lg) {
-  switch (rc) {
-    case 1: return score8_fn_g<2>(lg);
-    case 2: return score8_fn_g<3>(lg);
-    case 3: return score8_fn_g<4>(lg);
-    case 4: return score8_fn_g<5>(lg);
-    case 5: return score8_fn_g<6>(lg);
-    case 6: return score8_fn_g<7>(lg);
-    default: return score8_fn_g<8>(lg);
-  }
-}
-template <typename T>
-ScoreFn score16_fn_t(int rc, int lg) {
-  switch (rc) {
-    case 1: return score16_fn_g<T, 2>(lg);
-    case 2: return score16_fn_g<T, 3>(lg);
-    case 3: return score16_fn_g<T, 4>(lg);
-    case 4: return score16_fn_g<T, 5>(lg);
-    case 5: return score16_fn_g<T, 6>(lg);
-    case 6: return score16_fn_g<T, 7>(lg);
-    default: return score16_fn_g<T, 8>(lg);
-  }
-}
 inline bool rank_class_16(int rc) { return rc >= 1 && rc <= 7; }
 // ... and several queries per key/value head: the key rebuilt once per key/value head and pass of up to 8 query
 // rows (ranks 192 .. 256) or 4 (ranks 64 .. 160); the kernel is compiled for 2, 4 and 8 rows
 inline bool shared16_ok(int rc) { return rc >= 1 && rc <= 7; }
 inline int shared16_rows_per_pass(int rc) { return rc >= 5 ? 8 : 4; }
-template <typename T, int NK>
-ScoreFn score16q_fn_n(int nq) {
-  if (nq <= 2) return score16_kernel<T, NK, 1, 2>;
-  if (nq <= 4) return score16_kernel<T, NK, 1, 4>;
-  if constexpr (NK >= 6) { if (nq <= 8) return score16_kernel<T, NK, 1, 8>; }
-  return nullptr;
-}
-// 4-bit key latents (ranks 128 and 256: whole quantization blocks) with several queries per key/value head
-ScoreFn score16q4_fn(int rc, int nq) {
-  if (rc == 3) return nq <= 2 ? score16_kernel<F16, 4, 1, 2, 4> : (nq <= 4 ? score16_kernel<F16, 4, 1, 4, 4> : nullptr);
-  if (rc == 7) return nq <= 2 ? score16_kernel<F16, 8, 1, 2, 4> : (nq <= 4 ? score16_kernel<F16, 8, 1, 4, 4> : score16_kernel<F16, 8, 1, 8, 4>);
-  return nullptr;
-}
 constexpr int score16q4_lds_bytes(int width) { return 3 * score_tile_bytes(width) + 3 * kRopeTileBytes; }
-template <typename T>
-ScoreFn score16q_fn_t(int rc, int nq) {
-  switch (rc) {
-    case 1: return score16q_fn_n<T, 2>(nq);
-    case 2: return score16q_fn_n<T, 3>(nq);
-    case 3: return score16q_fn_n<T, 4>(nq);
-    case 4: return score16q_fn_n<T, 5>(nq);
-    case 5: return score16q_fn_n<T, 6>(nq);
-    case 6: return score16q_fn_n<T, 7>(nq);
-    case 7: return score16q_fn_n<T, 8>(nq);
-    default: return nullptr;
-  }
-}
-
-// 3- and 2-bit key latents: one group per workgroup, 8 wavefronts up to rank 256, 4 half-head wavefronts above
-template <int NKS>
-ScoreFn score_fn_lowbit_n() {
-  if constexpr (NKS > 16) return score_kernel<F16, NKS, 2, 1, 4, true, 0, true>;
-  else return score_kernel<F16, NKS, 2, 1, 8, true, 0, true>;
-}
-ScoreFn score_fn_lowbit(int rc) {
-  switch (rc) {
-    case 0: return score_fn_lowbit_n<2>();
-    case 1: return score_fn_lowbit_n<4>();
-    case 2: return score_fn_lowbit_n<6>();
-    case 3: return score_fn_lowbit_n<8>();
-    case 4: return score_fn_lowbit_n<10>();
-    case 5: return score_fn_lowbit_n<12>();
-    case 6: return score_fn_lowbit_n<14>();
-    case 7: return score_fn_lowbit_n<16>();
-    case 8: return score_fn_lowbit_n<18>();
-    case 9: return score_fn_lowbit_n<20>();
-    case 10: return score_fn_lowbit_n<22>();
-    case 11: return score_fn_lowbit_n<24>();
-    case 12: return score_fn_lowbit_n<26>();
-    case 13: return score_fn_lowbit_n<28>();
-    case 14: return score_fn_lowbit_n<30>();
-    default: return score_fn_lowbit_n<32>();
-  }
-}
-
-// shared-key form (several queries per key/value head): fp16 latents, ranks up to 256, 8 wavefronts, up to 16 queries
-// QP = 1: at most 4 queries per key/value head, QP = 2: at most 16
-template <int QP>
-ScoreFn score_fn_shared(int rc) {
-  switch (rc) {
-    case 0: return score_kernel<F16, 2, 2, 1, 8, false, QP>;
-    case 1: return score_kernel<F16, 4, 2, 1, 8, false, QP>;
-    case 2: return score_kernel<F16, 6, 2, 1, 8, false, QP>;
-    case 3: return score_kernel<F16, 8, 2, 1, 8, false, QP>;
-    case 4: return score_kernel<F16, 10, 2, 1, 8, false, QP>;
-    case 5: return score_kernel<F16, 12, 2, 1, 8, false, QP>;
-    case 6: return score_kernel<F16, 14, 2, 1, 8, false, QP>;
-    default: return score_kernel<F16, 16, 2, 1, 8, false, QP>;
-  }
-}
 
 // The same layer with one (virtual) query head per key/value head: the units of the shared-key score form.
 Meta kv_head_meta(const Meta& m) {
@@ -603,28 +454,6 @@ Meta kv_head_meta(const Meta& m) {
       for (int h = k.head_off[j]; h < m.head_off[j + 1] / m.qpk; ++h) k.group_of_head[h] = (uint8_t)j;
   }
   return k;
-}
-
-using PvFn = void (*)(PvArgs);
-template <typename T, int QB, bool TWO>
-PvFn pv_fn_t(int cls) {
-  switch (cls) {
-    case 0: return pv_kernel<T, 2, 1, QB, TWO>;
-    case 1: return pv_kernel<T, 2, 2, QB, TWO>;
-    case 2: return pv_kernel<T, 8, 1, QB, TWO>;
-    default: return pv_kernel<T, 8, 2, QB, TWO>;
-  }
-}
-template <bool TWO>
-PvFn pv_fn_p(int act, int bits, int cls) {
-  if (bits == 4) return pv_fn_t<F16, 4, TWO>(cls);
-  if (bits == 3) return pv_fn_t<F16, 3, TWO>(cls);
-  if (bits == 2) return pv_fn_t<F16, 2, TWO>(cls);
-  return act == PALU_F16 ? pv_fn_t<F16, 0, TWO>(cls) : pv_fn_t<BF16, 0, TWO>(cls);
-}
-// bits: 4, 3 or 2 for quantized value latents, else 0; two_planes: some head's scores lie in two planes
-PvFn pv_fn(int act, int bits, int cls, bool two_planes) {
-  return two_planes ? pv_fn_p<true>(act, bits, cls) : pv_fn_p<false>(act, bits, cls);
 }
 
 // First launch of a fused decode step: the split-K partial products of the new token's down-projection
@@ -1434,8 +1263,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       f8.w8 = ws + w.w8;
       f8.scale = reinterpret_cast<float*>(ws + w.w_scale);
       f8.meta = m;
-      hipLaunchKernelGGL(fold8_kernel<F16>, dim3((unsigned)m.n_heads, 4u), dim3(256), 0, s, f8);
-      if ((st = launch_ok()) != PALU_OK) return st;
+      if ((st = launch_fold8(f8, s)) != PALU_OK) return st;
     }
 
     // 2. scores
@@ -1578,7 +1406,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           lds = std::max(lds, (size_t)score16_lds_bytes(32 * nk));
         }
         if (first >= (1LL << 31)) return PALU_ERR_UNSUPPORTED;
-        ScoreFn fn = act == PALU_F16 ? score16_mixed_kernel<F16> : score16_mixed_kernel<BF16>;
+        ScoreFn fn = score16_mixed_fn(act);
         if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
         a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
         hipLaunchKernelGGL(fn, dim3((unsigned)first), dim3(256), lds, s, a);
@@ -1593,9 +1421,9 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         const bool pingpong = (waves8 && !rank_class_half(rc)) || shared_key;
         size_t lds = (size_t)score_lds_bytes(width, dma, !shared_key, pingpong);
         const bool k16 = use16 && rank_class_16(rc);
-        ScoreFn fn = shared_key ? (m.qpk <= 4 ? score_fn_shared<1>(rc) : score_fn_shared<2>(rc))
+        ScoreFn fn = shared_key ? score_fn_shared(rc, m.qpk <= 4)
                    : shared16 ? nullptr            // chosen per pass below
-                   : k16 ? (act == PALU_F16 ? score16_fn_t<F16>(rc, lg) : score16_fn_t<BF16>(rc, lg))
+                   : k16 ? score16_fn(act, rc, lg)
                    : (k_lowbit ? score_fn_lowbit(rc) : score_fn(act, k_i4, rc * 3 + lg, waves8));
         if (k16) lds = (size_t)score16_lds_bytes(width);
         if (shared16 || shared4) {
@@ -1604,8 +1432,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           // launch per flush of units (the key tile is rebuilt once per pass)
           for (int row0 = 0; row0 < m.qpk; row0 += sk_pass_rows) {
             const int rows = std::min(sk_pass_rows, m.qpk - row0);
-            fn = shared4 ? score16q4_fn(rc, rows)
-                         : (act == PALU_F16 ? score16q_fn_t<F16>(rc, rows) : score16q_fn_t<BF16>(rc, rows));
+            fn = shared4 ? score16q4_fn(rc, rows) : score16q_fn(act, rc, rows);
             if (!fn) return PALU_ERR_UNSUPPORTED;
             if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
             a.sk_row0 = row0;
@@ -1680,9 +1507,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       ps.seq_len = seq_len;
       ps.n_heads = m.n_heads;
       std::memcpy(ps.n_parts, n_parts, sizeof(n_parts));
-      hipLaunchKernelGGL(plane_sum_kernel, dim3((unsigned)ceil_div(seq_len, 256), (unsigned)m.n_heads, (unsigned)batch),
-                         dim3(256), 0, s, ps);
-      if ((st = launch_ok()) != PALU_OK) return st;
+      if ((st = launch_plane_sum(ps, batch, s)) != PALU_OK) return st;
     }
     PvArgs a;
     a.hv = hv;

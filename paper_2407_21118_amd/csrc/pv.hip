@@ -29,60 +29,13 @@
 // exceeds it by more than 8 (scores are base-2 logarithms), so probabilities reach 256 at most; the (max, sum)
 // pair a split reports is consistent with its accumulators, which is all the combination needs.
 
-#include "palu_dev.h"
+#include "launch.h"
 
 #ifndef PALU_PV_PAIR_DEPTH
 #define PALU_PV_PAIR_DEPTH 2
 #endif
 
 namespace palu {
-
-struct PvUnit {
-  int32_t c0;         // first column of the value-latent row
-  uint16_t h0;        // first head
-  uint16_t ncols;     // columns (multiple of 32, at most 128 * NG)
-  uint8_t nh;         // heads (at most 16 in the built forms); a head only keeps the columns of its own group
-  uint8_t write_ml;   // this unit stores the (max, sum) pair of its heads
-};
-constexpr int kMaxPvUnits = 128;
-struct PvUnits {
-  int n_units;
-  PvUnit u[kMaxPvUnits];
-};
-
-struct PvArgs {
-  const void* hv;
-  const uint16_t* hv_scale;
-  const uint16_t* hv_zero;
-  const float* scores;       // [parts][batch][n_heads][lpad]; planes 0 and 1 are read
-  const int32_t* seq_lens;
-  const int32_t* q_len;      // several queries per sequence: rows attended by query j of sequence b at [b * nq + j]; or NULL
-  float* o_part;             // [batch][n_split][o_stride]
-  float* ml_part;            // [batch][n_split][n_heads][2]
-  long long row_elems;       // R_v
-  long long max_seq;
-  long long part_stride;
-  int seq_len;
-  int lpad;
-  int batch;
-  int split_tokens;          // tokens per wavefront (multiple of 32)
-  int n_split;
-  int o_stride;
-  int n_blocks_q;
-  int units_per_wg;          // 1, 2 or 4: the wavefronts of a workgroup take this many units of the same splits
-  uint8_t n_parts[PALU_MAX_HEADS];   // 1 or 2 score planes per head
-  Meta meta;
-  PvUnits units;
-};
-
-struct PlaneSumArgs {
-  float* scores;
-  long long part_stride;
-  int lpad;
-  int seq_len;
-  int n_heads;
-  uint8_t n_parts[PALU_MAX_HEADS];
-};
 
 // scores[0] += scores[1] + ... + scores[n_parts-1] for heads with more than two
 // partial planes (ranks contracted in slices); the value kernel then reads one.
@@ -509,16 +462,33 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
   }
 }
 
-#define PALU_PV_INST2(T, I4, TWO)                                      \
-  template __global__ void pv_kernel<T, 2, 1, I4, TWO>(PvArgs);         \
-  template __global__ void pv_kernel<T, 2, 2, I4, TWO>(PvArgs);         \
-  template __global__ void pv_kernel<T, 8, 1, I4, TWO>(PvArgs);         \
-  template __global__ void pv_kernel<T, 8, 2, I4, TWO>(PvArgs);
-#define PALU_PV_INST(T, I4) PALU_PV_INST2(T, I4, true) PALU_PV_INST2(T, I4, false)
-PALU_PV_INST(F16, 0)
-PALU_PV_INST(BF16, 0)
-PALU_PV_INST(F16, 4)
-PALU_PV_INST(F16, 3)
-PALU_PV_INST(F16, 2)
+namespace {
+
+template <typename T, int QB, bool TWO>
+PvFn pv_fn_t(int cls) {
+  switch (cls) {
+    case 0: return pv_kernel<T, 2, 1, QB, TWO>;
+    case 1: return pv_kernel<T, 2, 2, QB, TWO>;
+    case 2: return pv_kernel<T, 8, 1, QB, TWO>;
+    default: return pv_kernel<T, 8, 2, QB, TWO>;
+  }
+}
+template <bool TWO>
+PvFn pv_fn_p(int act, int bits, int cls) {
+  if (bits == 4) return pv_fn_t<F16, 4, TWO>(cls);
+  if (bits == 3) return pv_fn_t<F16, 3, TWO>(cls);
+  if (bits == 2) return pv_fn_t<F16, 2, TWO>(cls);
+  return act == PALU_F16 ? pv_fn_t<F16, 0, TWO>(cls) : pv_fn_t<BF16, 0, TWO>(cls);
+}
+}  // namespace
+
+PvFn pv_fn(int act, int bits, int cls, bool two_planes) {
+  return two_planes ? pv_fn_p<true>(act, bits, cls) : pv_fn_p<false>(act, bits, cls);
+}
+
+int launch_plane_sum(const PlaneSumArgs& a, int batch, hipStream_t s) {
+  hipLaunchKernelGGL(plane_sum_kernel, dim3((unsigned)((a.seq_len + 255) / 256), (unsigned)a.n_heads, (unsigned)batch), dim3(256), 0, s, a);
+  return hipGetLastError() == hipSuccess ? PALU_OK : PALU_ERR_HIP;
+}
 
 }  // namespace palu

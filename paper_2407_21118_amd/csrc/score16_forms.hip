@@ -1,0 +1,59 @@
+// Instantiations of the whole-head score kernel (score16.hip), one query per head, and of its 8-bit variant.
+#include "launch.h"
+#include "score16.hip"
+#include "score8.hip"
+
+namespace palu {
+
+namespace {
+
+// unquantized latents, ranks 64 .. 256, one query per head: one whole head per wavefront (score16.hip)
+template <typename T, int NK>
+ScoreFn score16_fn_g(int lg) {
+  if constexpr (NK <= 2) { if (lg == 2) return score16_kernel<T, NK, 4>; }
+  if constexpr (NK <= 4) { if (lg >= 1) return score16_kernel<T, NK, 2>; }
+  return score16_kernel<T, NK, 1>;
+}
+template <typename T>
+ScoreFn score16_fn_t(int rc, int lg) {
+  switch (rc) {
+    case 1: return score16_fn_g<T, 2>(lg);
+    case 2: return score16_fn_g<T, 3>(lg);
+    case 3: return score16_fn_g<T, 4>(lg);
+    case 4: return score16_fn_g<T, 5>(lg);
+    case 5: return score16_fn_g<T, 6>(lg);
+    case 6: return score16_fn_g<T, 7>(lg);
+    default: return score16_fn_g<T, 8>(lg);
+  }
+}
+template <int NK>
+ScoreFn score8_fn_g(int lg) {
+  if constexpr (NK <= 2) { if (lg == 2) return score8_kernel<NK, 4>; }
+  if constexpr (NK <= 4) { if (lg >= 1) return score8_kernel<NK, 2>; }
+  return score8_kernel<NK, 1>;
+}
+}  // namespace
+
+ScoreFn score8_fn(int rc, int lg) {
+  switch (rc) {
+    case 1: return score8_fn_g<2>(lg);
+    case 2: return score8_fn_g<3>(lg);
+    case 3: return score8_fn_g<4>(lg);
+    case 4: return score8_fn_g<5>(lg);
+    case 5: return score8_fn_g<6>(lg);
+    case 6: return score8_fn_g<7>(lg);
+    default: return score8_fn_g<8>(lg);
+  }
+}
+
+ScoreFn score16_fn(int act, int rc, int lg) {
+  return act == PALU_F16 ? score16_fn_t<F16>(rc, lg) : score16_fn_t<BF16>(rc, lg);
+}
+ScoreFn score16_mixed_fn(int act) { return act == PALU_F16 ? score16_mixed_kernel<F16> : score16_mixed_kernel<BF16>; }
+
+int launch_fold8(const Fold8Args& a, hipStream_t s) {
+  hipLaunchKernelGGL(fold8_kernel<F16>, dim3((unsigned)a.meta.n_heads, 4u), dim3(256), 0, s, a);
+  return hipGetLastError() == hipSuccess ? PALU_OK : PALU_ERR_HIP;
+}
+
+}  // namespace palu

@@ -1,0 +1,42 @@
+// Instantiations of the whole-head score kernel (score16.hip) for several queries per key/value head.
+#include "launch.h"
+#include "score16.hip"
+
+namespace palu {
+
+namespace {
+
+template <typename T, int NK>
+ScoreFn score16q_fn_n(int nq) {
+  if (nq <= 2) return score16_kernel<T, NK, 1, 2>;
+  if (nq <= 4) return score16_kernel<T, NK, 1, 4>;
+  if constexpr (NK >= 6) { if (nq <= 8) return score16_kernel<T, NK, 1, 8>; }
+  return nullptr;
+}
+template <typename T>
+ScoreFn score16q_fn_t(int rc, int nq) {
+  switch (rc) {
+    case 1: return score16q_fn_n<T, 2>(nq);
+    case 2: return score16q_fn_n<T, 3>(nq);
+    case 3: return score16q_fn_n<T, 4>(nq);
+    case 4: return score16q_fn_n<T, 5>(nq);
+    case 5: return score16q_fn_n<T, 6>(nq);
+    case 6: return score16q_fn_n<T, 7>(nq);
+    case 7: return score16q_fn_n<T, 8>(nq);
+    default: return nullptr;
+  }
+}
+
+}  // namespace
+
+ScoreFn score16q_fn(int act, int rc, int nq) {
+  return act == PALU_F16 ? score16q_fn_t<F16>(rc, nq) : score16q_fn_t<BF16>(rc, nq);
+}
+// 4-bit key latents (ranks 128 and 256: whole quantization blocks) with several queries per key/value head
+ScoreFn score16q4_fn(int rc, int nq) {
+  if (rc == 3) return nq <= 2 ? score16_kernel<F16, 4, 1, 2, 4> : (nq <= 4 ? score16_kernel<F16, 4, 1, 4, 4> : nullptr);
+  if (rc == 7) return nq <= 2 ? score16_kernel<F16, 8, 1, 2, 4> : (nq <= 4 ? score16_kernel<F16, 8, 1, 4, 4> : score16_kernel<F16, 8, 1, 8, 4>);
+  return nullptr;
+}
+
+}  // namespace palu

@@ -14,21 +14,16 @@
 // sub-tile's vector work between the matrix instructions); the latent tile goes through registers (it is
 // converted on the way), the angle tiles stay LDS-direct.
 
+#pragma once
 #include <type_traits>
 
+#include "launch.h"
 #include "score16.hip"
 
 namespace palu {
 
 // ---- B_k -> E4M3 in operand order, and its column scales ----------------------------------------
 typedef int int8v __attribute__((ext_vector_type(8)));
-
-struct Fold8Args {
-  const uint16_t* Bk;
-  unsigned char* w8;         // per head r * 128 bytes at byte offset (bk_off[group] + head in group * r * 128)
-  float* scale;              // [n_heads][128]
-  Meta meta;
-};
 
 // two floats -> two E4M3 bytes in the low half of the result (round to nearest even; inputs within +-448)
 __device__ __forceinline__ uint32_t cvt2_e4m3(float a, float b) {
