@@ -473,8 +473,9 @@ struct StepHeadArgs {
   int sk_blocks, sk_n_kv, sk_qpk, sk_nq, sk_n_heads, sk_small;
 };
 
-template <typename T, int kEncTok, bool TR>
-__global__ __launch_bounds__(256) void step_head_kernel(StepHeadArgs a) {
+// N: 16-token tiles of the projection, or (TR) its tokens per pass
+template <typename T, int N, bool TR>
+__global__ __launch_bounds__(256, (!TR && N <= 2) ? 2 : 1) void step_head_kernel(StepHeadArgs a) {
   const int id = blockIdx.x;
   auto fold_item = [&]() __attribute__((always_inline)) {
     if (id < a.fold_blocks) {
@@ -498,10 +499,10 @@ __global__ __launch_bounds__(256) void step_head_kernel(StepHeadArgs a) {
   };
   if (id < a.enc_blocks) {
     if constexpr (TR) {
-      encode_t_body<T, kEncTok>(a.enc_t, id, fold_item);
+      encode_t_body<T, N>(a.enc_t, id, fold_item);
     } else {
       const int bx = id % a.enc_gx, rest = id / a.enc_gx;
-      encode_partial_body<T, kEncTok>(a.enc, bx, rest % a.enc_gy, rest / a.enc_gy, fold_item);
+      encode_partial_body<T, N>(a.enc, bx, rest % a.enc_gy, rest / a.enc_gy, fold_item);
     }
   } else {
     fold_item();
@@ -517,8 +518,8 @@ struct StepHeadNoRopeArgs {
   int enc_blocks, enc_gx, enc_gy;
 };
 
-template <typename T, int kEncTok, bool TR>
-__global__ __launch_bounds__(256) void step_head_norope_kernel(StepHeadNoRopeArgs a) {
+template <typename T, int N, bool TR>
+__global__ __launch_bounds__(256, (!TR && N <= 2) ? 2 : 1) void step_head_norope_kernel(StepHeadNoRopeArgs a) {
   const int id = blockIdx.x;
   auto item = [&]() __attribute__((always_inline)) {
     if (id < a.q_blocks) {
@@ -528,10 +529,10 @@ __global__ __launch_bounds__(256) void step_head_norope_kernel(StepHeadNoRopeArg
   };
   if (id < a.enc_blocks) {
     if constexpr (TR) {
-      encode_t_body<T, kEncTok>(a.enc_t, id, item);
+      encode_t_body<T, N>(a.enc_t, id, item);
     } else {
       const int bx = id % a.enc_gx, rest = id / a.enc_gx;
-      encode_partial_body<T, kEncTok>(a.enc, bx, rest % a.enc_gy, rest / a.enc_gy, item);
+      encode_partial_body<T, N>(a.enc, bx, rest % a.enc_gy, rest / a.enc_gy, item);
     }
   } else {
     item();
@@ -540,16 +541,16 @@ __global__ __launch_bounds__(256) void step_head_norope_kernel(StepHeadNoRopeArg
 
 using StepHeadNoRopeFn = void (*)(StepHeadNoRopeArgs);
 StepHeadNoRopeFn step_head_norope_fn(int act, int tok_cls, bool tr) {
-#define PALU_SH(K, T, TR) {K<T, 1, TR>, K<T, 2, TR>, K<T, 4, TR>, K<T, 8, TR>}
-  static const StepHeadNoRopeFn f16[2][4] = {PALU_SH(step_head_norope_kernel, F16, false), PALU_SH(step_head_norope_kernel, F16, true)};
-  static const StepHeadNoRopeFn bf16[2][4] = {PALU_SH(step_head_norope_kernel, BF16, false), PALU_SH(step_head_norope_kernel, BF16, true)};
+#define PALU_SH(K, T) {{K<T, 1, false>, K<T, 2, false>, K<T, 3, false>, K<T, 4, false>}, {K<T, 1, true>, K<T, 2, true>, K<T, 4, true>, K<T, 8, true>}}
+  static const StepHeadNoRopeFn f16[2][4] = PALU_SH(step_head_norope_kernel, F16);
+  static const StepHeadNoRopeFn bf16[2][4] = PALU_SH(step_head_norope_kernel, BF16);
   return act == PALU_F16 ? f16[tr][tok_cls] : bf16[tr][tok_cls];
 }
 
 using StepHeadFn = void (*)(StepHeadArgs);
 StepHeadFn step_head_fn(int act, int tok_cls, bool tr) {
-  static const StepHeadFn f16[2][4] = {PALU_SH(step_head_kernel, F16, false), PALU_SH(step_head_kernel, F16, true)};
-  static const StepHeadFn bf16[2][4] = {PALU_SH(step_head_kernel, BF16, false), PALU_SH(step_head_kernel, BF16, true)};
+  static const StepHeadFn f16[2][4] = PALU_SH(step_head_kernel, F16);
+  static const StepHeadFn bf16[2][4] = PALU_SH(step_head_kernel, BF16);
 #undef PALU_SH
   return act == PALU_F16 ? f16[tr][tok_cls] : bf16[tr][tok_cls];
 }
@@ -649,7 +650,7 @@ int palu_encode_workspace_bytes(const palu_layer_desc* desc, int which, int32_t 
   for (int side = 0; side < 2; ++side) {
     if (which != 2 && which != side) continue;
     const int R = side ? m.v_off[m.n_groups] : m.k_off[m.n_groups];
-    total += align_up((size_t)(d / kEncRows) * std::min(n_tok, kEncodeGemmTokens - 1) * R * 4);
+    total += align_up((size_t)ceil_div(d, kEncRows) * std::min(n_tok, kEncodeGemmTokens - 1) * R * 4);
   }
   *out_bytes = std::max<size_t>(total, 256);
   return PALU_OK;
@@ -661,7 +662,7 @@ struct EncodePlan {
   EncodeArgs a;
   bool gemm;              // many tokens: tiled GEMM, no workspace
   int n_sides, max_R;
-  int tok_cls;            // split-K and transposed forms: 8, 4, 2 or 1 tokens per pass (index 3 .. 0)
+  int tok_cls;            // split-K form: 16-token tiles - 1; transposed form: 8, 4, 2 or 1 tokens per pass (3 .. 0)
   bool transposed;        // weights given as At [R, d]: one launch, no partial sums (t, t_lds, t_blocks)
   EncodeTArgs t;
   size_t t_lds;
@@ -686,7 +687,7 @@ int plan_encode(const palu_layer_desc* desc, bool do_k, bool do_v, const void* x
   a.dst_row = dst_row;
   a.n_tok = n_tok;
   a.d = d;
-  a.k_splits = p->gemm ? 0 : d / kEncRows;
+  a.k_splits = p->gemm ? 0 : ceil_div(d, kEncRows);
   size_t off = 0;
   p->n_sides = 0;
   p->max_R = 0;
@@ -708,7 +709,7 @@ int plan_encode(const palu_layer_desc* desc, bool do_k, bool do_v, const void* x
     p->max_R = std::max(p->max_R, R);
   }
   if (workspace_bytes < off) return PALU_ERR_WORKSPACE_TOO_SMALL;
-  p->tok_cls = n_tok >= 5 ? 3 : (n_tok >= 3 ? 2 : (n_tok == 2 ? 1 : 0));
+  p->tok_cls = p->gemm ? 0 : (n_tok - 1) / 16;
   return PALU_OK;
 }
 
@@ -770,7 +771,7 @@ void encode_partial_grid(const EncodePlan& p, unsigned g[3]) {
 // second launch of the split-K form: sum the partials, round, scatter the rows
 int launch_encode_finish(int act, const EncodePlan& p, hipStream_t s) {
   if (p.transposed) return PALU_OK;         // nothing left to sum
-  const dim3 g2((unsigned)ceil_div(p.max_R, 64), (unsigned)p.a.n_tok, (unsigned)p.n_sides);
+  const dim3 g2((unsigned)ceil_div(p.max_R, 256), (unsigned)p.a.n_tok, (unsigned)p.n_sides);
   if (act == PALU_F16) hipLaunchKernelGGL(encode_finish_kernel<F16>, g2, dim3(256), 0, s, p.a);
   else hipLaunchKernelGGL(encode_finish_kernel<BF16>, g2, dim3(256), 0, s, p.a);
   return launch_ok();
@@ -792,9 +793,9 @@ int launch_encode(int act, const EncodePlan& p, hipStream_t s) {
   }
   using EncFn = void (*)(EncodeArgs);
   static const EncFn partial_f16[4] = {encode_partial_kernel<F16, 1>, encode_partial_kernel<F16, 2>,
-                                       encode_partial_kernel<F16, 4>, encode_partial_kernel<F16, 8>};
+                                       encode_partial_kernel<F16, 3>, encode_partial_kernel<F16, 4>};
   static const EncFn partial_bf16[4] = {encode_partial_kernel<BF16, 1>, encode_partial_kernel<BF16, 2>,
-                                        encode_partial_kernel<BF16, 4>, encode_partial_kernel<BF16, 8>};
+                                        encode_partial_kernel<BF16, 3>, encode_partial_kernel<BF16, 4>};
   unsigned g1[3];
   encode_partial_grid(p, g1);
   hipLaunchKernelGGL(act == PALU_F16 ? partial_f16[p.tok_cls] : partial_bf16[p.tok_cls], dim3(g1[0], g1[1], g1[2]), dim3(256), 0, s, a);

@@ -2,9 +2,9 @@
 // tokens, and the 4-bit asymmetric quantizer of Appendix A.
 //
 // At decode time the projection reads all of A (d x R) for n_tok = batch
-// tokens: a weight-streaming problem (HBM-bound, 2*n_tok FLOP per weight
-// element), so it is a split-K float32 FMA kernel on 16-byte coalesced loads
-// followed by a small reduction that rounds once and scatters the rows.
+// tokens: a weight-streaming problem.  Up to 63 tokens it is a split-K product on the
+// matrix cores (the weights are read once whatever the number of tokens), followed by a
+// small reduction that rounds once and scatters the rows.
 
 #pragma once
 
@@ -12,9 +12,8 @@
 
 namespace palu {
 
-constexpr int kEncRows = 64;      // rows of A per workgroup (16 per wavefront)
-constexpr int kEncCols = 512;     // columns of A per workgroup (8 per lane)
-constexpr int kEncTokMax = 8;     // most tokens accumulated per pass over the weights
+constexpr int kEncRows = 256;     // rows of A per workgroup, a quarter of them per wavefront (two k-steps of 32)
+constexpr int kEncCols = 128;     // columns of A per workgroup
 
 struct EncodeSide {
   const uint16_t* A;       // [d, R]
@@ -39,9 +38,19 @@ struct EncodeArgs {
 int launch_encode_gemm_tiles(int act, const EncodeArgs& a, int max_R, int n_sides, bool quant, int tile_opt, int n_cu,
                              hipStream_t s);
 
-// grid (ceil(max R / 512), d / 64, sides), 256 threads.
-// kEncTok: tokens accumulated per pass over the weights (1, 2, 4 or 8: a decode
-// step of one sequence should not pay for eight).
+// Split-K projection of up to 16 MT tokens.  Bound by the HBM stream of A: 32 MiB for a 7B-shaped layer whatever the
+// number of tokens.  (The vector-ALU form this replaces took 8 tokens per pass over weights kept in registers and wrote
+// 64 partial sums per output: 48 tokens of a 7B-shaped layer took 40 us + 9 us for the sums, 16 tokens 19 + 5 us.)
+//
+// A workgroup takes 256 rows of A (k) x 128 columns, a wavefront 64 of the rows.  A is column-contiguous while the
+// matrix cores want 8 consecutive k of one column per lane: a lane loads the same 8-column chunk of 8 consecutive rows
+// and transposes the 8 x 8 block in registers (one byte permute per operand register, as the value kernel does with its
+// latents), so that column e of every chunk is the operand of the e-th of 8 accumulator sets.  All 16 loads of a
+// wavefront (16 KiB) go out before anything else; a 7B-shaped layer is 512 workgroups, two to a compute unit, i.e. all
+// of A is in flight at once.  The four wavefronts' sums meet in LDS, so that a workgroup writes one partial sum per
+// output: d / 256 of them per output in all, summed in a fixed order by encode_finish_kernel.
+//
+// grid (ceil(max R / 128), ceil(d / 256), sides), 256 threads.
 // (bx, by, bz): the workgroup's position in that grid (the kernel below passes blockIdx; the fused
 // first launch of a decode step runs the same body next to the query fold)
 // while_loading(): work of the whole workgroup that is independent of the projection, run after the
@@ -49,114 +58,115 @@ int launch_encode_gemm_tiles(int act, const EncodeArgs& a, int max_R, int n_side
 struct NoExtraWork {
   __device__ __forceinline__ void operator()() const {}
 };
-template <typename T, int kEncTok, typename Extra = NoExtraWork>
+template <typename T, int MT, typename Extra = NoExtraWork>
 __device__ __forceinline__ void encode_partial_body(const EncodeArgs& a, int bx, int by, int bz, Extra while_loading = Extra{}) {
-  __shared__ float xs[kEncTok][kEncRows];
-  __shared__ float red[3][kEncTok][kEncCols];     // wavefronts 1..3 hand their sums to wavefront 0
+  constexpr int kPitch = kEncCols + 4;            // floats per token row: the 8-float stores of the four token quads hit distinct banks
+  __shared__ __attribute__((aligned(16))) float red[4][16 * kPitch];
   const EncodeSide sd = a.side[bz];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int c0 = bx * kEncCols + lane * 8;
-  const int k0 = by * kEncRows;
-  const bool col_ok = c0 < sd.R;                  // R is a multiple of 32, so 8 columns are all in or all out
   if (bx * kEncCols >= sd.R) {                    // uniform
     while_loading();
     return;
   }
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int n = lane & 15, kq = lane >> 4;        // column chunk (B), token (A) or accumulator column; k-octet or token quad
+  const int k0 = by * kEncRows + wave * (kEncRows / 4);
+  const bool k_ok = k0 < a.d;                     // wavefront-uniform: d is a multiple of 128, a wavefront's 64 rows are all in or all out
+  const int kw = k_ok ? k0 : 0;
+  const int c0 = bx * kEncCols + n * 8;
+  const int cc = min(c0, sd.R - 8);               // R is a multiple of 32: a chunk is all in or all out; clamped ones are never stored
 
-  // the weight rows go out first: they are the long-latency HBM stream and do
-  // not depend on the activations
-  uint4v wraw[16];
+  // activations (A operand: token 16 mt + n, k-octet kq of the step) ahead of the weights, which are the long stream
+  typename T::vec8 xa[MT][2];
 #pragma unroll
-  for (int kk = 0; kk < 16; ++kk) {
-    const int k = wave * 16 + kk;
-    wraw[kk] = col_ok ? *reinterpret_cast<const uint4v*>(sd.A + (size_t)(k0 + k) * sd.R + c0) : uint4v{0, 0, 0, 0};
-  }
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      xa[mt][s] = *reinterpret_cast<const typename T::vec8*>(a.x + (size_t)min(16 * mt + n, a.n_tok - 1) * a.d + kw + 32 * s + 8 * kq);
+  uint4v w[2][8];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      w[s][j] = *reinterpret_cast<const uint4v*>(sd.A + (size_t)(kw + 32 * s + 8 * kq + j) * sd.R + cc);
   while_loading();
 
-  for (int tb = 0; tb < a.n_tok; tb += kEncTok) {
-    const int nt = min(kEncTok, a.n_tok - tb);
-    __syncthreads();
-    for (int i = tid; i < kEncTok * kEncRows; i += 256) {
-      const int t = i / kEncRows, k = i - t * kEncRows;
-      xs[t][k] = t < nt ? T::to_float(a.x[(size_t)(tb + t) * a.d + k0 + k]) : 0.f;
-    }
-    __syncthreads();
-    float acc[kEncTok][8];
+  float4v acc[MT][8];
 #pragma unroll
-    for (int t = 0; t < kEncTok; ++t)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[t][e] = 0.f;
+    for (int e = 0; e < 8; ++e) acc[mt][e] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const int k = wave * 16 + kk;
-      float wv[8];
+  for (int s = 0; s < 2; ++s) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        wv[2 * e] = T::to_float((uint16_t)(wraw[kk][e] & 0xffffu));
-        wv[2 * e + 1] = T::to_float((uint16_t)(wraw[kk][e] >> 16));
-      }
+    for (int e = 0; e < 8; ++e) {
+      uint4v t;                                   // column e of the chunk over the 8 rows, as four (k, k + 1) pairs
 #pragma unroll
-      for (int t = 0; t < kEncTok; ++t) {
-        const float xv = xs[t][k];
+      for (int jp = 0; jp < 4; ++jp)
+        t[jp] = __builtin_amdgcn_perm(w[s][2 * jp + 1][e >> 1], w[s][2 * jp][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+      const typename T::vec8 b = __builtin_bit_cast(typename T::vec8, t);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[t][e] = fmaf(xv, wv[e], acc[t][e]);
+      for (int mt = 0; mt < MT; ++mt) {
+        if constexpr (__is_same(T, F16)) acc[mt][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[mt][s], b, acc[mt][e], 0, 0, 0);
+        else acc[mt][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][s], b, acc[mt][e], 0, 0, 0);
       }
     }
-    if (wave > 0) {
+  }
+
+  // accumulator e, entry r: token 16 mt + 4 kq + r, column c0 + e.  The wavefronts' tiles meet in LDS, 16 tokens at a time.
 #pragma unroll
-      for (int t = 0; t < kEncTok; ++t)
+  for (int mt = 0; mt < MT; ++mt) {
+    if (mt > 0) __syncthreads();                  // the previous 16 tokens have been summed
 #pragma unroll
-        for (int e = 0; e < 8; ++e) red[wave - 1][t][e * 64 + lane] = acc[t][e];
+    for (int r = 0; r < 4; ++r) {
+      float* dst = &red[wave][(4 * kq + r) * kPitch + n * 8];
+      const float on = k_ok ? 1.f : 0.f;
+      *reinterpret_cast<float4v*>(dst) = float4v{acc[mt][0][r], acc[mt][1][r], acc[mt][2][r], acc[mt][3][r]} * on;
+      *reinterpret_cast<float4v*>(dst + 4) = float4v{acc[mt][4][r], acc[mt][5][r], acc[mt][6][r], acc[mt][7][r]} * on;
     }
     __syncthreads();
-    if (wave == 0 && col_ok) {
 #pragma unroll
-      for (int t = 0; t < kEncTok; ++t) {
-        if (t >= nt) break;
-        float* dst = sd.partial + ((size_t)by * a.n_tok + tb + t) * sd.R + c0;
-        float4v o0, o1;
+    for (int x = 0; x < 2; ++x) {
+      const int id = x * 256 + tid, tok = id >> 5, c4 = (id & 31) * 4;
+      float4v s = *reinterpret_cast<const float4v*>(&red[0][tok * kPitch + c4]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float s = acc[t][e] + red[0][t][e * 64 + lane] + red[1][t][e * 64 + lane] + red[2][t][e * 64 + lane];
-          if (e < 4) o0[e] = s; else o1[e - 4] = s;
-        }
-        *reinterpret_cast<float4v*>(dst) = o0;
-        *reinterpret_cast<float4v*>(dst + 4) = o1;
-      }
+      for (int v = 1; v < 4; ++v) s += *reinterpret_cast<const float4v*>(&red[v][tok * kPitch + c4]);
+      const int t = 16 * mt + tok, col = bx * kEncCols + c4;
+      if (t < a.n_tok && col < sd.R) *reinterpret_cast<float4v*>(sd.partial + ((size_t)by * a.n_tok + t) * sd.R + col) = s;
     }
   }
 }
 
-template <typename T, int kEncTok>
-__global__ __launch_bounds__(256) void encode_partial_kernel(EncodeArgs a) {
-  encode_partial_body<T, kEncTok>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+template <typename T, int MT>
+__global__ __launch_bounds__(256, MT <= 2 ? 2 : 1) void encode_partial_kernel(EncodeArgs a) {
+  encode_partial_body<T, MT>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Sums the split-K partials in a fixed order, rounds once, scatters the rows.
-// Workgroup = 64 columns of one token; thread = (quarter of the splits, column).
-// grid (ceil(max R / 64), n_tok, sides), 256 threads.
+// Workgroup = 256 columns of one token; thread = (quarter of the splits, 4 columns).
+// grid (ceil(max R / 256), n_tok, sides), 256 threads.
 template <typename T>
 __global__ __launch_bounds__(256) void encode_finish_kernel(EncodeArgs a) {
-  __shared__ float part[4][64];
+  __shared__ __attribute__((aligned(16))) float part[4][256];
   const EncodeSide sd = a.side[blockIdx.z];
-  if ((int)blockIdx.x * 64 >= sd.R) return;       // uniform
+  if ((int)blockIdx.x * 256 >= sd.R) return;      // uniform
   const int tid = threadIdx.x;
-  const int c = blockIdx.x * 64 + (tid & 63), t = blockIdx.y, sub = tid >> 6;
+  const int c = blockIdx.x * 256 + (tid & 63) * 4, t = blockIdx.y, sub = tid >> 6;
   const int per = (a.k_splits + 3) / 4;
-  float s = 0.f;
+  float4v s = {0.f, 0.f, 0.f, 0.f};
   if (c < sd.R) {
     const float* p = sd.partial + (size_t)t * sd.R + c;
-#pragma unroll 8
-    for (int ks = sub * per; ks < min((sub + 1) * per, a.k_splits); ++ks) s += p[(size_t)ks * a.n_tok * sd.R];
+#pragma unroll 4
+    for (int ks = sub * per; ks < min((sub + 1) * per, a.k_splits); ++ks)
+      s += *reinterpret_cast<const float4v*>(p + (size_t)ks * a.n_tok * sd.R);
   }
-  part[sub][tid & 63] = s;
+  *reinterpret_cast<float4v*>(&part[sub][(tid & 63) * 4]) = s;
   __syncthreads();
-  if (tid < 32 && (int)blockIdx.x * 64 + tid * 2 < sd.R) {
-    const int cc = tid * 2;
+  const int cc = tid * 2;
+  if (tid < 128 && (int)blockIdx.x * 256 + cc < sd.R) {
     const float s0 = (part[0][cc] + part[1][cc]) + (part[2][cc] + part[3][cc]);
     const float s1 = (part[0][cc + 1] + part[1][cc + 1]) + (part[2][cc + 1] + part[3][cc + 1]);
     const long long row = a.dst_row ? a.dst_row[t] : t;
-    uint32_t* dst = reinterpret_cast<uint32_t*>(sd.latent + row * sd.row_stride + blockIdx.x * 64 + cc);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(sd.latent + row * sd.row_stride + blockIdx.x * 256 + cc);
     *dst = (uint32_t)T::from_float(s0) | ((uint32_t)T::from_float(s1) << 16);
   }
 }

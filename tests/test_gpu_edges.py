@@ -1,0 +1,43 @@
+"""Kernels at the sizes where their tiling can go wrong: edges of tiles, remainders, the smallest and largest of a
+form's range, against the CPU oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_21118_amd as P
+from oracle import palu_oracle as O
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import make_desc, say, to_dev  # noqa: E402
+
+
+@pytest.mark.parametrize("heads,group,rk,rv,dtype", [(1, 1, 32, 96, "f16"), (3, 1, 32, 64, "bf16"), (5, 1, 96, 32, "f16"),
+                                                      (32, 4, 256, 256, "bf16")])
+def test_encode_token_tiles(heads, group, rk, rv, dtype):
+    """The split-K projection at token counts around its tiles of 16 and depths (128 .. 4096) that leave wavefronts of the
+    last workgroup without rows; column counts that end inside a workgroup's 128."""
+    layer = synth.uniform_layer(heads, group, rk, rv)
+    rng = np.random.default_rng(31)
+    d = heads * 128
+    Ak = synth.round_to(rng.standard_normal((d, layer.R_k)) / np.sqrt(d), dtype)
+    Av = synth.round_to(rng.standard_normal((d, layer.R_v)) / np.sqrt(d), dtype)
+    desc = make_desc(layer, dtype)
+    dev_k, dev_v = to_dev(Ak, dtype), to_dev(Av, dtype)
+    # one rounding to the cache dtype (half a unit in the last place, relative to the value) plus float32 sums of d
+    # products: d eps / 2 of the sum of magnitudes, itself about sqrt(d) / d ... 1 of the result's size: 1e-5 is ample
+    eps = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8
+    for n_tok in (1, 2, 15, 16, 17, 32, 33, 48, 49, 63):
+        x = synth.round_to(rng.standard_normal((n_tok, d)), dtype)
+        hk = torch.full((n_tok + 1, layer.R_k), 7.0, dtype=dev_k.dtype, device="cuda")
+        hv = torch.full((n_tok + 1, layer.R_v), 7.0, dtype=dev_v.dtype, device="cuda")
+        P.palu_encode_kv(desc, to_dev(x, dtype), dev_k, dev_v, hk, layer.R_k, hv, layer.R_v)
+        torch.cuda.synchronize()
+        for got, A in ((hk, Ak), (hv, Av)):
+            g, ref = got.float().cpu().numpy(), O.encode(x, A)
+            err = np.abs(g[:n_tok] - ref) - eps * np.abs(ref)
+            assert err.max() <= 1e-5 * np.abs(ref).max(), (n_tok, err.max())
+            assert (g[n_tok] == 7.0).all()
+    say(f"[edges] encode heads={heads} R={layer.R_k}/{layer.R_v} {dtype}")
