@@ -119,8 +119,8 @@ int palu_version(void);
  *                         reached at logits of about +-25).  Default 0: keys are rebuilt and rotated in float32,
  *                         once per key/value head and pass of up to 8 of its queries where every key rank of
  *                         the layer is 64 .. 512 (4-bit keys: 128 or 256), else once per query head.
- *   "encode_tile_rows"    token rows per workgroup of the prompt-sized projection (64, 128 or 256, each
- *                         with 256 columns; 32 selects the narrow tile of 64 rows x 128 columns)
+ *   "encode_tile_rows"    token rows per workgroup of the prompt-sized projection (128 or 256, each
+ *                         with 256 columns; 32 or 64, each with 128)
  * Unknown names and out-of-range values return PALU_ERR_INVALID_ARG.  Set
  * value_split_tokens before querying the workspace size: a smaller split needs
  * more workspace, and palu_attn_decode reports a shortfall.

@@ -6,121 +6,152 @@
 // compiled with the matrix instructions writing ordinary vector registers, an option that
 // applies to a whole compilation and that this kernel does not fit.
 
+#include <type_traits>
+
 #include "encode_quant.hip"
 
 namespace palu {
 
-// A tiled GEMM on the matrix cores, C[n_tok, R] = X[n_tok, d] A[d, R].  Workgroup = TM x 256 outputs (TM = 256, or
-// 128 / 64 for shorter prompts), four wavefronts of TM/2 x 128 (TM/64 x 4 tiles of
-// v_mfma_f32_32x32x16), one per SIMD with up to 256 accumulator registers.  k advances
-// in stages of 64 through two LDS buffers: while a stage is multiplied, the next one
-// (already in registers) is written to the other buffer and the one after it is
-// requested from memory, so a stage's loads have a whole stage of matrix work to
-// arrive and there is one barrier per stage.  X is k-contiguous, which is what an MFMA
-// operand wants; A is column-contiguous, so each thread loads one 8-column chunk of 8
-// consecutive k and transposes the 8 x 8 block in registers (one byte permute per
-// operand register) on its way to LDS.  The finished tile goes through LDS once more,
-// so that rows leave in 16-byte pieces (or as codes, QUANT).
+// A tiled GEMM on the matrix cores, C[n_tok, R] = X[n_tok, d] A[d, R].  Workgroup = TM x TN outputs, four wavefronts (WM rows of
+// them) on v_mfma_f32_32x32x16, with 256 accumulator registers per lane in the 256 x 256 tile.
+// k advances in stages of KS rows through a ring of NBUF stages in LDS, filled by LDS-direct loads: no staging
+// registers, NBUF - 1 stages of memory requests in flight, one barrier per stage.
 //
-// Workgroups are numbered so that each of the 8 XCDs (workgroup id mod 8) owns a
-// contiguous range of the tiles, columns fastest: the column tiles of a token row share
-// their X rows through that XCD's L2.
-// output columns per workgroup: 256, or 128 with the 64-row tile where even that leaves compute units idle
-constexpr int kGemmK = 64;                     // k per stage
-constexpr int kGemmPitch = kGemmK + 8;         // halfs per LDS row: 16-byte reads of 16 consecutive rows hit distinct banks
-// token rows per workgroup: 256, or 128 / 64 while the taller tile would leave compute units without a workgroup
-
-constexpr size_t gemm_lds_bytes(int tm, int tn) {
-  const size_t stages = (size_t)2 * (tm + tn) * kGemmPitch * 2, out = (size_t)tm * (tn + 8) * 2;
+// X is k-contiguous, which is what a matrix operand wants: 16-byte reads.  A is column-contiguous: its rows lie in LDS as
+// they are and the operand is read with the transposing LDS read, 4 k of 16 columns per 16 lanes.  LDS-direct loads fill
+// consecutive 16-byte slots, so the swizzle that keeps the reads free of bank conflicts is in which chunk a lane requests.
+//
+// G k-steps of 16 make a step: the operands of a step are read while the previous one is multiplied (one wavefront
+// per SIMD: nobody else hides them), its reads and the stage's requests dealt out between the matrix instructions.  The
+// hand-over to the next stage (its loads waited for, one barrier, the finished stage's buffer requested anew) lies
+// inside the last step of a stage, whose operands are in registers by then.
+//
+// Bound by the matrix pipe at the power limit from about 4096 tokens on; below, by how fast one compute unit takes its
+// tile's operands in (70 .. 85 GB/s each here) over 64 k-stages, hence small tiles.  Measured, R = 2048 per side, against the
+// form this replaces (two LDS buffers filled through registers, A transposed there with byte permutes): both sides of 64 / 500 / 1024 /
+// 4096 tokens 35 / 39 / 63 / 128 -> 17 / 26 / 41 / 120 us; one side quantized of 64 / 500 / 2048 tokens 33 / 39 / 67 -> 15 / 22 / 43 us.
+// (Wavefronts that split k instead of the tile, to read every byte from LDS once, were slower: 27 us where this takes 22.)
+//
+// Workgroups are numbered so that each of the 8 XCDs (workgroup id mod 8) owns a contiguous range of the tiles, columns
+// fastest (the column tiles of a token row share their X rows through that XCD's L2) or, where X is smaller than A, rows
+// fastest (the row tiles share a column slice of A, which then comes from memory once and not once per XCD).
+constexpr int gemm_buffers(int tm, int tn, int ks) {             // stages in LDS: as many as fit 144 KiB, at most 6
+  const int n = 144 * 1024 / ((tm + tn) * ks * 2);
+  return n < 6 ? n : 6;
+}
+constexpr size_t gemm_lds_bytes(int tm, int tn, int ks) {
+  const size_t stages = (size_t)gemm_buffers(tm, tn, ks) * (tm + tn) * ks * 2, out = (size_t)tm * (tn + 8) * 2;
   return stages > out ? stages : out;
 }
 
 struct GemmGrid {
   int n_col_tiles, n_row_tiles, n_tiles, per_xcd;     // tiles: sides x row tiles x column tiles
+  int rows_fastest;
 };
 
 // QUANT: every 128 columns of the tile are exactly one quantization block per token, so the
 // workgroup quantizes its rounded outputs in place of storing them (Sec. 3.4 applied
 // while the cache is filled): codes, scales and zero-points are the ones quant_kernel
 // gives for the latents the plain kernel stores.
-// grid (8 * per_xcd), 256 threads, gemm_lds_bytes(TM, TN) of LDS.
-template <typename T, bool QUANT, int TM, int TN>
+// grid (8 * per_xcd), 256 threads, gemm_lds_bytes(TM, TN, KS) of LDS.
+template <typename T, bool QUANT, int TM, int TN, int KS, int G, int WM>
 __global__ __launch_bounds__(256) void encode_gemm_kernel(EncodeArgs a, GemmGrid gg) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_lds[];
-  constexpr int MI = TM / 64;                                            // 32-row tiles of a wavefront
-  constexpr int XC = TM / 32;                                            // 16-byte X chunks per thread and stage
-  constexpr int NJ = TN / 64;                                            // 32-column tiles of a wavefront
+  constexpr int NBUF = gemm_buffers(TM, TN, KS);
+  static_assert(NBUF >= 3, "the schedule keeps at least one stage in flight beyond the next");
+  constexpr int WN = 4 / WM, MI = TM / WM / 32, NJ = TN / WN / 32;       // wavefronts: WM rows of WN, each MI x NJ tiles of 32 x 32
+  constexpr int SPS = KS / 16 / G;                                       // steps per stage
+  static_assert(SPS == 1 || SPS % 2 == 0, "register sets alternate step by step");
   constexpr int kOutPitch = TN + 8;                                      // halfs per row of the output tile
-  constexpr int kAL = TN == 256 ? 8 : 4;                                 // 16-byte A loads per thread and stage
-  constexpr int kBufHalfs = (TM + TN) * kGemmPitch;
+  constexpr int kXB = TM * KS * 2, kStageB = (TM + TN) * KS * 2;
+  constexpr int kXOps = kXB / 4096, kAOps = TN * KS * 2 / 4096, kOps = kXOps + kAOps;      // LDS-direct requests per wavefront and stage
+  static_assert(kXB % 4096 == 0 && (TN * KS * 2) % 4096 == 0 && (NBUF - 1) * kOps < 64, "whole requests, counted by the wait");
+  constexpr int kCh = KS / 8;                                            // 16-byte chunks per X row and stage
   uint16_t* lds16 = reinterpret_cast<uint16_t*>(gemm_lds);
 
   const int tile = (blockIdx.x & 7) * gg.per_xcd + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= gg.per_xcd || tile >= gg.n_tiles) return;          // uniform
   const int per_side = gg.n_col_tiles * gg.n_row_tiles;
   const int side = tile / per_side, in_side = tile - side * per_side;
-  const int row_tile = in_side / gg.n_col_tiles, col_tile = in_side - row_tile * gg.n_col_tiles;
+  const int row_tile = gg.rows_fastest ? in_side % gg.n_row_tiles : in_side / gg.n_col_tiles;
+  const int col_tile = gg.rows_fastest ? in_side / gg.n_row_tiles : in_side % gg.n_col_tiles;
   const EncodeSide sd = a.side[side];
   const int n0 = col_tile * TN, m0 = row_tile * TM;
   if (n0 >= sd.R) return;                                                // uniform
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane_lo = lane & 31, lane_hi = lane >> 5;
-  const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TN / 2);     // this wavefront's corner of the tile
+  const int wm = wave / WN * (TM / WM), wn = wave % WN * (TN / WN);     // this wavefront's corner of the tile
 
-  // staging roles.  X: 16-byte piece lane % 8 of the stage's 64 k of row x_row(i) (i < XC): the 16 lanes of a store
-  // pass hold rows r and r + 8, whose pieces lie 32 banks apart with this pitch (neighbouring rows overlap by 4 banks).
-  // A, 256 columns: one (k-octet oct, 8-column chunk cc) item per thread: rows k0 + 8 oct + j (j < 8), columns
-  // n0 + 8 cc ..; 128 columns: half an octet per thread (quad = tid / 16: rows k0 + 4 quad + j, j < 4).
-  const int quad = tid >> 4;
-  const int oct = TN == 256 ? tid >> 5 : quad >> 1, cc = TN == 256 ? tid & 31 : tid & 15;
-  const int a_col = min(n0 + cc * 8, sd.R - 8);                          // R is a multiple of 32: clamped chunks are never stored
-  const uint16_t* x_base = a.x + (size_t)m0 * a.d;
-  unsigned x_off[XC];                                                    // rows past the last token re-read it; they are never stored
-  auto x_row = [&](int i) { return 16 * (wave + 4 * (i >> 1)) + 4 * (i & 1) + (lane >> 4) + 8 * ((lane >> 3) & 1); };
+  // ---- requests.  X: slot p of row r holds chunk p ^ x_swz(r), so that 16 rows' reads of one chunk fall on distinct
+  // banks.  A: slot p of row k holds chunk p ^ 4 (k mod 4) (rows of 128 bytes: p ^ 4 (k / 2 mod 2)), i.e. the four rows of a
+  // transposing read lie in different 64-byte quarters of the 256-byte bank space.  Rows past the last token re-read it and columns past R the
+  // last chunk (R is a multiple of 32): their products are never stored.
+  auto x_swz = [](int r) { return (r / (16 / kCh)) & (kCh - 1); };
+  auto a_swz = [](int k) { return TN >= 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; };
+  unsigned x_off[kXOps], a_off[kAOps];
 #pragma unroll
-  for (int i = 0; i < XC; ++i)
-    x_off[i] = (unsigned)min(x_row(i), a.n_tok - 1 - m0) * (unsigned)a.d + (unsigned)(lane & 7) * 8u;
-  const uint16_t* a_src = sd.A + (size_t)(TN == 256 ? oct * 8 : quad * 4) * sd.R + a_col;
-  // the stage after the one being multiplied waits in these registers; the one after that is requested as
-  // soon as they have been written to LDS
-  uint4v xr[XC], ar[kAL];
-  auto fetch_x = [&](int stage) {
+  for (int x = 0; x < kXOps; ++x) {
+    const int o = (wave * kXOps + x) * 1024 + lane * 16, r = o / (KS * 2), p = (o % (KS * 2)) / 16;
+    x_off[x] = ((unsigned)min(r, a.n_tok - 1 - m0) * (unsigned)a.d + (unsigned)((p ^ x_swz(r)) * 8)) * 2u;
+  }
 #pragma unroll
-    for (int i = 0; i < XC; ++i) xr[i] = *reinterpret_cast<const uint4v*>(x_base + x_off[i] + stage * kGemmK);
+  for (int x = 0; x < kAOps; ++x) {
+    const int o = (wave * kAOps + x) * 1024 + lane * 16, k = o / (TN * 2), p = (o % (TN * 2)) / 16;
+    a_off[x] = ((unsigned)k * (unsigned)sd.R + (unsigned)min(n0 + (p ^ a_swz(k)) * 8, sd.R - 8)) * 2u;
+  }
+  const unsigned char* x_base = uniform_ptr(reinterpret_cast<const unsigned char*>(a.x + (size_t)m0 * a.d));
+  const unsigned char* a_base = uniform_ptr(reinterpret_cast<const unsigned char*>(sd.A));
+  const unsigned lds_base = __builtin_amdgcn_readfirstlane((unsigned)(size_t)gemm_lds);
+  const unsigned a_stage_bytes = (unsigned)KS * 2u * (unsigned)sd.R;
+  const int n_stages = a.d / KS;                                         // even: d is a multiple of 128
+  struct Req {
+    const unsigned char *xs, *as;
+    unsigned m0;
   };
-  auto fetch_a = [&](int stage) {
-#pragma unroll
-    for (int j = 0; j < kAL; ++j) ar[j] = *reinterpret_cast<const uint4v*>(a_src + (size_t)(stage * kGemmK + j) * sd.R);
+  auto request_stage = [&](int stage, unsigned buf_off) __attribute__((always_inline)) {       // past the last stage: that one again, unused
+    const int st = min(stage, n_stages - 1);
+    Req r;
+    r.xs = uniform_ptr(x_base + (size_t)st * (KS * 2));
+    r.as = uniform_ptr(a_base + (size_t)st * a_stage_bytes);
+    r.m0 = __builtin_amdgcn_readfirstlane(lds_base + buf_off);
+    return r;
   };
-  auto stash_x = [&](int buf) {
-    uint16_t* Xs = lds16 + buf * kBufHalfs;
-#pragma unroll
-    for (int i = 0; i < XC; ++i) *reinterpret_cast<uint4v*>(Xs + x_row(i) * kGemmPitch + (lane & 7) * 8) = xr[i];
+  auto request_op = [&](const Req& r, int x) __attribute__((always_inline)) {
+    const unsigned m0v = r.m0 + (x < kXOps ? (unsigned)((wave * kXOps + x) * 1024) : (unsigned)(kXB + (wave * kAOps + x - kXOps) * 1024));
+    if (x < kXOps) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(m0v), "v"(x_off[x]), "s"(r.xs) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(m0v), "v"(a_off[x - kXOps]), "s"(r.as) : "memory");
   };
-  auto stash_a = [&](int buf) {
-    uint16_t* As = lds16 + buf * kBufHalfs + TM * kGemmPitch;
-    // 8 x 8 transpose: column e of the chunk over the 8 k rows, as four (k, k+1) pairs
+
+  // ---- operand reads, byte offsets inside a stage.  X: row wm + 32 i + lane_lo, k-octet 2 ks + lane_hi.  A: k = 16 ks +
+  // 8 lane_hi + 4 q + 0..3 of columns wn + 32 j + 16 (lane bit 4) + 0..15: the lane hands in row (lane / 4) % 4, columns
+  // 4 (lane % 4) .. + 3 of that block and receives column lane % 16.
+  int x_rd[KS / 16], a_rd[NJ];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      uint4v t;
-#pragma unroll
-      for (int jp = 0; jp < kAL / 2; ++jp)
-        t[jp] = __builtin_amdgcn_perm(ar[2 * jp + 1][e >> 1], ar[2 * jp][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
-      // the 16-byte k-octets of a row are stored XOR-swizzled by bits 3..5 of the row number (its chunk
-      // number): the lanes of a store pass (chunks, rows 8 apart) would otherwise share two bank groups
-      uint16_t* dst = As + (cc * 8 + e) * kGemmPitch + ((oct ^ cc) & 7) * 8;
-      if constexpr (TN == 256) *reinterpret_cast<uint4v*>(dst) = t;
-      else *reinterpret_cast<uint2v*>(dst + (quad & 1) * 4) = uint2v{t[0], t[1]};
-    }
-  };
-  // read side of the swizzle: k-step ks reads octet 2 ks + lane_hi of row n, stored at octet ^ ((n >> 3) & 7)
-  int a_row[NJ], a_swz[NJ];
+  for (int ks = 0; ks < KS / 16; ++ks) {
+    const int r = wm + lane_lo;
+    x_rd[ks] = r * (KS * 2) + (((2 * ks + lane_hi) ^ x_swz(r)) * 16);
+  }
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int n = wn + 32 * j + lane_lo;
-    a_row[j] = n * kGemmPitch;
-    a_swz[j] = (n >> 3) & 7;
+    const int kr = (lane >> 2) & 3, c = (wn >> 3) + 4 * j + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+    a_rd[j] = kXB + (8 * lane_hi + kr) * (TN * 2) + ((c ^ a_swz(kr)) * 16) + (lane & 1) * 8;
   }
+  using Vec = typename T::vec8;
+  Vec xa[2][G][MI], ab[2][G][NJ];
+  constexpr int kRd = G * (MI + NJ);                                     // operands per step
+  auto read_op = [&](int set, unsigned buf_off, int p, int x) __attribute__((always_inline)) {      // operand x of step p of the stage at buf_off
+    const int g = x / (MI + NJ), y = x % (MI + NJ), ks = p * G + g;
+    if (y < MI) {
+      xa[set][g][y] = *reinterpret_cast<const Vec*>(gemm_lds + buf_off + x_rd[ks] + y * (32 * KS * 2));
+    } else {
+      typedef short short4v __attribute__((ext_vector_type(4)));
+      using LdsV = __attribute__((address_space(3))) short4v;
+      const unsigned char* src = gemm_lds + buf_off + a_rd[y - MI] + ks * (16 * TN * 2);
+      const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsV*)src);
+      const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsV*)(src + 4 * TN * 2));
+      ab[set][g][y - MI] = __builtin_bit_cast(Vec, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+  };
 
   float16v acc[MI][NJ];
 #pragma unroll
@@ -130,93 +161,72 @@ __global__ __launch_bounds__(256) void encode_gemm_kernel(EncodeArgs a, GemmGrid
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // operand registers of one k-step (16 k); two sets, so that a k-step's reads are in flight
-  // while the previous one is multiplied (one wavefront per SIMD: nobody else hides them)
-  typename T::vec8 xa[2][MI], ab[2][NJ];
-  auto read_step = [&](int set, int buf, int ks) {
-    const uint16_t* Xs = lds16 + buf * kBufHalfs;
-    const uint16_t* As = Xs + TM * kGemmPitch;
+  // Step P of stage s (its operands in register set SET).  buf / next_buf: the stage's buffer and the next one's.
+  constexpr int kMma = G * MI * NJ;
+  constexpr int kHand = SPS == 1 ? 0 : kMma / 2;                         // matrix instruction before which the hand-over of the last step lies
+  auto step = [&](auto p_c, auto set_c, int s, unsigned buf, unsigned next_buf) __attribute__((always_inline)) {
+    constexpr int P = decltype(p_c)::value, SET = decltype(set_c)::value;
+    constexpr bool last = P == SPS - 1;
+    constexpr int from = last ? kHand : 0, span = kMma - from;
+    Req req;
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
-      xa[set][i] = *reinterpret_cast<const typename T::vec8*>(Xs + (wm + 32 * i + lane_lo) * kGemmPitch + ks * 16 + lane_hi * 8);
+    for (int mi = 0; mi < kMma; ++mi) {
+      if (last && mi == from) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NBUF - 2) * kOps));       // stage s + 1 has landed (this wavefront's share)
+        __syncthreads();                                                 // ... everybody's; and stage s has been read by everybody
+        req = request_stage(s + NBUF, buf);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (mi >= from) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      ab[set][j] = *reinterpret_cast<const typename T::vec8*>(As + a_row[j] + (((2 * ks + lane_hi) ^ a_swz[j]) * 8));
+        for (int x = (mi - from) * kRd / span; x < (mi - from + 1) * kRd / span; ++x)
+          read_op(SET ^ 1, last ? next_buf : buf, last ? 0 : P + 1, x);
+        if (last) {
+#pragma unroll
+          for (int x = (mi - from) * kOps / span; x < (mi - from + 1) * kOps / span; ++x) request_op(req, x);
+        }
+      }
+      const int g = mi / (MI * NJ), i = mi / NJ % MI, j = mi % NJ;
+      acc[i][j] = T::mfma(xa[SET][g][i], ab[SET][g][j], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 
-  auto multiply = [&](int set) {
+  // ---- start-up: the whole ring requested, stage 0 landed, its first operands read
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+  for (int b = 0; b < NBUF; ++b) {
+    const Req r = request_stage(b, (unsigned)(b * kStageB));
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j] = T::mfma(xa[set][i], ab[set][j], acc[i][j]);
-  };
-  // One stage: four k-steps, each with the next step's operand reads in flight.  The first writes the X rows of
-  // stage s + 1 from their registers to the other LDS buffer (last read before the previous barrier), the second
-  // requests those of stage s + 2 into the same registers; the third and fourth do the same for A.  The
-  // scheduling barriers keep this order (left alone, the compiler sinks the loads to the end of the stage and
-  // hoists their use to its start), and inside a k-step the other work is dealt out one piece per matrix
-  // instruction: a wavefront is alone on its SIMD, so whatever it issues in a row between two of them leaves
-  // the matrix pipe idle.  Past the end of k the last stage is fetched and stored again, into the buffer nobody
-  // reads any more.
-  const int n_stages = a.d / kGemmK;
-  constexpr int kMma = MI * NJ, kRd = MI + NJ;   // matrix instructions and operand reads of a k-step
-  constexpr int kHalf = kMma / 2, kRdPer = (kRd + kHalf - 1) / kHalf;
-  constexpr int kXwPer = (XC + kHalf - 1) / kHalf, kAwPer = (8 + kHalf - 1) / kHalf, kLdPerMma = (kAL + kMma - 1) / kMma;
-  fetch_x(0);
-  fetch_a(0);
-  stash_x(0);
-  stash_a(0);
-  fetch_x(min(1, n_stages - 1));
-  fetch_a(min(1, n_stages - 1));
-  __syncthreads();
-  read_step(0, 0, 0);
-  for (int s = 0; s < n_stages; ++s) {
-    const int buf = s & 1, next = min(s + 2, n_stages - 1);
-    read_step(1, buf, 1);
-    multiply(0);
-    stash_x(buf ^ 1);
-#pragma unroll
-    for (int i = 0; i < kMma; ++i) {             // LDS accesses keep their program order: reads first
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i < kHalf && i * kRdPer < kRd) __builtin_amdgcn_sched_group_barrier(0x100, kRdPer, 0);
-      if (i >= kHalf && (i - kHalf) * kXwPer < XC) __builtin_amdgcn_sched_group_barrier(0x200, kXwPer, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    read_step(0, buf, 2);
-    multiply(1);
-    fetch_x(next);
-#pragma unroll
-    for (int i = 0; i < kMma; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i < kRd) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      if (i < XC) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    read_step(1, buf, 3);
-    multiply(0);
-    stash_a(buf ^ 1);
-#pragma unroll
-    for (int i = 0; i < kMma; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i < kHalf && i * kRdPer < kRd) __builtin_amdgcn_sched_group_barrier(0x100, kRdPer, 0);
-      if (i >= kHalf && (i - kHalf) * kAwPer < 8) __builtin_amdgcn_sched_group_barrier(0x200, kAwPer, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(1);
-    fetch_a(next);
-#pragma unroll
-    for (int i = 0; i < kMma; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i * kLdPerMma < kAL) __builtin_amdgcn_sched_group_barrier(0x020, kLdPerMma, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();                             // the next stage is in LDS; this one has been read
-    read_step(0, buf ^ 1, 0);                    // (after the last stage: unused)
-    __builtin_amdgcn_sched_barrier(0);
+    for (int x = 0; x < kOps; ++x) request_op(r, x);
   }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm((NBUF - 1) * kOps));
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < kRd; ++x) read_op(0, 0, 0, x);
+  unsigned buf = 0;
+  auto after = [](unsigned b) { return b + kStageB == (unsigned)(NBUF * kStageB) ? 0u : b + kStageB; };
+  for (int s = 0; s < n_stages; s += SPS == 1 ? 2 : 1) {
+    const unsigned b1 = after(buf);
+    if constexpr (SPS == 1) {
+      const unsigned b2 = after(b1);
+      step(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, s, buf, b1);
+      step(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, s + 1, b1, b2);
+      buf = b2;
+    } else {
+      step(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, s, buf, b1);
+      step(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, s, buf, b1);
+      if constexpr (SPS == 4) {
+        step(std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{}, s, buf, b1);
+        step(std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{}, s, buf, b1);
+      }
+      buf = b1;
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));       // the ring becomes the output tile: no request may still write it, nobody still read it
+  __syncthreads();
 
   // accumulator element e of tile (i, j): token m0 + wm + 32 i + mfma_row(e), column n0 + wn + 32 j + lane_lo.
-  // Every stage has been read (barrier above): LDS becomes the rounded output tile [TM][kOutPitch].
+  // LDS becomes the rounded output tile [TM][kOutPitch].
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -227,47 +237,53 @@ __global__ __launch_bounds__(256) void encode_gemm_kernel(EncodeArgs a, GemmGrid
   __syncthreads();
 
   if constexpr (QUANT) {
-    // two threads per (token, 128-column block), 64 channels each
     const int n_blocks = sd.R / 128;
     constexpr int NB = TN / 128;                     // quantization blocks per token in the tile
+    // threads per (token, block): up to 16 where the tile has few blocks (every thread at work; a block's parameters,
+    // two divisions, are computed by each of them)
+    constexpr int TPB = 1024 / (TM * NB) < 16 ? 1024 / (TM * NB) : 16, CH8 = 16 / TPB;
 #pragma unroll 1
-    for (int item = tid; item < TM * NB * 2; item += 256) {
-      const int tr = item / (NB * 2), bl = (item >> 1) % NB, hf = item & 1;
-      uint4v v[8];
+    for (int item = tid; item < TM * NB * TPB; item += 256) {
+      const int tr = item / (NB * TPB), bl = (item / TPB) % NB, part = item % TPB;
+      uint4v v[CH8];                                 // channels 8 CH8 part .. of the block
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const uint4v*>(lds16 + tr * kOutPitch + bl * 128 + hf * 64 + i * 8);
+      for (int i = 0; i < CH8; ++i) v[i] = *reinterpret_cast<const uint4v*>(lds16 + tr * kOutPitch + bl * 128 + (part * CH8 + i) * 8);
       float mn = T::to_float((uint16_t)(v[0][0] & 0xffffu)), mx = mn;
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < CH8; ++i)
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
           const float x0 = T::to_float((uint16_t)(v[i][w] & 0xffffu)), x1 = T::to_float((uint16_t)(v[i][w] >> 16));
           mn = fminf(mn, fminf(x0, x1));
           mx = fmaxf(mx, fmaxf(x0, x1));
         }
-      mn = fminf(mn, __shfl_xor(mn, 1, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
+#pragma unroll
+      for (int off = 1; off < TPB; off <<= 1) {
+        mn = fminf(mn, __shfl_xor(mn, off, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+      }
       const int t = m0 + tr, blk = col_tile * NB + bl;
       if (t >= a.n_tok || blk >= n_blocks) continue;
       const QuantParams qp = quant_params(mn, mx);
       const size_t orow = a.dst_row ? (size_t)a.dst_row[t] : (size_t)t;
-      uint4v* dst = reinterpret_cast<uint4v*>(sd.codes + orow * (size_t)(sd.R / 2) + blk * 64 + hf * 32);
+      uint32_t word[CH8];
 #pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        uint4v pk;
+      for (int i = 0; i < CH8; ++i) {
+        word[i] = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {           // output word w of this store: channels 8 (4 o + w) .. + 7 of the thread's 64
-          uint32_t word = 0;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const uint32_t pr = v[4 * o + w][c];
-            word |= (quant_code(T::to_float((uint16_t)(pr & 0xffffu)), qp) | (quant_code(T::to_float((uint16_t)(pr >> 16)), qp) << 4)) << (8 * c);
-          }
-          pk[w] = word;
-        }
-        dst[o] = pk;
+        for (int c = 0; c < 4; ++c)
+          word[i] |= (quant_code(T::to_float((uint16_t)(v[i][c] & 0xffffu)), qp) | (quant_code(T::to_float((uint16_t)(v[i][c] >> 16)), qp) << 4)) << (8 * c);
       }
-      if (hf == 0) {
+      uint8_t* dst = sd.codes + orow * (size_t)(sd.R / 2) + blk * 64 + part * (4 * CH8);
+      if constexpr (CH8 >= 4) {
+#pragma unroll
+        for (int i = 0; i < CH8; i += 4) *reinterpret_cast<uint4v*>(dst + 4 * i) = uint4v{word[i], word[i + 1], word[i + 2], word[i + 3]};
+      } else if constexpr (CH8 == 2) {
+        *reinterpret_cast<uint2v*>(dst) = uint2v{word[0], word[1]};
+      } else {
+        *reinterpret_cast<uint32_t*>(dst) = word[0];
+      }
+      if (part == 0) {
         sd.scale[orow * n_blocks + blk] = qp.s16;
         sd.zero[orow * n_blocks + blk] = qp.z16;
       }
@@ -302,28 +318,43 @@ int allow_gemm_lds(K kernel, size_t bytes) {
                              (int)bytes) == hipSuccess ? PALU_OK : PALU_ERR_HIP;
 }
 
-// Tile height by the number of tokens, tiles dealt to the XCDs in contiguous ranges.
+// The tiles in use and what one costs: microseconds per 4096 inputs of a workgroup with every compute unit busy (measured,
+// R = 2048 per side).  A launch takes the tile whose rounds of workgroups cost least: a larger one reads fewer bytes
+// per product, a smaller one leaves no compute unit idle.
+struct GemmTile {
+  int tm, tn, ks;
+  float us;
+};
+constexpr GemmTile kGemmTiles[] = {{256, 256, 32, 119.f}, {128, 256, 64, 70.f}, {128, 128, 64, 41.f}, {64, 128, 64, 25.f}, {32, 128, 64, 21.f}, {64, 64, 64, 16.f}};
+constexpr int kNumGemmTiles = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]);
+
 template <typename T, bool Q>
 int launch_gemm_t(const EncodeArgs& a, int max_R, int n_sides, int tile_opt, int n_cu, hipStream_t s) {
   auto ceil_div = [](int x, int y) { return (x + y - 1) / y; };
-  // the largest tile that still gives most compute units (7 of 10: measured at 512 .. 4096 tokens) a workgroup:
-  // 256 or 128 token rows of 256 columns; below that 64 rows of 128 columns, two workgroups to a compute unit
-  int tm = 256, tn = 256;
-  auto tiles = [&]() { return ceil_div(max_R, tn) * ceil_div(a.n_tok, tm) * n_sides; };
-  while (tm > 64 && tiles() * 10 < n_cu * 7) tm >>= 1;
-  if (tm == 64) tn = 128;
-  if (tile_opt > 0) {
-    tm = tile_opt == 32 ? 64 : tile_opt;     // 32: the narrow tile
-    tn = tile_opt == 32 ? 128 : 256;
+  auto tiles = [&](const GemmTile& g) { return ceil_div(max_R, g.tn) * ceil_div(a.n_tok, g.tm) * n_sides; };
+  int best = 0;
+  for (int i = 1; i < kNumGemmTiles; ++i) {
+    if (Q && kGemmTiles[i].tn % 128 != 0) continue;                      // whole quantization blocks
+    if (ceil_div(tiles(kGemmTiles[i]), n_cu) * kGemmTiles[i].us < ceil_div(tiles(kGemmTiles[best]), n_cu) * kGemmTiles[best].us) best = i;
   }
+  // option: the first tile of that many rows (32: the smallest tile)
+  for (int i = kNumGemmTiles - 1; tile_opt > 0 && i >= 0; --i)
+    if (kGemmTiles[i].tm == tile_opt && !(Q && kGemmTiles[i].tn % 128 != 0)) best = i;
+  const GemmTile& g = kGemmTiles[best];
   GemmGrid gg;
-  gg.n_col_tiles = ceil_div(max_R, tn);
-  gg.n_row_tiles = ceil_div(a.n_tok, tm);
-  gg.n_tiles = gg.n_col_tiles * gg.n_row_tiles * n_sides;
+  gg.n_col_tiles = ceil_div(max_R, g.tn);
+  gg.n_row_tiles = ceil_div(a.n_tok, g.tm);
+  gg.n_tiles = tiles(g);
   gg.per_xcd = ceil_div(gg.n_tiles, 8);
-  const size_t lds = gemm_lds_bytes(tm, tn);
-  auto fn = tn == 128 ? encode_gemm_kernel<T, Q, 64, 128>
-                      : tm == 256 ? encode_gemm_kernel<T, Q, 256, 256> : tm == 128 ? encode_gemm_kernel<T, Q, 128, 256> : encode_gemm_kernel<T, Q, 64, 256>;
+  gg.rows_fastest = a.n_tok < max_R;
+  const size_t lds = gemm_lds_bytes(g.tm, g.tn, g.ks);
+  using Fn = void (*)(EncodeArgs, GemmGrid);
+  // (a quantized call takes no tile of 64 columns; the entry repeats its neighbour)
+  static const Fn fns[kNumGemmTiles] = {encode_gemm_kernel<T, Q, 256, 256, 32, 1, 2>, encode_gemm_kernel<T, Q, 128, 256, 64, 1, 2>,
+                                        encode_gemm_kernel<T, Q, 128, 128, 64, 1, 2>, encode_gemm_kernel<T, Q, 64, 128, 64, 4, 2>,
+                                        encode_gemm_kernel<T, Q, 32, 128, 64, 4, 1>,
+                                        encode_gemm_kernel<T, Q, Q ? 32 : 64, Q ? 128 : 64, 64, 4, Q ? 1 : 2>};
+  const Fn fn = fns[best];
   if (allow_gemm_lds(fn, lds) != PALU_OK) return PALU_ERR_HIP;
   hipLaunchKernelGGL(fn, dim3((unsigned)(8 * gg.per_xcd)), dim3(256), lds, s, a, gg);
   return hipGetLastError() == hipSuccess ? PALU_OK : PALU_ERR_HIP;

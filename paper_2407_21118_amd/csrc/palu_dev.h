@@ -71,6 +71,17 @@ struct BF16 {
   }
 };
 
+// A wavefront-uniform pointer, made scalar for the compiler too (operands of "s" asm constraints).
+__device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (const unsigned char*)(((uint64_t)hi << 32) | lo);
+}
+
+// s_waitcnt immediate that waits only for the vector-memory counter (gfx9 layout:
+// vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at "no wait").
+constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
+
 // A constant in a vector register that the compiler takes for a per-lane value.  (x & mask) | c becomes one
 // v_and_or_b32 only if at most one of its operands is uniform: with two constants the compiler emits v_and + v_or.
 // The statement emits no instruction, so the compiler still sees, and spaces, everything around the matrix instructions.

@@ -42,17 +42,6 @@ __device__ __forceinline__ float sum_across_halves(float x) {
   return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
 }
 
-// A wavefront-uniform pointer, made scalar for the compiler too (operands of "s" asm constraints).
-__device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const unsigned char*)(((uint64_t)hi << 32) | lo);
-}
-
-// s_waitcnt immediate that waits only for the vector-memory counter (gfx9 layout:
-// vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at "no wait").
-constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
-
 constexpr int kRowPad = 16;                      // bytes of padding per LDS latent row: 16-byte column reads hit distinct banks
 constexpr int kRopeTileB = kTile * kDHead * 2;   // shared-key form: float16 cos/sin rows of one tile in LDS (unpadded, XOR-swizzled)
 constexpr int kLdsBudget = 160 * 1024 - 1024;    // LDS of one CU, less a little slack

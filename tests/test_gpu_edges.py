@@ -41,3 +41,36 @@ def test_encode_token_tiles(heads, group, rk, rv, dtype):
             assert err.max() <= 1e-5 * np.abs(ref).max(), (n_tok, err.max())
             assert (g[n_tok] == 7.0).all()
     say(f"[edges] encode heads={heads} R={layer.R_k}/{layer.R_v} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("heads,rk,rv", [(1, 32, 160), (3, 64, 96), (8, 256, 32)])
+def test_encode_gemm_tiles(heads, rk, rv, dtype):
+    """The prompt-sized projection with every tile, at token counts around the tiles' rows, column counts that end inside
+    a tile (32 .. 2048) and depths shorter than the ring of stages (128 rows: two stages of six)."""
+    layer = synth.uniform_layer(heads, 1, rk, rv)
+    rng = np.random.default_rng(33)
+    d = heads * 128
+    Ak = synth.round_to(rng.standard_normal((d, layer.R_k)) / np.sqrt(d), dtype)
+    Av = synth.round_to(rng.standard_normal((d, layer.R_v)) / np.sqrt(d), dtype)
+    desc = make_desc(layer, dtype)
+    dev_k, dev_v = to_dev(Ak, dtype), to_dev(Av, dtype)
+    eps = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8                # the bound of test_encode_token_tiles
+    for n_tok in (64, 65, 127, 129, 257):
+        x = synth.round_to(rng.standard_normal((n_tok, d)), dtype)
+        refs = O.encode(x, Ak), O.encode(x, Av)
+        for tile in (0, 32, 64, 128, 256):
+            hk = torch.full((n_tok + 1, layer.R_k), 7.0, dtype=dev_k.dtype, device="cuda")
+            hv = torch.full((n_tok + 1, layer.R_v), 7.0, dtype=dev_v.dtype, device="cuda")
+            P.palu_set_option("encode_tile_rows", tile)
+            try:
+                P.palu_encode_kv(desc, to_dev(x, dtype), dev_k, dev_v, hk, layer.R_k, hv, layer.R_v)
+            finally:
+                P.palu_set_option("encode_tile_rows", 0)
+            torch.cuda.synchronize()
+            for got, ref in zip((hk, hv), refs):
+                g = got.float().cpu().numpy()
+                err = np.abs(g[:n_tok] - ref) - eps * np.abs(ref)
+                assert err.max() <= 1e-5 * np.abs(ref).max(), (n_tok, tile, err.max())
+                assert (g[n_tok] == 7.0).all()
+    say(f"[edges] encode GEMM heads={heads} R={layer.R_k}/{layer.R_v} {dtype}")
