@@ -140,7 +140,10 @@ struct ScorePlan {
 };
 
 // widen: let a unit of small groups span 2 or 4 adjacent groups of equal rank and size
-int plan_score(const Meta& m, ScorePlan* p, bool widen = true, bool split16 = false) {
+// split: how the whole-head kernel takes ranks 288 .. 512, as two units of one head each: 0 it does not (half-head
+// wavefronts), 1 halves (multiples of 32), 2 slices of 256 and the rest (4-bit keys: whole quantization blocks)
+inline int first_slice(int r, int split) { return split == 2 ? kSliceRank : (r + 63) / 64 * 32; }
+int plan_score(const Meta& m, ScorePlan* p, bool widen = true, int split = 0) {
   p->n_cls = 0;
   p->total_units = 0;
   p->max_slices = 1;
@@ -191,11 +194,10 @@ int plan_score(const Meta& m, ScorePlan* p, bool widen = true, bool split16 = fa
     const int rc = rank_class(r);
     if (rc < 0) return PALU_ERR_UNSUPPORTED;
     if (rank_class_half(rc)) p->max_slices = std::max(p->max_slices, 2);      // planes for either form below
-    if (rank_class_half(rc) && split16) {
-      // rank 288 .. 512 on the whole-head kernel: two slices of 128 .. 256 rows (multiples of 32), each a unit
-      // of its own rank class that writes one score plane
+    if (rank_class_half(rc) && split != 0) {
+      // rank 288 .. 512 on the whole-head kernel: two slices, each a unit of its own rank class that writes one score plane
       const int nh = std::min(4, m.head_off[j0 + 1] - h);
-      const int r0 = (r + 63) / 64 * 32;
+      const int r0 = first_slice(r, split);
       for (int sl = 0; sl < 2; ++sl) {
         u.nh = nh;
         u.k_off0 = m.k_off[j0] + sl * r0;
@@ -970,7 +972,10 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   // (ranks above 256 in slices); the shared-key form, which leaves it, only takes layers without such ranks
   // (not with option score_fp8, whose weights are laid out per whole head)
   const bool split16 = !k_i4 && g_opt_score_waves == 0 && g_opt_score_fp8 == 0;
-  if ((st = plan_score(m, &sp, !k_lowbit, split16)) != PALU_OK) return st;
+  // 4-bit keys: every head on the whole-head kernel (their ranks are multiples of 128)
+  const bool whole4 = k_bits == 4 && g_opt_score_waves == 0;
+  const int split = split16 ? 1 : (whole4 ? 2 : 0);
+  if ((st = plan_score(m, &sp, !k_lowbit, split)) != PALU_OK) return st;
   if ((st = plan_pv(m, &pp)) != PALU_OK) return st;
   const int quant_block = desc->quant_block > 0 ? desc->quant_block : 128;
   int split_tokens, n_split;
@@ -1000,7 +1005,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       if (!stage_events[i]) return PALU_ERR_INVALID_ARG;
 
   bool enc_pending = enc != nullptr;
-  bool used16 = false, used4 = false;
+  bool used16 = false;
   if (enc_pending && enc->gemm) {
     if ((st = launch_encode(act, *enc, s)) != PALU_OK) return st;
     enc_pending = false;
@@ -1152,28 +1157,26 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         if (shared16) sk_pass_rows = std::min(sk_pass_rows, shared16_rows_per_pass(rcj));
       }
     }
-    // the same with 4-bit keys (blocks of 128 channels, ranks 128 and 256): their tiles are dequantized once per pass
-    // for the queries that share them
-    bool shared4 = !shared_key && k_bits == 4 && quant_block == 128 && m.qpk > 1 && g_opt_score_waves == 0;
+    // the same with 4-bit keys of ranks up to 512: their tiles are dequantized once per pass for the queries that share them
+    bool shared4 = whole4 && m.qpk > 1;
     for (int j = 0; j < m.n_groups && shared4; ++j) {
       const int r = m.k_off[j + 1] - m.k_off[j];
-      shared4 = r == 128 || r == 256;
-      if (shared4) sk_pass_rows = std::min(sk_pass_rows, r == 256 ? 8 : 4);
+      shared4 = r <= 512;
+      if (r % 256 != 0) sk_pass_rows = std::min(sk_pass_rows, 4);
     }
-    used4 = shared4;
     const bool kv_units = shared_key || shared16 || shared4;   // the score units are key/value heads
     const Meta mk = kv_units ? kv_head_meta(m) : m;
     used16 = use16;
     // option score_fp8: those heads rebuild their keys from E4M3-rounded latents and weights (fp16 layers)
     const bool use8 = use16 && g_opt_score_fp8 != 0 && act == PALU_F16;
-    if (use16) {
+    if (use16 || whole4) {
       // the 256-row slices of ranks above 512 run there too and write one score plane each (the planned two are
       // those of the half-head wavefronts)
       for (int i = 0; i < sp.total_units; ++i)
         if (sp.cls_id[sp.unit_cls[i]] == kSlicedCls) sp.units[i].part0 /= 2;
     }
     static thread_local ScorePlan spk;                 // units over key/value heads (shared-key form only)
-    if (kv_units && (st = plan_score(mk, &spk, false, shared16 && split16)) != PALU_OK) return st;
+    if (kv_units && (st = plan_score(mk, &spk, false, shared16 || shared4 ? split : 0)) != PALU_OK) return st;
     const ScorePlan& plan = kv_units ? spk : sp;
 
     // 1. B_k in the score kernel's operand order (shared-key form: and the rotated queries beside it)
@@ -1188,7 +1191,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         fa.rev_lo[f] = (float)(rev - (double)fa.rev_hi[f]);
       }
       fa.meta = mk;
-      fa.layout16 = use16 ? (split16 ? 2 : 1) : (shared4 ? 1 : 0);
+      fa.layout16 = use16 ? (split16 ? 2 : 1) : (whole4 ? 2 : 0);
       int max_r = 0;
       for (int j = 0; j < m.n_groups; ++j) max_r = std::max(max_r, m.k_off[j + 1] - m.k_off[j]);
       const dim3 g((unsigned)(max_r / 16), (unsigned)mk.n_heads, 1u);
@@ -1425,15 +1428,16 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         ScoreFn fn = shared_key ? score_fn_shared(rc, m.qpk <= 4)
                    : shared16 ? nullptr            // chosen per pass below
                    : k16 ? score16_fn(act, rc, lg)
+                   : whole4 ? score16q4_fn(rc, 1, lg)
                    : (k_lowbit ? score_fn_lowbit(rc) : score_fn(act, k_i4, rc * 3 + lg, waves8));
         if (k16) lds = (size_t)score16_lds_bytes(width);
+        if (whole4) lds = (size_t)score16q4_lds_bytes(width);
         if (shared16 || shared4) {
-          if (shared4) lds = (size_t)score16q4_lds_bytes(width);
           // exact shared-key form: passes of up to sk_pass_rows query rows of every key/value head, each pass one
           // launch per flush of units (the key tile is rebuilt once per pass)
           for (int row0 = 0; row0 < m.qpk; row0 += sk_pass_rows) {
             const int rows = std::min(sk_pass_rows, m.qpk - row0);
-            fn = shared4 ? score16q4_fn(rc, rows) : score16q_fn(act, rc, rows);
+            fn = shared4 ? score16q4_fn(rc, std::max(rows, 2), 0) : score16q_fn(act, rc, rows);     // a last pass of one row: an idle one beside it
             if (!fn) return PALU_ERR_UNSUPPORTED;
             if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
             a.sk_row0 = row0;
@@ -1467,7 +1471,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
         }
         if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
-        const unsigned threads = (waves8 && !rank_class_half(rc) && !k16) ? 512 : 256;
+        const unsigned threads = (waves8 && !rank_class_half(rc) && !k16 && !whole4) ? 512 : 256;
         auto flush = [&]() -> int {
           if (a.units.n_units == 0) return PALU_OK;
           set_chunks(a.units.n_units);
@@ -1494,7 +1498,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   for (int h = 0; h < m.n_heads; ++h) {      // half-head wavefronts write two planes per rank slice
     const int rk = m.k_off[m.group_of_head[h] + 1] - m.k_off[m.group_of_head[h]];
     // one wavefront per head: one plane (per rank slice)
-    const bool whole = used4 || (used16 && (split16 ? rk >= 64 : (rank_class_16(rank_class(rk)) || rk > 512)));
+    const bool whole = (whole4 && !no_rope) || (used16 && (split16 ? rk >= 64 : (rank_class_16(rank_class(rk)) || rk > 512)));
     n_parts[h] = no_rope ? (uint8_t)1 : (uint8_t)(((waves8 || sp.half_heads[h]) && !whole) ? 2 * sp.slices[h] : sp.slices[h]);
     max_parts = std::max(max_parts, (int)n_parts[h]);
   }

@@ -21,8 +21,8 @@ ScoreFn score16_fn(int act, int rc, int lg);
 ScoreFn score16_mixed_fn(int act);
 // several queries per key/value head, the key rebuilt once per pass of nq rows (NULL: not compiled)
 ScoreFn score16q_fn(int act, int rc, int nq);
-// the same with 4-bit key latents (ranks 128 and 256)
-ScoreFn score16q4_fn(int rc, int nq);
+// the same with 4-bit key latents (ranks 128 and 256); one query per head (nq = 1): also 2 or 4 groups per workgroup (lg)
+ScoreFn score16q4_fn(int rc, int nq, int lg);
 // option score_fp8
 ScoreFn score8_fn(int rc, int lg);
 struct Fold8Args {

@@ -59,11 +59,18 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 //     the unit's heads are then key/value heads with a.m_qpk query rows each; this launch takes rows a.sk_row0 ..
 //     + a.sk_rows - 1 (at most NQ) of every key/value head: the key tile is rebuilt once, rotated once in float32
 //     and multiplied by each rotated query (NQ = 1: the head's own query)
-// QB: 4: the key latents are 4-bit codes (Sec. 3.4, Appendix A; fp16 layers).  Their tiles then go through registers:
-//     codes, scales and zero-points are requested a tile ahead, dequantized to fp16 at the tile hand-over ((code -
-//     zero) * scale, one rounding; see dequant8_packed) and written to LDS in the layout the matrix instructions
-//     read; only the angle tiles stay LDS-direct.  The hand-over's vector work is not hidden by matrix instructions,
-//     which is why this form is used where several queries share the key tile (NQ > 1) and score_kernel elsewhere.
+// QB: 4: the key latents are 4-bit codes (Sec. 3.4, Appendix A; fp16 layers).  Their tiles go through registers: codes,
+//     scales and zero-points are requested two tiles ahead, dequantized to fp16 ((code - zero) * scale, one rounding; see
+//     dequant8_packed) between the matrix instructions of the tile before and written to LDS in the layout these
+//     read; only the angle tiles stay LDS-direct.  16 x 8192 tokens of a 7B-shaped layer, rank 256: 327 .. 370 us on
+//     score_kernel (two half-head wavefronts per SIMD), 257 .. 288 us here.
+//
+// One wavefront per SIMD issues in order, so the kernel's time is its instruction count where that exceeds the matrix
+// pipe's (128 matrix instructions of 16 cycles per 32-token tile at rank 256).  Two things keep the count down: the
+// weights are pinned to the accumulation registers, which the matrix instructions read in place (left to
+// itself the compiler kept part of them as spilled copies, up to four moves per matrix instruction), and the loop
+// has no branch inside a sub-tile.  Instructions per tile at rank 256: one query 519 -> 500, four queries 1300 -> 790
+// (4 x 16384 tokens, 8 key/value heads: 65 -> 45 us).
 template <typename T, int NK, int G, int NQ = 1, int QB = 0>
 __global__ __launch_bounds__(256) void score16_kernel(ScoreArgs a) {
   const int chunk = blockIdx.x, unit = blockIdx.y, b = blockIdx.z;

@@ -33,10 +33,19 @@ ScoreFn score16q_fn(int act, int rc, int nq) {
   return act == PALU_F16 ? score16q_fn_t<F16>(rc, nq) : score16q_fn_t<BF16>(rc, nq);
 }
 // 4-bit key latents (ranks 128 and 256: whole quantization blocks) with several queries per key/value head
-ScoreFn score16q4_fn(int rc, int nq) {
-  if (rc == 3) return nq <= 2 ? score16_kernel<F16, 4, 1, 2, 4> : (nq <= 4 ? score16_kernel<F16, 4, 1, 4, 4> : nullptr);
-  if (rc == 7) return nq <= 2 ? score16_kernel<F16, 8, 1, 2, 4> : (nq <= 4 ? score16_kernel<F16, 8, 1, 4, 4> : score16_kernel<F16, 8, 1, 8, 4>);
+namespace {
+template <int NK>
+ScoreFn score16q4_fn_n(int nq, int lg) {
+  if (nq == 1) {
+    if constexpr (NK <= 4) { if (lg == 2) return score16_kernel<F16, NK, 4, 1, 4>; }
+    return lg == 1 ? score16_kernel<F16, NK, 2, 1, 4> : score16_kernel<F16, NK, 1, 1, 4>;
+  }
+  if (nq <= 2) return score16_kernel<F16, NK, 1, 2, 4>;
+  if (nq <= 4) return score16_kernel<F16, NK, 1, 4, 4>;
+  if constexpr (NK == 8) return score16_kernel<F16, NK, 1, 8, 4>;
   return nullptr;
 }
+}  // namespace
+ScoreFn score16q4_fn(int rc, int nq, int lg) { return rc == 3 ? score16q4_fn_n<4>(nq, lg) : (rc == 7 ? score16q4_fn_n<8>(nq, lg) : nullptr); }
 
 }  // namespace palu

@@ -11,7 +11,7 @@ from workloads import synth
 
 pytestmark = pytest.mark.gpu
 
-from gpu_util import make_desc, say, to_dev  # noqa: E402
+from gpu_util import TOL_I4, make_desc, rel_err, run_hip, run_oracle, say, to_dev  # noqa: E402
 
 
 @pytest.mark.parametrize("heads,group,rk,rv,dtype", [(1, 1, 32, 96, "f16"), (3, 1, 32, 64, "bf16"), (5, 1, 96, 32, "f16"),
@@ -74,3 +74,29 @@ def test_encode_gemm_tiles(heads, rk, rv, dtype):
                 assert err.max() <= 1e-5 * np.abs(ref).max(), (n_tok, tile, err.max())
                 assert (g[n_tok] == 7.0).all()
     say(f"[edges] encode GEMM heads={heads} R={layer.R_k}/{layer.R_v} {dtype}")
+
+
+@pytest.mark.parametrize("odd_zero", [False, True])
+@pytest.mark.parametrize("heads,group,rk,q_per_kv", [(4, 1, 128, 1), (3, 1, 128, 1), (2, 1, 256, 1), (4, 2, 256, 1), (8, 4, 128, 1),
+                                                     (5, 5, 256, 1), (4, 4, 384, 1), (4, 4, 512, 2), (8, 8, 1024, 1), (2, 2, 128, 5)])
+def test_quantized_keys_whole_head(heads, group, rk, q_per_kv, odd_zero):
+    """4-bit keys on the whole-head score kernel: one, two and four groups to a workgroup, ranks in one slice and in several,
+    lengths around its 32-token tiles; zero-points that the packed dequantization does not hold for (a fraction, a large one)
+    in some tokens of some blocks."""
+    layer = synth.uniform_layer(heads, group, rk, 128, q_per_kv=q_per_kv)
+    rng = np.random.default_rng(5)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    lens = np.array([161, 1, 33, 96], np.int32)
+    case = synth.Case("edges", layer, "f16", 4, 161, draw(4, layer.n_q_heads, 128), lens - 1, draw(4, 161, layer.R_k),
+                      draw(4, 161, layer.R_v), draw(layer.b_elems("k"), by=rk ** -0.5), draw(layer.b_elems("v"), by=128 ** -0.5))
+    case.seq_lens = lens
+    quant = {"k": O.quant_latent(case.Hk)}
+    if odd_zero:
+        zero = quant["k"][2]
+        zero[0, 70, 0] += np.float16(0.5)
+        zero[0, 160, -1] = 2001.0
+        zero[2, 32, -1] -= np.float16(0.25)
+    got, ref = run_hip(case, True, False, quant), run_oracle(case, quant, True, False)
+    err = max(rel_err(got, ref))
+    say(f"[edges] 4-bit keys heads={heads} group={group} rank={rk} q_per_kv={q_per_kv} odd={odd_zero} rel err {err:.3e}")
+    assert err <= TOL_I4
