@@ -27,10 +27,16 @@ VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-pragma-unroll-thres
 BUILD_DIR = os.path.join(HERE, "_build")
 
 
+FLAT = ["-DPALU_SCORE_FLAT=1"]
+
+
 def sources():
-    """(source file, extra flags) of every translation unit."""
-    vgpr = ["score_forms.hip", "score_forms_lowbit.hip", "score16_forms.hip", "score16_shared_forms.hip", "pv.hip", "api.hip"]
-    return [(os.path.join(CSRC, f), VGPR_FORM) for f in vgpr] + [(os.path.join(CSRC, "encode_gemm.hip"), [])]
+    """(source file, extra flags, object name) of every translation unit."""
+    vgpr = ["score16_shared_forms.hip", "score_forms.hip", "score_forms_lowbit.hip", "score16_forms.hip", "pv.hip", "api.hip"]
+    units = [(f, VGPR_FORM, "") for f in vgpr]
+    units += [(f, VGPR_FORM + FLAT, "_flat") for f in ("score16_shared_forms.hip", "score16_forms.hip")]
+    units += [("encode_gemm.hip", [], "")]
+    return [(os.path.join(CSRC, f), extra, os.path.splitext(f)[0] + suffix + ".o") for f, extra, suffix in units]
 
 
 def _run(procs, verbose):
@@ -49,8 +55,8 @@ def build_library(verbose: bool = True) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     inc = ["-I", os.path.join(HERE, "..", "include")]
     objects, procs = [], []
-    for src, extra in sources():
-        obj = os.path.join(BUILD_DIR, os.path.splitext(os.path.basename(src))[0] + ".o")
+    for src, extra, name in sources():
+        obj = os.path.join(BUILD_DIR, name)
         cmd = [hipcc] + HIPCC_FLAGS + extra + inc + ["-c", "-o", obj, src]
         if verbose:
             print(" ".join(cmd), flush=True)

@@ -1320,35 +1320,54 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         a.rope_tile_stride = shared_key ? kRopeRowsBytes : kRopeTileBytes;
       }
       const int tiles = ceil_div(seq_len, kTile);
+      // the kernels address a run of the cache with 32-bit byte offsets, and rows of it with 24-bit numbers (and its
+      // angle tiles with 32-bit byte offsets)
+      const int seg_limit = (int)std::max(1LL, std::min<long long>({(1LL << 31) / ((long long)Rk * 2 * kTile), (1LL << 24) / kTile,
+                                                                    (1LL << 31) / kRopeTableStride}));
+      a.seg_tiles = seg_limit;
       // Sequence chunks per (sequence, unit): every launch (one per rank class) should fill
       // the chip by itself, since launches on one stream run one after the other.
       auto set_chunks = [&](int launch_units) {
         int n_chunks = std::max(1, std::min(tiles, (int)std::lround((double)device_cu_count() / (launch_units * batch))));
         if (g_opt_score_chunks > 0) n_chunks = std::min(tiles, (int)g_opt_score_chunks);
-        // the kernel addresses a chunk of the cache with 32-bit byte offsets, and rows of it with 24-bit numbers
-        // (and its angle tiles with 32-bit byte offsets)
-        const long long chunk_limit_tiles = std::max(1LL, std::min<long long>({(1LL << 31) / ((long long)Rk * 2 * kTile), (1LL << 24) / kTile,
-                                                                                 (1LL << 31) / kRopeTableStride}));
-        n_chunks = std::max(n_chunks, (int)ceil_div(tiles, (int)std::min<long long>(chunk_limit_tiles, tiles)));
+        n_chunks = std::max(n_chunks, (int)ceil_div(tiles, std::min(seg_limit, tiles)));
         const int chunk_tiles = ceil_div(tiles, n_chunks);
         a.chunk_tokens = chunk_tiles * kTile;
         a.n_chunks = ceil_div(tiles, chunk_tiles);
+      };
+      // The whole-head kernel's grid: one workgroup per compute unit over all units of the launch.  Where the sequences have
+      // one length and as many workgroups per (unit, sequence) as fit the chip fill 15/16 of it, a workgroup's run of tiles lies in
+      // one sequence; else the runs go through the tiles of all sequences (48 sequences of 1022 .. 2043 tokens, 8 units: 384
+      // workgroups of one sequence each 185 us, 256 equal runs 144 us; the way into the longer start costs 0.4 us).
+      auto flat16 = [&](int launch_units) {
+        const int fit = device_cu_count() / std::max(1, (int)std::min<long long>((long long)launch_units * batch, 1 << 30));
+        if (seq_lens != nullptr) return true;
+        return g_opt_score_chunks == 0 && batch > 1 && (long long)fit * launch_units * batch * 16 < device_cu_count() * 15LL && tiles > fit;
+      };
+      auto grid16 = [&](int launch_units, bool flat) {
+        const int per = (int)std::min<long long>((long long)launch_units * (flat ? 1 : batch), 1 << 30);
+        const long long all = flat ? (long long)batch * tiles : tiles;               // at 64 bytes and more a row: far below 2^31
+        const long long want = g_opt_score_chunks > 0 ? (long long)g_opt_score_chunks * (flat ? batch : 1) : std::max(1, device_cu_count() / per);
+        a.n_wg = (int)std::min(std::min(all, std::max<long long>(want, flat ? 1 : ceil_div(tiles, seg_limit))), 1LL << 20);
+        a.run = (int)(all / a.n_wg);
+        a.run_more = (int)(all % a.n_wg);
+        return dim3((unsigned)a.n_wg, (unsigned)launch_units, flat ? 1u : (unsigned)batch);
       };
       // Groups of different ranks, every class on the whole-head kernel with one group per workgroup: ONE launch
       // where one round of workgroups covers the layer.  Launches on one stream run one after the other and every
       // workgroup start costs several microseconds (the head's weights go to registers, the tile ring fills), so
       // a launch per class pays that once per class; here every workgroup has a compute unit to itself, starts
-      // once, and the chunk lengths per class are chosen so that all of them end at about the same time.
+      // once, and the workgroups per class are chosen so that all of them end at about the same time.
       bool mixed = use16 && !shared16 && !shared4 && !use8 && g_opt_score_mixed != 0 && g_opt_score_chunks == 0 &&
                    plan.n_cls > 1 && plan.n_cls <= kMaxMixClasses && plan.total_units <= kMaxScoreUnits;
       for (int cls = 0; cls < plan.n_cls && mixed; ++cls) {
         const int id = plan.cls_id[cls];
         if (id == kSlicedCls || id % 3 != 0 || !rank_class_16(id / 3)) mixed = false;
       }
-      int order[kMaxMixClasses], n_units_cls[kMaxMixClasses] = {}, one_round[kMaxMixClasses];
+      int order[kMaxMixClasses], n_units_cls[kMaxMixClasses] = {}, one_round[kMaxMixClasses];     // one_round: workgroups per unit of a class
       bool use_one_round = false;
       double mix_per_wg = 0.0;
-      long long mix_chunk_limit_tiles = 1;
+      const long long all_tiles = (long long)batch * tiles;
       // measured (uniform layers of each rank, 2048- and 1024-token chunks with every compute unit busy): microseconds per
       // 1000 tokens of one workgroup by rank / 32
       static const double kCost[9] = {0, 0, 30, 34, 38, 43, 47, 53, 56};
@@ -1362,22 +1381,20 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         for (int cls = 0; cls < plan.n_cls; ++cls) work += weight(plan.cls_id[cls] / 3 + 1) * n_units_cls[cls] * (double)batch * seq_len;
         const int cus = device_cu_count();
         mix_per_wg = work / ((g_opt_score_mixed > 1 ? (double)g_opt_score_mixed : 3.0) * cus);
-        const long long chunk_limit_tiles = mix_chunk_limit_tiles = std::max(1LL, std::min<long long>({(1LL << 31) / ((long long)Rk * 2 * kTile), (1LL << 24) / kTile,
-                                                                                 (1LL << 31) / kRopeTableStride}));
-        // One round where it fits: every workgroup has a compute unit to itself and starts once.  Chunks go, one at
-        // a time, to the class whose workgroups would run longest, while the launch still fits the chip.
+        // One round where it fits: every workgroup has a compute unit to itself and starts once.  Workgroups go, one per
+        // unit at a time, to the class whose workgroups would run longest, while the launch still fits the chip.
         if (g_opt_score_mixed == 1) {
           long long total = 0;
           for (int cls = 0; cls < plan.n_cls; ++cls) {
-            one_round[cls] = (int)ceil_div(tiles, (int)std::min<long long>(tiles, chunk_limit_tiles));
-            total += (long long)one_round[cls] * n_units_cls[cls] * batch;
+            one_round[cls] = 1;
+            total += n_units_cls[cls];
           }
-          auto wg_us = [&](int cls) { return kStartUs + ceil_div(tiles, one_round[cls]) * kTile * weight(plan.cls_id[cls] / 3 + 1) * 1e-3; };
+          auto wg_us = [&](int cls) { return kStartUs + (double)((all_tiles + one_round[cls] - 1) / one_round[cls]) * kTile * weight(plan.cls_id[cls] / 3 + 1) * 1e-3; };
           while (total <= cus) {
             int worst = 0;
             for (int cls = 1; cls < plan.n_cls; ++cls) if (wg_us(cls) > wg_us(worst)) worst = cls;
-            const long long more = (long long)n_units_cls[worst] * batch;
-            if (one_round[worst] >= tiles || total + more > cus) break;
+            const int more = n_units_cls[worst];
+            if (one_round[worst] >= all_tiles || total + more > cus) break;
             ++one_round[worst];
             total += more;
           }
@@ -1395,18 +1412,16 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         size_t lds = 0;
         for (int x = 0; x < plan.n_cls; ++x) {
           const int cls = order[x], nk = plan.cls_id[cls] / 3 + 1;
-          int chunk_tiles = (int)std::min<long long>(std::max<long long>(1, std::llround(mix_per_wg / weight(nk) / kTile)), std::min<long long>(tiles, mix_chunk_limit_tiles));
-          const int n_chunks = use_one_round ? one_round[cls] : ceil_div(tiles, chunk_tiles);
-          chunk_tiles = ceil_div(tiles, n_chunks);               // chunks of equal length
+          const long long run = std::max<long long>(1, std::llround(mix_per_wg / weight(nk) / kTile));       // option: several rounds of about this many tiles
           a.mix.first[x] = (int)first;
-          a.mix.n_chunks[x] = ceil_div(tiles, chunk_tiles);
-          a.mix.chunk_tokens[x] = chunk_tiles * kTile;
+          a.mix.n_wg[x] = use_one_round ? one_round[cls] : (int)std::min((all_tiles + run - 1) / run, 1LL << 20);
+          a.mix.run[x] = (int)(all_tiles / a.mix.n_wg[x]);
+          a.mix.run_more[x] = (int)(all_tiles % a.mix.n_wg[x]);
           a.mix.unit0[x] = a.units.n_units;
-          a.mix.n_units[x] = n_units_cls[cls];
           a.mix.nk[x] = nk;
           for (int i = 0; i < plan.total_units; ++i)
             if (plan.unit_cls[i] == cls) a.units.u[a.units.n_units++] = plan.units[i];
-          first += (long long)a.mix.n_chunks[x] * n_units_cls[cls] * batch;
+          first += (long long)a.mix.n_wg[x] * n_units_cls[cls];
           lds = std::max(lds, (size_t)score16_lds_bytes(32 * nk));
         }
         if (first >= (1LL << 31)) return PALU_ERR_UNSUPPORTED;
@@ -1427,8 +1442,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         const bool k16 = use16 && rank_class_16(rc);
         ScoreFn fn = shared_key ? score_fn_shared(rc, m.qpk <= 4)
                    : shared16 ? nullptr            // chosen per pass below
-                   : k16 ? score16_fn(act, rc, lg)
-                   : whole4 ? score16q4_fn(rc, 1, lg)
+                   : (k16 || whole4) ? nullptr     // chosen per launch below
                    : (k_lowbit ? score_fn_lowbit(rc) : score_fn(act, k_i4, rc * 3 + lg, waves8));
         if (k16) lds = (size_t)score16_lds_bytes(width);
         if (whole4) lds = (size_t)score16q4_lds_bytes(width);
@@ -1437,18 +1451,19 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           // launch per flush of units (the key tile is rebuilt once per pass)
           for (int row0 = 0; row0 < m.qpk; row0 += sk_pass_rows) {
             const int rows = std::min(sk_pass_rows, m.qpk - row0);
-            fn = shared4 ? score16q4_fn(rc, std::max(rows, 2), 0) : score16q_fn(act, rc, rows);     // a last pass of one row: an idle one beside it
-            if (!fn) return PALU_ERR_UNSUPPORTED;
-            if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
             a.sk_row0 = row0;
             a.sk_rows = rows;
             a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
             a.units.n_units = 0;
             auto flush_q = [&]() -> int {
               if (a.units.n_units == 0) return PALU_OK;
-              set_chunks(a.units.n_units);
-              const dim3 grid((unsigned)a.n_chunks, (unsigned)a.units.n_units, (unsigned)batch);
-              hipLaunchKernelGGL(fn, grid, dim3(256), lds, s, a);
+              const bool flat = flat16(a.units.n_units);
+              const int nq = std::max(rows, 2);                  // a last pass of one row: an idle one beside it
+              fn = shared4 ? (flat ? score16q4_fn<true>(rc, nq, 0) : score16q4_fn<false>(rc, nq, 0))
+                           : (flat ? score16q_fn<true>(act, rc, nq) : score16q_fn<false>(act, rc, nq));
+              if (!fn) return PALU_ERR_UNSUPPORTED;
+              if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
+              hipLaunchKernelGGL(fn, grid16(a.units.n_units, flat), dim3(256), lds, s, a);
               a.units.n_units = 0;
               return launch_ok();
             };
@@ -1461,7 +1476,8 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           }
           continue;
         }
-        if (!fn) return PALU_ERR_UNSUPPORTED;
+        const bool form16 = k16 || whole4;
+        if (!fn && !form16) return PALU_ERR_UNSUPPORTED;
         const bool k8 = k16 && use8 && !sliced;
         if (k8) {
           fn = score8_fn(rc, lg);
@@ -1470,12 +1486,22 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         } else {
           a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
         }
-        if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
         const unsigned threads = (waves8 && !rank_class_half(rc) && !k16 && !whole4) ? 512 : 256;
         auto flush = [&]() -> int {
           if (a.units.n_units == 0) return PALU_OK;
-          set_chunks(a.units.n_units);
-          const dim3 grid((unsigned)a.n_chunks, (unsigned)a.units.n_units, (unsigned)batch);
+          dim3 grid(1);
+          if (form16 && !k8) {
+            const bool flat = flat16(a.units.n_units);
+            fn = whole4 ? (flat ? score16q4_fn<true>(rc, 1, lg) : score16q4_fn<false>(rc, 1, lg))
+                        : (flat ? score16_fn<true>(act, rc, lg) : score16_fn<false>(act, rc, lg));
+            if (!fn) return PALU_ERR_UNSUPPORTED;
+            grid = grid16(a.units.n_units, flat);
+          } else {
+            set_chunks(a.units.n_units);
+            grid = dim3((unsigned)a.n_chunks, (unsigned)a.units.n_units, (unsigned)batch);
+          }
+          const int rc2 = allow_lds(fn, lds);
+          if (rc2 != PALU_OK) return rc2;
           hipLaunchKernelGGL(fn, grid, dim3(threads), lds, s, a);
           a.units.n_units = 0;
           return launch_ok();

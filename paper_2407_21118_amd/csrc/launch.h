@@ -15,14 +15,15 @@ ScoreFn score_fn(int act, bool i4, int cls_id, bool w8);
 ScoreFn score_fn_lowbit(int rc);
 // fp16 shared-key form (option shared_key_fp16): at most 4, else at most 16 queries per key/value head
 ScoreFn score_fn_shared(int rc, bool four);
-// unquantized latents, ranks 64 .. 256, one whole head per wavefront
-ScoreFn score16_fn(int act, int rc, int lg);
-// one launch over several rank classes of the above
+// unquantized latents, ranks 64 .. 256, one whole head per wavefront.  FLAT: runs through the tiles of all sequences
+// (each value is a translation unit of its own, also of the forms below)
+template <bool FLAT> ScoreFn score16_fn(int act, int rc, int lg);
+// one launch over several rank classes of the above, FLAT
 ScoreFn score16_mixed_fn(int act);
 // several queries per key/value head, the key rebuilt once per pass of nq rows (NULL: not compiled)
-ScoreFn score16q_fn(int act, int rc, int nq);
+template <bool FLAT> ScoreFn score16q_fn(int act, int rc, int nq);
 // the same with 4-bit key latents (ranks 128 and 256); one query per head (nq = 1): also 2 or 4 groups per workgroup (lg)
-ScoreFn score16q4_fn(int rc, int nq, int lg);
+template <bool FLAT> ScoreFn score16q4_fn(int rc, int nq, int lg);
 // option score_fp8
 ScoreFn score8_fn(int rc, int lg);
 struct Fold8Args {

@@ -209,10 +209,9 @@ constexpr int kMaxMixClasses = 7;       // ranks 64, 96, .. 256
 struct ScoreMix {
   int n_cls;
   int first[kMaxMixClasses];            // first workgroup of the class
-  int n_chunks[kMaxMixClasses];         // sequence chunks per (unit, sequence)
-  int chunk_tokens[kMaxMixClasses];     // tokens per chunk (multiple of kTile)
-  int unit0[kMaxMixClasses];            // the class's units: unit0 .. unit0 + n_units - 1 of ScoreArgs.units
-  int n_units[kMaxMixClasses];
+  int n_wg[kMaxMixClasses];             // workgroups per unit ...
+  int run[kMaxMixClasses], run_more[kMaxMixClasses];   // ... as in ScoreArgs
+  int unit0[kMaxMixClasses];            // the class's first unit in ScoreArgs.units
   int nk[kMaxMixClasses];               // rank / 32
 };
 struct ScoreUnits {
@@ -239,6 +238,9 @@ struct ScoreArgs {
   int lpad;                  // row pitch of the score buffer (floats)
   int batch;
   int chunk_tokens;          // tokens per workgroup (multiple of kTile)
+  int seg_tiles;             // score16_kernel: longest run of tiles that its 32-bit offsets address
+  int n_wg;                  // ... workgroups that share a unit's tiles, of all sequences or of one ...
+  int run, run_more;         // ... and, for sequences of equal length, the number of those tiles / n_wg and the remainder
   int n_chunks;
   int n_heads;
   int n_blocks_q;            // R_k / quant_block (int4 only)

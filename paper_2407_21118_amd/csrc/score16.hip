@@ -53,7 +53,8 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // NK: k-steps of 32: the rank of every head of the workgroup is 32 * NK (NK <= 8)
 // G:  groups spanned by the workgroup's heads (1, 2 or 4 adjacent groups of equal rank): the staged
 //     latent row is G * 32 * NK columns wide
-// grid (sequence chunks, units, batch), 256 threads.  a.mfold: B_k^T in the operand order of
+// FLAT: a workgroup's run goes through the tiles of all sequences, else it lies in one
+// grid (workgroups per unit and sequence, units, sequences; FLAT: per unit, units), 256 threads.  a.mfold: B_k^T in the operand order of
 // fold_body's 16-feature layout.
 // NQ: queries that share the wavefront's key/value head (grouped-query layers, several query tokens per sequence):
 //     the unit's heads are then key/value heads with a.m_qpk query rows each; this launch takes rows a.sk_row0 ..
@@ -71,24 +72,25 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // itself the compiler kept part of them as spilled copies, up to four moves per matrix instruction), and the loop
 // has no branch inside a sub-tile.  Instructions per tile at rank 256: one query 519 -> 500, four queries 1300 -> 790
 // (4 x 16384 tokens, 8 key/value heads: 65 -> 45 us).
-template <typename T, int NK, int G, int NQ = 1, int QB = 0>
+template <typename T, int NK, int G, int NQ, int QB, bool FLAT>
 __global__ __launch_bounds__(256) void score16_kernel(ScoreArgs a) {
-  const int chunk = blockIdx.x, unit = blockIdx.y, b = blockIdx.z;
-  const int chunk_tokens = a.chunk_tokens;
+  const int wg = blockIdx.x, n_wg = a.n_wg, unit = blockIdx.y, seq = blockIdx.z, run = a.run, run_more = a.run_more;
 #include "score16_body.inc"
 }
 
-// The same body with its place in the launch as arguments (sequence chunk of chunk_tokens tokens, unit, sequence), so
-// that a launch over several rank classes can hand each workgroup the body of its unit's class.
-template <typename T, int NK, int G, int NQ = 1, int QB = 0>
-__device__ __forceinline__ void score16_body(const ScoreArgs& a, const int chunk, const int unit, const int b, const int chunk_tokens) {
+// The same body with its place in the launch as arguments (workgroup wg of n_wg of the unit), so that a launch over
+// several rank classes can hand each workgroup the body of its unit's class.
+template <typename T, int NK, int G>
+__device__ __forceinline__ void score16_body(const ScoreArgs& a, const int wg, const int n_wg, const int unit, const int run, const int run_more) {
+  constexpr int NQ = 1, QB = 0, seq = 0;
+  constexpr bool FLAT = true;
 #include "score16_body.inc"
 }
 
 // One launch for a layer whose groups have different ranks (the ranks a search assigns per group, Sec. 3.3):
-// a.mix lists the rank classes, heaviest first, each with its own chunk length (chosen by the host so that
-// workgroups of different classes take about as long) and its units, which lie side by side in a.units.
-// grid (sum over classes of chunks x units x batch), 256 threads; the workgroups of a class are consecutive.
+// a.mix lists the rank classes, heaviest first, each with its own number of workgroups per unit (chosen by the host so
+// that workgroups of different classes take about as long) and its units, which lie side by side in a.units.
+// grid (sum over classes of workgroups x units), 256 threads; the workgroups of a class are consecutive.
 template <typename T>
 __global__ __launch_bounds__(256) void score16_mixed_kernel(ScoreArgs a) {
   int c = 0;
@@ -96,18 +98,16 @@ __global__ __launch_bounds__(256) void score16_mixed_kernel(ScoreArgs a) {
   for (int i = 1; i < kMaxMixClasses; ++i)
     if (i < a.mix.n_cls && (int)blockIdx.x >= a.mix.first[i]) c = i;
   const int local = (int)blockIdx.x - a.mix.first[c];
-  const int n_chunks = a.mix.n_chunks[c], n_units = a.mix.n_units[c];
-  const int chunk = local % n_chunks, rest = local / n_chunks;
-  const int unit = a.mix.unit0[c] + rest % n_units, b = rest / n_units;
-  const int ct = a.mix.chunk_tokens[c];
+  const int n_wg = a.mix.n_wg[c], wg = local % n_wg, unit = a.mix.unit0[c] + local / n_wg;
+  const int run = a.mix.run[c], run_more = a.mix.run_more[c];
   switch (a.mix.nk[c]) {
-    case 2: score16_body<T, 2, 1>(a, chunk, unit, b, ct); break;
-    case 3: score16_body<T, 3, 1>(a, chunk, unit, b, ct); break;
-    case 4: score16_body<T, 4, 1>(a, chunk, unit, b, ct); break;
-    case 5: score16_body<T, 5, 1>(a, chunk, unit, b, ct); break;
-    case 6: score16_body<T, 6, 1>(a, chunk, unit, b, ct); break;
-    case 7: score16_body<T, 7, 1>(a, chunk, unit, b, ct); break;
-    default: score16_body<T, 8, 1>(a, chunk, unit, b, ct); break;
+    case 2: score16_body<T, 2, 1>(a, wg, n_wg, unit, run, run_more); break;
+    case 3: score16_body<T, 3, 1>(a, wg, n_wg, unit, run, run_more); break;
+    case 4: score16_body<T, 4, 1>(a, wg, n_wg, unit, run, run_more); break;
+    case 5: score16_body<T, 5, 1>(a, wg, n_wg, unit, run, run_more); break;
+    case 6: score16_body<T, 6, 1>(a, wg, n_wg, unit, run, run_more); break;
+    case 7: score16_body<T, 7, 1>(a, wg, n_wg, unit, run, run_more); break;
+    default: score16_body<T, 8, 1>(a, wg, n_wg, unit, run, run_more); break;
   }
 }
 

@@ -3,16 +3,21 @@
 #include "score16.hip"
 #include "score8.hip"
 
+#ifndef PALU_SCORE_FLAT
+#define PALU_SCORE_FLAT 0
+#endif
+
 namespace palu {
 
 namespace {
+constexpr bool kFlat = PALU_SCORE_FLAT != 0;
 
 // unquantized latents, ranks 64 .. 256, one query per head: one whole head per wavefront (score16.hip)
 template <typename T, int NK>
 ScoreFn score16_fn_g(int lg) {
-  if constexpr (NK <= 2) { if (lg == 2) return score16_kernel<T, NK, 4>; }
-  if constexpr (NK <= 4) { if (lg >= 1) return score16_kernel<T, NK, 2>; }
-  return score16_kernel<T, NK, 1>;
+  if constexpr (NK <= 2) { if (lg == 2) return score16_kernel<T, NK, 4, 1, 0, kFlat>; }
+  if constexpr (NK <= 4) { if (lg >= 1) return score16_kernel<T, NK, 2, 1, 0, kFlat>; }
+  return score16_kernel<T, NK, 1, 1, 0, kFlat>;
 }
 template <typename T>
 ScoreFn score16_fn_t(int rc, int lg) {
@@ -26,6 +31,17 @@ ScoreFn score16_fn_t(int rc, int lg) {
     default: return score16_fn_g<T, 8>(lg);
   }
 }
+}  // namespace
+
+template <>
+ScoreFn score16_fn<kFlat>(int act, int rc, int lg) {
+  return act == PALU_F16 ? score16_fn_t<F16>(rc, lg) : score16_fn_t<BF16>(rc, lg);
+}
+
+#if PALU_SCORE_FLAT
+ScoreFn score16_mixed_fn(int act) { return act == PALU_F16 ? score16_mixed_kernel<F16> : score16_mixed_kernel<BF16>; }
+#else
+namespace {
 template <int NK>
 ScoreFn score8_fn_g(int lg) {
   if constexpr (NK <= 2) { if (lg == 2) return score8_kernel<NK, 4>; }
@@ -46,14 +62,10 @@ ScoreFn score8_fn(int rc, int lg) {
   }
 }
 
-ScoreFn score16_fn(int act, int rc, int lg) {
-  return act == PALU_F16 ? score16_fn_t<F16>(rc, lg) : score16_fn_t<BF16>(rc, lg);
-}
-ScoreFn score16_mixed_fn(int act) { return act == PALU_F16 ? score16_mixed_kernel<F16> : score16_mixed_kernel<BF16>; }
-
 int launch_fold8(const Fold8Args& a, hipStream_t s) {
   hipLaunchKernelGGL(fold8_kernel<F16>, dim3((unsigned)a.meta.n_heads, 4u), dim3(256), 0, s, a);
   return hipGetLastError() == hipSuccess ? PALU_OK : PALU_ERR_HIP;
 }
+#endif
 
 }  // namespace palu

@@ -2,15 +2,20 @@
 #include "launch.h"
 #include "score16.hip"
 
+#ifndef PALU_SCORE_FLAT
+#define PALU_SCORE_FLAT 0
+#endif
+
 namespace palu {
 
 namespace {
+constexpr bool kFlat = PALU_SCORE_FLAT != 0;
 
 template <typename T, int NK>
 ScoreFn score16q_fn_n(int nq) {
-  if (nq <= 2) return score16_kernel<T, NK, 1, 2>;
-  if (nq <= 4) return score16_kernel<T, NK, 1, 4>;
-  if constexpr (NK >= 6) { if (nq <= 8) return score16_kernel<T, NK, 1, 8>; }
+  if (nq <= 2) return score16_kernel<T, NK, 1, 2, 0, kFlat>;
+  if (nq <= 4) return score16_kernel<T, NK, 1, 4, 0, kFlat>;
+  if constexpr (NK >= 6) { if (nq <= 8) return score16_kernel<T, NK, 1, 8, 0, kFlat>; }
   return nullptr;
 }
 template <typename T>
@@ -29,7 +34,8 @@ ScoreFn score16q_fn_t(int rc, int nq) {
 
 }  // namespace
 
-ScoreFn score16q_fn(int act, int rc, int nq) {
+template <>
+ScoreFn score16q_fn<kFlat>(int act, int rc, int nq) {
   return act == PALU_F16 ? score16q_fn_t<F16>(rc, nq) : score16q_fn_t<BF16>(rc, nq);
 }
 // 4-bit key latents (ranks 128 and 256: whole quantization blocks) with several queries per key/value head
@@ -37,15 +43,16 @@ namespace {
 template <int NK>
 ScoreFn score16q4_fn_n(int nq, int lg) {
   if (nq == 1) {
-    if constexpr (NK <= 4) { if (lg == 2) return score16_kernel<F16, NK, 4, 1, 4>; }
-    return lg == 1 ? score16_kernel<F16, NK, 2, 1, 4> : score16_kernel<F16, NK, 1, 1, 4>;
+    if constexpr (NK <= 4) { if (lg == 2) return score16_kernel<F16, NK, 4, 1, 4, kFlat>; }
+    return lg == 1 ? score16_kernel<F16, NK, 2, 1, 4, kFlat> : score16_kernel<F16, NK, 1, 1, 4, kFlat>;
   }
-  if (nq <= 2) return score16_kernel<F16, NK, 1, 2, 4>;
-  if (nq <= 4) return score16_kernel<F16, NK, 1, 4, 4>;
-  if constexpr (NK == 8) return score16_kernel<F16, NK, 1, 8, 4>;
+  if (nq <= 2) return score16_kernel<F16, NK, 1, 2, 4, kFlat>;
+  if (nq <= 4) return score16_kernel<F16, NK, 1, 4, 4, kFlat>;
+  if constexpr (NK == 8) return score16_kernel<F16, NK, 1, 8, 4, kFlat>;
   return nullptr;
 }
 }  // namespace
-ScoreFn score16q4_fn(int rc, int nq, int lg) { return rc == 3 ? score16q4_fn_n<4>(nq, lg) : (rc == 7 ? score16q4_fn_n<8>(nq, lg) : nullptr); }
+template <>
+ScoreFn score16q4_fn<kFlat>(int rc, int nq, int lg) { return rc == 3 ? score16q4_fn_n<4>(nq, lg) : (rc == 7 ? score16q4_fn_n<8>(nq, lg) : nullptr); }
 
 }  // namespace palu

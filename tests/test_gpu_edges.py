@@ -11,7 +11,7 @@ from workloads import synth
 
 pytestmark = pytest.mark.gpu
 
-from gpu_util import TOL_I4, make_desc, rel_err, run_hip, run_oracle, say, to_dev  # noqa: E402
+from gpu_util import TOL_FP, TOL_I4, make_desc, rel_err, run_hip, run_oracle, say, to_dev  # noqa: E402
 
 
 @pytest.mark.parametrize("heads,group,rk,rv,dtype", [(1, 1, 32, 96, "f16"), (3, 1, 32, 64, "bf16"), (5, 1, 96, 32, "f16"),
@@ -100,3 +100,26 @@ def test_quantized_keys_whole_head(heads, group, rk, q_per_kv, odd_zero):
     err = max(rel_err(got, ref))
     say(f"[edges] 4-bit keys heads={heads} group={group} rank={rk} q_per_kv={q_per_kv} odd={odd_zero} rel err {err:.3e}")
     assert err <= TOL_I4
+
+
+@pytest.mark.parametrize("ranks,q_per_kv,dtype", [([64], 1, "f16"), ([256], 1, "bf16"), ([128], 3, "f16"), ([64, 96, 256], 1, "f16"), ([320], 1, "f16")])
+@pytest.mark.parametrize("lens", ["mixed", "many", "equal"])
+def test_runs_through_sequences(ranks, q_per_kv, dtype, lens):
+    """Score workgroups whose run of tiles goes through several sequences: empty sequences among them, more sequences than
+    lanes, sequences of one tile, one length but more sequences than compute units."""
+    n = len(ranks)
+    layer = synth.Layer(4 * n, 128, list(range(0, 4 * n + 1, 4)), list(np.cumsum([0] + ranks)), list(np.cumsum([0] + [64] * n)), q_per_kv=q_per_kv)
+    seq = {"mixed": 193, "many": 65, "equal": 65}[lens]
+    sl = {"mixed": [193, 0, 1, 64, 0, 0, 32, 33, 160], "many": [(37 * i) % 66 for i in range(150)], "equal": [65] * 300}[lens]
+    batch = len(sl)
+    rng = np.random.default_rng(6)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, dtype)  # noqa: E731
+    case = synth.Case("edges", layer, dtype, batch, seq, draw(batch, layer.n_q_heads, 128), np.maximum(np.array(sl, np.int32) - 1, 0),
+                      draw(batch, seq, layer.R_k), draw(batch, seq, layer.R_v), draw(layer.b_elems("k"), by=0.1), draw(layer.b_elems("v"), by=0.1))
+    if lens != "equal":
+        case.seq_lens = np.array(sl, np.int32)
+    got, ref = run_hip(case), run_oracle(case)
+    some = np.array(sl) > 0
+    err = max(rel_err(got[some], ref[some]))
+    say(f"[edges] runs ranks={ranks} q_per_kv={q_per_kv} {dtype} {lens} rel err {err:.3e}")
+    assert err <= TOL_FP and not got[~some].any()
