@@ -304,6 +304,7 @@ struct CombineArgs {
   int split_tokens;
   int seq_len;
   int o_stride;
+  int batch;
   Meta meta;
 };
 

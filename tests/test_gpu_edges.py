@@ -123,3 +123,38 @@ def test_runs_through_sequences(ranks, q_per_kv, dtype, lens):
     err = max(rel_err(got[some], ref[some]))
     say(f"[edges] runs ranks={ranks} q_per_kv={q_per_kv} {dtype} {lens} rel err {err:.3e}")
     assert err <= TOL_FP and not got[~some].any()
+
+
+@pytest.mark.parametrize("batch,heads,group,rv,q_per_kv", [(31, 4, 4, 64, 1), (32, 4, 4, 96, 1), (33, 3, 1, 32, 2), (256, 4, 2, 64, 1), (257, 2, 2, 288, 3), (1, 256, 4, 32, 1)])
+def test_merge_of_many_rows(batch, heads, group, rv, q_per_kv):
+    """The merge kernels around their row counts (128 and 1024 rows; rows that do not fill a workgroup): outputs against the
+    oracle, and the latent output times B_v against them."""
+    layer = synth.uniform_layer(heads, group, 64, rv, q_per_kv=q_per_kv)
+    rng = np.random.default_rng(8)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    seq = 130
+    lens = np.array([(61 * i) % (seq + 1) for i in range(batch)], np.int32)
+    lens[0] = seq
+    case = synth.Case("edges", layer, "f16", batch, seq, draw(batch, layer.n_q_heads, 128), np.maximum(lens - 1, 0), draw(batch, seq, layer.R_k),
+                      draw(batch, seq, layer.R_v), draw(layer.b_elems("k"), by=0.1), draw(layer.b_elems("v"), by=0.1))
+    case.seq_lens = lens
+    got, ref = run_hip(case), run_oracle(case)
+    some = lens > 0
+    err = max(rel_err(got[some], ref[some]))
+    assert err <= TOL_FP and not got[~some].any()
+    desc = make_desc(layer, "f16")
+    table = P.palu_rope_table_init(layer.rope_theta, 128, seq)
+    lat = P.palu_attn_decode_latent(desc, batch, seq, seq, to_dev(case.q, "f16"), torch.from_numpy(case.q_pos).cuda(), to_dev(case.Hk, "f16"),
+                                    to_dev(case.Hv, "f16"), to_dev(case.Bk, "f16"), table, seq, seq_lens=torch.from_numpy(lens).cuda())
+    torch.cuda.synchronize()
+    z = lat.cpu().numpy().astype(np.float64).reshape(batch, layer.n_q_heads, rv)
+    B = np.asarray(case.Bv, np.float64)
+    out = np.empty((batch, layer.n_q_heads, 128))
+    for h in range(layer.n_q_heads):
+        kv = h // q_per_kv
+        j, u = kv // group, kv % group
+        Bj = B[j * rv * group * 128:(j + 1) * rv * group * 128].reshape(rv, group * 128)
+        out[:, h] = z[:, h] @ Bj[:, u * 128:(u + 1) * 128]
+    # float32 sums of at most 288 products on either side
+    assert np.abs(out - got).max() <= 1e-5 * np.abs(out).max()
+    say(f"[edges] merge rows={batch * layer.n_q_heads} rv={rv} q_per_kv={q_per_kv} rel err {err:.3e}")
