@@ -98,7 +98,8 @@ int palu_version(void);
  * Process-wide tuning knobs for experiments; every default (0, where not stated otherwise) lets the library
  * choose.  Not thread-safe against concurrent decode calls.
  *   "score_waves"         4 or 8 wavefronts per score workgroup for ranks <= 256
- *   "score_chunks"        sequence chunks per (sequence, head block) in the score kernel
+ *   "score_chunks"        sequence chunks per (sequence, head block) in the score kernel (sequences of different
+ *                         lengths: that many workgroups per sequence and head block, with equal shares of all tiles)
  *   "score_mixed"         default 1: a layer whose groups have different ranks (all 64 .. 256 after slicing, fp16 or
  *                         bf16 latents, one query per head) gets ONE score launch over all rank classes; 0: one
  *                         launch per rank class
@@ -118,7 +119,7 @@ int palu_version(void);
  *                         than the default, but the logit error is about 4e-4 of the logit (output error 2e-3
  *                         reached at logits of about +-25).  Default 0: keys are rebuilt and rotated in float32,
  *                         once per key/value head and pass of up to 8 of its queries where every key rank of
- *                         the layer is 64 .. 512 (4-bit keys: 128 or 256), else once per query head.
+ *                         the layer is 64 .. 512 (4-bit keys: 128 .. 512), else once per query head.
  *   "encode_tile_rows"    token rows per workgroup of the prompt-sized projection (128 or 256, each
  *                         with 256 columns; 32 or 64, each with 128)
  * Unknown names and out-of-range values return PALU_ERR_INVALID_ARG.  Set
