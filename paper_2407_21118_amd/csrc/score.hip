@@ -207,7 +207,7 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(ScoreArgs a) {
   const int t_end = min(t_begin + a.chunk_tokens, L);
   const int n_tiles = (t_end - t_begin + kTile - 1) / kTile;
   const int last_tile = n_tiles - 1;
-  const int rel_last = L - 1 - t_begin;                         // last attendable row, relative to the chunk
+  const int rel_last = t_end - 1 - t_begin;                     // the chunk's last attendable row, relative to it: its byte offset fits 32 bits
 
   // ---- addressing: a uniform 64-bit base (first row of this workgroup's sequence
   // chunk) plus 32-bit byte offsets (the host keeps a chunk of the cache below 2^31 bytes)

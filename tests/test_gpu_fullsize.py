@@ -317,3 +317,38 @@ def test_one_sequence_longer_than_4gib():
     """One sequence of 1.2 M tokens in the 7B shape: 4.6 GiB of key latents attended in one
     call, more splits than compute units, the value kernel's split count at its limit."""
     run_full("2", [(0, 3, [2])], seq=1_200_007)
+
+
+@pytest.mark.parametrize("score_waves,lens", [(0, False), (0, True), (4, False), (8, False)])
+def test_rows_a_multiple_of_4gib_before_the_end(score_waves, lens):
+    """A tile whose first row lies 2^32 bytes of key latents before the last one (2^20 rows of 4096 bytes) is read like any
+    other: one of its later rows carries all of the softmax, every other key is zero."""
+    from gpu_util import to_dev
+    L, row = (1 << 20) + 33, 50
+    layer = synth.uniform_layer(32, 4, 256, 32)
+    assert layer.R_k * 2 * (L - 1 - row // 32 * 32) == 1 << 32
+    rng = np.random.default_rng(12)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    hk1, hv1 = draw(1, 1, layer.R_k), draw(1, 1, layer.R_v)
+    Bk, Bv = draw(layer.b_elems("k"), by=256 ** -0.5), draw(layer.b_elems("v"), by=32 ** -0.5)
+    keys = np.concatenate([hk1[0, :, 256 * j:256 * j + 256] @ Bk[256 * 512 * j:256 * 512 * (j + 1)].reshape(256, 512) for j in range(8)], 1)
+    keys = keys.reshape(1, 32, 128)
+    norm = np.linalg.norm(keys, axis=-1, keepdims=True)
+    q, q_pos = synth.round_to(keys / norm * (40 * 128 ** 0.5 / norm), "f16"), np.array([row], np.int32)      # logits of 40 against row's key
+    hk = torch.zeros((1, L, layer.R_k), dtype=torch.float16, device="cuda")
+    hv = torch.zeros((1, L, layer.R_v), dtype=torch.float16, device="cuda")
+    hk[:, row], hv[:, row] = to_dev(hk1[:, 0], "f16"), to_dev(hv1[:, 0], "f16")
+    table = P.palu_rope_table_init(layer.rope_theta, layer.d_head, L)
+    P.palu_set_option("score_waves", score_waves)
+    try:
+        out = P.palu_attn_decode(make_desc(layer, "f16"), 1, L, L, to_dev(q, "f16"), torch.from_numpy(q_pos).cuda(), hk, hv, to_dev(Bk, "f16"),
+                                 to_dev(Bv, "f16"), table, L, seq_lens=torch.tensor([L], dtype=torch.int32, device="cuda") if lens else None)
+        torch.cuda.synchronize()
+    finally:
+        P.palu_set_option("score_waves", 0)
+    # the other rows' share of the softmax: 2^20 e^-40 < 1e-11
+    ref = O.attn_decode(q, q_pos, hk1, hv1, Bk, Bv, layer.group_head_off, layer.k_rank_off, layer.v_rank_off, layer.d_head, layer.rope_theta,
+                        np.array([row], np.int32), None, layer.q_per_kv)
+    err = max(rel_err(out.cpu().numpy(), ref))
+    say(f"[4gib before the end] score_waves={score_waves} seq_lens={lens} rel err {err:.3e}")
+    assert err <= TOL_FP
