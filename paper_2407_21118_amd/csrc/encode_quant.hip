@@ -119,9 +119,10 @@ __device__ __forceinline__ void encode_partial_body(const EncodeArgs& a, int bx,
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float* dst = &red[wave][(4 * kq + r) * kPitch + n * 8];
-      const float on = k_ok ? 1.f : 0.f;
-      *reinterpret_cast<float4v*>(dst) = float4v{acc[mt][0][r], acc[mt][1][r], acc[mt][2][r], acc[mt][3][r]} * on;
-      *reinterpret_cast<float4v*>(dst + 4) = float4v{acc[mt][4][r], acc[mt][5][r], acc[mt][6][r], acc[mt][7][r]} * on;
+      // a wavefront without rows contributes zeros, selected: its sums over the rows it re-read may be infinite
+      const float4v none = {0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<float4v*>(dst) = k_ok ? float4v{acc[mt][0][r], acc[mt][1][r], acc[mt][2][r], acc[mt][3][r]} : none;
+      *reinterpret_cast<float4v*>(dst + 4) = k_ok ? float4v{acc[mt][4][r], acc[mt][5][r], acc[mt][6][r], acc[mt][7][r]} : none;
     }
     __syncthreads();
 #pragma unroll

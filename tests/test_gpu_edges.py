@@ -44,6 +44,33 @@ def test_encode_token_tiles(heads, group, rk, rv, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("heads", [1, 3, 2])
+def test_encode_infinities(heads, dtype):
+    """The split-K projection of infinite inputs and weights in its first rows: infinities of the right sign where the sum has
+    them and NaN only where it has both, also at depths (128, 384) whose last workgroup has wavefronts without rows."""
+    layer = synth.uniform_layer(heads, 1, 64, 32)
+    rng = np.random.default_rng(35)
+    d = heads * 128
+    sides = [synth.round_to(1.0 + rng.random((d, R)), dtype) * np.where(np.arange(R) % 2, -1.0, 1.0) for R in (layer.R_k, layer.R_v)]
+    sides[0][3, 1], sides[1][63, 0] = np.inf, -np.inf
+    desc = make_desc(layer, dtype)
+    for n_tok in (1, 2, 17, 63):
+        x = synth.round_to(1.0 + rng.random((n_tok, d)), dtype)
+        x[n_tok - 1, 5] = np.inf
+        hk, hv = (torch.full((n_tok, A.shape[1]), 7.0, dtype=to_dev(x, dtype).dtype, device="cuda") for A in sides)
+        P.palu_encode_kv(desc, to_dev(x, dtype), *(to_dev(A, dtype) for A in sides), hk, layer.R_k, hv, layer.R_v)
+        torch.cuda.synchronize()
+        for got, A in ((hk, sides[0]), (hv, sides[1])):
+            with np.errstate(invalid="ignore"):
+                g, ref = got.float().cpu().numpy(), x.astype(np.float64) @ A.astype(np.float64)
+            finite = np.isfinite(ref)
+            assert np.array_equal(g[~finite], ref[~finite].astype(np.float32), equal_nan=True), (heads, n_tok)
+            # one rounding to the cache dtype, sums of at most 384 products of one sign in float32
+            assert (np.abs(g[finite] / ref[finite] - 1) <= (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) + 1e-5).all()
+    say(f"[edges] encode infinities heads={heads} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("heads,rk,rv", [(1, 32, 160), (3, 64, 96), (8, 256, 32)])
 def test_encode_gemm_tiles(heads, rk, rv, dtype):
     """The prompt-sized projection with every tile, at token counts around the tiles' rows, column counts that end inside
