@@ -103,6 +103,24 @@ def test_encode_gemm_tiles(heads, rk, rv, dtype):
     say(f"[edges] encode GEMM heads={heads} R={layer.R_k}/{layer.R_v} {dtype}")
 
 
+def odd_zero_rows(case, quant, b, rows):
+    """Gives 128-channel block blk of row t of sequence b, for every (t, blk) of rows, a zero-point of n + 1/2 and codes n and
+    n + 1 that fit the query of its group's first head: logits of 12, so that these rows share that head's softmax and a
+    zero-point rounded to an integer, half a step in every channel, shows."""
+    layer, (codes, scale, zero) = case.layer, quant["k"]
+    for i, (t, blk) in enumerate(rows):
+        blk %= layer.R_k // 128
+        j = int(np.searchsorted(layer.k_rank_off, 128 * blk, side="right")) - 1
+        r, size = layer.k_rank_off[j + 1] - layer.k_rank_off[j], layer.group_size(j)
+        at = int(sum((layer.k_rank_off[g + 1] - layer.k_rank_off[g]) * layer.group_size(g) for g in range(j))) * 128
+        B = case.Bk[at:at + r * size * 128].reshape(r, size * 128)[128 * blk - layer.k_rank_off[j]:][:128, :128]
+        q = O.rope_rotate(case.q[b, layer.group_head_off[j] * layer.q_per_kv].astype(np.float64), case.q_pos[b], layer.rope_theta)
+        w = B @ O.rope_rotate(q, -t, layer.rope_theta) / 128 ** 0.5
+        n = (0, 7, 14)[i % 3]
+        scale[b, t, blk], zero[b, t, blk] = 24.0 / np.abs(w).sum(), n + 0.5
+        codes[b, t, 64 * blk:64 * blk + 64] = O.pack_codes((n + (w > 0)).astype(np.uint8), 4)
+
+
 @pytest.mark.parametrize("odd_zero", [False, True])
 @pytest.mark.parametrize("heads,group,rk,q_per_kv", [(4, 1, 128, 1), (3, 1, 128, 1), (2, 1, 256, 1), (4, 2, 256, 1), (8, 4, 128, 1),
                                                      (5, 5, 256, 1), (4, 4, 384, 1), (4, 4, 512, 2), (8, 8, 1024, 1), (2, 2, 128, 5)])
@@ -119,14 +137,49 @@ def test_quantized_keys_whole_head(heads, group, rk, q_per_kv, odd_zero):
     case.seq_lens = lens
     quant = {"k": O.quant_latent(case.Hk)}
     if odd_zero:
-        zero = quant["k"][2]
-        zero[0, 70, 0] += np.float16(0.5)
-        zero[0, 160, -1] = 2001.0
-        zero[2, 32, -1] -= np.float16(0.25)
+        odd_zero_rows(case, quant, 0, [(70, 0), (160, 0), (70, -1), (160, -1)])
+        odd_zero_rows(case, quant, 2, [(31, 0), (32, 0), (31, -1), (32, -1)])
+        quant["k"][2][3, 50, 0] = 2001.0
     got, ref = run_hip(case, True, False, quant), run_oracle(case, quant, True, False)
     err = max(rel_err(got, ref))
     say(f"[edges] 4-bit keys heads={heads} group={group} rank={rk} q_per_kv={q_per_kv} odd={odd_zero} rel err {err:.3e}")
     assert err <= TOL_I4
+
+
+@pytest.mark.parametrize("odd_zero", ["none", "some", "all"])
+@pytest.mark.parametrize("lens", [None, [2245], [700, 0, 2245, 33, 96]])
+@pytest.mark.parametrize("heads,group,rk,q_per_kv", [(2, 1, 128, 1), (4, 2, 256, 1), (3, 3, 384, 1), (2, 2, 256, 3), (8, 2, 128, 1)])
+def test_quantized_keys_long_runs(heads, group, rk, q_per_kv, lens, odd_zero):
+    """4-bit keys in runs of many tiles, one workgroup to a sequence and head block (option score_chunks): 71 tiles of one
+    sequence (more than the 64 that are looked through at a time), and runs that begin and end inside sequences; zero-points
+    that the packed dequantization does not hold for in no tile, in single ones (early, late, neighbours, three apart, the
+    last; a sequence without any between two with) and in all."""
+    layer = synth.uniform_layer(heads, group, rk, 128, q_per_kv=q_per_kv)
+    rng = np.random.default_rng(9)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    n = np.array(lens or [2245], np.int32)
+    batch, seq = len(n), 2245
+    case = synth.Case("edges", layer, "f16", batch, seq, draw(batch, layer.n_q_heads, 128), np.maximum(n - 1, 0), draw(batch, seq, layer.R_k),
+                      draw(batch, seq, layer.R_v), draw(layer.b_elems("k"), by=rk ** -0.5), draw(layer.b_elems("v"), by=128 ** -0.5))
+    if lens:
+        case.seq_lens = n
+    quant = {"k": O.quant_latent(case.Hk)}
+    if odd_zero == "some":
+        odd_zero_rows(case, quant, int(np.argmax(n)), [(40, 0), (64, -1), (165, 0), (261, -1), (2079, 0), (2080, -1), (2244, 0)])
+        if batch > 1:
+            odd_zero_rows(case, quant, batch - 1, [(32, 0), (95, 0), (32, -1), (95, -1)])
+    elif odd_zero == "all":
+        quant["k"][2][:] += np.float16(0.5)
+    P.palu_set_option("score_chunks", 1)
+    try:
+        got = run_hip(case, True, False, quant)
+    finally:
+        P.palu_set_option("score_chunks", 0)
+    ref = run_oracle(case, quant, True, False)
+    some = n > 0
+    err = max(rel_err(got[some], ref[some]))
+    say(f"[edges] 4-bit keys, long runs heads={heads} group={group} rank={rk} q_per_kv={q_per_kv} lens={lens} odd={odd_zero} rel err {err:.3e}")
+    assert err <= TOL_I4 and not got[~some].any()
 
 
 @pytest.mark.parametrize("ranks,q_per_kv,dtype", [([64], 1, "f16"), ([256], 1, "bf16"), ([128], 3, "f16"), ([64, 96, 256], 1, "f16"), ([320], 1, "f16")])
