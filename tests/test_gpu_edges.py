@@ -148,7 +148,7 @@ def test_quantized_keys_whole_head(heads, group, rk, q_per_kv, odd_zero):
 
 @pytest.mark.parametrize("odd_zero", ["none", "some", "all"])
 @pytest.mark.parametrize("lens", [None, [2245], [700, 0, 2245, 33, 96]])
-@pytest.mark.parametrize("heads,group,rk,q_per_kv", [(2, 1, 128, 1), (4, 2, 256, 1), (3, 3, 384, 1), (2, 2, 256, 3), (8, 2, 128, 1)])
+@pytest.mark.parametrize("heads,group,rk,q_per_kv", [(2, 1, 128, 1), (4, 2, 256, 1), (3, 3, 384, 1), (2, 2, 256, 3), (2, 2, 256, 8), (8, 2, 128, 1)])
 def test_quantized_keys_long_runs(heads, group, rk, q_per_kv, lens, odd_zero):
     """4-bit keys in runs of many tiles, one workgroup to a sequence and head block (option score_chunks): 71 tiles of one
     sequence (more than the 64 that are looked through at a time), and runs that begin and end inside sequences; zero-points
