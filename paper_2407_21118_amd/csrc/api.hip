@@ -770,6 +770,17 @@ void encode_partial_grid(const EncodePlan& p, unsigned g[3]) {
   g[2] = (unsigned)p.n_sides;
 }
 
+// Query-fold items that ride in the projection's first launch instead of one of their own: as many as it has workgroups
+// and, where few columns make these few, one per 512 columns and 64 rows of either side's weights (16 heads, 256 columns,
+// 64 items: 31 us a step as two launches, 28 as one; 7B shape: 512 items, 512 workgroups).  Beyond that the items
+// would dominate the launch.
+long long ride_along_items(const EncodePlan& p) {
+  unsigned g[3];
+  encode_partial_grid(p, g);
+  const long long wgs = (long long)g[0] * g[1] * g[2];
+  return p.transposed ? wgs : std::max(wgs, (long long)ceil_div(p.max_R, 512) * (p.a.d / 64) * p.n_sides);
+}
+
 // second launch of the split-K form: sum the partials, round, scatter the rows
 int launch_encode_finish(int act, const EncodePlan& p, hipStream_t s) {
   if (p.transposed) return PALU_OK;         // nothing left to sum
@@ -1065,9 +1076,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       }
       f.head0 = h_lo;
       const dim3 g((unsigned)(wmax / 128), (unsigned)(h_hi - h_lo), (unsigned)ceil_div(batch, 4));
-      unsigned gq[3] = {0, 0, 0};
-      if (enc_pending) encode_partial_grid(*enc, gq);
-      if (enc_pending && (long long)g.x * g.y * g.z > (long long)gq[0] * gq[1] * gq[2]) {     // more items than workgroups to ride in
+      if (enc_pending && (long long)g.x * g.y * g.z > ride_along_items(*enc)) {
         if ((st = launch_encode(act, *enc, s)) != PALU_OK) return st;
         enc_pending = false;
       }
@@ -1196,12 +1205,8 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       for (int j = 0; j < m.n_groups; ++j) max_r = std::max(max_r, m.k_off[j + 1] - m.k_off[j]);
       const dim3 g((unsigned)(max_r / 16), (unsigned)mk.n_heads, 1u);
       if ((st = mark(0)) != PALU_OK) return st;
-      // Fused only while every item finds a projection workgroup to ride in (the 7B shape: 512 items,
-      // 512 workgroups); with more items than that they would dominate the launch.
-      unsigned ge0[3] = {0, 0, 0};
-      if (enc_pending) encode_partial_grid(*enc, ge0);
       const long long fold_items = (long long)g.x * g.y * g.z + (shared_key ? (long long)mk.n_heads * batch : 0);
-      const bool fused_head = enc_pending && fold_items <= (long long)ge0[0] * ge0[1] * ge0[2];
+      const bool fused_head = enc_pending && fold_items <= ride_along_items(*enc);
       if (enc_pending && !fused_head) {
         if ((st = launch_encode(act, *enc, s)) != PALU_OK) return st;
         enc_pending = false;

@@ -205,6 +205,32 @@ def test_runs_through_sequences(ranks, q_per_kv, dtype, lens):
     assert err <= TOL_FP and not got[~some].any()
 
 
+@pytest.mark.parametrize("theta", [10000.0, 0.0])
+@pytest.mark.parametrize("heads,group,rk,batch", [(4, 1, 64, 1), (16, 4, 64, 5), (20, 4, 128, 2), (28, 4, 256, 1), (3, 1, 96, 17), (2, 2, 512, 63)])
+def test_step_with_few_columns(heads, group, rk, batch, theta):
+    """A decode step whose query folds outnumber the projection's workgroups, in one launch with it or beside it: rows and
+    outputs equal to the projection's and the attention's own calls."""
+    layer = synth.uniform_layer(heads, group, rk, 64, rope_theta=theta)
+    rng = np.random.default_rng(21)
+    seq, d = 40, heads * 128
+    draw = lambda *shape, by=1.0: to_dev(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    desc, x, q = make_desc(layer, "f16"), draw(batch, d), draw(batch, heads, 128)
+    A = [draw(d, R, by=d ** -0.5) for R in (layer.R_k, layer.R_v)]
+    caches = [draw(batch, seq, R) for R in (layer.R_k, layer.R_v)]
+    B = [draw(layer.b_elems("k"), by=rk ** -0.5), draw(layer.b_elems("v"), by=64 ** -0.5)]
+    rows = torch.arange(batch, dtype=torch.int32, device="cuda") * seq + seq - 1
+    q_pos = torch.full((batch,), seq - 1, dtype=torch.int32, device="cuda")
+    table = P.palu_rope_table_init(theta, 128, seq)
+    step = [c.clone() for c in caches]
+    got = P.palu_decode_step(desc, batch, seq, seq, x, *A, rows, q, q_pos, *step, *B, table, seq)
+    P.palu_encode_kv(desc, x, *A, caches[0], layer.R_k, caches[1], layer.R_v, rows)
+    ref = P.palu_attn_decode(desc, batch, seq, seq, q, q_pos, *caches, *B, table, seq)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(step, caches)) and torch.equal(got, ref)
+    assert ref.abs().max() > 0
+    say(f"[edges] step heads={heads} group={group} rank={rk} batch={batch} theta={theta}")
+
+
 @pytest.mark.parametrize("batch,heads,group,rv,q_per_kv", [(31, 4, 4, 64, 1), (32, 4, 4, 96, 1), (33, 3, 1, 32, 2), (256, 4, 2, 64, 1), (257, 2, 2, 288, 3), (1, 256, 4, 32, 1)])
 def test_merge_of_many_rows(batch, heads, group, rv, q_per_kv):
     """The merge kernels around their row counts (128 and 1024 rows; rows that do not fill a workgroup): outputs against the
