@@ -438,6 +438,27 @@ inline bool shared16_ok(int rc) { return rc >= 1 && rc <= 7; }
 inline int shared16_rows_per_pass(int rc) { return rc >= 5 ? 8 : 4; }
 constexpr int score16q4_lds_bytes(int width) { return 3 * score_tile_bytes(width) + 3 * kRopeTileBytes; }
 
+// 4-bit keys of ranks 384 and 512: two slices of whole heads (score16_kernel, four heads or key/value heads to a workgroup) or
+// half heads of the full rank (score_kernel, two query heads to a workgroup)?  The slices where they are fewer than 3/2 as many
+// workgroups: 16 heads, 8 x 4096 tokens, rank 384 in groups of 1 / 2 (2 : 1) 187 / 108 us as half heads, 230 / 133 as slices; 15
+// heads in groups of 5 (4 : 3) 186 and 112; groups of 4 (1 : 1) 106 and 80.  Rank 384 makes two launches of them, 256 and 128 rows,
+// where a layer of that rank alone is one launch otherwise: worth it from about six tiles of half heads per compute unit on
+// (32 heads in groups of 4, one sequence of 500 / 1000 / 4000 tokens, captured: 47 / 49 / 63 us as half heads, 49 / 49 / 58 as slices).
+bool split_keys4(const Meta& m, int batch, int seq_len) {
+  bool shared = m.qpk > 1, alone = true;         // alone: no other rank shares a launch with either slice
+  for (int j = 0; j < m.n_groups; ++j) shared = shared && m.k_off[j + 1] - m.k_off[j] <= 512;
+  long long slices = 0, halves = 0;
+  for (int j = 0; j < m.n_groups; ++j) {
+    const int r = m.k_off[j + 1] - m.k_off[j], s = m.head_off[j + 1] - m.head_off[j];
+    if (r <= 512 && r != 384) alone = false;
+    if (r <= 256 || r > 512) continue;
+    slices += shared ? 2 * ceil_div(s / m.qpk, 4) * ceil_div(m.qpk, r % 256 != 0 ? 4 : 8) : 2 * ceil_div(s, 4);
+    halves += ceil_div(s, 2);
+  }
+  if (2 * slices >= 3 * halves) return halves == 0;
+  return !alone || halves * batch * ceil_div(seq_len, kTile) >= 6LL * device_cu_count();
+}
+
 // The same layer with one (virtual) query head per key/value head: the units of the shared-key score form.
 Meta kv_head_meta(const Meta& m) {
   Meta k;
@@ -983,9 +1004,10 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   // (ranks above 256 in slices); the shared-key form, which leaves it, only takes layers without such ranks
   // (not with option score_fp8, whose weights are laid out per whole head)
   const bool split16 = !k_i4 && g_opt_score_waves == 0 && g_opt_score_fp8 == 0;
-  // 4-bit keys: every head on the whole-head kernel (their ranks are multiples of 128)
+  // 4-bit keys: every head on the whole-head kernel (their ranks are multiples of 128), ranks 384 and 512 where split4
   const bool whole4 = k_bits == 4 && g_opt_score_waves == 0;
-  const int split = split16 ? 1 : (whole4 ? 2 : 0);
+  const bool split4 = whole4 && split_keys4(m, batch, seq_len);
+  const int split = split16 ? 1 : (split4 ? 2 : 0);
   if ((st = plan_score(m, &sp, !k_lowbit, split)) != PALU_OK) return st;
   if ((st = plan_pv(m, &pp)) != PALU_OK) return st;
   const int quant_block = desc->quant_block > 0 ? desc->quant_block : 128;
@@ -1166,11 +1188,11 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         if (shared16) sk_pass_rows = std::min(sk_pass_rows, shared16_rows_per_pass(rcj));
       }
     }
-    // the same with 4-bit keys of ranks up to 512: their tiles are dequantized once per pass for the queries that share them
+    // the same with 4-bit keys of ranks up to 256, or 512 in slices: their tiles are dequantized once per pass for the queries that share them
     bool shared4 = whole4 && m.qpk > 1;
     for (int j = 0; j < m.n_groups && shared4; ++j) {
       const int r = m.k_off[j + 1] - m.k_off[j];
-      shared4 = r <= 512;
+      shared4 = r <= (split4 ? 512 : 256);
       if (r % 256 != 0) sk_pass_rows = std::min(sk_pass_rows, 4);
     }
     const bool kv_units = shared_key || shared16 || shared4;   // the score units are key/value heads
@@ -1200,7 +1222,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         fa.rev_lo[f] = (float)(rev - (double)fa.rev_hi[f]);
       }
       fa.meta = mk;
-      fa.layout16 = use16 ? (split16 ? 2 : 1) : (whole4 ? 2 : 0);
+      fa.layout16 = use16 ? (split16 ? 2 : 1) : (whole4 ? (split4 ? 2 : 1) : 0);
       int max_r = 0;
       for (int j = 0; j < m.n_groups; ++j) max_r = std::max(max_r, m.k_off[j + 1] - m.k_off[j]);
       const dim3 g((unsigned)(max_r / 16), (unsigned)mk.n_heads, 1u);
@@ -1444,13 +1466,13 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         const bool dma = !k_i4;
         const bool pingpong = (waves8 && !rank_class_half(rc)) || shared_key;
         size_t lds = (size_t)score_lds_bytes(width, dma, !shared_key, pingpong);
-        const bool k16 = use16 && rank_class_16(rc);
+        const bool k16 = use16 && rank_class_16(rc), w4 = whole4 && rank_class_16(rc);
         ScoreFn fn = shared_key ? score_fn_shared(rc, m.qpk <= 4)
                    : shared16 ? nullptr            // chosen per pass below
-                   : (k16 || whole4) ? nullptr     // chosen per launch below
+                   : (k16 || w4) ? nullptr         // chosen per launch below
                    : (k_lowbit ? score_fn_lowbit(rc) : score_fn(act, k_i4, rc * 3 + lg, waves8));
         if (k16) lds = (size_t)score16_lds_bytes(width);
-        if (whole4) lds = (size_t)score16q4_lds_bytes(width);
+        if (w4) lds = (size_t)score16q4_lds_bytes(width);
         if (shared16 || shared4) {
           // exact shared-key form: passes of up to sk_pass_rows query rows of every key/value head, each pass one
           // launch per flush of units (the key tile is rebuilt once per pass)
@@ -1481,7 +1503,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           }
           continue;
         }
-        const bool form16 = k16 || whole4;
+        const bool form16 = k16 || w4;
         if (!fn && !form16) return PALU_ERR_UNSUPPORTED;
         const bool k8 = k16 && use8 && !sliced;
         if (k8) {
@@ -1491,14 +1513,14 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         } else {
           a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
         }
-        const unsigned threads = (waves8 && !rank_class_half(rc) && !k16 && !whole4) ? 512 : 256;
+        const unsigned threads = (waves8 && !rank_class_half(rc) && !k16 && !w4) ? 512 : 256;
         auto flush = [&]() -> int {
           if (a.units.n_units == 0) return PALU_OK;
           dim3 grid(1);
           if (form16 && !k8) {
             const bool flat = flat16(a.units.n_units);
-            fn = whole4 ? (flat ? score16q4_fn<true>(rc, 1, lg) : score16q4_fn<false>(rc, 1, lg))
-                        : (flat ? score16_fn<true>(act, rc, lg) : score16_fn<false>(act, rc, lg));
+            fn = w4 ? (flat ? score16q4_fn<true>(rc, 1, lg) : score16q4_fn<false>(rc, 1, lg))
+                    : (flat ? score16_fn<true>(act, rc, lg) : score16_fn<false>(act, rc, lg));
             if (!fn) return PALU_ERR_UNSUPPORTED;
             grid = grid16(a.units.n_units, flat);
           } else {
@@ -1529,7 +1551,8 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   for (int h = 0; h < m.n_heads; ++h) {      // half-head wavefronts write two planes per rank slice
     const int rk = m.k_off[m.group_of_head[h] + 1] - m.k_off[m.group_of_head[h]];
     // one wavefront per head: one plane (per rank slice)
-    const bool whole = (whole4 && !no_rope) || (used16 && (split16 ? rk >= 64 : (rank_class_16(rank_class(rk)) || rk > 512)));
+    const bool whole = (whole4 && !no_rope && (split4 || rk <= 256 || rk > 512)) ||
+                       (used16 && (split16 ? rk >= 64 : (rank_class_16(rank_class(rk)) || rk > 512)));
     n_parts[h] = no_rope ? (uint8_t)1 : (uint8_t)(((waves8 || sp.half_heads[h]) && !whole) ? 2 * sp.slices[h] : sp.slices[h]);
     max_parts = std::max(max_parts, (int)n_parts[h]);
   }

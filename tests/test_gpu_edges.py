@@ -148,19 +148,20 @@ def test_quantized_keys_whole_head(heads, group, rk, q_per_kv, odd_zero):
 
 @pytest.mark.parametrize("odd_zero", ["none", "some", "all"])
 @pytest.mark.parametrize("lens", [None, [2245], [700, 0, 2245, 33, 96]])
-@pytest.mark.parametrize("heads,group,rk,q_per_kv", [(2, 1, 128, 1), (4, 2, 256, 1), (3, 3, 384, 1), (2, 2, 256, 3), (2, 2, 256, 8), (8, 2, 128, 1)])
-def test_quantized_keys_long_runs(heads, group, rk, q_per_kv, lens, odd_zero):
+@pytest.mark.parametrize("group,ranks,q_per_kv", [(1, [128, 128], 1), (2, [256, 256], 1), (3, [384, 256], 1), (2, [256], 3), (2, [256], 8),
+                                                  (2, [128] * 4, 1), (4, [512], 2), (2, [128, 384], 4)])
+def test_quantized_keys_long_runs(group, ranks, q_per_kv, lens, odd_zero):
     """4-bit keys in runs of many tiles, one workgroup to a sequence and head block (option score_chunks): 71 tiles of one
     sequence (more than the 64 that are looked through at a time), and runs that begin and end inside sequences; zero-points
     that the packed dequantization does not hold for in no tile, in single ones (early, late, neighbours, three apart, the
     last; a sequence without any between two with) and in all."""
-    layer = synth.uniform_layer(heads, group, rk, 128, q_per_kv=q_per_kv)
+    layer = synth.ragged_layer(group * len(ranks), group, ranks, [128] * len(ranks), q_per_kv=q_per_kv)
     rng = np.random.default_rng(9)
     draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
     n = np.array(lens or [2245], np.int32)
     batch, seq = len(n), 2245
     case = synth.Case("edges", layer, "f16", batch, seq, draw(batch, layer.n_q_heads, 128), np.maximum(n - 1, 0), draw(batch, seq, layer.R_k),
-                      draw(batch, seq, layer.R_v), draw(layer.b_elems("k"), by=rk ** -0.5), draw(layer.b_elems("v"), by=128 ** -0.5))
+                      draw(batch, seq, layer.R_v), draw(layer.b_elems("k"), by=max(ranks) ** -0.5), draw(layer.b_elems("v"), by=128 ** -0.5))
     if lens:
         case.seq_lens = n
     quant = {"k": O.quant_latent(case.Hk)}
@@ -178,8 +179,28 @@ def test_quantized_keys_long_runs(heads, group, rk, q_per_kv, lens, odd_zero):
     ref = run_oracle(case, quant, True, False)
     some = n > 0
     err = max(rel_err(got[some], ref[some]))
-    say(f"[edges] 4-bit keys, long runs heads={heads} group={group} rank={rk} q_per_kv={q_per_kv} lens={lens} odd={odd_zero} rel err {err:.3e}")
+    say(f"[edges] 4-bit keys, long runs group={group} ranks={ranks} q_per_kv={q_per_kv} lens={lens} odd={odd_zero} rel err {err:.3e}")
     assert err <= TOL_I4 and not got[~some].any()
+
+
+@pytest.mark.parametrize("lens", [False, True])
+@pytest.mark.parametrize("group,ranks,q_per_kv", [(1, [384, 384], 1), (1, [512, 128, 512], 2), (2, [384, 256, 384], 1), (2, [512, 1024], 1), (4, [384], 1),
+                                                  (4, [384, 128], 2), (3, [512, 384, 1024], 2), (1, [384], 4), (5, [384, 256], 1)])
+def test_quantized_keys_of_ranks_above_256(group, ranks, q_per_kv, lens):
+    """4-bit keys of ranks 384 and 512 on either side of the rule that slices them for the whole-head kernel (few heads per
+    group; rank 384 alone or beside ranks that share its launches), beside ranks on the other kernel, shared and not."""
+    layer = synth.ragged_layer(group * len(ranks), group, ranks, [64] * len(ranks), q_per_kv=q_per_kv)
+    rng = np.random.default_rng(10)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    n = np.array([300, 65, 1], np.int32)
+    case = synth.Case("edges", layer, "f16", 3, 300, draw(3, layer.n_q_heads, 128), n - 1, draw(3, 300, layer.R_k), draw(3, 300, layer.R_v),
+                      draw(layer.b_elems("k"), by=max(ranks) ** -0.5), draw(layer.b_elems("v"), by=64 ** -0.5))
+    if lens:
+        case.seq_lens = n
+    quant = {"k": O.quant_latent(case.Hk)}
+    err = max(rel_err(run_hip(case, True, False, quant), run_oracle(case, quant, True, False)))
+    say(f"[edges] 4-bit keys group={group} ranks={ranks} q_per_kv={q_per_kv} lens={lens} rel err {err:.3e}")
+    assert err <= TOL_I4
 
 
 @pytest.mark.parametrize("ranks,q_per_kv,dtype", [([64], 1, "f16"), ([256], 1, "bf16"), ([128], 3, "f16"), ([64, 96, 256], 1, "f16"), ([320], 1, "f16")])
