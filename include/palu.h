@@ -98,8 +98,8 @@ int palu_version(void);
  * Process-wide tuning knobs for experiments; every default (0, where not stated otherwise) lets the library
  * choose.  Not thread-safe against concurrent decode calls.
  *   "score_waves"         4 or 8 wavefronts per score workgroup for ranks <= 256
- *   "score_chunks"        sequence chunks per (sequence, head block) in the score kernel (sequences of different
- *                         lengths: that many workgroups per sequence and head block, with equal shares of all tiles)
+ *   "score_chunks"        sequence chunks per (sequence, head block) in the score kernel (with seq_lens: that many
+ *                         workgroups per sequence and head block, with equal shares of all sequences' tiles)
  *   "score_mixed"         default 1: a layer whose groups have different ranks (all 64 .. 256 after slicing, fp16 or
  *                         bf16 latents, one query per head) gets ONE score launch over all rank classes; 0: one
  *                         launch per rank class

@@ -1362,14 +1362,17 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         a.chunk_tokens = chunk_tiles * kTile;
         a.n_chunks = ceil_div(tiles, chunk_tiles);
       };
-      // The whole-head kernel's grid: one workgroup per compute unit over all units of the launch.  Where the sequences have
-      // one length and as many workgroups per (unit, sequence) as fit the chip fill 15/16 of it, a workgroup's run of tiles lies in
-      // one sequence; else the runs go through the tiles of all sequences (48 sequences of 1022 .. 2043 tokens, 8 units: 384
-      // workgroups of one sequence each 185 us, 256 equal runs 144 us; the way into the longer start costs 0.4 us).
+      // The whole-head kernel's grid: one workgroup per compute unit over all units of the launch.  Where as many workgroups per
+      // (unit, sequence) as fit the chip fill 15/16 of it, a workgroup's run of tiles lies in one sequence; else the runs go
+      // through the tiles of all sequences (48 sequences of 1022 .. 2043 tokens, 8 units: 384 workgroups of one sequence each
+      // 185 us, 256 equal runs 144 us).  Lengths on the device may differ, which such runs even out, but finding their place
+      // takes 1 .. 2.5 us a launch, and with several queries per key a tile takes 15 % longer (rank 256, 4 queries, 2 x 8000 tokens
+      // of equal length 50.2 against 46.4 us a step, half as long on average 49.0 against 45.1): from 16 tiles per compute unit on.
       auto flat16 = [&](int launch_units) {
         const int fit = device_cu_count() / std::max(1, (int)std::min<long long>((long long)launch_units * batch, 1 << 30));
-        if (seq_lens != nullptr) return true;
-        return g_opt_score_chunks == 0 && batch > 1 && (long long)fit * launch_units * batch * 16 < device_cu_count() * 15LL && tiles > fit;
+        if (g_opt_score_chunks > 0) return seq_lens != nullptr;
+        if (batch > 1 && (long long)fit * launch_units * batch * 16 < device_cu_count() * 15LL && tiles > fit) return true;
+        return seq_lens != nullptr && (long long)launch_units * batch * tiles >= 16LL * device_cu_count();
       };
       auto grid16 = [&](int launch_units, bool flat) {
         const int per = (int)std::min<long long>((long long)launch_units * (flat ? 1 : batch), 1 << 30);

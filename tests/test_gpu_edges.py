@@ -204,14 +204,15 @@ def test_quantized_keys_of_ranks_above_256(group, ranks, q_per_kv, lens):
 
 
 @pytest.mark.parametrize("ranks,q_per_kv,dtype", [([64], 1, "f16"), ([256], 1, "bf16"), ([128], 3, "f16"), ([64, 96, 256], 1, "f16"), ([320], 1, "f16")])
-@pytest.mark.parametrize("lens", ["mixed", "many", "equal"])
+@pytest.mark.parametrize("lens", ["mixed", "mixed, long runs", "many", "equal"])
 def test_runs_through_sequences(ranks, q_per_kv, dtype, lens):
-    """Score workgroups whose run of tiles goes through several sequences: empty sequences among them, more sequences than
-    lanes, sequences of one tile, one length but more sequences than compute units."""
+    """Score workgroups over sequences of different lengths, empty ones and ones of one tile among them: runs inside a sequence
+    (nine of up to 193 rows), runs that go through several (the same with as many workgroups as sequences, option score_chunks;
+    more sequences than lanes, a few tiles to a run), and one length but more sequences than compute units."""
     n = len(ranks)
     layer = synth.Layer(4 * n, 128, list(range(0, 4 * n + 1, 4)), list(np.cumsum([0] + ranks)), list(np.cumsum([0] + [64] * n)), q_per_kv=q_per_kv)
-    seq = {"mixed": 193, "many": 65, "equal": 65}[lens]
-    sl = {"mixed": [193, 0, 1, 64, 0, 0, 32, 33, 160], "many": [(37 * i) % 66 for i in range(150)], "equal": [65] * 300}[lens]
+    seq = {"mixed": 193, "mixed, long runs": 193, "many": 300, "equal": 65}[lens]
+    sl = {"many": [(37 * i) % 301 for i in range(150)], "equal": [65] * 300}.get(lens, [193, 0, 1, 64, 0, 0, 32, 33, 160])
     batch = len(sl)
     rng = np.random.default_rng(6)
     draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, dtype)  # noqa: E731
@@ -219,7 +220,12 @@ def test_runs_through_sequences(ranks, q_per_kv, dtype, lens):
                       draw(batch, seq, layer.R_k), draw(batch, seq, layer.R_v), draw(layer.b_elems("k"), by=0.1), draw(layer.b_elems("v"), by=0.1))
     if lens != "equal":
         case.seq_lens = np.array(sl, np.int32)
-    got, ref = run_hip(case), run_oracle(case)
+    P.palu_set_option("score_chunks", 1 if "long" in lens else 0)
+    try:
+        got = run_hip(case)
+    finally:
+        P.palu_set_option("score_chunks", 0)
+    ref = run_oracle(case)
     some = np.array(sl) > 0
     err = max(rel_err(got[some], ref[some]))
     say(f"[edges] runs ranks={ranks} q_per_kv={q_per_kv} {dtype} {lens} rel err {err:.3e}")
