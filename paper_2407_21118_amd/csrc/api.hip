@@ -1394,10 +1394,14 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         const int id = plan.cls_id[cls];
         if (id == kSlicedCls || id % 3 != 0 || !rank_class_16(id / 3)) mixed = false;
       }
-      int order[kMaxMixClasses], n_units_cls[kMaxMixClasses] = {}, one_round[kMaxMixClasses];     // one_round: workgroups per unit of a class
+      int order[kMaxMixClasses], n_units_cls[kMaxMixClasses] = {}, one_round[kMaxMixClasses];     // one_round: workgroups per unit (and sequence) of a class
       bool use_one_round = false;
       double mix_per_wg = 0.0;
-      const long long all_tiles = (long long)batch * tiles;
+      // Runs through the tiles of all sequences from three sequences on; with one or two, a run inside a sequence leaves few
+      // compute units idle and starts sooner (ranks 96 .. 416, 2 x 4000 tokens 54.0 us a step against 57, 3 x 4000 69.7 against 67.7).
+      const bool mix_flat = batch > 2 || g_opt_score_mixed > 1;
+      const int mix_seqs = mix_flat ? 1 : batch;                 // sequences that have workgroups of their own
+      const long long run_tiles = mix_flat ? (long long)batch * tiles : tiles;
       // measured (uniform layers of each rank, 2048- and 1024-token chunks with every compute unit busy): microseconds per
       // 1000 tokens of one workgroup by rank / 32
       static const double kCost[9] = {0, 0, 30, 34, 38, 43, 47, 53, 56};
@@ -1416,15 +1420,15 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         if (g_opt_score_mixed == 1) {
           long long total = 0;
           for (int cls = 0; cls < plan.n_cls; ++cls) {
-            one_round[cls] = 1;
-            total += n_units_cls[cls];
+            one_round[cls] = mix_flat ? 1 : ceil_div(tiles, std::min(seg_limit, tiles));
+            total += (long long)one_round[cls] * n_units_cls[cls] * mix_seqs;
           }
-          auto wg_us = [&](int cls) { return kStartUs + (double)((all_tiles + one_round[cls] - 1) / one_round[cls]) * kTile * weight(plan.cls_id[cls] / 3 + 1) * 1e-3; };
+          auto wg_us = [&](int cls) { return kStartUs + (double)((run_tiles + one_round[cls] - 1) / one_round[cls]) * kTile * weight(plan.cls_id[cls] / 3 + 1) * 1e-3; };
           while (total <= cus) {
             int worst = 0;
             for (int cls = 1; cls < plan.n_cls; ++cls) if (wg_us(cls) > wg_us(worst)) worst = cls;
-            const int more = n_units_cls[worst];
-            if (one_round[worst] >= all_tiles || total + more > cus) break;
+            const int more = n_units_cls[worst] * mix_seqs;
+            if (one_round[worst] >= run_tiles || total + more > cus) break;
             ++one_round[worst];
             total += more;
           }
@@ -1444,18 +1448,19 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           const int cls = order[x], nk = plan.cls_id[cls] / 3 + 1;
           const long long run = std::max<long long>(1, std::llround(mix_per_wg / weight(nk) / kTile));       // option: several rounds of about this many tiles
           a.mix.first[x] = (int)first;
-          a.mix.n_wg[x] = use_one_round ? one_round[cls] : (int)std::min((all_tiles + run - 1) / run, 1LL << 20);
-          a.mix.run[x] = (int)(all_tiles / a.mix.n_wg[x]);
-          a.mix.run_more[x] = (int)(all_tiles % a.mix.n_wg[x]);
+          a.mix.n_wg[x] = use_one_round ? one_round[cls] : (int)std::min((run_tiles + run - 1) / run, 1LL << 20);
+          a.mix.run[x] = (int)(run_tiles / a.mix.n_wg[x]);
+          a.mix.run_more[x] = (int)(run_tiles % a.mix.n_wg[x]);
           a.mix.unit0[x] = a.units.n_units;
+          a.mix.n_units[x] = n_units_cls[cls];
           a.mix.nk[x] = nk;
           for (int i = 0; i < plan.total_units; ++i)
             if (plan.unit_cls[i] == cls) a.units.u[a.units.n_units++] = plan.units[i];
-          first += (long long)a.mix.n_wg[x] * n_units_cls[cls];
+          first += (long long)a.mix.n_wg[x] * n_units_cls[cls] * mix_seqs;
           lds = std::max(lds, (size_t)score16_lds_bytes(32 * nk));
         }
         if (first >= (1LL << 31)) return PALU_ERR_UNSUPPORTED;
-        ScoreFn fn = score16_mixed_fn(act);
+        ScoreFn fn = mix_flat ? score16_mixed_fn<true>(act) : score16_mixed_fn<false>(act);
         if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
         a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
         hipLaunchKernelGGL(fn, dim3((unsigned)first), dim3(256), lds, s, a);

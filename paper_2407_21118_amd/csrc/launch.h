@@ -18,8 +18,8 @@ ScoreFn score_fn_shared(int rc, bool four);
 // unquantized latents, ranks 64 .. 256, one whole head per wavefront.  FLAT: runs through the tiles of all sequences
 // (each value is a translation unit of its own, also of the forms below)
 template <bool FLAT> ScoreFn score16_fn(int act, int rc, int lg);
-// one launch over several rank classes of the above, FLAT
-ScoreFn score16_mixed_fn(int act);
+// one launch over several rank classes of the above
+template <bool FLAT> ScoreFn score16_mixed_fn(int act);
 // several queries per key/value head, the key rebuilt once per pass of nq rows (NULL: not compiled)
 template <bool FLAT> ScoreFn score16q_fn(int act, int rc, int nq);
 // the same with 4-bit key latents (ranks 128 and 256); one query per head (nq = 1): also 2 or 4 groups per workgroup (lg)

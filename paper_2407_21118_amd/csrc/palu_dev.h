@@ -209,9 +209,10 @@ constexpr int kMaxMixClasses = 7;       // ranks 64, 96, .. 256
 struct ScoreMix {
   int n_cls;
   int first[kMaxMixClasses];            // first workgroup of the class
-  int n_wg[kMaxMixClasses];             // workgroups per unit ...
+  int n_wg[kMaxMixClasses];             // workgroups per unit, or per unit and sequence ...
   int run[kMaxMixClasses], run_more[kMaxMixClasses];   // ... as in ScoreArgs
   int unit0[kMaxMixClasses];            // the class's first unit in ScoreArgs.units
+  int n_units[kMaxMixClasses];
   int nk[kMaxMixClasses];               // rank / 32
 };
 struct ScoreUnits {

@@ -80,34 +80,35 @@ __global__ __launch_bounds__(256) void score16_kernel(ScoreArgs a) {
 
 // The same body with its place in the launch as arguments (workgroup wg of n_wg of the unit), so that a launch over
 // several rank classes can hand each workgroup the body of its unit's class.
-template <typename T, int NK, int G>
-__device__ __forceinline__ void score16_body(const ScoreArgs& a, const int wg, const int n_wg, const int unit, const int run, const int run_more) {
-  constexpr int NQ = 1, QB = 0, seq = 0;
-  constexpr bool FLAT = true;
+template <typename T, int NK, int G, bool FLAT>
+__device__ __forceinline__ void score16_body(const ScoreArgs& a, const int wg, const int n_wg, const int unit, const int seq, const int run, const int run_more) {
+  constexpr int NQ = 1, QB = 0;
 #include "score16_body.inc"
 }
 
 // One launch for a layer whose groups have different ranks (the ranks a search assigns per group, Sec. 3.3):
 // a.mix lists the rank classes, heaviest first, each with its own number of workgroups per unit (chosen by the host so
 // that workgroups of different classes take about as long) and its units, which lie side by side in a.units.
-// grid (sum over classes of workgroups x units), 256 threads; the workgroups of a class are consecutive.
-template <typename T>
+// grid (sum over classes of workgroups x units, and x sequences where a run lies in one), 256 threads; the workgroups of a
+// class are consecutive.
+template <typename T, bool FLAT>
 __global__ __launch_bounds__(256) void score16_mixed_kernel(ScoreArgs a) {
   int c = 0;
 #pragma unroll
   for (int i = 1; i < kMaxMixClasses; ++i)
     if (i < a.mix.n_cls && (int)blockIdx.x >= a.mix.first[i]) c = i;
   const int local = (int)blockIdx.x - a.mix.first[c];
-  const int n_wg = a.mix.n_wg[c], wg = local % n_wg, unit = a.mix.unit0[c] + local / n_wg;
+  const int n_wg = a.mix.n_wg[c], wg = local % n_wg, rest = local / n_wg;
+  const int unit = a.mix.unit0[c] + (FLAT ? rest : rest % a.mix.n_units[c]), seq = FLAT ? 0 : rest / a.mix.n_units[c];
   const int run = a.mix.run[c], run_more = a.mix.run_more[c];
   switch (a.mix.nk[c]) {
-    case 2: score16_body<T, 2, 1>(a, wg, n_wg, unit, run, run_more); break;
-    case 3: score16_body<T, 3, 1>(a, wg, n_wg, unit, run, run_more); break;
-    case 4: score16_body<T, 4, 1>(a, wg, n_wg, unit, run, run_more); break;
-    case 5: score16_body<T, 5, 1>(a, wg, n_wg, unit, run, run_more); break;
-    case 6: score16_body<T, 6, 1>(a, wg, n_wg, unit, run, run_more); break;
-    case 7: score16_body<T, 7, 1>(a, wg, n_wg, unit, run, run_more); break;
-    default: score16_body<T, 8, 1>(a, wg, n_wg, unit, run, run_more); break;
+    case 2: score16_body<T, 2, 1, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 3: score16_body<T, 3, 1, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 4: score16_body<T, 4, 1, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 5: score16_body<T, 5, 1, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 6: score16_body<T, 6, 1, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 7: score16_body<T, 7, 1, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
+    default: score16_body<T, 8, 1, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
   }
 }
 

@@ -38,9 +38,10 @@ ScoreFn score16_fn<kFlat>(int act, int rc, int lg) {
   return act == PALU_F16 ? score16_fn_t<F16>(rc, lg) : score16_fn_t<BF16>(rc, lg);
 }
 
-#if PALU_SCORE_FLAT
-ScoreFn score16_mixed_fn(int act) { return act == PALU_F16 ? score16_mixed_kernel<F16> : score16_mixed_kernel<BF16>; }
-#else
+template <>
+ScoreFn score16_mixed_fn<kFlat>(int act) { return act == PALU_F16 ? score16_mixed_kernel<F16, kFlat> : score16_mixed_kernel<BF16, kFlat>; }
+
+#if !PALU_SCORE_FLAT
 namespace {
 template <int NK>
 ScoreFn score8_fn_g(int lg) {

@@ -204,21 +204,21 @@ def test_quantized_keys_of_ranks_above_256(group, ranks, q_per_kv, lens):
 
 
 @pytest.mark.parametrize("ranks,q_per_kv,dtype", [([64], 1, "f16"), ([256], 1, "bf16"), ([128], 3, "f16"), ([64, 96, 256], 1, "f16"), ([320], 1, "f16")])
-@pytest.mark.parametrize("lens", ["mixed", "mixed, long runs", "many", "equal"])
+@pytest.mark.parametrize("lens", ["mixed", "mixed, long runs", "many", "equal", "two", "one, equal"])
 def test_runs_through_sequences(ranks, q_per_kv, dtype, lens):
     """Score workgroups over sequences of different lengths, empty ones and ones of one tile among them: runs inside a sequence
-    (nine of up to 193 rows), runs that go through several (the same with as many workgroups as sequences, option score_chunks;
+    (nine of up to 193 rows, two, one), runs that go through several (the same with as many workgroups as sequences, option score_chunks;
     more sequences than lanes, a few tiles to a run), and one length but more sequences than compute units."""
     n = len(ranks)
     layer = synth.Layer(4 * n, 128, list(range(0, 4 * n + 1, 4)), list(np.cumsum([0] + ranks)), list(np.cumsum([0] + [64] * n)), q_per_kv=q_per_kv)
-    seq = {"mixed": 193, "mixed, long runs": 193, "many": 300, "equal": 65}[lens]
-    sl = {"many": [(37 * i) % 301 for i in range(150)], "equal": [65] * 300}.get(lens, [193, 0, 1, 64, 0, 0, 32, 33, 160])
+    seq = {"mixed": 193, "mixed, long runs": 193, "many": 300, "equal": 65, "two": 193, "one, equal": 193}[lens]
+    sl = {"many": [(37 * i) % 301 for i in range(150)], "equal": [65] * 300, "two": [70, 193], "one, equal": [193]}.get(lens, [193, 0, 1, 64, 0, 0, 32, 33, 160])
     batch = len(sl)
     rng = np.random.default_rng(6)
     draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, dtype)  # noqa: E731
     case = synth.Case("edges", layer, dtype, batch, seq, draw(batch, layer.n_q_heads, 128), np.maximum(np.array(sl, np.int32) - 1, 0),
                       draw(batch, seq, layer.R_k), draw(batch, seq, layer.R_v), draw(layer.b_elems("k"), by=0.1), draw(layer.b_elems("v"), by=0.1))
-    if lens != "equal":
+    if "equal" not in lens:
         case.seq_lens = np.array(sl, np.int32)
     P.palu_set_option("score_chunks", 1 if "long" in lens else 0)
     try:
