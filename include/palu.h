@@ -196,10 +196,10 @@ int palu_encode_kv(const palu_layer_desc* desc, const void* x, int32_t n_tok, co
  * channel are contiguous (h = x A of Sec. 3.1 with A stored column by column; the
  * projection matrices are fixed after the decomposition, so this layout is made once,
  * offline).  A wavefront then owns whole columns and finishes their sums by itself:
- * one launch, no workspace, no partial sums in memory.  It pays for one or two tokens
- * per call (a decode step of one or two sequences: one launch instead of two, about
- * 3 us less on a 7B-shaped layer); from about four tokens on the row-major form is
- * the faster one.
+ * one launch, no workspace, no partial sums in memory.  It pays for one token per call
+ * (a decode step of one sequence: one launch instead of two, 1 to 2 us less on a
+ * 7B-shaped layer); with two tokens the forms are level, from three on the row-major
+ * form is the faster one.
  *   n_tok       1 <= n_tok < 64 (a prompt goes through palu_encode / palu_encode_kv)
  *   hk, hv      DEVICE caches, act_dtype; 2-byte aligned, any row stride >= R
  * Everything else as for palu_encode_kv.  Accumulates in float32, rounds once to
@@ -241,8 +241,9 @@ int palu_quant_latent(const palu_layer_desc* desc, int which, const void* latent
  * are those of palu_encode (its many-token form, n_tok >= 64) followed by
  * palu_quant_latent: the product is accumulated in float32, rounded once to
  * act_dtype, and quantized from that rounded value.  Works for any n_tok >= 1 but
- * computes in tiles of 128 tokens, so for a handful of tokens the two-call form
- * is cheaper.
+ * computes in tiles of 32 tokens and more: on a 7B-shaped layer palu_encode and
+ * palu_quant_latent take less time for up to about 50 tokens of one side, and
+ * palu_encode_kv with a palu_quant_latent per side for up to about 1000 tokens of both.
  *   which       0 = key side, 1 = value side; R = rank_off[n_groups] must be a multiple of 128
  *   x, A        as for palu_encode (16-byte aligned)
  *   codes       DEVICE uint8 rows of R/2 bytes, 16-byte aligned, layout as palu_quant_latent

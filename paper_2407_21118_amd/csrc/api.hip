@@ -1640,7 +1640,8 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     const long long rows = (long long)batch * m.n_heads;
     // From 128 rows on the kernel with one workgroup per row, from 1024 on with two rows per workgroup (128 rows of 103 splits
     // 12.5 -> 8.6 us, 512 of 32 15.7 -> 9.0, 1536 of 4 33 -> 10.8); below, four workgroups per row: the chip is empty
-    // otherwise (32 rows of 103 splits 7.2 us, 7.9 with one).
+    // otherwise (32 rows of 103 splits 7.2 us, 7.9 with one).  Wide ranks do not move the lines: rank 2048 per group of 32 heads, a
+    // step with four workgroups per row and with this rule: 128 rows of 2048 tokens 71 / 64 us, 256 107 / 83, 1024 of 1024 tokens 213 / 135.
     const int nb = rows >= 1024 ? 2 : 1, waves = rows >= 1024 ? 4 : 8;
     const long long row_groups = ((long long)batch * m.qpk + nb - 1) / nb;
     if (rows >= 128 && row_groups <= 65535) {

@@ -8,7 +8,7 @@ namespace palu {
 
 // ---- score kernels (score_forms.hip, score16_forms.hip)
 using ScoreFn = void (*)(ScoreArgs);
-// quantized keys of 4 bits (i4), rank 32 and the forced schedules: class id = rank class * 3 + log2(groups per workgroup);
+// 4-bit keys (i4) of ranks 384 and 512 that are not sliced, rank 32 and the forced schedules: class id = rank class * 3 + log2(groups per workgroup);
 // w8: four heads as 8 half-head wavefronts (two per SIMD) instead of 4 whole-head ones
 ScoreFn score_fn(int act, bool i4, int cls_id, bool w8);
 // 3- and 2-bit key latents
@@ -22,7 +22,8 @@ template <bool FLAT> ScoreFn score16_fn(int act, int rc, int lg);
 template <bool FLAT> ScoreFn score16_mixed_fn(int act);
 // several queries per key/value head, the key rebuilt once per pass of nq rows (NULL: not compiled)
 template <bool FLAT> ScoreFn score16q_fn(int act, int rc, int nq);
-// the same with 4-bit key latents (ranks 128 and 256); one query per head (nq = 1): also 2 or 4 groups per workgroup (lg)
+// the same with 4-bit key latents (rank classes 128 and 256, also slices of larger ranks); one query per head (nq = 1): also 2 or 4
+// groups per workgroup (lg)
 template <bool FLAT> ScoreFn score16q4_fn(int rc, int nq, int lg);
 // option score_fp8
 ScoreFn score8_fn(int rc, int lg);

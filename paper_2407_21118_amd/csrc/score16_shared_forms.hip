@@ -1,4 +1,4 @@
-// Instantiations of the whole-head score kernel (score16.hip) for several queries per key/value head.
+// Instantiations of the whole-head score kernel (score16.hip) for several queries per key/value head, and for 4-bit keys.
 #include "launch.h"
 #include "score16.hip"
 
@@ -38,7 +38,7 @@ template <>
 ScoreFn score16q_fn<kFlat>(int act, int rc, int nq) {
   return act == PALU_F16 ? score16q_fn_t<F16>(rc, nq) : score16q_fn_t<BF16>(rc, nq);
 }
-// 4-bit key latents (ranks 128 and 256: whole quantization blocks) with several queries per key/value head
+// 4-bit key latents (ranks 128 and 256: whole quantization blocks), one query per head or several per key/value head
 namespace {
 template <int NK>
 ScoreFn score16q4_fn_n(int nq, int lg) {

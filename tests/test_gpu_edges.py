@@ -73,7 +73,7 @@ def test_encode_infinities(heads, dtype):
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("heads,rk,rv", [(1, 32, 160), (3, 64, 96), (8, 256, 32)])
 def test_encode_gemm_tiles(heads, rk, rv, dtype):
-    """The prompt-sized projection with every tile, at token counts around the tiles' rows, column counts that end inside
+    """The prompt-sized projection with every tile that the option names and the one it takes by itself, at token counts around the tiles' rows, column counts that end inside
     a tile (32 .. 2048) and depths shorter than the ring of stages (128 rows: two stages of six)."""
     layer = synth.uniform_layer(heads, 1, rk, rv)
     rng = np.random.default_rng(33)
@@ -230,6 +230,37 @@ def test_runs_through_sequences(ranks, q_per_kv, dtype, lens):
     err = max(rel_err(got[some], ref[some]))
     say(f"[edges] runs ranks={ranks} q_per_kv={q_per_kv} {dtype} {lens} rel err {err:.3e}")
     assert err <= TOL_FP and not got[~some].any()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n_tok", [77, 290, 600, 1030, 2055, 4099])
+def test_encode_gemm_tiles_by_cost(n_tok, dtype):
+    """The prompt-sized projection with the tile it takes by itself, 2048 columns a side on 256 compute units, so that every tile
+    is taken: both sides of 77 .. 2055 tokens 64 x 64, 64 x 128, 128 x 128, 128 x 256, 256 x 256; one side quantized of 77, 600,
+    1030, 2055 and 4099 32 x 128, 64 x 128, 128 x 128, 128 x 256, 256 x 256.  Quantized: the bytes that the quantizer makes of
+    the latents."""
+    layer = synth.uniform_layer(2, 1, 1024)
+    rng = np.random.default_rng(34)
+    d, R = 256, 2048
+    A = [synth.round_to(rng.standard_normal((d, R)) / np.sqrt(d), dtype) for _ in range(2)]
+    x = synth.round_to(rng.standard_normal((n_tok, d)), dtype)
+    xd, Ad = to_dev(x, dtype), [to_dev(a, dtype) for a in A]
+    h = [torch.full((n_tok + 1, R), 7.0, dtype=xd.dtype, device="cuda") for _ in range(2)]
+    P.palu_encode_kv(make_desc(layer, dtype), xd, *Ad, h[0], R, h[1], R)
+    torch.cuda.synchronize()
+    eps = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8                # the bound of test_encode_token_tiles
+    for got, a in zip(h, A):
+        g, ref = got.float().cpu().numpy(), x.astype(np.float32) @ a.astype(np.float32)
+        assert (np.abs(g[:n_tok] - ref) - eps * np.abs(ref)).max() <= 1e-5 * np.abs(ref).max() and (g[n_tok] == 7.0).all()
+    if n_tok != 290:
+        q = [torch.full((n_tok + 1, R // 2), 0xA5, dtype=torch.uint8, device="cuda")] + [torch.full((n_tok + 1, R // 128), 7.0, dtype=torch.float16, device="cuda") for _ in range(2)]
+        desc = P.LayerDesc(2, 128, layer.group_head_off, layer.k_rank_off, layer.v_rank_off, P.PALU_F16 if dtype == "f16" else P.PALU_BF16, quant_block=128)
+        P.palu_encode_quant(desc, 0, xd, n_tok, Ad[0], *q)
+        torch.cuda.synchronize()
+        for got, ref in zip(q, O.quant_latent(h[0][:n_tok].float().cpu().numpy())):
+            assert np.array_equal(got[:n_tok].cpu().numpy(), ref)
+        assert (q[0][n_tok] == 0xA5).all() and (q[1][n_tok] == 7.0).all() and (q[2][n_tok] == 7.0).all()
+    say(f"[edges] encode GEMM, tile by cost n_tok={n_tok} {dtype}")
 
 
 @pytest.mark.parametrize("theta", [10000.0, 0.0])

@@ -269,9 +269,9 @@ def test_decode_step_in_a_captured_graph(one_call):
 
 @pytest.fixture
 def encode_tile(request):
-    """Forces the projection's tile (the library picks it from the token count: short prompts get
-    64 x 128, the tall tiles are otherwise reached only by prompts of thousands of tokens; 32 names
-    the 64 x 128 tile)."""
+    """Forces the projection's tile (the library picks it by the cost of its rounds of workgroups: the tall
+    tiles are otherwise reached only by prompts of thousands of tokens).  128 and 256 name tiles of 256
+    columns, 32 and 64 of 128; the others, 64 x 64 and 128 x 128, have no option value."""
     P.palu_set_option("encode_tile_rows", request.param)
     yield request.param
     P.palu_set_option("encode_tile_rows", 0)
