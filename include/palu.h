@@ -357,10 +357,10 @@ int palu_attn_decode_latent(const palu_layer_desc* desc, int32_t batch, int32_t 
 /*
  * One whole decode step in one call: append the new token of every sequence to both
  * caches (h = x A, Sec. 3.1) and attend (palu_attn_decode).  Same results, bit for
- * bit, as palu_encode_kv followed by palu_attn_decode; where the step folds the
- * query into B_k (RoPE, fp16 / bf16 latents, one query per key/value head, fewer
- * than 64 sequences) the projection's first launch and the fold, which do not depend
- * on each other, share one grid, so the step has one launch less.
+ * bit, as palu_encode_kv followed by palu_attn_decode.  What attention needs of B_k
+ * beforehand (non-RoPE: the queries folded into it; RoPE: its layout for the few forms that
+ * want one, else its first read) does not depend on the projection and, with fewer
+ * than 64 sequences, rides in the projection's first launch.
  *   x            DEVICE [batch, n_heads*q_per_kv*d_head] act_dtype: the new tokens' activations
  *   Ak, Av       as for palu_encode_kv
  *   dst_row      DEVICE int32 [batch]: row of hk / hv (counted over all batch*max_seq rows)
@@ -381,9 +381,8 @@ int palu_decode_step(const palu_layer_desc* desc, int32_t batch, int32_t seq_len
 
 /*
  * palu_decode_step from transposed weights (palu_encode_kv_t followed by
- * palu_attn_decode, in one call): the projection is one launch, and where the step
- * folds the query into B_k that fold rides in the projection's workgroups, so the
- * whole append costs one launch.  No encode workspace.  Arguments as for
+ * palu_attn_decode, in one call): the projection is one launch, and what attention needs
+ * of B_k beforehand rides in its workgroups, so the whole append costs one launch.  No encode workspace.  Arguments as for
  * palu_decode_step with Akt, Avt as for palu_encode_kv_t; batch < 64.
  */
 int palu_decode_step_t(const palu_layer_desc* desc, int32_t batch, int32_t seq_len, int32_t max_seq,

@@ -246,6 +246,17 @@ int plan_score(const Meta& m, ScorePlan* p, bool widen = true, int split = 0) {
   return PALU_OK;
 }
 
+// A unit of plan_score over the heads of `m` as score16_kernel takes it, whose weights come straight from B_k: bk_off0 is the
+// first row (of the slice) of the unit's first group, head_stride the row pitch, heads are counted from the group's first.
+ScoreUnit unit16(const Meta& m, ScoreUnit u) {
+  const int j = m.group_of_head[u.h0];
+  const int width = (m.head_off[j + 1] - m.head_off[j]) / m.qpk * PALU_D_HEAD;
+  u.bk_off0 = m.bk_off[j] / m.qpk + (u.k_off0 - m.k_off[j]) * width;
+  u.head_stride = width;
+  u.head_off0 = m.head_off[j];
+  return u;
+}
+
 // ---- value-path work units -----------------------------------------------------
 // Units of the matrix-core value kernel: at most 256 latent columns and 16 heads each.
 // Small adjacent groups are merged (up to 4 heads, 256 columns) so that a
@@ -815,14 +826,16 @@ int launch_encode_gemm(int act, const EncodeArgs& a, int max_R, int n_sides, boo
   return launch_encode_gemm_tiles(act, a, max_R, n_sides, quant, (int)g_opt_encode_tile, device_cu_count(), s);
 }
 
-int launch_encode(int act, const EncodePlan& p, hipStream_t s) {
-  const EncodeArgs& a = p.a;
-  if (p.gemm) return launch_encode_gemm(act, a, p.max_R, p.n_sides, false, s);
+// warm: see WarmArgs
+int launch_encode(int act, const EncodePlan& p, hipStream_t s, WarmArgs warm = WarmArgs{nullptr, 0}) {
+  if (p.gemm) return launch_encode_gemm(act, p.a, p.max_R, p.n_sides, false, s);
   if (p.transposed) {
     using EncTFn = void (*)(EncodeTArgs);
     static const EncTFn t_f16[4] = {encode_t_kernel<F16, 1>, encode_t_kernel<F16, 2>, encode_t_kernel<F16, 4>, encode_t_kernel<F16, 8>};
     static const EncTFn t_bf16[4] = {encode_t_kernel<BF16, 1>, encode_t_kernel<BF16, 2>, encode_t_kernel<BF16, 4>, encode_t_kernel<BF16, 8>};
-    hipLaunchKernelGGL(act == PALU_F16 ? t_f16[p.tok_cls] : t_bf16[p.tok_cls], dim3(p.t_blocks), dim3(256), p.t_lds, s, p.t);
+    EncodeTArgs t = p.t;
+    t.warm = warm;
+    hipLaunchKernelGGL(act == PALU_F16 ? t_f16[p.tok_cls] : t_bf16[p.tok_cls], dim3(p.t_blocks), dim3(256), p.t_lds, s, t);
     return launch_ok();
   }
   using EncFn = void (*)(EncodeArgs);
@@ -832,6 +845,8 @@ int launch_encode(int act, const EncodePlan& p, hipStream_t s) {
                                         encode_partial_kernel<BF16, 3>, encode_partial_kernel<BF16, 4>};
   unsigned g1[3];
   encode_partial_grid(p, g1);
+  EncodeArgs a = p.a;
+  a.warm = warm;
   hipLaunchKernelGGL(act == PALU_F16 ? partial_f16[p.tok_cls] : partial_bf16[p.tok_cls], dim3(g1[0], g1[1], g1[2]), dim3(256), 0, s, a);
   if (launch_ok() != PALU_OK) return PALU_ERR_HIP;
   return launch_encode_finish(act, p, s);
@@ -1210,7 +1225,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     if (kv_units && (st = plan_score(mk, &spk, false, shared16 || shared4 ? split : 0)) != PALU_OK) return st;
     const ScorePlan& plan = kv_units ? spk : sp;
 
-    // 1. B_k in the score kernel's operand order (shared-key form: and the rotated queries beside it)
+    // 1. B_k in score_kernel's operand order, where a head runs there (shared-key form: and the rotated queries beside it)
     static thread_local FoldArgs fa;
     {
       fa.Bk = static_cast<const uint16_t*>(Bk);
@@ -1222,15 +1237,23 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         fa.rev_lo[f] = (float)(rev - (double)fa.rev_hi[f]);
       }
       fa.meta = mk;
-      fa.layout16 = use16 ? (split16 ? 2 : 1) : (whole4 ? (split4 ? 2 : 1) : 0);
-      int max_r = 0;
-      for (int j = 0; j < m.n_groups; ++j) max_r = std::max(max_r, m.k_off[j + 1] - m.k_off[j]);
+      fa.skip16 = use16 ? (split16 ? 2 : 1) : (whole4 ? (split4 ? 2 : 1) : 0);
+      int max_r = PALU_RANK_MULTIPLE;                            // of the groups that are laid out
+      for (int j = 0; j < m.n_groups; ++j) {
+        const int r = m.k_off[j + 1] - m.k_off[j];
+        if (!(fa.skip16 && r >= 64 && (fa.skip16 == 2 || r <= 256 || r > 512))) max_r = std::max(max_r, r);
+      }
       const dim3 g((unsigned)(max_r / 16), (unsigned)mk.n_heads, 1u);
       if ((st = mark(0)) != PALU_OK) return st;
       const long long fold_items = (long long)g.x * g.y * g.z + (shared_key ? (long long)mk.n_heads * batch : 0);
-      const bool fused_head = enc_pending && fold_items <= ride_along_items(*enc);
+      // score16_kernel reads B_k as it is: the layout is for what runs on score_kernel
+      bool need_fold = shared_key || !(use16 || whole4);
+      for (int cls = 0; cls < plan.n_cls; ++cls)
+        need_fold = need_fold || (plan.cls_id[cls] != kSlicedCls && !rank_class_16(plan.cls_id[cls] / 3));
+      const bool fused_head = need_fold && enc_pending && fold_items <= ride_along_items(*enc);
       if (enc_pending && !fused_head) {
-        if ((st = launch_encode(act, *enc, s)) != PALU_OK) return st;
+        const WarmArgs warm{static_cast<const uint4v*>(Bk), need_fold ? 0u : (unsigned)((size_t)(m.bk_off[m.n_groups] / m.qpk) * 2 / 16)};
+        if ((st = launch_encode(act, *enc, s, warm)) != PALU_OK) return st;
         enc_pending = false;
       }
       if (fused_head) {
@@ -1266,7 +1289,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         if ((st = launch_ok()) != PALU_OK) return st;
         if ((st = launch_encode_finish(act, *enc, s)) != PALU_OK) return st;
         enc_pending = false;
-      } else {
+      } else if (need_fold) {
         hipLaunchKernelGGL(fold_kernel, g, dim3(256), 0, s, fa);
         if ((st = launch_ok()) != PALU_OK) return st;
       }
@@ -1305,6 +1328,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       a.hk_zero = static_cast<const uint16_t*>(hk_zero);
       a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
       a.w_scale = reinterpret_cast<const float*>(ws + w.w_scale);
+      a.Bk = static_cast<const uint16_t*>(Bk);
       // the table's tiles: float32 part first, the shared-key form's float16 rows behind it
       a.rope_rows = static_cast<const unsigned char*>(rope_table) + (shared_key ? kRopeTileBytes : 0);
       a.rope_tile_stride = kRopeTableStride;
@@ -1455,14 +1479,13 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           a.mix.n_units[x] = n_units_cls[cls];
           a.mix.nk[x] = nk;
           for (int i = 0; i < plan.total_units; ++i)
-            if (plan.unit_cls[i] == cls) a.units.u[a.units.n_units++] = plan.units[i];
+            if (plan.unit_cls[i] == cls) a.units.u[a.units.n_units++] = unit16(m, plan.units[i]);
           first += (long long)a.mix.n_wg[x] * n_units_cls[cls] * mix_seqs;
           lds = std::max(lds, (size_t)score16_lds_bytes(32 * nk));
         }
         if (first >= (1LL << 31)) return PALU_ERR_UNSUPPORTED;
         ScoreFn fn = mix_flat ? score16_mixed_fn<true>(act) : score16_mixed_fn<false>(act);
         if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
-        a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
         hipLaunchKernelGGL(fn, dim3((unsigned)first), dim3(256), lds, s, a);
         if ((st = launch_ok()) != PALU_OK) return st;
       }
@@ -1488,7 +1511,6 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
             const int rows = std::min(sk_pass_rows, m.qpk - row0);
             a.sk_row0 = row0;
             a.sk_rows = rows;
-            a.mfold = reinterpret_cast<const uint16_t*>(ws + w.mfold);
             a.units.n_units = 0;
             auto flush_q = [&]() -> int {
               if (a.units.n_units == 0) return PALU_OK;
@@ -1504,7 +1526,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
             };
             for (int i = 0; i < plan.total_units; ++i) {
               if (plan.unit_cls[i] != cls) continue;
-              a.units.u[a.units.n_units++] = plan.units[i];
+              a.units.u[a.units.n_units++] = unit16(mk, plan.units[i]);
               if (a.units.n_units == kMaxScoreUnits && (st = flush_q()) != PALU_OK) return st;
             }
             if ((st = flush_q()) != PALU_OK) return st;
@@ -1544,7 +1566,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         a.units.n_units = 0;
         for (int i = 0; i < plan.total_units; ++i) {
           if (plan.unit_cls[i] != cls) continue;
-          a.units.u[a.units.n_units++] = plan.units[i];
+          a.units.u[a.units.n_units++] = form16 && !k8 ? unit16(mk, plan.units[i]) : plan.units[i];
           if (a.units.n_units == kMaxScoreUnits && (st = flush()) != PALU_OK) return st;
         }
         if ((st = flush()) != PALU_OK) return st;

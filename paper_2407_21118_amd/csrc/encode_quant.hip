@@ -25,11 +25,27 @@ struct EncodeSide {
   uint16_t* scale;         // ... and the fp16 (scale, zero) pairs, rows of R/128
   uint16_t* zero;
 };
+// Memory that the next launch begins by reading (a decode step: B_k, which every workgroup of the score kernel loads before it
+// can do anything): each thread of the projection's first launch requests 16 bytes of it and drops them, so that the
+// next launch finds them in the caches.  n_words: 16-byte words, 0: nothing to fetch.
+struct WarmArgs {
+  const uint4v* p;
+  unsigned n_words;
+};
+__device__ __forceinline__ uint4v warm_request(const WarmArgs& w, unsigned wg) {
+  uint4v v = {0, 0, 0, 0};
+  const unsigned i = wg * 256 + threadIdx.x;
+  if (i < w.n_words) v = w.p[i];
+  return v;
+}
+__device__ __forceinline__ void warm_done(const uint4v& v) { asm volatile("" :: "v"(v)); }
+
 struct EncodeArgs {
   const uint16_t* x;       // [n_tok, d]
   const int32_t* dst_row;
   EncodeSide side[2];      // key and value caches; blockIdx.z selects (one launch may cover both)
   int n_tok, d, k_splits;
+  WarmArgs warm;
 };
 
 // The prompt-sized projection (encode_gemm.hip, compiled on its own): C[n_tok, R] = X A on the matrix
@@ -139,7 +155,9 @@ __device__ __forceinline__ void encode_partial_body(const EncodeArgs& a, int bx,
 
 template <typename T, int MT>
 __global__ __launch_bounds__(256, MT <= 2 ? 2 : 1) void encode_partial_kernel(EncodeArgs a) {
+  const uint4v warm = warm_request(a.warm, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
   encode_partial_body<T, MT>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+  warm_done(warm);
 }
 
 // Sums the split-K partials in a fixed order, rounds once, scatters the rows.
@@ -186,6 +204,7 @@ struct EncodeTArgs {
   long long row_stride[2];
   int R[2];
   int n_tok, d, wg_side1;          // workgroups below wg_side1 work on side 0
+  WarmArgs warm;
 };
 // acc + sum of the 8 products of two packed 16-byte operands
 template <typename T>
@@ -292,7 +311,9 @@ __device__ __forceinline__ void encode_t_body(const EncodeTArgs& a, int wg_id, E
 
 template <typename T, int TOK>
 __global__ __launch_bounds__(256) void encode_t_kernel(EncodeTArgs a) {
+  const uint4v warm = warm_request(a.warm, blockIdx.x);
   encode_t_body<T, TOK>(a, blockIdx.x);
+  warm_done(warm);
 }
 
 // The quantizer of Appendix A with B = 4 (s = (max-min)/(2^B-1), z = round(-min/s),

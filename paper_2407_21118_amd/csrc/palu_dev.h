@@ -200,8 +200,9 @@ struct ScoreUnit {
   int s;                     // heads per group inside the unit
   int head_off0;             // first head of the unit's first group
   int k_off0;                // first latent column the unit stages (group start + rank slice)
-  int bk_off0;               // element offset of the unit's first head's folded weights (+ rank slice)
-  int head_stride;           // elements between the folded weights of consecutive heads (rank * 128)
+  int bk_off0;               // element offset of the unit's first head's folded weights (+ rank slice); score16_kernel: of the
+                             // first group's (first row of the slice's) B_k
+  int head_stride;           // elements between the folded weights of consecutive heads (rank * 128); score16_kernel: between rows of B_k
   int part0;                 // first partial-score plane the unit writes (2 per rank slice)
 };
 constexpr int kMaxScoreUnits = 64;      // per launch
@@ -225,6 +226,7 @@ struct ScoreArgs {
   const uint16_t* hk_scale;  // fp16 bits (int4 only)
   const uint16_t* hk_zero;
   const uint16_t* mfold;     // B_k transposed, in matrix-core operand order (fold_kernel); per batch stride mfold_bstride elements
+  const uint16_t* Bk;        // score16_kernel: the reconstruction matrices as the caller has them
   const void* rope_rows;     // angles of the cached tokens in tiles of 32 tokens, rope_tile_stride bytes apart (the table
                              // itself, or tiles gathered by k_pos): float32 parts (1) for the one-query form, float16 rows (2)
                              // for the shared-key form
@@ -290,7 +292,7 @@ struct FoldArgs {
   uint16_t* mfold;           // B_k transposed per head, in matrix-core operand order
   float rev_hi[kHalf];       // theta^(-2f/128) / (2 pi) from the host's float64 value, as a float pair hi + lo
   float rev_lo[kHalf];       // (read by the query items that ride in the same launch, see qfrag_body)
-  int layout16;              // score16_kernel's operand order for: 1 = heads of rank 64 .. 256 and above 512 (slices of 256); 2 = every head of rank 64 and more
+  int skip16;                // heads on score16_kernel, which need no layout: 1 = those of rank 64 .. 256 and above 512, 2 = of rank 64 and more
   Meta meta;
 };
 

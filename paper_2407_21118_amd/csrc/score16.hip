@@ -54,8 +54,7 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // G:  groups spanned by the workgroup's heads (1, 2 or 4 adjacent groups of equal rank): the staged
 //     latent row is G * 32 * NK columns wide
 // FLAT: a workgroup's run goes through the tiles of all sequences, else it lies in one
-// grid (workgroups per unit and sequence, units, sequences; FLAT: per unit, units), 256 threads.  a.mfold: B_k^T in the operand order of
-// fold_body's 16-feature layout.
+// grid (workgroups per unit and sequence, units, sequences; FLAT: per unit, units), 256 threads.
 // NQ: queries that share the wavefront's key/value head (grouped-query layers, several query tokens per sequence):
 //     the unit's heads are then key/value heads with a.m_qpk query rows each; this launch takes rows a.sk_row0 ..
 //     + a.sk_rows - 1 (at most NQ) of every key/value head: the key tile is rebuilt once, rotated once in float32
@@ -71,7 +70,14 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // weights are pinned to the accumulation registers, which the matrix instructions read in place (left to
 // itself the compiler kept part of them as spilled copies, up to four moves per matrix instruction), and the loop
 // has no branch inside a sub-tile.  Instructions per tile at rank 256: one query 519 -> 500, four queries 1300 -> 790
-// (4 x 16384 tokens, 8 key/value heads: 65 -> 45 us).
+// (4 x 16384 tokens, 8 key/value heads: 65 -> 45 us).  LDS offsets that move on with the tile instead of being computed from
+// its number: 500 -> 492, 4-bit keys 627 -> 603, with four queries 922 -> 904.
+//
+// The weights come from B_k as the caller has it.  A launch of its own used to lay them out (5 us, or 3 us more for the
+// projection that it rode in); transposing them in registers, 64 byte permutes per k-step of which all but the first are
+// dealt out between the first sub-tile's matrix instructions (FLAT, 4-bit keys: ahead of them), adds about 1 us to the
+// kernel: one sequence of 1024 / 16384 tokens 22.9 / 69.6 -> 21.4 / 67.8 us a step, 16 x 8192 in 4 bits 300 -> 296,
+// four queries over 2 x 8190 77.6 -> 75.1; long launches, which are at the power limit, level.
 template <typename T, int NK, int G, int NQ, int QB, bool FLAT>
 __global__ __launch_bounds__(256) void score16_kernel(ScoreArgs a) {
   const int wg = blockIdx.x, n_wg = a.n_wg, unit = blockIdx.y, seq = blockIdx.z, run = a.run, run_more = a.run_more;

@@ -322,3 +322,21 @@ def test_merge_of_many_rows(batch, heads, group, rv, q_per_kv):
     # float32 sums of at most 288 products on either side
     assert np.abs(out - got).max() <= 1e-5 * np.abs(out).max()
     say(f"[edges] merge rows={batch * layer.n_q_heads} rv={rv} q_per_kv={q_per_kv} rel err {err:.3e}")
+
+
+@pytest.mark.parametrize("group,ranks,q_per_kv,dtype", [(4, [64, 32, 256, 320, 512, 1024], 1, "f16"), (1, [96, 32, 512, 2048, 64], 3, "bf16"), (5, [288, 64, 128, 224], 1, "f16"),
+                                                        (3, [160, 512, 768], 2, "f16"), (2, [64, 64, 64, 128, 128, 96, 96], 1, "bf16"), (1, [64] * 7 + [32], 1, "f16")])
+def test_score_weights_straight_from_b(group, ranks, q_per_kv, dtype):
+    """Key weights that score workgroups transpose from B_k themselves: units of one, two and four groups, heads that do not fill
+    a workgroup, ranks in one slice and in several, beside a rank of 32, which alone is laid out by the launch before."""
+    layer = synth.ragged_layer(group * len(ranks), group, ranks, [64] * len(ranks), q_per_kv=q_per_kv)
+    rng = np.random.default_rng(12)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, dtype)  # noqa: E731
+    n = np.array([70, 1, 33], np.int32)
+    Bk = np.concatenate([draw(r * group * 128, by=r ** -0.5) for r in ranks])
+    case = synth.Case("edges", layer, dtype, 3, 70, draw(3, layer.n_q_heads, 128), n - 1, draw(3, 70, layer.R_k), draw(3, 70, layer.R_v), Bk,
+                      draw(layer.b_elems("v"), by=64 ** -0.5))
+    case.seq_lens = n
+    err = max(rel_err(run_hip(case), run_oracle(case)))
+    say(f"[edges] weights from B group={group} ranks={ranks} q_per_kv={q_per_kv} {dtype} rel err {err:.3e}")
+    assert err <= TOL_FP
