@@ -830,24 +830,20 @@ int launch_encode_gemm(int act, const EncodeArgs& a, int max_R, int n_sides, boo
 int launch_encode(int act, const EncodePlan& p, hipStream_t s, WarmArgs warm = WarmArgs{nullptr, 0}) {
   if (p.gemm) return launch_encode_gemm(act, p.a, p.max_R, p.n_sides, false, s);
   if (p.transposed) {
-    using EncTFn = void (*)(EncodeTArgs);
+    using EncTFn = void (*)(EncodeTArgs, WarmArgs);
     static const EncTFn t_f16[4] = {encode_t_kernel<F16, 1>, encode_t_kernel<F16, 2>, encode_t_kernel<F16, 4>, encode_t_kernel<F16, 8>};
     static const EncTFn t_bf16[4] = {encode_t_kernel<BF16, 1>, encode_t_kernel<BF16, 2>, encode_t_kernel<BF16, 4>, encode_t_kernel<BF16, 8>};
-    EncodeTArgs t = p.t;
-    t.warm = warm;
-    hipLaunchKernelGGL(act == PALU_F16 ? t_f16[p.tok_cls] : t_bf16[p.tok_cls], dim3(p.t_blocks), dim3(256), p.t_lds, s, t);
+    hipLaunchKernelGGL(act == PALU_F16 ? t_f16[p.tok_cls] : t_bf16[p.tok_cls], dim3(p.t_blocks), dim3(256), p.t_lds, s, p.t, warm);
     return launch_ok();
   }
-  using EncFn = void (*)(EncodeArgs);
+  using EncFn = void (*)(EncodeArgs, WarmArgs);
   static const EncFn partial_f16[4] = {encode_partial_kernel<F16, 1>, encode_partial_kernel<F16, 2>,
                                        encode_partial_kernel<F16, 3>, encode_partial_kernel<F16, 4>};
   static const EncFn partial_bf16[4] = {encode_partial_kernel<BF16, 1>, encode_partial_kernel<BF16, 2>,
                                         encode_partial_kernel<BF16, 3>, encode_partial_kernel<BF16, 4>};
   unsigned g1[3];
   encode_partial_grid(p, g1);
-  EncodeArgs a = p.a;
-  a.warm = warm;
-  hipLaunchKernelGGL(act == PALU_F16 ? partial_f16[p.tok_cls] : partial_bf16[p.tok_cls], dim3(g1[0], g1[1], g1[2]), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(act == PALU_F16 ? partial_f16[p.tok_cls] : partial_bf16[p.tok_cls], dim3(g1[0], g1[1], g1[2]), dim3(256), 0, s, p.a, warm);
   if (launch_ok() != PALU_OK) return PALU_ERR_HIP;
   return launch_encode_finish(act, p, s);
 }

@@ -45,7 +45,6 @@ struct EncodeArgs {
   const int32_t* dst_row;
   EncodeSide side[2];      // key and value caches; blockIdx.z selects (one launch may cover both)
   int n_tok, d, k_splits;
-  WarmArgs warm;
 };
 
 // The prompt-sized projection (encode_gemm.hip, compiled on its own): C[n_tok, R] = X A on the matrix
@@ -154,8 +153,8 @@ __device__ __forceinline__ void encode_partial_body(const EncodeArgs& a, int bx,
 }
 
 template <typename T, int MT>
-__global__ __launch_bounds__(256, MT <= 2 ? 2 : 1) void encode_partial_kernel(EncodeArgs a) {
-  const uint4v warm = warm_request(a.warm, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
+__global__ __launch_bounds__(256, MT <= 2 ? 2 : 1) void encode_partial_kernel(EncodeArgs a, WarmArgs w) {
+  const uint4v warm = warm_request(w, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
   encode_partial_body<T, MT>(a, blockIdx.x, blockIdx.y, blockIdx.z);
   warm_done(warm);
 }
@@ -204,7 +203,6 @@ struct EncodeTArgs {
   long long row_stride[2];
   int R[2];
   int n_tok, d, wg_side1;          // workgroups below wg_side1 work on side 0
-  WarmArgs warm;
 };
 // acc + sum of the 8 products of two packed 16-byte operands
 template <typename T>
@@ -310,8 +308,8 @@ __device__ __forceinline__ void encode_t_body(const EncodeTArgs& a, int wg_id, E
 }
 
 template <typename T, int TOK>
-__global__ __launch_bounds__(256) void encode_t_kernel(EncodeTArgs a) {
-  const uint4v warm = warm_request(a.warm, blockIdx.x);
+__global__ __launch_bounds__(256) void encode_t_kernel(EncodeTArgs a, WarmArgs w) {
+  const uint4v warm = warm_request(w, blockIdx.x);
   encode_t_body<T, TOK>(a, blockIdx.x);
   warm_done(warm);
 }
