@@ -444,9 +444,9 @@ int allow_lds(K kernel, size_t bytes) {
 
 inline bool rank_class_16(int rc) { return rc >= 1 && rc <= 7; }
 // ... and several queries per key/value head: the key rebuilt once per key/value head and pass of up to 8 query
-// rows (ranks 192 .. 256) or 4 (ranks 64 .. 160); the kernel is compiled for 2, 4 and 8 rows
+// rows; the kernel is compiled for 2, 4 and 8 rows
 inline bool shared16_ok(int rc) { return rc >= 1 && rc <= 7; }
-inline int shared16_rows_per_pass(int rc) { return rc >= 5 ? 8 : 4; }
+constexpr int kShared16Rows = 8;
 constexpr int score16q4_lds_bytes(int width) { return 3 * score_tile_bytes(width) + 3 * kRopeTileBytes; }
 
 // 4-bit keys of ranks 384 and 512: two slices of whole heads (score16_kernel, four heads or key/value heads to a workgroup) or
@@ -1187,16 +1187,13 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     // ... and with 2, 4 or 8 queries per key/value head and ranks 128 .. 256 one whole key/value head per wavefront:
     // the key is rebuilt and rotated once in float32 for the queries that share it (exact shared-key form)
     bool shared16 = use16 && m.qpk > 1 && g_opt_score_fp8 == 0;
-    int sk_pass_rows = 8;
     for (int j = 0; j < m.n_groups && shared16; ++j) {
       const int r = m.k_off[j + 1] - m.k_off[j];
       // ranks 288 .. 512 run as two slices of 128 .. 256 rows (plan_score), each a unit of its own rank class
       const int r0 = (r > 256 && r <= 512 && split16) ? (r + 63) / 64 * 32 : r;
       for (int rs : {r0, r - r0}) {
         if (rs == 0) continue;
-        const int rcj = rank_class(rs);
-        shared16 = shared16 && shared16_ok(rcj);
-        if (shared16) sk_pass_rows = std::min(sk_pass_rows, shared16_rows_per_pass(rcj));
+        shared16 = shared16 && shared16_ok(rank_class(rs));
       }
     }
     // the same with 4-bit keys of ranks up to 256, or 512 in slices: their tiles are dequantized once per pass for the queries that share them
@@ -1204,7 +1201,6 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     for (int j = 0; j < m.n_groups && shared4; ++j) {
       const int r = m.k_off[j + 1] - m.k_off[j];
       shared4 = r <= (split4 ? 512 : 256);
-      if (r % 256 != 0) sk_pass_rows = std::min(sk_pass_rows, 4);
     }
     const bool kv_units = shared_key || shared16 || shared4;   // the score units are key/value heads
     const Meta mk = kv_units ? kv_head_meta(m) : m;
@@ -1501,10 +1497,10 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         if (k16) lds = (size_t)score16_lds_bytes(width);
         if (w4) lds = (size_t)score16q4_lds_bytes(width);
         if (shared16 || shared4) {
-          // exact shared-key form: passes of up to sk_pass_rows query rows of every key/value head, each pass one
+          // exact shared-key form: passes of up to kShared16Rows query rows of every key/value head, each pass one
           // launch per flush of units (the key tile is rebuilt once per pass)
-          for (int row0 = 0; row0 < m.qpk; row0 += sk_pass_rows) {
-            const int rows = std::min(sk_pass_rows, m.qpk - row0);
+          for (int row0 = 0; row0 < m.qpk; row0 += kShared16Rows) {
+            const int rows = std::min(kShared16Rows, m.qpk - row0);
             a.sk_row0 = row0;
             a.sk_rows = rows;
             a.units.n_units = 0;

@@ -19,8 +19,17 @@
 // Several queries per key/value head (grouped-query layers, several query tokens per sequence; NQ = 2, 4, 8, other
 // counts in passes with idle rows): the
 // wavefront's head is a key/value head; its key tile is rebuilt once, each key pair rotated once in float32 and
-// multiplied by each of the NQ rotated queries (4 + 2 NQ operations per token and pair instead of 6 NQ), then one
-// lane exchange and one score row per query.
+// multiplied by each of the NQ rotated queries.  NQ = 2: on the vector ALU (8 operations per token and pair instead of 12), then one
+// lane exchange and one score row per query.  NQ = 4, 8 (kMx): vector work of 4 + 2 NQ operations per pair would
+// take longer than the matrix instructions (which leave room for two vector operations each: 16.8 cycles alone or
+// with two, 21.6 with three, 33.8 with six), so the products go to v_mfma_f32_4x4x1_16b, exact float32 at twice the
+// vector rate.  It wants tokens across lanes, so the operands of the key product are exchanged (a lane then holds one token of 16
+// pairs), and the angles are read token by token from the same tile.  The 32 (64) products of a sub-tile are issued in
+// one go behind its rotations: alone each takes 8.8 cycles, but one between two 16-bit matrix instructions 28 (one
+// at a time they were no faster than the vector form).  What is left to sum lies in the four quarters of the wavefront: three lane
+// swaps and adds for four queries instead of eleven operations each.  us a call, vector form -> this: 4 queries over 2 x 8190
+// tokens of 32 heads, rank 128 75.1 -> 69.5, 256 74.5 -> 68.5, 64 120.8 -> 94.8; 4 x 16384 tokens of 8 heads 76.6 -> 74.1;
+// 8 queries, rank 256 89.6 -> 77.1, and at the ranks that took passes of four before, 128 99.9 -> 66.6, 64 225 -> 123.
 
 #pragma once
 #include <type_traits>
@@ -69,7 +78,7 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // pipe's (128 matrix instructions of 16 cycles per 32-token tile at rank 256).  Two things keep the count down: the
 // weights are pinned to the accumulation registers, which the matrix instructions read in place (left to
 // itself the compiler kept part of them as spilled copies, up to four moves per matrix instruction), and the loop
-// has no branch inside a sub-tile.  Instructions per tile at rank 256: one query 519 -> 500, four queries 1300 -> 790
+// has no branch inside a sub-tile.  Instructions per tile at rank 256: one query 519 -> 500, four queries (vector form) 1300 -> 790
 // (4 x 16384 tokens, 8 key/value heads: 65 -> 45 us).  LDS offsets that move on with the tile instead of being computed from
 // its number: 500 -> 492, 4-bit keys 627 -> 603, with four queries 922 -> 904.
 //

@@ -15,8 +15,7 @@ template <typename T, int NK>
 ScoreFn score16q_fn_n(int nq) {
   if (nq <= 2) return score16_kernel<T, NK, 1, 2, 0, kFlat>;
   if (nq <= 4) return score16_kernel<T, NK, 1, 4, 0, kFlat>;
-  if constexpr (NK >= 6) { if (nq <= 8) return score16_kernel<T, NK, 1, 8, 0, kFlat>; }
-  return nullptr;
+  return score16_kernel<T, NK, 1, 8, 0, kFlat>;
 }
 template <typename T>
 ScoreFn score16q_fn_t(int rc, int nq) {
@@ -48,8 +47,7 @@ ScoreFn score16q4_fn_n(int nq, int lg) {
   }
   if (nq <= 2) return score16_kernel<F16, NK, 1, 2, 4, kFlat>;
   if (nq <= 4) return score16_kernel<F16, NK, 1, 4, 4, kFlat>;
-  if constexpr (NK == 8) return score16_kernel<F16, NK, 1, 8, 4, kFlat>;
-  return nullptr;
+  return score16_kernel<F16, NK, 1, 8, 4, kFlat>;
 }
 }  // namespace
 template <>

@@ -340,3 +340,35 @@ def test_score_weights_straight_from_b(group, ranks, q_per_kv, dtype):
     err = max(rel_err(run_hip(case), run_oracle(case)))
     say(f"[edges] weights from B group={group} ranks={ranks} q_per_kv={q_per_kv} {dtype} rel err {err:.3e}")
     assert err <= TOL_FP
+
+
+@pytest.mark.parametrize("rk,q_per_kv,dtype,bits", [(64, 4, "f16", 16), (96, 7, "bf16", 16), (64, 8, "f16", 16), (128, 5, "f16", 16), (160, 8, "bf16", 16), (256, 9, "f16", 16),
+                                                    (128, 8, "f16", 4), (256, 8, "f16", 4)])
+@pytest.mark.parametrize("flat", [False, True])
+def test_query_products_on_matrix_cores(rk, q_per_kv, dtype, bits, flat):
+    """Four queries and more of one key: every rank class with few matrix instructions to deal work out between, blocks of four
+    queries with idle ones, a pass of one row behind one of eight; one run per sequence, and runs over the tiles of all
+    sequences (FLAT); 4-bit keys with and without zero-points that need the float32 form."""
+    layer = synth.uniform_layer(2, 2, rk, 128, q_per_kv=q_per_kv)
+    rng = np.random.default_rng(3)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, dtype)  # noqa: E731
+    seq = 330
+    n = np.array([seq, 1, 16, 33, 177], np.int32)
+    batch = len(n)
+    case = synth.Case("edges", layer, dtype, batch, seq, draw(batch, layer.n_q_heads, 128), n + 5, draw(batch, seq, layer.R_k), draw(batch, seq, layer.R_v),
+                      draw(layer.b_elems("k"), by=rk ** -0.5), draw(layer.b_elems("v"), by=128 ** -0.5))
+    case.seq_lens = n
+    quant = {}
+    if bits == 4:
+        quant = {"k": O.quant_latent(case.Hk), "v": O.quant_latent(case.Hv)}
+        odd_zero_rows(case, quant, batch - 1, [(32, 0), (95, -1)])
+    args = (bits == 4, bits == 4, quant)
+    ref = run_oracle(case, args[2], *args[:2])
+    P.palu_set_option("score_chunks", 3 if flat else 0)           # forced runs go through all sequences
+    try:
+        got = run_hip(case, *args)
+    finally:
+        P.palu_set_option("score_chunks", 0)
+    err = max(rel_err(got, ref))
+    say(f"[edges] query products rank={rk} q_per_kv={q_per_kv} {dtype} bits={bits} flat={flat} rel err {err:.3e}")
+    assert err <= (TOL_I4 if bits == 4 else TOL_FP)
