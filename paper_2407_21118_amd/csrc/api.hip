@@ -372,17 +372,25 @@ int plan_qk(const Meta& m, bool quantized, QkPlan* p) {
 }
 
 // Wavefronts per compute unit the value kernel's splits aim at.
-inline int value_waves_per_cu(const palu_layer_desc* d) { return latent_bits(d->v_latent_dtype) ? 8 : 4; }
+constexpr int kValueWavesPerCu = 4;
+// Tokens per wavefront, whole sets of 32, such that items x seq_len tokens are at most waves_per_cu wavefronts per compute unit.
+// Quantized latents: the exact quotient, so that lengths that divide evenly fill the chip (524288 tokens of a 4-bit unit: 512
+// instead of 544).  Unquantized ones take the next set on an exact quotient: 160 tokens instead of 128 (1 x 16384 tokens,
+// 4 x 16384 of two units) left one compute unit in five idle and was 0.4 .. 0.8 us faster all the same, there being fewer splits to merge.
+long long wave_tokens(long long items, int seq_len, int waves_per_cu, bool quantized) {
+  const long long waves = (long long)waves_per_cu * device_cu_count();
+  return ceil_div((int)std::min<long long>((items * seq_len + (quantized ? waves - 1 : waves)) / waves, 1 << 30), 32) * 32LL;
+}
 
 // Tokens per value split and number of splits for a given attended length: a
-// split is one wavefront's share; aim at four wavefronts per compute unit,
+// split is one wavefront's share; aim at four wavefronts per compute unit (eight, which 4-bit latents had, give their merge
+// twice the splits: 1 x 65536 tokens without RoPE 67.6 us a step, with four 62.2, 1 x 32768 56.2 / 51.2, 2 bits 68 / 65),
 // splits of 64 to 512 tokens (more where the merge kernel's split limit asks for it).  Units of more than 4 heads
 // write larger partial results per split (heads x columns floats against tokens x columns latents read), which the
 // merge kernel reads again: their splits may be four times as long, where that still fills the chip.
 constexpr int kPvSplitMin = 64, kPvSplitMax = 512;
-void split_geometry(int total_units, int batch, int seq_len, int waves_per_cu, int max_unit_heads, int* split_tokens, int* n_split) {
-  const long long items = std::max(1, total_units * batch);
-  long long st = ceil_div((int)std::min<long long>(items * seq_len / ((long long)waves_per_cu * device_cu_count()) + 1, 1 << 30), 32) * 32LL;
+void split_geometry(int total_units, int batch, int seq_len, bool quantized, int max_unit_heads, int* split_tokens, int* n_split) {
+  long long st = wave_tokens(std::max(1, total_units * batch), seq_len, kValueWavesPerCu, quantized);
   st = std::min<long long>(std::max<long long>(st, kPvSplitMin), max_unit_heads > 4 ? 4 * kPvSplitMax : kPvSplitMax);
   if (g_opt_value_split > 0) st = g_opt_value_split;
   st = std::max<long long>(st, ceil_div(ceil_div(seq_len, kMaxSplits), 32) * 32LL);
@@ -390,8 +398,8 @@ void split_geometry(int total_units, int batch, int seq_len, int waves_per_cu, i
   *n_split = ceil_div(seq_len, (int)st);
 }
 // Upper bound of the number of splits of any attended length up to max_seq.
-int split_bound(int total_units, int batch, int max_seq, int waves_per_cu) {
-  int cap = std::max(ceil_div(waves_per_cu * device_cu_count(), std::max(1, total_units * batch)), ceil_div(max_seq, kPvSplitMax));
+int split_bound(int total_units, int batch, int max_seq) {
+  int cap = std::max(ceil_div(kValueWavesPerCu * device_cu_count(), std::max(1, total_units * batch)), ceil_div(max_seq, kPvSplitMax));
   if (g_opt_value_split > 0) cap = std::max(cap, ceil_div(max_seq, (int)g_opt_value_split));
   return std::min(cap, kMaxSplits) + 2;
 }
@@ -961,7 +969,7 @@ static int decode_workspace_bytes(const palu_layer_desc* desc, int32_t batch, in
   if ((st = plan_score(m, &sp, !(kb == 2 || kb == 3))) != PALU_OK) return st;
   if ((st = plan_pv(m, &pp)) != PALU_OK) return st;
   Workspace w;
-  carve(m, batch, max_seq, split_bound(pp.total_units, batch, max_seq, value_waves_per_cu(desc)), 2 * sp.max_slices,
+  carve(m, batch, max_seq, split_bound(pp.total_units, batch, max_seq), 2 * sp.max_slices,
         !(desc->rope_theta > 0.f), &w);
   *out_bytes = w.total;
   return PALU_OK;
@@ -1025,11 +1033,11 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   int split_tokens, n_split;
   int max_unit_heads = 0;
   for (int i = 0; i < pp.total_units; ++i) max_unit_heads = std::max(max_unit_heads, (int)pp.units[i].nh);
-  split_geometry(pp.total_units, batch, seq_len, value_waves_per_cu(desc), max_unit_heads, &split_tokens, &n_split);
+  split_geometry(pp.total_units, batch, seq_len, v_bits != 0, max_unit_heads, &split_tokens, &n_split);
   if (n_split > kMaxSplits) return PALU_ERR_UNSUPPORTED;
   // the value and no-RoPE kernels address a split of the cache with 32-bit byte offsets
   if ((long long)split_tokens * std::max(Rk, Rv) * 2 >= (1LL << 32)) return PALU_ERR_UNSUPPORTED;
-  const int n_split_cap = split_bound(pp.total_units, batch, max_seq, value_waves_per_cu(desc));
+  const int n_split_cap = split_bound(pp.total_units, batch, max_seq);
   Workspace w;
   const bool no_rope = !(desc->rope_theta > 0.f);
   carve(m, batch, max_seq, n_split_cap, 2 * sp.max_slices, no_rope, &w);
@@ -1086,10 +1094,8 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     a.n_heads = m.n_heads;
     a.n_blocks_q = Rk / quant_block;
     a.scale = 1.4426950408889634f / std::sqrt((float)PALU_D_HEAD);
-    {   // tokens per wavefront: four wavefronts per compute unit, 64 to 512 tokens
-      const long long items = std::max(1, qp.total_units * batch);
-      const long long waves_per_cu = k_i4 ? 8 : 4;
-      long long stq = ceil_div((int)std::min<long long>(items * seq_len / (waves_per_cu * device_cu_count()) + 1, 1 << 30), 32) * 32LL;
+    {   // tokens per wavefront: four wavefronts per compute unit, 64 to 512 tokens (quantized keys: eight; nothing is merged here)
+      long long stq = wave_tokens(std::max(1, qp.total_units * batch), seq_len, k_i4 ? 8 : 4, k_i4);
       stq = std::min<long long>(std::max<long long>(stq, kPvSplitMin), kPvSplitMax);
       a.split_tokens = (int)stq;
       a.n_split = ceil_div(seq_len, (int)stq);
