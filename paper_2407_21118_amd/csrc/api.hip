@@ -371,8 +371,8 @@ int plan_qk(const Meta& m, bool quantized, QkPlan* p) {
   return PALU_OK;
 }
 
-// Wavefronts per compute unit the value kernel's splits aim at.
-constexpr int kValueWavesPerCu = 4;
+// Wavefronts per compute unit the value kernel's splits aim at; eight for quantized latents where that makes few splits.
+constexpr int kValueWavesPerCu = 4, kValueFewSplits = 32;
 // Tokens per wavefront, whole sets of 32, such that items x seq_len tokens are at most waves_per_cu wavefronts per compute unit.
 // Quantized latents: the exact quotient, so that lengths that divide evenly fill the chip (524288 tokens of a 4-bit unit: 512
 // instead of 544).  Unquantized ones take the next set on an exact quotient: 160 tokens instead of 128 (1 x 16384 tokens,
@@ -383,23 +383,32 @@ long long wave_tokens(long long items, int seq_len, int waves_per_cu, bool quant
 }
 
 // Tokens per value split and number of splits for a given attended length: a
-// split is one wavefront's share; aim at four wavefronts per compute unit (eight, which 4-bit latents had, give their merge
-// twice the splits: 1 x 65536 tokens without RoPE 67.6 us a step, with four 62.2, 1 x 32768 56.2 / 51.2, 2 bits 68 / 65),
+// split is one wavefront's share; aim at four wavefronts per compute unit.  Quantized latents: at eight, whose shorter rounds end
+// more evenly (five queries of 32 heads in one group, 3 x 4765 tokens: 240 units, 9 splits, 1908 us a call, with 5 splits 1957), unless
+// that leaves the merge more than 32 splits (1 x 65536 tokens without RoPE: 228 splits 67.6 us a step, 128 62.2; 1 x 32768 56.2 / 51.2),
+// or units of more than 4 heads partial results (16 KiB) that rival the latents of a split (36 x 5816 tokens, 3 bits, grouped
+// queries: 224 tokens a split 186 us a step, 416 175);
 // splits of 64 to 512 tokens (more where the merge kernel's split limit asks for it).  Units of more than 4 heads
 // write larger partial results per split (heads x columns floats against tokens x columns latents read), which the
 // merge kernel reads again: their splits may be four times as long, where that still fills the chip.
 constexpr int kPvSplitMin = 64, kPvSplitMax = 512;
 void split_geometry(int total_units, int batch, int seq_len, bool quantized, int max_unit_heads, int* split_tokens, int* n_split) {
-  long long st = wave_tokens(std::max(1, total_units * batch), seq_len, kValueWavesPerCu, quantized);
-  st = std::min<long long>(std::max<long long>(st, kPvSplitMin), max_unit_heads > 4 ? 4 * kPvSplitMax : kPvSplitMax);
+  auto tokens = [&](int waves_per_cu) {
+    const long long st = wave_tokens(std::max(1, total_units * batch), seq_len, waves_per_cu, quantized);
+    return std::min<long long>(std::max<long long>(st, kPvSplitMin), max_unit_heads > 4 ? 4 * kPvSplitMax : kPvSplitMax);
+  };
+  long long st = tokens(quantized ? 2 * kValueWavesPerCu : kValueWavesPerCu);
+  if (quantized && (ceil_div(seq_len, (int)st) > kValueFewSplits || (max_unit_heads > 4 && st < kPvSplitMax))) st = tokens(kValueWavesPerCu);
   if (g_opt_value_split > 0) st = g_opt_value_split;
   st = std::max<long long>(st, ceil_div(ceil_div(seq_len, kMaxSplits), 32) * 32LL);
   *split_tokens = (int)st;
   *n_split = ceil_div(seq_len, (int)st);
 }
 // Upper bound of the number of splits of any attended length up to max_seq.
-int split_bound(int total_units, int batch, int max_seq) {
-  int cap = std::max(ceil_div(kValueWavesPerCu * device_cu_count(), std::max(1, total_units * batch)), ceil_div(max_seq, kPvSplitMax));
+int split_bound(int total_units, int batch, int max_seq, bool quantized) {
+  const int waves = kValueWavesPerCu * device_cu_count(), items = std::max(1, total_units * batch);
+  int cap = std::max(ceil_div(waves, items), ceil_div(max_seq, kPvSplitMax));
+  if (quantized) cap = std::max(cap, std::min(kValueFewSplits, ceil_div(2 * waves, items)));
   if (g_opt_value_split > 0) cap = std::max(cap, ceil_div(max_seq, (int)g_opt_value_split));
   return std::min(cap, kMaxSplits) + 2;
 }
@@ -969,7 +978,7 @@ static int decode_workspace_bytes(const palu_layer_desc* desc, int32_t batch, in
   if ((st = plan_score(m, &sp, !(kb == 2 || kb == 3))) != PALU_OK) return st;
   if ((st = plan_pv(m, &pp)) != PALU_OK) return st;
   Workspace w;
-  carve(m, batch, max_seq, split_bound(pp.total_units, batch, max_seq), 2 * sp.max_slices,
+  carve(m, batch, max_seq, split_bound(pp.total_units, batch, max_seq, latent_bits(desc->v_latent_dtype) != 0), 2 * sp.max_slices,
         !(desc->rope_theta > 0.f), &w);
   *out_bytes = w.total;
   return PALU_OK;
@@ -1037,7 +1046,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   if (n_split > kMaxSplits) return PALU_ERR_UNSUPPORTED;
   // the value and no-RoPE kernels address a split of the cache with 32-bit byte offsets
   if ((long long)split_tokens * std::max(Rk, Rv) * 2 >= (1LL << 32)) return PALU_ERR_UNSUPPORTED;
-  const int n_split_cap = split_bound(pp.total_units, batch, max_seq);
+  const int n_split_cap = split_bound(pp.total_units, batch, max_seq, v_bits != 0);
   Workspace w;
   const bool no_rope = !(desc->rope_theta > 0.f);
   carve(m, batch, max_seq, n_split_cap, 2 * sp.max_slices, no_rope, &w);
