@@ -81,6 +81,9 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // has no branch inside a sub-tile.  Instructions per tile at rank 256: one query 519 -> 500, four queries (vector form) 1300 -> 790
 // (4 x 16384 tokens, 8 key/value heads: 65 -> 45 us).  LDS offsets that move on with the tile instead of being computed from
 // its number: 500 -> 492, 4-bit keys 627 -> 603, with four queries 922 -> 904.
+// Waits count as well: the first angles of a sub-tile, requested by the body that needs them, cost about 100 cycles each; requested in
+// the last slots of the body before, and with a hand-over barrier that waits for no LDS read (unquantized latents), a step of
+// ranks 96 .. 416 over 4 x 16384 tokens went from 217 to 211 us, 1 x 65536 from 177.5 to 176, 16 x 8192 in 4 bits from 293.5 to 291.4.
 //
 // The weights come from B_k as the caller has it.  A launch of its own used to lay them out (5 us, or 3 us more for the
 // projection that it rode in); transposing them in registers, 64 byte permutes per k-step of which all but the first are
