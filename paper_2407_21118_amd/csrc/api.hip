@@ -116,12 +116,13 @@ int check_desc(const palu_layer_desc* d, Meta* m, int nq = 1) {
 // The weight-stationary score kernel is compiled once per (rank, groups per
 // workgroup): rank = 32*(c+1), c = 0..15.  Up to rank 256 a wavefront owns a whole
 // head and a workgroup takes 4 heads; they may come from 1, 2 or 4 adjacent groups
-// of equal rank as long as the staged row stays within 512 columns.  Above rank
+// of equal rank as long as the staged row stays within 512 columns (unquantized latents on the whole-head kernels: 256).  Above rank
 // 256 a wavefront owns half a head and a workgroup takes 2 heads of one group.
 constexpr int kNumRankCls = 16;
 constexpr int kSlicedCls = kNumRankCls * 3;       // class of the 256-row slices of ranks above 512
 constexpr int kNumScoreCls = kNumRankCls * 3 + 1; // (rank class, log2 of groups per workgroup), and the slices
 constexpr int kScoreMaxWidth = 512;               // latent columns one workgroup stages per token
+constexpr int kScore16MaxWidth = 256;             // ... of the whole-head kernels for unquantized latents, whose tile rows take 256 columns in LDS
 
 int rank_class(int r) { return (r >= 32 && r <= 512 && r % 32 == 0) ? r / 32 - 1 : -1; }
 constexpr int kSliceRank = 256;                   // ranks above 512 are contracted in slices of this many rows
@@ -139,11 +140,11 @@ struct ScorePlan {
   int max_slices;
 };
 
-// widen: let a unit of small groups span 2 or 4 adjacent groups of equal rank and size
+// max_width: a unit of small groups spans 2 or 4 adjacent groups of equal rank and size within this many columns (0: it does not)
 // split: how the whole-head kernel takes ranks 288 .. 512, as two units of one head each: 0 it does not (half-head
 // wavefronts), 1 halves (multiples of 32), 2 slices of 256 and the rest (4-bit keys: whole quantization blocks)
 inline int first_slice(int r, int split) { return split == 2 ? kSliceRank : (r + 63) / 64 * 32; }
-int plan_score(const Meta& m, ScorePlan* p, bool widen = true, int split = 0) {
+int plan_score(const Meta& m, ScorePlan* p, int max_width, int split = 0) {
   p->n_cls = 0;
   p->total_units = 0;
   p->max_slices = 1;
@@ -219,10 +220,10 @@ int plan_score(const Meta& m, ScorePlan* p, bool widen = true, int split = 0) {
       nh = std::min(2, m.head_off[j0 + 1] - h);
     } else {
       nh = std::min(4, m.head_off[j0 + 1] - h);
-      if (widen && h == m.head_off[j0] && s <= 2) {
+      if (h == m.head_off[j0] && s <= 2) {
         // a small group: widen the unit over 2 or 4 whole adjacent groups of the same rank and size
         for (int g : {4, 2}) {
-          if (g * s > 4 || g * r > kScoreMaxWidth || j0 + g > m.n_groups) continue;
+          if (g * s > 4 || g * r > max_width || j0 + g > m.n_groups) continue;
           bool same = true;
           for (int x = 1; x < g; ++x)
             same = same && (m.k_off[j0 + x + 1] - m.k_off[j0 + x] == r) &&
@@ -974,8 +975,7 @@ static int decode_workspace_bytes(const palu_layer_desc* desc, int32_t batch, in
   if (!out_bytes || batch <= 0 || max_seq <= 0) return PALU_ERR_INVALID_ARG;
   ScorePlan sp;
   PvPlan pp;
-  const int kb = latent_bits(desc->k_latent_dtype);
-  if ((st = plan_score(m, &sp, !(kb == 2 || kb == 3))) != PALU_OK) return st;
+  if ((st = plan_score(m, &sp, 0)) != PALU_OK) return st;      // the number of planes does not depend on the width
   if ((st = plan_pv(m, &pp)) != PALU_OK) return st;
   Workspace w;
   carve(m, batch, max_seq, split_bound(pp.total_units, batch, max_seq, latent_bits(desc->v_latent_dtype) != 0), 2 * sp.max_slices,
@@ -1036,7 +1036,8 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   const bool whole4 = k_bits == 4 && g_opt_score_waves == 0;
   const bool split4 = whole4 && split_keys4(m, batch, seq_len);
   const int split = split16 ? 1 : (split4 ? 2 : 0);
-  if ((st = plan_score(m, &sp, !k_lowbit, split)) != PALU_OK) return st;
+  const int max_width = k_lowbit ? 0 : (!k_i4 && g_opt_score_waves == 0 ? kScore16MaxWidth : kScoreMaxWidth);
+  if ((st = plan_score(m, &sp, max_width, split)) != PALU_OK) return st;
   if ((st = plan_pv(m, &pp)) != PALU_OK) return st;
   const int quant_block = desc->quant_block > 0 ? desc->quant_block : 128;
   int split_tokens, n_split;
@@ -1229,7 +1230,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         if (sp.cls_id[sp.unit_cls[i]] == kSlicedCls) sp.units[i].part0 /= 2;
     }
     static thread_local ScorePlan spk;                 // units over key/value heads (shared-key form only)
-    if (kv_units && (st = plan_score(mk, &spk, false, shared16 || shared4 ? split : 0)) != PALU_OK) return st;
+    if (kv_units && (st = plan_score(mk, &spk, 0, shared16 || shared4 ? split : 0)) != PALU_OK) return st;
     const ScorePlan& plan = kv_units ? spk : sp;
 
     // 1. B_k in score_kernel's operand order, where a head runs there (shared-key form: and the rotated queries beside it)

@@ -12,12 +12,13 @@ namespace palu {
 namespace {
 constexpr bool kFlat = PALU_SCORE_FLAT != 0;
 
-// unquantized latents, ranks 64 .. 256, one query per head: one whole head per wavefront (score16.hip)
+// unquantized latents, ranks 64 .. 256, one query per head: one whole head per wavefront (score16.hip); 1, 2 or 4 groups of at
+// most 256 columns in all
 template <typename T, int NK>
 ScoreFn score16_fn_g(int lg) {
   if constexpr (NK <= 2) { if (lg == 2) return score16_kernel<T, NK, 4, 1, 0, kFlat>; }
-  if constexpr (NK <= 4) { if (lg >= 1) return score16_kernel<T, NK, 2, 1, 0, kFlat>; }
-  return score16_kernel<T, NK, 1, 1, 0, kFlat>;
+  if constexpr (NK <= 4) { if (lg == 1) return score16_kernel<T, NK, 2, 1, 0, kFlat>; }
+  return lg == 0 ? score16_kernel<T, NK, 1, 1, 0, kFlat> : nullptr;
 }
 template <typename T>
 ScoreFn score16_fn_t(int rc, int lg) {
@@ -46,8 +47,8 @@ namespace {
 template <int NK>
 ScoreFn score8_fn_g(int lg) {
   if constexpr (NK <= 2) { if (lg == 2) return score8_kernel<NK, 4>; }
-  if constexpr (NK <= 4) { if (lg >= 1) return score8_kernel<NK, 2>; }
-  return score8_kernel<NK, 1>;
+  if constexpr (NK <= 4) { if (lg == 1) return score8_kernel<NK, 2>; }
+  return lg == 0 ? score8_kernel<NK, 1> : nullptr;
 }
 }  // namespace
 

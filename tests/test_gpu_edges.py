@@ -372,3 +372,34 @@ def test_query_products_on_matrix_cores(rk, q_per_kv, dtype, bits, flat):
     err = max(rel_err(got, ref))
     say(f"[edges] query products rank={rk} q_per_kv={q_per_kv} {dtype} bits={bits} flat={flat} rel err {err:.3e}")
     assert err <= (TOL_I4 if bits == 4 else TOL_FP)
+
+
+@pytest.mark.parametrize("group,ranks", [(1, [96] * 4), (1, [128] * 5), (1, [128, 128, 96, 96, 96, 32, 32]), (1, [256, 256, 160]), (2, [128] * 3), (2, [160] * 2),
+                                         (2, [192] * 3), (2, [256, 256, 224, 224, 64, 64])])
+@pytest.mark.parametrize("option", ["", "bf16", "score_waves 4", "score_waves 8", "score_fp8"])
+def test_score_units_over_small_groups(group, ranks, option):
+    """Groups of one and two heads, of which a workgroup takes two or four where their ranks fit the columns of its tile row
+    (256 in the whole-head kernels, 512 in the general one), around those limits: equal neighbours that fit, fit in pairs only, or not at all."""
+    layer = synth.ragged_layer(group * len(ranks), group, ranks, [64] * len(ranks))
+    dtype = "bf16" if option == "bf16" else "f16"
+    rng = np.random.default_rng(14)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, dtype)  # noqa: E731
+    n = np.array([101, 17], np.int32)
+    Bk = np.concatenate([draw(r * group * 128, by=r ** -0.5) for r in ranks])
+    case = synth.Case("edges", layer, dtype, 2, 101, draw(2, layer.n_q_heads, 128), n - 1, draw(2, 101, layer.R_k), draw(2, 101, layer.R_v), Bk,
+                      draw(layer.b_elems("v"), by=64 ** -0.5))
+    case.seq_lens = n
+    ref = run_oracle(case)
+    if option == "score_fp8":                                     # ranks 64 .. 256 only
+        ref8 = O.attn_decode_fp8_keys(case.q, case.q_pos, case.Hk, case.Hv, case.Bk, case.Bv, layer.group_head_off, layer.k_rank_off,
+                                      layer.v_rank_off, layer.d_head, layer.rope_theta, case.k_pos, case.seq_lens, layer.q_per_kv)
+        ref = np.where(np.repeat(np.array(ranks) >= 64, group)[None, :, None], ref8, ref)
+    name, value = (option.split() + ["1"])[:2] if option.startswith("score") else ("score_waves", "0")
+    P.palu_set_option(name, int(value))
+    try:
+        got = run_hip(case)
+    finally:
+        P.palu_set_option(name, 0)
+    err = max(rel_err(got, ref))
+    say(f"[edges] small groups group={group} ranks={ranks} {option} rel err {err:.3e}")
+    assert err <= TOL_FP
