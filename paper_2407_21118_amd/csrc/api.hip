@@ -372,44 +372,32 @@ int plan_qk(const Meta& m, bool quantized, QkPlan* p) {
   return PALU_OK;
 }
 
-// Wavefronts per compute unit the value kernel's splits aim at; eight for quantized latents where that makes few splits.
-constexpr int kValueWavesPerCu = 4, kValueFewSplits = 32;
-// Tokens per wavefront, whole sets of 32, such that items x seq_len tokens are at most waves_per_cu wavefronts per compute unit.
-// Quantized latents: the exact quotient, so that lengths that divide evenly fill the chip (524288 tokens of a 4-bit unit: 512
-// instead of 544).  Unquantized ones take the next set on an exact quotient: 160 tokens instead of 128 (1 x 16384 tokens,
-// 4 x 16384 of two units) left one compute unit in five idle and was 0.4 .. 0.8 us faster all the same, there being fewer splits to merge.
-long long wave_tokens(long long items, int seq_len, int waves_per_cu, bool quantized) {
-  const long long waves = (long long)waves_per_cu * device_cu_count();
-  return ceil_div((int)std::min<long long>((items * seq_len + (quantized ? waves - 1 : waves)) / waves, 1 << 30), 32) * 32LL;
-}
+// Wavefronts per compute unit the value kernel's splits aim at.  Quantized latents: eight.  Four would halve the partial results to be
+// merged (1 x 65536 tokens of 4 bits without RoPE 77.6 -> 72.6 us a step) but cost precision: probability times scale is a 16-bit float
+// against its split's running maximum, and the longer the split, the more of them are subnormal (error against 64 bits, 1 x 16384
+// tokens of 4 bits 3.36e-4 -> 3.51e-4; beside one token that outweighs all others, a split's share of the sequence, 1 x 65536
+// 0.44 -> 0.78 %).  They also fill fewer, longer rounds (one group of 32 heads, 20 x 1500 tokens: value kernel 27 -> 37 us).
+inline int value_waves_per_cu(const palu_layer_desc* d) { return latent_bits(d->v_latent_dtype) ? 8 : 4; }
 
 // Tokens per value split and number of splits for a given attended length: a
-// split is one wavefront's share; aim at four wavefronts per compute unit.  Quantized latents: at eight, whose shorter rounds end
-// more evenly (five queries of 32 heads in one group, 3 x 4765 tokens: 240 units, 9 splits, 1908 us a call, with 5 splits 1957), unless
-// that leaves the merge more than 32 splits (1 x 65536 tokens without RoPE: 228 splits 67.6 us a step, 128 62.2; 1 x 32768 56.2 / 51.2),
-// or units of more than 4 heads partial results (16 KiB) that rival the latents of a split (36 x 5816 tokens, 3 bits, grouped
-// queries: 224 tokens a split 186 us a step, 416 175);
+// split is one wavefront's share; aim at value_waves_per_cu wavefronts per compute unit (a whole number of sets of 32 tokens goes on to
+// the next one: 160 tokens instead of 128 at 1 x 16384 is level, 63.2 against 63.4 us a step, as it is at 16383 and 16385),
 // splits of 64 to 512 tokens (more where the merge kernel's split limit asks for it).  Units of more than 4 heads
 // write larger partial results per split (heads x columns floats against tokens x columns latents read), which the
 // merge kernel reads again: their splits may be four times as long, where that still fills the chip.
 constexpr int kPvSplitMin = 64, kPvSplitMax = 512;
-void split_geometry(int total_units, int batch, int seq_len, bool quantized, int max_unit_heads, int* split_tokens, int* n_split) {
-  auto tokens = [&](int waves_per_cu) {
-    const long long st = wave_tokens(std::max(1, total_units * batch), seq_len, waves_per_cu, quantized);
-    return std::min<long long>(std::max<long long>(st, kPvSplitMin), max_unit_heads > 4 ? 4 * kPvSplitMax : kPvSplitMax);
-  };
-  long long st = tokens(quantized ? 2 * kValueWavesPerCu : kValueWavesPerCu);
-  if (quantized && (ceil_div(seq_len, (int)st) > kValueFewSplits || (max_unit_heads > 4 && st < kPvSplitMax))) st = tokens(kValueWavesPerCu);
+void split_geometry(int total_units, int batch, int seq_len, int waves_per_cu, int max_unit_heads, int* split_tokens, int* n_split) {
+  const long long items = std::max(1, total_units * batch);
+  long long st = ceil_div((int)std::min<long long>(items * seq_len / ((long long)waves_per_cu * device_cu_count()) + 1, 1 << 30), 32) * 32LL;
+  st = std::min<long long>(std::max<long long>(st, kPvSplitMin), max_unit_heads > 4 ? 4 * kPvSplitMax : kPvSplitMax);
   if (g_opt_value_split > 0) st = g_opt_value_split;
   st = std::max<long long>(st, ceil_div(ceil_div(seq_len, kMaxSplits), 32) * 32LL);
   *split_tokens = (int)st;
   *n_split = ceil_div(seq_len, (int)st);
 }
 // Upper bound of the number of splits of any attended length up to max_seq.
-int split_bound(int total_units, int batch, int max_seq, bool quantized) {
-  const int waves = kValueWavesPerCu * device_cu_count(), items = std::max(1, total_units * batch);
-  int cap = std::max(ceil_div(waves, items), ceil_div(max_seq, kPvSplitMax));
-  if (quantized) cap = std::max(cap, std::min(kValueFewSplits, ceil_div(2 * waves, items)));
+int split_bound(int total_units, int batch, int max_seq, int waves_per_cu) {
+  int cap = std::max(ceil_div(waves_per_cu * device_cu_count(), std::max(1, total_units * batch)), ceil_div(max_seq, kPvSplitMax));
   if (g_opt_value_split > 0) cap = std::max(cap, ceil_div(max_seq, (int)g_opt_value_split));
   return std::min(cap, kMaxSplits) + 2;
 }
@@ -978,7 +966,7 @@ static int decode_workspace_bytes(const palu_layer_desc* desc, int32_t batch, in
   if ((st = plan_score(m, &sp, 0)) != PALU_OK) return st;      // the number of planes does not depend on the width
   if ((st = plan_pv(m, &pp)) != PALU_OK) return st;
   Workspace w;
-  carve(m, batch, max_seq, split_bound(pp.total_units, batch, max_seq, latent_bits(desc->v_latent_dtype) != 0), 2 * sp.max_slices,
+  carve(m, batch, max_seq, split_bound(pp.total_units, batch, max_seq, value_waves_per_cu(desc)), 2 * sp.max_slices,
         !(desc->rope_theta > 0.f), &w);
   *out_bytes = w.total;
   return PALU_OK;
@@ -1043,11 +1031,11 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   int split_tokens, n_split;
   int max_unit_heads = 0;
   for (int i = 0; i < pp.total_units; ++i) max_unit_heads = std::max(max_unit_heads, (int)pp.units[i].nh);
-  split_geometry(pp.total_units, batch, seq_len, v_bits != 0, max_unit_heads, &split_tokens, &n_split);
+  split_geometry(pp.total_units, batch, seq_len, value_waves_per_cu(desc), max_unit_heads, &split_tokens, &n_split);
   if (n_split > kMaxSplits) return PALU_ERR_UNSUPPORTED;
   // the value and no-RoPE kernels address a split of the cache with 32-bit byte offsets
   if ((long long)split_tokens * std::max(Rk, Rv) * 2 >= (1LL << 32)) return PALU_ERR_UNSUPPORTED;
-  const int n_split_cap = split_bound(pp.total_units, batch, max_seq, v_bits != 0);
+  const int n_split_cap = split_bound(pp.total_units, batch, max_seq, value_waves_per_cu(desc));
   Workspace w;
   const bool no_rope = !(desc->rope_theta > 0.f);
   carve(m, batch, max_seq, n_split_cap, 2 * sp.max_slices, no_rope, &w);
@@ -1104,8 +1092,11 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     a.n_heads = m.n_heads;
     a.n_blocks_q = Rk / quant_block;
     a.scale = 1.4426950408889634f / std::sqrt((float)PALU_D_HEAD);
-    {   // tokens per wavefront: four wavefronts per compute unit, 64 to 512 tokens (quantized keys: eight; nothing is merged here)
-      long long stq = wave_tokens(std::max(1, qp.total_units * batch), seq_len, k_i4 ? 8 : 4, k_i4);
+    {   // tokens per wavefront: four wavefronts per compute unit (quantized keys: eight), 64 to 512 tokens; the exact quotient, since nothing
+        // is merged here: 1 x 16384 tokens of 2 bits 51.0 -> 48.2 us a step, 4 x 16384 of 4 bits 69.4 -> 68.4; unquantized level
+      const long long items = std::max(1, qp.total_units * batch);
+      const long long waves = (k_i4 ? 8LL : 4LL) * device_cu_count();
+      long long stq = ceil_div((int)std::min<long long>((items * seq_len + waves - 1) / waves, 1 << 30), 32) * 32LL;
       stq = std::min<long long>(std::max<long long>(stq, kPvSplitMin), kPvSplitMax);
       a.split_tokens = (int)stq;
       a.n_split = ceil_div(seq_len, (int)stq);

@@ -403,3 +403,34 @@ def test_score_units_over_small_groups(group, ranks, option):
     err = max(rel_err(got, ref))
     say(f"[edges] small groups group={group} ranks={ranks} {option} rel err {err:.3e}")
     assert err <= TOL_FP
+
+
+def test_quantized_values_beside_one_dominant_token():
+    """One cached row that outweighs each other one by exp(13.3), with a value of zero, over 65536 rows of one value: what the others add up to, a
+    tenth of the weight, is the whole output.  Probability times scale is a 16-bit float against the running maximum of its split, so the rows that share
+    the dominant one's split are below half its smallest step and lost: one split's share of the output, and the reason why
+    splits of quantized values are kept short.  Eight units of four heads on 256 compute units: 288 rows or 0.44 % with eight
+    wavefronts per compute unit (rows that share nothing with it are in one of the other splits)."""
+    layer = synth.uniform_layer(32, 4, 128, 128, rope_theta=0.0)
+    rng = np.random.default_rng(15)
+    n, gap, scale, code = 65536, 13.3, 2.0 ** -6, 8
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    q, Bk, Bv = draw(1, 32, 128), draw(layer.b_elems("k"), by=128 ** -0.5), draw(layer.b_elems("v"), by=128 ** -0.5)
+    Hk = np.zeros((1, n, layer.R_k))
+    logits = np.empty(32)
+    for j in range(8):
+        fold = np.einsum("ruc,uc->ur", Bk[j * 65536:(j + 1) * 65536].reshape(128, 4, 128), q[0, 4 * j:4 * j + 4]) / np.sqrt(128)
+        h = synth.round_to(np.linalg.lstsq(fold, np.full(4, gap), rcond=None)[0], "f16")
+        Hk[0, 0, 128 * j:128 * j + 128] = h
+        logits[4 * j:4 * j + 4] = fold @ h
+    codes = torch.full((1, n, layer.R_v // 2), code * 17, dtype=torch.uint8, device="cuda")
+    codes[0, 0] = 0
+    hv_scale = torch.full((1, n, layer.R_v // 128), scale, dtype=torch.float16, device="cuda")
+    table = P.palu_rope_table_init(0.0, 128, n)
+    got = P.palu_attn_decode(make_desc(layer, "f16", v_i4=True), 1, n, n, to_dev(q, "f16"), torch.zeros(1, dtype=torch.int32, device="cuda"), to_dev(Hk, "f16"),
+                             codes, to_dev(Bk, "f16"), to_dev(Bv, "f16"), table, n, hv_scale=hv_scale, hv_zero=torch.zeros_like(hv_scale))
+    value = np.concatenate([Bv[j * 65536:(j + 1) * 65536].reshape(128, 4, 128).sum(0) for j in range(8)]) * code * scale
+    ref = value * ((n - 1) / (n - 1 + np.exp(logits)))[:, None]
+    err = max(rel_err(got.cpu().numpy(), ref[None]))
+    say(f"[edges] dominant token: logits {logits.min():.3f} .. {logits.max():.3f}, rel err {err:.3e}")
+    assert err <= TOL_I4
