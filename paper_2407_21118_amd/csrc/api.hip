@@ -1214,9 +1214,9 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     used16 = use16;
     // option score_fp8: those heads rebuild their keys from E4M3-rounded latents and weights (fp16 layers)
     const bool use8 = use16 && g_opt_score_fp8 != 0 && act == PALU_F16;
-    if (use16 || whole4) {
-      // the 256-row slices of ranks above 512 run there too and write one score plane each (the planned two are
-      // those of the half-head wavefronts)
+    if (use16 || whole4 || !waves8) {
+      // the 256-row slices of ranks above 512 run there too, or with four wavefronts (option score_waves), and write one score plane
+      // each (the planned two are those of the half-head wavefronts)
       for (int i = 0; i < sp.total_units; ++i)
         if (sp.cls_id[sp.unit_cls[i]] == kSlicedCls) sp.units[i].part0 /= 2;
     }

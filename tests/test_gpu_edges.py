@@ -434,3 +434,28 @@ def test_quantized_values_beside_one_dominant_token():
     err = max(rel_err(got.cpu().numpy(), ref[None]))
     say(f"[edges] dominant token: logits {logits.min():.3f} .. {logits.max():.3f}, rel err {err:.3e}")
     assert err <= TOL_I4
+
+
+@pytest.mark.parametrize("waves", [0, 4, 8])
+@pytest.mark.parametrize("ranks,bits", [([768, 1024], 16), ([512, 1024, 320], 16), ([1024], 4), ([2048, 128], 3)])
+def test_rank_slices_with_every_schedule(ranks, bits, waves):
+    """Ranks above 512, contracted in slices of 256 rows, under each schedule that option score_waves selects: as many score planes are
+    summed as the slices write (one each where a wavefront has a whole head, two where it has half of one)."""
+    layer = synth.ragged_layer(6 * len(ranks), 6, ranks, [128] * len(ranks))
+    rng = np.random.default_rng(16)
+    draw = lambda *shape, by=1.0: synth.round_to(rng.standard_normal(shape) * by, "f16")  # noqa: E731
+    n = np.array([77, 32], np.int32)
+    Bk = np.concatenate([draw(r * 6 * 128, by=r ** -0.5) for r in ranks])
+    case = synth.Case("edges", layer, "f16", 2, 77, draw(2, layer.n_q_heads, 128), n - 1, draw(2, 77, layer.R_k), draw(2, 77, layer.R_v), Bk,
+                      draw(layer.b_elems("v"), by=128 ** -0.5))
+    case.seq_lens = n
+    quant = {} if bits == 16 else {"k": O.quant_latent(case.Hk, bits=bits), "v": O.quant_latent(case.Hv, bits=bits)}
+    ref = run_oracle(case, quant, bits != 16, bits != 16, bits=min(bits, 4))
+    P.palu_set_option("score_waves", waves)
+    try:
+        got = run_hip(case, bits != 16, bits != 16, quant, bits=min(bits, 4))
+    finally:
+        P.palu_set_option("score_waves", 0)
+    err = max(rel_err(got, ref))
+    say(f"[edges] rank slices ranks={ranks} bits={bits} score_waves={waves} rel err {err:.3e}")
+    assert err <= (TOL_FP if bits == 16 else TOL_I4)
