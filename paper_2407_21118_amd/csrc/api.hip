@@ -469,7 +469,7 @@ bool split_keys4(const Meta& m, int batch, int seq_len) {
     const int r = m.k_off[j + 1] - m.k_off[j], s = m.head_off[j + 1] - m.head_off[j];
     if (r <= 512 && r != 384) alone = false;
     if (r <= 256 || r > 512) continue;
-    slices += shared ? 2 * ceil_div(s / m.qpk, 4) * ceil_div(m.qpk, r % 256 != 0 ? 4 : 8) : 2 * ceil_div(s, 4);
+    slices += shared ? 2 * ceil_div(s / m.qpk, 4) * ceil_div(m.qpk, kShared16Rows) : 2 * ceil_div(s, 4);
     halves += ceil_div(s, 2);
   }
   if (2 * slices >= 3 * halves) return halves == 0;
