@@ -359,8 +359,8 @@ int palu_attn_decode_latent(const palu_layer_desc* desc, int32_t batch, int32_t 
  * caches (h = x A, Sec. 3.1) and attend (palu_attn_decode).  Same results, bit for
  * bit, as palu_encode_kv followed by palu_attn_decode.  What attention needs of B_k
  * beforehand (non-RoPE: the queries folded into it; RoPE: its layout for the few forms that
- * want one, else its first read) does not depend on the projection and, with fewer
- * than 64 sequences, rides in the projection's first launch.
+ * want one, else a first read of it into the caches, as far as 4 KiB per workgroup go) does
+ * not depend on the projection and, with fewer than 64 sequences, rides in its first launch.
  *   x            DEVICE [batch, n_heads*q_per_kv*d_head] act_dtype: the new tokens' activations
  *   Ak, Av       as for palu_encode_kv
  *   dst_row      DEVICE int32 [batch]: row of hk / hv (counted over all batch*max_seq rows)
@@ -382,8 +382,8 @@ int palu_decode_step(const palu_layer_desc* desc, int32_t batch, int32_t seq_len
 /*
  * palu_decode_step from transposed weights (palu_encode_kv_t followed by
  * palu_attn_decode, in one call): the projection is one launch, and what attention needs
- * of B_k beforehand rides in its workgroups, so the whole append costs one launch.  No encode workspace.  Arguments as for
- * palu_decode_step with Akt, Avt as for palu_encode_kv_t; batch < 64.
+ * of B_k beforehand rides in its workgroups, so the whole append costs one launch.  No
+ * encode workspace.  Arguments as for palu_decode_step with Akt, Avt as for palu_encode_kv_t; batch < 64.
  */
 int palu_decode_step_t(const palu_layer_desc* desc, int32_t batch, int32_t seq_len, int32_t max_seq,
                        const void* x, const void* Akt, const void* Avt, const int32_t* dst_row,

@@ -122,7 +122,11 @@ constexpr int kNumRankCls = 16;
 constexpr int kSlicedCls = kNumRankCls * 3;       // class of the 256-row slices of ranks above 512
 constexpr int kNumScoreCls = kNumRankCls * 3 + 1; // (rank class, log2 of groups per workgroup), and the slices
 constexpr int kScoreMaxWidth = 512;               // latent columns one workgroup stages per token
-constexpr int kScore16MaxWidth = 256;             // ... of the whole-head kernels for unquantized latents, whose tile rows take 256 columns in LDS
+// ... of the whole-head kernels for unquantized latents, whose tile rows take 256 columns in LDS.  Groups of one head of ranks 96 and 128 then
+// go in pairs and groups of two heads of ranks 160 .. 256 alone, and half of a workgroup's wavefronts repeat another one's head: 32
+// heads, 1 x 1000 / 6 x 5000 / 40 x 700 tokens, rank 128 per head 32 / 153 / 164 us a step, 256 per two heads 34 / 184 / 195.  (score_kernel, whose
+// tile rows take 512, option score_waves = 4: 34 / 136 / 168 and 37 / 152 / 188; which of them the library takes has not been made a rule.)
+constexpr int kScore16MaxWidth = 256;
 
 int rank_class(int r) { return (r >= 32 && r <= 512 && r % 32 == 0) ? r / 32 - 1 : -1; }
 constexpr int kSliceRank = 256;                   // ranks above 512 are contracted in slices of this many rows
@@ -409,7 +413,8 @@ struct Workspace {
 };
 
 // per_sequence_fold: the region behind `mfold` holds something per sequence (the folded queries of the non-RoPE
-// form); with RoPE it holds B_k in operand order, once.
+// form); with RoPE it holds B_k in operand order, once.  It is asked for also where every head runs on score16_kernel and nothing is
+// laid out: an option set between the query and the call (score_waves, shared_key_fp16) may want it.
 int carve(const Meta& m, int batch, int max_seq, int n_split_cap, int n_parts, bool per_sequence_fold, Workspace* w) {
   w->lpad = ceil_div(max_seq, 32) * 32;
   w->mfold_bstride = m.bk_off[m.n_groups];
@@ -1191,7 +1196,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     // unquantized latents, one query per head: heads of rank 64 .. 256 run one whole head per wavefront
     // (option score_waves = 4 or 8 forces the half-head / ping-pong schedules of score_kernel)
     const bool use16 = !shared_key && !k_i4 && g_opt_score_waves == 0;
-    // ... and with 2, 4 or 8 queries per key/value head and ranks 128 .. 256 one whole key/value head per wavefront:
+    // ... and with several queries per key/value head and ranks 64 .. 256 (512 in slices) one whole key/value head per wavefront:
     // the key is rebuilt and rotated once in float32 for the queries that share it (exact shared-key form)
     bool shared16 = use16 && m.qpk > 1 && g_opt_score_fp8 == 0;
     for (int j = 0; j < m.n_groups && shared16; ++j) {

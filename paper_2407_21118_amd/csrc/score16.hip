@@ -82,14 +82,15 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // (4 x 16384 tokens, 8 key/value heads: 65 -> 45 us).  LDS offsets that move on with the tile instead of being computed from
 // its number: 500 -> 492, 4-bit keys 627 -> 603, with four queries 922 -> 904.
 // Waits count as well: the first angles of a sub-tile, requested by the body that needs them, cost about 100 cycles each; requested in
-// the last slots of the body before, and with a hand-over barrier that waits for no LDS read (unquantized latents), a step of
-// ranks 96 .. 416 over 4 x 16384 tokens went from 217 to 211 us, 1 x 65536 from 177.5 to 176, 16 x 8192 in 4 bits from 293.5 to 291.4.
+// the last slots of the body before, and with a hand-over barrier that waits for no LDS read (unquantized latents), they
+// are gone from the tile: a step of ranks 96 .. 416 over 4 x 16384 tokens 226.2 -> 223.5 us, of rank 64 per head over 8 x 16384
+// 202.8 -> 201.1; 16 x 8192 in 4 bits and 1 x 65536, at the power limit, level.
 //
 // The weights come from B_k as the caller has it.  A launch of its own used to lay them out (5 us, or 3 us more for the
 // projection that it rode in); transposing them in registers, 64 byte permutes per k-step of which all but the first are
 // dealt out between the first sub-tile's matrix instructions (FLAT, 4-bit keys: ahead of them), adds about 1 us to the
-// kernel: one sequence of 1024 / 16384 tokens 22.9 / 69.6 -> 21.4 / 67.8 us a step, 16 x 8192 in 4 bits 300 -> 296,
-// four queries over 2 x 8190 77.6 -> 75.1; long launches, which are at the power limit, level.
+// kernel: one sequence of 1024 / 16384 tokens 22.9 / 64.7 -> 20.8 / 62.5 us a step, 28.0 / 83.0 -> 25.5 / 79.1 with all inputs out of the
+// caches; 16 x 8192 in 4 bits 302 -> 298, four queries over 2 x 8190 70.6 -> 67.4; long launches, at the power limit, level.
 template <typename T, int NK, int G, int NQ, int QB, bool FLAT>
 __global__ __launch_bounds__(256) void score16_kernel(ScoreArgs a) {
   const int wg = blockIdx.x, n_wg = a.n_wg, unit = blockIdx.y, seq = blockIdx.z, run = a.run, run_more = a.run_more;
