@@ -6,6 +6,7 @@
 #include "rope_fold.hip"
 #include "score.hip"
 #include "score16.hip"
+#include "attend16.hip"
 #include "score8.hip"
 #include "combine.hip"
 #include "qk.hip"
@@ -458,6 +459,9 @@ inline bool rank_class_16(int rc) { return rc >= 1 && rc <= 7; }
 // rows; the kernel is compiled for 2, 4 and 8 rows
 inline bool shared16_ok(int rc) { return rc >= 1 && rc <= 7; }
 constexpr int kShared16Rows = 8;
+// Longest run of tiles whose values follow in the score launch: 512 tokens to a wavefront, the value kernel's longest split (one
+// running maximum per split; longer ones would make more of its 16-bit probabilities subnormal).
+constexpr int kMaxAttendTiles = 64;
 constexpr int score16q4_lds_bytes(int width) { return 3 * score_tile_bytes(width) + 3 * kRopeTileBytes; }
 
 // 4-bit keys of ranks 384 and 512: two slices of whole heads (score16_kernel, four heads or key/value heads to a workgroup) or
@@ -1061,6 +1065,8 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
 
   bool enc_pending = enc != nullptr;
   bool used16 = false;
+  bool attended = false;                  // scores and values in one launch: its runs of tiles are the splits that are merged
+  int attend_wgs = 0, attend_run = 0, attend_run_more = 0;
   if (enc_pending && enc->gemm) {
     if ((st = launch_encode(act, *enc, s)) != PALU_OK) return st;
     enc_pending = false;
@@ -1493,7 +1499,48 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         hipLaunchKernelGGL(fn, dim3((unsigned)first), dim3(256), lds, s, a);
         if ((st = launch_ok()) != PALU_OK) return st;
       }
-      for (int cls = 0; cls < plan.n_cls && !mixed; ++cls) {
+      // Scores and values in one launch (attend16_kernel).  A unit's heads have to be whole groups (their value latents are then read by
+      // one workgroup of a run only) of one value rank, all in one launch with one pass of query rows, every head in one unit.
+      // Wherever that holds it is the faster form (attend16.hip); with stage events the stages have to be launches.
+      if (use16 && !use8 && (shared16 || m.qpk == 1) && m.qpk <= kShared16Rows && !v_i4 && !stage_events && g_opt_value_split == 0 &&
+          plan.n_cls == 1 && plan.total_units <= kMaxAttendUnits && rank_class_16(plan.cls_id[0] / 3) && plan.max_slices == 1 &&
+          !flat16(plan.total_units)) {
+        static thread_local AttendArgs t;
+        const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3, groups = 1 << lg;
+        bool whole = true;
+        for (int i = 0; i < plan.total_units && whole; ++i) {
+          const ScoreUnit& x = t.units.u[i] = unit16(mk, plan.units[i]);
+          const int j = mk.group_of_head[x.h0], rv = m.v_off[j + 1] - m.v_off[j];
+          whole = x.h0 == mk.head_off[j] && x.h0 + x.nh == mk.head_off[j + groups];
+          for (int g = 1; g < groups && whole; ++g) whole = m.v_off[j + g + 1] - m.v_off[j + g] == rv;
+          t.val[i] = AttendValue{m.v_off[j], rv, m.bv_off[j] / PALU_D_HEAD};
+        }
+        a.sk_row0 = 0;
+        a.sk_rows = m.qpk;
+        const dim3 grid = grid16(plan.total_units, false);
+        if (whole && w.lpad <= (1 << 24) && a.n_wg <= n_split_cap && a.n_wg <= kMaxSplits && a.run + (a.run_more ? 1 : 0) <= kMaxAttendTiles) {
+          static_cast<ScoreCommon&>(t) = a;
+          t.hv = static_cast<const uint16_t*>(hv);
+          t.q_len = q_len;
+          t.o_part = reinterpret_cast<float*>(ws + w.o_part);
+          t.ml_part = reinterpret_cast<float*>(ws + w.ml_part);
+          t.v_row_elems = Rv;
+          t.n_split = a.n_wg;
+          t.o_stride = w.o_stride;
+          t.units.n_units = plan.total_units;
+          const AttendFn fn = shared16 ? attend16q_fn(act, rc, m.qpk) : attend16_fn(act, rc, lg);
+          const size_t lds = (size_t)attend_lds_bytes((32 * (rc + 1)) << lg);
+          if (!fn) return PALU_ERR_UNSUPPORTED;
+          if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
+          hipLaunchKernelGGL(fn, grid, dim3(256), lds, s, t);
+          if ((st = launch_ok()) != PALU_OK) return st;
+          attended = true;
+          attend_wgs = a.n_wg;
+          attend_run = a.run;
+          attend_run_more = a.run_more;
+        }
+      }
+      for (int cls = 0; cls < plan.n_cls && !mixed && !attended; ++cls) {
         const int id = plan.cls_id[cls];
         const bool sliced = id == kSlicedCls;
         const int rc = sliced ? rank_class(kSliceRank) : id / 3, lg = sliced ? 0 : id % 3;
@@ -1579,6 +1626,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   }
 
   // 3. softmax partials and P.H_v per split
+  if (!attended) {
   uint8_t n_parts[PALU_MAX_HEADS];
   std::memset(n_parts, 0, sizeof(n_parts));
   int max_parts = 0;
@@ -1646,6 +1694,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       if ((st = flush()) != PALU_OK) return st;
     }
   }
+  }
 
   // 4. merge splits, normalise, apply B_v
   {
@@ -1656,8 +1705,10 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     a.seq_lens = seq_lens;
     a.out = out;
     a.out_latent = out_latent;
-    a.n_split = n_split;
+    a.n_split = attended ? attend_wgs : n_split;
     a.split_tokens = split_tokens;
+    a.run = attended ? attend_run : 0;
+    a.run_more = attended ? attend_run_more : 0;
     a.seq_len = seq_len;
     a.o_stride = w.o_stride;
     a.batch = batch;

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   const Meta& m = a.meta;
   const int h = blockIdx.x >> 2, quarter = blockIdx.x & 3, b = blockIdx.y;
   const int L = a.seq_lens ? min(a.seq_lens[b], a.seq_len) : a.seq_len;
-  const int nsp = L > 0 ? (L + a.split_tokens - 1) / a.split_tokens : 0;
+  const int nsp = split_count(a, L);
   const int j = group_of(m, h);
   const int rv = m.v_off[j + 1] - m.v_off[j];
   int width;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64 * WAVES) void combine_rows_kernel(CombineArgs a,
   {
     const int row = min(row0 + wave / W, rows - 1), b = row / m.qpk, h = blockIdx.x * m.qpk + row % m.qpk, sg = wave % W;
     const int L = a.seq_lens ? min(a.seq_lens[b], a.seq_len) : a.seq_len;
-    const int nsp = L > 0 ? (L + a.split_tokens - 1) / a.split_tokens : 0;
+    const int nsp = split_count(a, L);
     const float* ml = a.ml_part + ((size_t)b * a.n_split * m.n_heads + h) * 2;
     const size_t ml_stride = (size_t)m.n_heads * 2;
     float mx = -INFINITY, sum = 0.f;

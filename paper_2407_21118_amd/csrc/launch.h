@@ -25,6 +25,11 @@ template <bool FLAT> ScoreFn score16q_fn(int act, int rc, int nq);
 // the same with 4-bit key latents (rank classes 128 and 256, also slices of larger ranks); one query per head (nq = 1): also 2 or 4
 // groups per workgroup (lg)
 template <bool FLAT> ScoreFn score16q4_fn(int rc, int nq, int lg);
+// score16_kernel's runs of tiles with the value contraction behind them, one launch for both (attend16.hip); nq: query rows per
+// key/value head (1, or up to 8)
+using AttendFn = void (*)(AttendArgs);
+AttendFn attend16_fn(int act, int rc, int lg);
+AttendFn attend16q_fn(int act, int rc, int nq);
 // option score_fp8
 ScoreFn score8_fn(int rc, int lg);
 struct Fold8Args {

@@ -221,7 +221,8 @@ struct ScoreUnits {
   ScoreUnit u[kMaxScoreUnits];
 };
 
-struct ScoreArgs {
+// What every score kernel reads.
+struct ScoreCommon {
   const void* hk;            // latents or packed codes
   const uint16_t* hk_scale;  // fp16 bits (int4 only)
   const uint16_t* hk_zero;
@@ -257,12 +258,38 @@ struct ScoreArgs {
   const float* w_scale;      // 8-bit weights (score8_kernel): the power-of-two scale of every feature column [heads][128]
   int m_qpk, m_nq;           // one-query form: Meta::qpk and Meta::nq of the call (layout of q, see q_row)
   int sk_row0, sk_rows;      // exact shared-key form: the query rows of every key/value head this launch takes
-  ScoreMix mix;              // one launch over several rank classes (score16_mixed_kernel)
   int rope_tile_stride;
   float rev_hi[kHalf];       // theta^(-2f/128) / (2 pi) from the host's float64 value, as a float pair hi + lo
   float rev_lo[kHalf];
+};
+struct ScoreArgs : ScoreCommon {
+  ScoreMix mix;              // one launch over several rank classes (score16_mixed_kernel)
   ScoreUnits units;
 };
+
+// attend16_kernel: scores and values of a run of tiles in one workgroup.  Its units cover whole groups, whose value ranks are equal.
+constexpr int kMaxAttendUnits = 32;     // keeps the arguments below 4 KiB
+struct AttendUnits {
+  int n_units;
+  ScoreUnit u[kMaxAttendUnits];
+};
+struct AttendValue {
+  int c0;                    // first value-latent column of the unit's first group
+  int rv;                    // value rank of each of its groups
+  int o0;                    // where the unit's first head begins in an o_part row; head x of the unit follows x * rv floats on
+};
+struct AttendArgs : ScoreCommon {
+  const uint16_t* hv;
+  const int32_t* q_len;      // as in PvArgs
+  float* o_part;             // [batch][n_split][o_stride]: one partial result per workgroup of a (unit, sequence)
+  float* ml_part;            // [batch][n_split][n_heads][2]
+  long long v_row_elems;     // R_v
+  int n_split;               // = n_wg
+  int o_stride;
+  AttendUnits units;
+  AttendValue val[kMaxAttendUnits];
+};
+static_assert(sizeof(AttendArgs) <= 4096, "kernel arguments");
 
 struct RopeGatherArgs {
   const void* table;         // the part of the table that is gathered
@@ -305,11 +332,19 @@ struct CombineArgs {
   float* out_latent;         // non-NULL: write the normalised latent output [batch, o_stride] instead and skip B_v
   int n_split;
   int split_tokens;
+  int run, run_more;         // run > 0: the splits are attend16_kernel's runs of tiles, the first run_more of them run + 1 tiles long, the rest run
   int seq_len;
   int o_stride;
   int batch;
   Meta meta;
 };
+// number of partial results of a sequence of L attended rows
+__device__ __forceinline__ int split_count(const CombineArgs& a, int L) {
+  if (L <= 0) return 0;
+  if (a.run == 0) return (L + a.split_tokens - 1) / a.split_tokens;
+  const int tiles = (L + kTile - 1) / kTile, longer = a.run_more * (a.run + 1);
+  return tiles <= longer ? (tiles + a.run) / (a.run + 1) : a.run_more + (tiles - longer + a.run - 1) / a.run;
+}
 
 // Where query head h of group j finds its 128 columns inside the concatenated
 // reconstruction matrices: `off` is bk_off[j] or bv_off[j]; *width receives the

@@ -58,6 +58,18 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
   return v + dpp_lane_move<0x128>(v);                                                                           // row_ror 8
 }
 
+// The value latents of a unit, where they are contracted in the same workgroup (attend16_kernel): the unit's first column in the cache's
+// first row, bytes between rows, 16-byte chunks of a row (at most 32: the first 256 columns)
+struct ValueView {
+  const unsigned char* base;
+  unsigned pitch;
+  int chunks;
+};
+__device__ __forceinline__ ValueView value_view(const ScoreArgs&, int, int) { return ValueView{nullptr, 0, 1}; }
+__device__ __forceinline__ ValueView value_view(const AttendArgs& a, int unit, int groups) {
+  return ValueView{(const unsigned char*)a.hv + (size_t)a.val[unit].c0 * 2, (unsigned)a.v_row_elems * 2u, min(groups * a.val[unit].rv, 256) >> 3};
+}
+
 // T:  storage type of the weights and latents (the matrix instruction of that type)
 // NK: k-steps of 32: the rank of every head of the workgroup is 32 * NK (NK <= 8)
 // G:  groups spanned by the workgroup's heads (1, 2 or 4 adjacent groups of equal rank): the staged
@@ -91,8 +103,10 @@ __device__ __forceinline__ float sum_quad_over_row(const float (&p)[4], int lane
 // dealt out between the first sub-tile's matrix instructions (FLAT, 4-bit keys: ahead of them), adds about 1 us to the
 // kernel: one sequence of 1024 / 16384 tokens 22.9 / 64.7 -> 20.8 / 62.5 us a step, 28.0 / 83.0 -> 25.5 / 79.1 with all inputs out of the
 // caches; 16 x 8192 in 4 bits 302 -> 298, four queries over 2 x 8190 70.6 -> 67.4; long launches, at the power limit, level.
+#define SCORE16_DRAIN __builtin_amdgcn_s_waitcnt(vmcnt_imm(0))      // no LDS-direct load may outlive the workgroup's LDS allocation
 template <typename T, int NK, int G, int NQ, int QB, bool FLAT>
 __global__ __launch_bounds__(256) void score16_kernel(ScoreArgs a) {
+  constexpr bool kValues = false;
   const int wg = blockIdx.x, n_wg = a.n_wg, unit = blockIdx.y, seq = blockIdx.z, run = a.run, run_more = a.run_more;
 #include "score16_body.inc"
 }
@@ -102,6 +116,7 @@ __global__ __launch_bounds__(256) void score16_kernel(ScoreArgs a) {
 template <typename T, int NK, int G, bool FLAT>
 __device__ __forceinline__ void score16_body(const ScoreArgs& a, const int wg, const int n_wg, const int unit, const int seq, const int run, const int run_more) {
   constexpr int NQ = 1, QB = 0;
+  constexpr bool kValues = false;
 #include "score16_body.inc"
 }
 

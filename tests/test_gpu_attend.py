@@ -1,0 +1,79 @@
+"""Scores and values of a run of tiles in one workgroup (csrc/attend16.hip) against the float64 oracle: runs shorter and longer than
+the ring of tiles, shares of a run that are empty for some wavefronts, value ranks of part of a 128-column block, of one, two and
+several, units over several groups, every number of query rows, row limits inside a run and before it."""
+
+import numpy as np
+import pytest
+
+from oracle import palu_oracle as O
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(n_kv, group, rk, rv, q_per_kv=1):
+    return synth.uniform_layer(n_kv, group, rk, rv, rope_theta=10000.0, q_per_kv=q_per_kv)
+
+
+# heads, group, key rank, value rank, queries per key/value head, dtype, lengths, workgroups per unit and sequence (0: the library's choice)
+CASES = [
+    (4, 4, 256, 256, 1, "f16", [1], 0), (4, 4, 128, 128, 1, "f16", [33], 1), (8, 4, 256, 160, 1, "bf16", [97], 1),
+    (4, 4, 224, 256, 1, "f16", [161], 1), (8, 4, 256, 384, 1, "f16", [257, 1], 1), (4, 4, 160, 32, 1, "f16", [2047], 1),
+    (4, 1, 64, 64, 1, "f16", [130, 65], 1), (4, 1, 64, 96, 1, "bf16", [200], 2), (4, 2, 128, 128, 1, "f16", [129], 1),
+    (4, 2, 96, 192, 1, "f16", [300, 40], 2), (6, 3, 192, 256, 1, "f16", [70], 1), (4, 4, 256, 256, 1, "f16", [511, 0, 96], 2),
+    (4, 4, 256, 256, 4, "f16", [161, 33], 1), (4, 4, 128, 384, 2, "f16", [129], 1), (4, 4, 64, 128, 8, "f16", [200, 64], 2),
+    (4, 2, 256, 160, 8, "bf16", [97], 1), (3, 3, 96, 96, 3, "f16", [333], 3), (4, 4, 160, 256, 5, "f16", [64, 0], 0),
+]
+
+
+@pytest.mark.parametrize("heads,group,rk,rv,qpk,dtype,lens,chunks", CASES)
+def test_run_of_tiles(heads, group, rk, rv, qpk, dtype, lens, chunks):
+    import paper_2407_21118_amd as P
+    from gpu_util import TOL_FP, rel_err, run_hip, run_oracle, say
+    case = synth.make_case_orthonormal(_layer(heads, group, rk, rv, qpk), len(lens), max(lens), seed=heads + rk + rv + qpk, dtype=dtype)
+    case.seq_lens = np.array(lens, np.int32) if len(lens) > 1 else None
+    case.q_pos = np.maximum(np.array(lens, np.int32) - 1, 0)
+    P.palu_set_option("score_chunks", 0 if case.seq_lens is not None else chunks)     # (with lengths the option means runs through all sequences)
+    try:
+        got = run_hip(case)
+    finally:
+        P.palu_set_option("score_chunks", 0)
+    ref = run_oracle(case)
+    err = rel_err(got, ref)[0]
+    say(f"[attend] {heads}/{group} heads rank {rk}/{rv} x{qpk} {dtype} {lens} chunks {chunks}: {err:.2e}")
+    assert err <= TOL_FP
+    for b, n in enumerate(lens):
+        if n == 0:
+            assert not got[b].any()
+
+
+@pytest.mark.parametrize("n_q,qpk,rk,rv", [(1, 1, 256, 256), (2, 1, 128, 384), (4, 1, 256, 256), (3, 2, 64, 128), (8, 1, 160, 256)])
+def test_row_limits_inside_a_run(n_q, qpk, rk, rv):
+    """Row limits per query: none attended, inside the first set, at a set's edge, in the last rows."""
+    import torch
+    import paper_2407_21118_amd as P
+    from gpu_util import TOL_FP, make_desc, rel_err, say, to_dev
+    layer = _layer(4, 4, rk, rv, qpk)
+    batch, seq = 2, 290
+    case = synth.make_case_orthonormal(layer, batch, seq, seed=17 + n_q + rk)
+    rng = np.random.default_rng(n_q * 100 + rk)
+    q = synth.round_to(rng.standard_normal((batch, n_q, layer.n_q_heads, 128)), "f16")
+    q_len = np.array([[0, 5, 32, 64, 128, 200, 289, 290][(j + b) % 8] if n_q > 1 else 37 + 200 * b for b in range(batch) for j in range(n_q)],
+                     np.int32).reshape(batch, n_q)
+    q_pos = np.maximum(q_len - 1, 0).astype(np.int32)
+    dv = lambda x: torch.from_numpy(x).cuda()
+    P.palu_set_option("score_chunks", 2)
+    try:
+        got = P.palu_attn_decode_multi(make_desc(layer, "f16"), batch, n_q, seq, seq, to_dev(q, "f16"), dv(q_pos), to_dev(case.Hk, "f16"),
+                                       to_dev(case.Hv, "f16"), to_dev(case.Bk, "f16"), to_dev(case.Bv, "f16"),
+                                       P.palu_rope_table_init(layer.rope_theta, 128, seq), seq, q_len=dv(q_len))
+        torch.cuda.synchronize()
+    finally:
+        P.palu_set_option("score_chunks", 0)
+    got = got.cpu().numpy()
+    ref = O.attn_decode_multi(q, q_pos, q_len, case.Hk, case.Hv, case.Bk, case.Bv, layer.group_head_off, layer.k_rank_off, layer.v_rank_off,
+                              128, layer.rope_theta, q_per_kv=qpk)
+    err = rel_err(got.reshape(batch * n_q, -1, 128), np.asarray(ref).reshape(batch * n_q, -1, 128))[0] if np.abs(ref).max() > 0 else 0.0
+    say(f"[attend] {n_q} queries x{qpk} rank {rk}/{rv}: {err:.2e}")
+    assert err <= TOL_FP
+    assert not got[q_len == 0].any()
