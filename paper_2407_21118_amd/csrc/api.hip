@@ -1067,6 +1067,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   bool used16 = false;
   bool attended = false;                  // scores and values in one launch: its runs of tiles are the splits that are merged
   int attend_wgs = 0, attend_run = 0, attend_run_more = 0;
+  const int* attend_slots = nullptr;
   if (enc_pending && enc->gemm) {
     if ((st = launch_encode(act, *enc, s)) != PALU_OK) return st;
     enc_pending = false;
@@ -1473,7 +1474,94 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           if (!use_one_round) mixed = false;      // several rounds of mixed workgroups measured no faster than a launch per class
         }
       }
-      if (mixed) {
+      // Scores and values in one launch (attend16_kernel).  A unit's heads have to be whole groups (their value latents are then read by
+      // one workgroup of a run only) of one value rank, all in one launch with one pass of query rows, every head in one unit.
+      // Wherever that holds it is the faster form (attend16.hip); with stage events the stages have to be launches.
+      bool attend = use16 && !use8 && (shared16 || m.qpk == 1) && m.qpk <= kShared16Rows && !v_i4 && !stage_events && g_opt_value_split == 0 &&
+                    plan.total_units <= kMaxAttendUnits && plan.max_slices == 1 && w.lpad <= (1 << 24) &&
+                    (plan.n_cls == 1 ? rank_class_16(plan.cls_id[0] / 3) : mixed && use_one_round);
+      static thread_local AttendArgs t;
+      for (int i = 0; i < plan.total_units && attend; ++i) {
+        const ScoreUnit& x = t.units.u[i] = unit16(mk, plan.units[i]);
+        const int j = mk.group_of_head[x.h0], rv = m.v_off[j + 1] - m.v_off[j], groups = 1 << plan.cls_id[plan.unit_cls[i]] % 3;
+        attend = x.h0 == mk.head_off[j] && x.h0 + x.nh == mk.head_off[j + groups];
+        for (int g = 1; g < groups && attend; ++g) attend = m.v_off[j + g + 1] - m.v_off[j + g] == rv;
+        t.val[i] = AttendValue{m.v_off[j], rv, m.bv_off[j] / PALU_D_HEAD};
+      }
+      if (attend) {
+        const bool flat = plan.n_cls == 1 ? flat16(plan.total_units) : mix_flat;
+        dim3 grid(1);
+        int n_wg = 0, run = 0;                                   // most workgroups of a unit (and sequence); longest run
+        if (plan.n_cls == 1) {
+          grid = grid16(plan.total_units, flat);
+          n_wg = a.n_wg;
+          run = a.run + (a.run_more ? 1 : 0);
+        } else {
+          // Workgroups go, one at a time, to the unit whose workgroups would run longest, by the cost of its keys (above) and its
+          // values (256 columns: 16 us per 1000 tokens of one workgroup, while others multiply)
+          const long long seqs = mix_seqs;
+          int n[kMaxAttendUnits];
+          long long total = 0;
+          auto us = [&](int i) {
+            return (double)((run_tiles + n[i] - 1) / n[i]) * (weight(plan.cls_id[plan.unit_cls[i]] / 3 + 1) + 16.0 * t.val[i].rv / 256.0);
+          };
+          for (int i = 0; i < plan.total_units; ++i) total += n[i] = 1;
+          for (;;) {
+            int worst = 0;
+            for (int i = 1; i < plan.total_units; ++i) if (us(i) > us(worst)) worst = i;
+            if (n[worst] >= run_tiles || (total + 1) * seqs > device_cu_count()) break;
+            ++n[worst];
+            ++total;
+          }
+          int first = 0;
+          for (int i = 0; i < plan.total_units; ++i) {
+            t.mix.first[i] = first;
+            t.mix.run[i] = (int)(run_tiles / n[i]);
+            t.mix.run_more[i] = (int)(run_tiles % n[i]);
+            t.mix.nk[i] = (uint8_t)(plan.cls_id[plan.unit_cls[i]] / 3 + 1);
+            first += n[i] * (int)seqs;
+            n_wg = std::max(n_wg, n[i]);
+            run = std::max(run, (int)((run_tiles + n[i] - 1) / n[i]));
+          }
+          t.mix.first[plan.total_units] = first;
+          grid = dim3((unsigned)first);
+        }
+        // the partial results, one per workgroup and sequence it works on, fit where the value kernel's go; runs through all sequences, and units
+        // of different ranks, note which they are per head in the region of B_k's layout, which this path leaves alone
+        const bool noted = flat || plan.n_cls > 1;
+        attend = (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
+                 (!noted || (size_t)batch * m.n_heads * 8 <= (size_t)w.mfold_bstride * 2) && n_wg <= kMaxSplits;
+        if (attend) {
+          const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3;
+          a.sk_row0 = 0;
+          a.sk_rows = m.qpk;
+          static_cast<ScoreCommon&>(t) = a;
+          t.hv = static_cast<const uint16_t*>(hv);
+          t.q_len = q_len;
+          t.o_part = reinterpret_cast<float*>(ws + w.o_part);
+          t.ml_part = reinterpret_cast<float*>(ws + w.ml_part);
+          t.v_row_elems = Rv;
+          t.seg_tiles = std::min(a.seg_tiles, kMaxAttendTiles);
+          t.slots = noted ? reinterpret_cast<int*>(ws + w.mfold) : nullptr;
+          t.n_split = n_wg;
+          t.o_stride = w.o_stride;
+          t.units.n_units = plan.total_units;
+          const AttendFn fn = plan.n_cls > 1 ? (flat ? attend16_mixed_fn<true>(act) : attend16_mixed_fn<false>(act))
+                            : shared16 ? attend16q_fn<false>(act, rc, m.qpk)
+                            : (flat ? attend16_fn<true>(act, rc, lg) : attend16_fn<false>(act, rc, lg));
+          const size_t lds = (size_t)attend_lds_bytes(plan.n_cls > 1 ? 256 : (32 * (rc + 1)) << lg, m.qpk);
+          if (!fn) return PALU_ERR_UNSUPPORTED;
+          if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
+          hipLaunchKernelGGL(fn, grid, dim3(256), lds, s, t);
+          if ((st = launch_ok()) != PALU_OK) return st;
+          attended = true;
+          attend_slots = t.slots;
+          attend_wgs = n_wg;
+          attend_run = a.run;
+          attend_run_more = a.run_more;
+        }
+      }
+      if (mixed && !attended) {
         a.units.n_units = 0;
         a.mix.n_cls = plan.n_cls;
         long long first = 0;
@@ -1498,47 +1586,6 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
         hipLaunchKernelGGL(fn, dim3((unsigned)first), dim3(256), lds, s, a);
         if ((st = launch_ok()) != PALU_OK) return st;
-      }
-      // Scores and values in one launch (attend16_kernel).  A unit's heads have to be whole groups (their value latents are then read by
-      // one workgroup of a run only) of one value rank, all in one launch with one pass of query rows, every head in one unit.
-      // Wherever that holds it is the faster form (attend16.hip); with stage events the stages have to be launches.
-      if (use16 && !use8 && (shared16 || m.qpk == 1) && m.qpk <= kShared16Rows && !v_i4 && !stage_events && g_opt_value_split == 0 &&
-          plan.n_cls == 1 && plan.total_units <= kMaxAttendUnits && rank_class_16(plan.cls_id[0] / 3) && plan.max_slices == 1 &&
-          !flat16(plan.total_units)) {
-        static thread_local AttendArgs t;
-        const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3, groups = 1 << lg;
-        bool whole = true;
-        for (int i = 0; i < plan.total_units && whole; ++i) {
-          const ScoreUnit& x = t.units.u[i] = unit16(mk, plan.units[i]);
-          const int j = mk.group_of_head[x.h0], rv = m.v_off[j + 1] - m.v_off[j];
-          whole = x.h0 == mk.head_off[j] && x.h0 + x.nh == mk.head_off[j + groups];
-          for (int g = 1; g < groups && whole; ++g) whole = m.v_off[j + g + 1] - m.v_off[j + g] == rv;
-          t.val[i] = AttendValue{m.v_off[j], rv, m.bv_off[j] / PALU_D_HEAD};
-        }
-        a.sk_row0 = 0;
-        a.sk_rows = m.qpk;
-        const dim3 grid = grid16(plan.total_units, false);
-        if (whole && w.lpad <= (1 << 24) && a.n_wg <= n_split_cap && a.n_wg <= kMaxSplits && a.run + (a.run_more ? 1 : 0) <= kMaxAttendTiles) {
-          static_cast<ScoreCommon&>(t) = a;
-          t.hv = static_cast<const uint16_t*>(hv);
-          t.q_len = q_len;
-          t.o_part = reinterpret_cast<float*>(ws + w.o_part);
-          t.ml_part = reinterpret_cast<float*>(ws + w.ml_part);
-          t.v_row_elems = Rv;
-          t.n_split = a.n_wg;
-          t.o_stride = w.o_stride;
-          t.units.n_units = plan.total_units;
-          const AttendFn fn = shared16 ? attend16q_fn(act, rc, m.qpk) : attend16_fn(act, rc, lg);
-          const size_t lds = (size_t)attend_lds_bytes((32 * (rc + 1)) << lg);
-          if (!fn) return PALU_ERR_UNSUPPORTED;
-          if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
-          hipLaunchKernelGGL(fn, grid, dim3(256), lds, s, t);
-          if ((st = launch_ok()) != PALU_OK) return st;
-          attended = true;
-          attend_wgs = a.n_wg;
-          attend_run = a.run;
-          attend_run_more = a.run_more;
-        }
       }
       for (int cls = 0; cls < plan.n_cls && !mixed && !attended; ++cls) {
         const int id = plan.cls_id[cls];
@@ -1707,6 +1754,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     a.out_latent = out_latent;
     a.n_split = attended ? attend_wgs : n_split;
     a.split_tokens = split_tokens;
+    a.slots = attend_slots;
     a.run = attended ? attend_run : 0;
     a.run_more = attended ? attend_run_more : 0;
     a.seq_len = seq_len;
@@ -1727,7 +1775,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       using CombFn = void (*)(CombineArgs, int);
       const CombFn fn = act == PALU_F16 ? (nb == 2 ? combine_rows_kernel<F16, 2, 4> : combine_rows_kernel<F16, 1, 8>)
                                         : (nb == 2 ? combine_rows_kernel<BF16, 2, 4> : combine_rows_kernel<BF16, 1, 8>);
-      const size_t lds = combine_rows_lds(nb, waves, rv_max, n_split);
+      const size_t lds = combine_rows_lds(nb, waves, rv_max, a.n_split);
       if ((st = allow_dynamic_lds(fn, lds)) != PALU_OK) return st;
       hipLaunchKernelGGL(fn, dim3((unsigned)(m.n_heads / m.qpk), (unsigned)row_groups), dim3(64 * waves), lds, s, a, rv_max);
     } else {

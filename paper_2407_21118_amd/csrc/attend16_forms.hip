@@ -1,20 +1,28 @@
-// Instantiations of the attention kernel (attend16.hip), one query per head, or (PALU_ATTEND_SHARED) several queries per key/value head.
+// Instantiations of the attention kernel (attend16.hip): one query per head, runs in one sequence or (PALU_SCORE_FLAT) through all; or (PALU_ATTEND_SHARED) several
+// queries per key/value head.
 #include "launch.h"
 #include "attend16.hip"
 
 #ifndef PALU_ATTEND_SHARED
 #define PALU_ATTEND_SHARED 0
 #endif
+#ifndef PALU_SCORE_FLAT
+#define PALU_SCORE_FLAT 0
+#endif
 
 namespace palu {
+
+namespace {
+constexpr bool kFlat = PALU_SCORE_FLAT != 0;
+}
 
 #if !PALU_ATTEND_SHARED
 namespace {
 template <typename T, int NK>
 AttendFn attend16_fn_g(int lg) {
-  if constexpr (NK <= 2) { if (lg == 2) return attend16_kernel<T, NK, 4, 1>; }
-  if constexpr (NK <= 4) { if (lg == 1) return attend16_kernel<T, NK, 2, 1>; }
-  return lg == 0 ? attend16_kernel<T, NK, 1, 1> : nullptr;
+  if constexpr (NK <= 2) { if (lg == 2) return attend16_kernel<T, NK, 4, 1, kFlat>; }
+  if constexpr (NK <= 4) { if (lg == 1) return attend16_kernel<T, NK, 2, 1, kFlat>; }
+  return lg == 0 ? attend16_kernel<T, NK, 1, 1, kFlat> : nullptr;
 }
 template <typename T>
 AttendFn attend16_fn_t(int rc, int lg) {
@@ -31,14 +39,15 @@ AttendFn attend16_fn_t(int rc, int lg) {
 }
 }  // namespace
 
-AttendFn attend16_fn(int act, int rc, int lg) { return act == PALU_F16 ? attend16_fn_t<F16>(rc, lg) : attend16_fn_t<BF16>(rc, lg); }
+template <>
+AttendFn attend16_fn<kFlat>(int act, int rc, int lg) { return act == PALU_F16 ? attend16_fn_t<F16>(rc, lg) : attend16_fn_t<BF16>(rc, lg); }
 #else
 namespace {
 template <typename T, int NK>
 AttendFn attend16q_fn_n(int nq) {
-  if (nq <= 2) return attend16_kernel<T, NK, 1, 2>;
-  if (nq <= 4) return attend16_kernel<T, NK, 1, 4>;
-  return attend16_kernel<T, NK, 1, 8>;
+  if (nq <= 2) return attend16_kernel<T, NK, 1, 2, kFlat>;
+  if (nq <= 4) return attend16_kernel<T, NK, 1, 4, kFlat>;
+  return attend16_kernel<T, NK, 1, 8, kFlat>;
 }
 template <typename T>
 AttendFn attend16q_fn_t(int rc, int nq) {
@@ -55,7 +64,8 @@ AttendFn attend16q_fn_t(int rc, int nq) {
 }
 }  // namespace
 
-AttendFn attend16q_fn(int act, int rc, int nq) { return act == PALU_F16 ? attend16q_fn_t<F16>(rc, nq) : attend16q_fn_t<BF16>(rc, nq); }
+template <>
+AttendFn attend16q_fn<kFlat>(int act, int rc, int nq) { return act == PALU_F16 ? attend16q_fn_t<F16>(rc, nq) : attend16q_fn_t<BF16>(rc, nq); }
 #endif
 
 }  // namespace palu

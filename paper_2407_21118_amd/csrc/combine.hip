@@ -51,14 +51,15 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   const Meta& m = a.meta;
   const int h = blockIdx.x >> 2, quarter = blockIdx.x & 3, b = blockIdx.y;
   const int L = a.seq_lens ? min(a.seq_lens[b], a.seq_len) : a.seq_len;
-  const int nsp = split_count(a, L);
+  size_t slot0;
+  const int nsp = split_count(a, b, h, L, &slot0);
   const int j = group_of(m, h);
   const int rv = m.v_off[j + 1] - m.v_off[j];
   int width;
   const int bv_blk = weight_block(m, j, h, m.bv_off[j], &width);
 
   // ---- softmax merge weights of the splits
-  const float* ml = a.ml_part + ((size_t)b * a.n_split * m.n_heads + h) * 2;
+  const float* ml = a.ml_part + (slot0 * m.n_heads + h) * 2;
   const size_t ml_stride = (size_t)m.n_heads * 2;
   float mx[1] = {-INFINITY};
   for (int c = tid; c < nsp; c += 256) mx[0] = fmaxf(mx[0], ml[c * ml_stride]);
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   block_reduce<1>(sum, red, false);      // barriers publish w[]
 
   // ---- o_lat[k] = sum_c w_c o_c[k]: thread = (split group sg of 4, k-quad kq of 64), 16-byte loads
-  const float* op = a.o_part + (size_t)b * a.n_split * a.o_stride + o_head_off(m, h);
+  const float* op = a.o_part + slot0 * a.o_stride + o_head_off(m, h);
   const int sg = tid >> 6, kq = tid & 63;
   for (int kb = 0; kb < rv; kb += 256) {
     const int k = kb + kq * 4;
@@ -179,8 +180,9 @@ __global__ __launch_bounds__(64 * WAVES) void combine_rows_kernel(CombineArgs a,
   {
     const int row = min(row0 + wave / W, rows - 1), b = row / m.qpk, h = blockIdx.x * m.qpk + row % m.qpk, sg = wave % W;
     const int L = a.seq_lens ? min(a.seq_lens[b], a.seq_len) : a.seq_len;
-    const int nsp = split_count(a, L);
-    const float* ml = a.ml_part + ((size_t)b * a.n_split * m.n_heads + h) * 2;
+    size_t slot0;
+    const int nsp = split_count(a, b, h, L, &slot0);
+    const float* ml = a.ml_part + (slot0 * m.n_heads + h) * 2;
     const size_t ml_stride = (size_t)m.n_heads * 2;
     float mx = -INFINITY, sum = 0.f;
     for (int c = lane; c < nsp; c += 64) mx = fmaxf(mx, ml[c * ml_stride]);
@@ -197,7 +199,7 @@ __global__ __launch_bounds__(64 * WAVES) void combine_rows_kernel(CombineArgs a,
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // w: written and read by this wavefront, whose LDS operations stay in order
     __builtin_amdgcn_wave_barrier();
 
-    const float* op = a.o_part + (size_t)b * a.n_split * a.o_stride + o_head_off(m, h);
+    const float* op = a.o_part + slot0 * a.o_stride + o_head_off(m, h);
     for (int k = lane * 4; k < rv; k += 256) {
       float4v acc = {0.f, 0.f, 0.f, 0.f};
       for (int c0 = sg; c0 < nsp; c0 += 8 * W) {               // 8 independent loads per batch

@@ -278,13 +278,20 @@ struct AttendValue {
   int rv;                    // value rank of each of its groups
   int o0;                    // where the unit's first head begins in an o_part row; head x of the unit follows x * rv floats on
 };
+struct AttendMix {
+  int first[kMaxAttendUnits + 1];       // first workgroup of every unit
+  int run[kMaxAttendUnits], run_more[kMaxAttendUnits];       // as in ScoreArgs
+  uint8_t nk[kMaxAttendUnits];          // key rank / 32
+};
 struct AttendArgs : ScoreCommon {
   const uint16_t* hv;
   const int32_t* q_len;      // as in PvArgs
-  float* o_part;             // [batch][n_split][o_stride]: one partial result per workgroup of a (unit, sequence)
-  float* ml_part;            // [batch][n_split][n_heads][2]
+  float* o_part;             // [slot][o_stride]: one partial result per workgroup and sequence it works on, at slot sequence * n_split + workgroup or, where
+  float* ml_part;            // [slot][n_heads][2]                                runs go through all sequences, workgroup + sequence
+  int* slots;                // non-NULL: the first and last slot of every [batch][n_heads] are written here
   long long v_row_elems;     // R_v
-  int n_split;               // = n_wg
+  int n_split;               // slots between sequences, where runs lie in one
+  AttendMix mix;             // attend16_mixed_kernel
   int o_stride;
   AttendUnits units;
   AttendValue val[kMaxAttendUnits];
@@ -332,15 +339,22 @@ struct CombineArgs {
   float* out_latent;         // non-NULL: write the normalised latent output [batch, o_stride] instead and skip B_v
   int n_split;
   int split_tokens;
+  const int* slots;          // non-NULL: the first and last partial result of every [batch][n_heads] (AttendArgs), n_split at most
   int run, run_more;         // run > 0: the splits are attend16_kernel's runs of tiles, the first run_more of them run + 1 tiles long, the rest run
   int seq_len;
   int o_stride;
   int batch;
   Meta meta;
 };
-// number of partial results of a sequence of L attended rows
-__device__ __forceinline__ int split_count(const CombineArgs& a, int L) {
+// number of partial results of head h of sequence b, of L attended rows; *first receives the first one's slot
+__device__ __forceinline__ int split_count(const CombineArgs& a, int b, int h, int L, size_t* first) {
+  *first = (size_t)b * a.n_split;
   if (L <= 0) return 0;
+  if (a.slots) {
+    const int* s = a.slots + ((size_t)b * a.meta.n_heads + h) * 2;
+    *first = (size_t)s[0];
+    return s[1] - s[0] + 1;
+  }
   if (a.run == 0) return (L + a.split_tokens - 1) / a.split_tokens;
   const int tiles = (L + kTile - 1) / kTile, longer = a.run_more * (a.run + 1);
   return tiles <= longer ? (tiles + a.run) / (a.run + 1) : a.run_more + (tiles - longer + a.run - 1) / a.run;

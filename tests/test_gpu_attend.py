@@ -26,21 +26,48 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("heads,group,rk,rv,qpk,dtype,lens,chunks", CASES)
-def test_run_of_tiles(heads, group, rk, rv, qpk, dtype, lens, chunks):
+# ... in runs through all sequences (chunks: workgroups per unit and sequence): runs that begin and end inside a sequence, empty sequences
+# between others, several sequences to a run, runs longer than the values of one go (64 tiles)
+FLAT_CASES = [
+    (4, 4, 256, 256, 1, "f16", [511, 0, 96, 33, 0, 0, 1], 1), (8, 4, 128, 384, 1, "bf16", [200, 333, 64], 2), (4, 1, 64, 64, 1, "f16", [700, 650, 32], 3),
+    (4, 2, 96, 160, 1, "f16", [65, 40, 0, 97, 31], 1), (4, 4, 256, 160, 1, "f16", [4200, 300], 1), (4, 1, 64, 96, 1, "f16", [300, 6500], 1),
+    (4, 4, 160, 256, 1, "f16", [31] * 70, 1),
+]
+
+
+@pytest.mark.parametrize("heads,group,rk,rv,qpk,dtype,lens,chunks,flat", [c + (False,) for c in CASES] + [c + (True,) for c in FLAT_CASES])
+def test_run_of_tiles(heads, group, rk, rv, qpk, dtype, lens, chunks, flat):
     import paper_2407_21118_amd as P
     from gpu_util import TOL_FP, rel_err, run_hip, run_oracle, say
     case = synth.make_case_orthonormal(_layer(heads, group, rk, rv, qpk), len(lens), max(lens), seed=heads + rk + rv + qpk, dtype=dtype)
     case.seq_lens = np.array(lens, np.int32) if len(lens) > 1 else None
     case.q_pos = np.maximum(np.array(lens, np.int32) - 1, 0)
-    P.palu_set_option("score_chunks", 0 if case.seq_lens is not None else chunks)     # (with lengths the option means runs through all sequences)
+    P.palu_set_option("score_chunks", chunks if flat or case.seq_lens is None else 0)     # (with lengths the option means runs through all sequences)
     try:
         got = run_hip(case)
     finally:
         P.palu_set_option("score_chunks", 0)
     ref = run_oracle(case)
     err = rel_err(got, ref)[0]
-    say(f"[attend] {heads}/{group} heads rank {rk}/{rv} x{qpk} {dtype} {lens} chunks {chunks}: {err:.2e}")
+    say(f"[attend] {heads}/{group} heads rank {rk}/{rv} x{qpk} {dtype} {lens[:8]} chunks {chunks}: {err:.2e}")
+    assert err <= TOL_FP
+    for b, n in enumerate(lens):
+        if n == 0:
+            assert not got[b].any()
+
+
+@pytest.mark.parametrize("kr,vr,dtype,lens", [([64, 256, 96], [384, 32, 160], "f16", [1]), ([256, 128, 224, 160], [96, 256, 128, 416], "bf16", [333, 0]),
+                                              ([192, 64, 256], [256, 160, 64], "f16", [129, 700, 0, 31, 65]), ([128, 96], [160, 512], "f16", [6000, 64, 5000])])
+def test_units_of_several_ranks(kr, vr, dtype, lens):
+    """One launch over groups of different key and value ranks: one sequence, two (runs inside one) and several (runs through all)."""
+    from gpu_util import TOL_FP, rel_err, run_hip, run_oracle, say
+    layer = synth.ragged_layer(4 * len(kr), 4, kr, vr)
+    case = synth.make_case_orthonormal(layer, len(lens), max(lens), seed=sum(kr) + len(lens), dtype=dtype)
+    case.seq_lens = np.array(lens, np.int32) if len(lens) > 1 else None
+    case.q_pos = np.maximum(np.array(lens, np.int32) - 1, 0)
+    got, ref = run_hip(case), run_oracle(case)
+    err = rel_err(got, ref)[0]
+    say(f"[attend] ranks {kr} / {vr} {dtype} {lens}: {err:.2e}")
     assert err <= TOL_FP
     for b, n in enumerate(lens):
         if n == 0:
@@ -77,3 +104,15 @@ def test_row_limits_inside_a_run(n_q, qpk, rk, rv):
     say(f"[attend] {n_q} queries x{qpk} rank {rk}/{rv}: {err:.2e}")
     assert err <= TOL_FP
     assert not got[q_len == 0].any()
+
+
+def test_more_runs_than_value_splits():
+    """Many sequences of one unit: more partial results per sequence, and in all, than the value kernel's splits would make."""
+    from gpu_util import TOL_FP, rel_err, run_hip, run_oracle
+    lens = [(37 * i) % 301 for i in range(140)] + [2500]
+    case = synth.make_case_orthonormal(_layer(4, 4, 64, 64), len(lens), max(lens), seed=5)
+    case.seq_lens = np.array(lens, np.int32)
+    case.q_pos = np.maximum(case.seq_lens - 1, 0)
+    some = case.seq_lens > 0
+    got, ref = run_hip(case), run_oracle(case)
+    assert max(rel_err(got[some], ref[some])) <= TOL_FP and not got[~some].any()
