@@ -1065,6 +1065,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
 
   bool enc_pending = enc != nullptr;
   bool used16 = false;
+  bool streamed = false;                  // non-RoPE: scores and values in one launch
   bool attended = false;                  // scores and values in one launch: its runs of tiles are the splits that are merged
   int attend_wgs = 0, attend_run = 0, attend_run_more = 0;
   const int* attend_slots = nullptr;
@@ -1160,7 +1161,62 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       }
     }
     if ((st = mark(1)) != PALU_OK) return st;
-    for (int cls = 0; cls < 2; ++cls) {              // 0: up to 16 heads per unit, 1: up to 32
+    // One pass over both sides (stream_kernel), where both are of one type and the two plans' units are the same heads, of at most 256
+    // columns each: nothing is written in between, and one launch less.  Units of more than 4 heads over codes keep their two launches: their registers
+    // make it one wavefront per SIMD, which issues for both (4 x 16384 tokens of 4 bits, 4 queries per key/value head 58.4 -> 64.4 us a
+    // step, a group of 8 heads over 4 x 8192 55.6 -> 61.0; unquantized 58.5 -> 52.7 and 45 -> 42).
+    streamed = !stage_events && k_bits == v_bits && qp.total_units == pp.total_units && pp.total_units <= kMaxStreamUnits;
+    for (int i = 0; i < pp.total_units && streamed; ++i)
+      streamed = qp.units[i].h0 == pp.units[i].h0 && qp.units[i].nh == pp.units[i].nh && qp.units[i].wpad == 256 && pp.unit_cls[i] == pp.unit_cls[0] &&
+                 (!k_i4 || pp.units[i].nh <= 4);
+    if (streamed) {
+      static thread_local StreamArgs t;
+      t.hv = hv;
+      t.hv_scale = static_cast<const uint16_t*>(hv_scale);
+      t.hv_zero = static_cast<const uint16_t*>(hv_zero);
+      t.scores = nullptr;
+      t.seq_lens = seq_lens;
+      t.q_len = q_len;
+      t.o_part = reinterpret_cast<float*>(ws + w.o_part);
+      t.ml_part = reinterpret_cast<float*>(ws + w.ml_part);
+      t.row_elems = Rv;
+      t.max_seq = max_seq;
+      t.part_stride = 0;
+      t.seq_len = seq_len;
+      t.lpad = w.lpad;
+      t.batch = batch;
+      t.split_tokens = split_tokens;
+      t.n_split = n_split;
+      t.o_stride = w.o_stride;
+      t.n_blocks_q = Rv / quant_block;
+      t.meta = m;
+      t.hk = hk;
+      t.hk_scale = a.hk_scale;
+      t.hk_zero = a.hk_zero;
+      t.qt = f.qt;
+      t.qsum = f.qsum;
+      t.qt_bstride = f.qt_bstride;
+      t.qs_bstride = f.qs_bstride;
+      t.k_row_elems = Rk;
+      t.k_blocks_q = Rk / quant_block;
+      t.scale = a.scale;
+      t.units.n_units = pp.total_units;
+      int max_nh = 0;
+      for (int i = 0; i < pp.total_units; ++i) {
+        t.units.u[i] = pp.units[i];
+        t.keys[i] = StreamKeys{qp.units[i].c0, qp.units[i].q_off, qp.units[i].qs_off, qp.units[i].ncols};
+        max_nh = std::max(max_nh, (int)pp.units[i].nh);
+      }
+      t.units_per_wg = pp.total_units >= 4 ? 4 : (pp.total_units >= 2 ? 2 : 1);
+      t.lds_unit_stride = (int)align_up(stream_unit_lds(k_i4, max_nh), 16);
+      const size_t lds = (size_t)t.lds_unit_stride * t.units_per_wg;
+      const StreamFn fn = stream_fn(act, k_bits, pp.unit_cls[0]);
+      if ((st = allow_dynamic_lds(fn, lds + kStaticLdsMax)) != PALU_OK) return st;
+      const dim3 grid((unsigned)ceil_div(pp.total_units, t.units_per_wg), (unsigned)ceil_div(n_split, 4 / t.units_per_wg), (unsigned)batch);
+      hipLaunchKernelGGL(fn, grid, dim3(256), lds, s, t);
+      if ((st = launch_ok()) != PALU_OK) return st;
+    }
+    for (int cls = 0; cls < 2 && !streamed; ++cls) {              // 0: up to 16 heads per unit, 1: up to 32
       using QkFn = void (*)(QkArgs);
       QkFn fn = k_bits == 4 ? (cls ? qk_kernel<F16, 2, 4> : qk_kernel<F16, 1, 4>)
               : k_bits == 3 ? (cls ? qk_kernel<F16, 2, 3> : qk_kernel<F16, 1, 3>)
@@ -1673,7 +1729,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
   }
 
   // 3. softmax partials and P.H_v per split
-  if (!attended) {
+  if (!attended && !streamed) {
   uint8_t n_parts[PALU_MAX_HEADS];
   std::memset(n_parts, 0, sizeof(n_parts));
   int max_parts = 0;

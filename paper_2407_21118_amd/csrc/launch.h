@@ -55,7 +55,7 @@ struct PvUnits {
   PvUnit u[kMaxPvUnits];
 };
 
-struct PvArgs {
+struct PvCommon {
   const void* hv;
   const uint16_t* hv_scale;
   const uint16_t* hv_zero;
@@ -75,10 +75,39 @@ struct PvArgs {
   int o_stride;
   int n_blocks_q;
   int units_per_wg;          // 1, 2 or 4: the wavefronts of a workgroup take this many units of the same splits
-  uint8_t n_parts[PALU_MAX_HEADS];   // 1 or 2 score planes per head
   Meta meta;
+};
+struct PvArgs : PvCommon {
+  uint8_t n_parts[PALU_MAX_HEADS];   // 1 or 2 score planes per head
   PvUnits units;
 };
+
+// Non-RoPE attention in one pass (pv.hip): every wavefront makes its split's scores itself, from the folded queries (qk.hip).  The units are
+// the value units; of each its key side:
+struct StreamKeys {
+  int32_t c0, q_off, qs_off;         // as in QkUnit
+  int32_t ncols;                     // at most 256
+};
+constexpr int kMaxStreamUnits = 32;
+struct StreamUnits {
+  int n_units;
+  PvUnit u[kMaxStreamUnits];
+};
+struct StreamArgs : PvCommon {
+  const void* hk;
+  const uint16_t* hk_scale;
+  const uint16_t* hk_zero;
+  const uint16_t* qt;
+  const float* qsum;
+  long long qt_bstride, qs_bstride;
+  long long k_row_elems;             // R_k
+  int k_blocks_q;
+  int lds_unit_stride;               // bytes of LDS per unit's folded queries
+  float scale;                       // log2(e) / sqrt(d_h)
+  StreamUnits units;
+  StreamKeys keys[kMaxStreamUnits];
+};
+static_assert(sizeof(PvArgs) <= 4096 && sizeof(StreamArgs) <= 4096, "kernel arguments");
 
 struct PlaneSumArgs {
   float* scores;
@@ -93,6 +122,11 @@ struct PlaneSumArgs {
 using PvFn = void (*)(PvArgs);
 // bits: 4, 3 or 2 for quantized value latents, else 0; two_planes: some head's scores lie in two planes
 PvFn pv_fn(int act, int bits, int cls, bool two_planes);
+// ... of the one-pass form, both sides of the same latent dtype; LDS per unit: stream_unit_lds
+using StreamFn = void (*)(StreamArgs);
+StreamFn stream_fn(int act, int bits, int cls);
+constexpr int kStreamPitch = 256 + 8;      // halfs per folded query: 16 bytes of padding keep the head rows on distinct banks
+constexpr int stream_unit_lds(bool quantized, int nh) { return quantized ? nh * kStreamPitch * 2 + nh * 2 * 4 : 2 * nh * kStreamPitch * 2; }
 int launch_plane_sum(const PlaneSumArgs& a, int batch, hipStream_t s);
 
 }  // namespace palu

@@ -32,6 +32,8 @@
 #include "launch.h"
 #include "softmax_dev.h"
 
+#include <type_traits>
+
 #ifndef PALU_PV_PAIR_DEPTH
 #define PALU_PV_PAIR_DEPTH 2
 #endif
@@ -60,8 +62,13 @@ __global__ __launch_bounds__(256) void plane_sum_kernel(PlaneSumArgs a) {
 //     4-bit register layout when they are consumed and then follow the 4-bit arithmetic.
 // TWO: some head of the launch has two score planes (the kernel then requests both planes of every head; with one
 //     plane everywhere the second request, an instruction per head slot and set, is left out)
-template <typename T, int HS, int NG, int QB, bool TWO>
-__global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(PvArgs a) {
+// QK: non-RoPE attention in one pass: the scores of a set are made from its key latents and the folded queries (the arithmetic of qk_kernel, same
+//     units and columns of at most 256) instead of being read; nothing goes through memory in between.  Bound like the two kernels
+//     it replaces, by the latent streams and, with codes, by the instructions beside them; what it saves is a launch and the scores' way
+//     through memory.  us a step, two launches -> one: 1 x 65536 tokens 129 -> 119, in 4 bits 76.9 -> 71.7; 16 x 8192 236 -> 218, in 4
+//     bits 108.5 -> 96.8; 1 x 1024 34.6 -> 33.2; rank 64 per head, 4 x 8000 80.8 -> 70.5.
+template <typename T, int HS, int NG, int QB, bool TWO, bool QK>
+__device__ __forceinline__ void pv_body(const std::conditional_t<QK, StreamArgs, PvArgs>& a) {
   constexpr bool I4 = QB != 0;
   constexpr bool kIsBf16 = !__is_same(T, F16);
   constexpr int MT = HS > 8 ? 2 : 1;
@@ -76,6 +83,9 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
   constexpr int kPitch = 40;                       // halfs per head row: 80-byte pitch, 16-byte reads of 16 rows hit distinct banks
   __shared__ __attribute__((aligned(16))) _Float16 p_lds[4][NT][MT * 16 * kPitch];
   __shared__ __attribute__((aligned(16))) float x_lds[4][MT * 16 * NA];
+  constexpr int kScPitch = 33;                     // floats per score row: the 16 tokens of two rows fall on distinct banks
+  __shared__ float sc_lds[QK ? 4 : 1][QK ? 2 * HS * kScPitch : 1];
+  extern __shared__ __attribute__((aligned(16))) unsigned char qk_lds_all[];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -90,6 +100,30 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
   const int upw = a.units_per_wg;
   const int unit = blockIdx.x * upw + (wave & (upw - 1)), b = blockIdx.z;
   const int split = blockIdx.y * (4 / upw) + wave / upw;
+  if constexpr (QK) {
+    // folded queries of the workgroup's units (one behind the other), in the order of channels that the quantized operands have
+    for (int j = 0; j < upw; ++j) {
+      const int uj = blockIdx.x * upw + j;
+      if (uj >= a.units.n_units) break;              // uniform
+      const int rows = (I4 ? 1 : 2) * a.units.u[uj].nh;
+      const uint16_t* src = a.qt + (size_t)blockIdx.z * a.qt_bstride + a.keys[uj].q_off;
+      unsigned char* dst = qk_lds_all + j * a.lds_unit_stride;
+      for (int i = threadIdx.x; i < rows * 32; i += 256) {
+        const int r = i >> 5, cc = i & 31;
+        uint4v v = *reinterpret_cast<const uint4v*>(src + r * 256 + cc * 8);
+        if constexpr (I4)
+          v = uint4v{__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
+                     __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u)};
+        *reinterpret_cast<uint4v*>(dst + (r * kStreamPitch + cc * 8) * 2) = v;
+      }
+      if constexpr (I4) {                            // their block sums behind the rows
+        const float* qs_src = a.qsum + (size_t)blockIdx.z * a.qs_bstride + a.keys[uj].qs_off;
+        float* qs_dst = reinterpret_cast<float*>(dst + rows * kStreamPitch * 2);
+        for (int i = threadIdx.x; i < rows * 2; i += 256) qs_dst[i] = qs_src[i];
+      }
+    }
+    __syncthreads();
+  }
   if (unit >= a.units.n_units) return;             // whole wavefront; nothing below synchronises wavefronts
   const int L = a.seq_lens ? min(a.seq_lens[b], a.seq_len) : a.seq_len;
   const int s0 = split * a.split_tokens;
@@ -127,19 +161,138 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
 #pragma unroll
   for (int i = 0; i < HS; ++i) {
     const int h = h0 + min(hp + 2 * i, nh - 1);
-    sc_ptr[i] = a.scores + ((size_t)b * m.n_heads + h) * a.lpad + s0;
-    two[i] = a.n_parts[h] > 1;
+    if constexpr (!QK) {
+      sc_ptr[i] = a.scores + ((size_t)b * m.n_heads + h) * a.lpad + s0;
+      two[i] = a.n_parts[h] > 1;
+    }
     lim[i] = a.q_len ? a.q_len[b * m.nq + q_token(m, h)] - s0 : 0x7fffffff;
   }
   const size_t sz_idx0 = I4 ? row0 * a.n_blocks_q + (c0 >> 7) : 0;
   const int n_blk = (u.ncols + 127) >> 7;          // 128-column blocks the unit really has
+
+  // QK: the key side, requests of a set and scores from it as in qk_kernel (one chunk of at most 256 columns)
+  constexpr int kKeyLoads = I4 ? 2 : 8;            // 16-byte loads per 16 tokens: one per 128-column block of codes, else one per 32 columns
+  unsigned k_row_bytes = 0, k_hi_plane = 0;
+  const unsigned char* k_base = nullptr;
+  size_t k_sz0 = 0;
+  int k_cols = 256, k_blk = 2;
+  const unsigned char* qk_lds = nullptr;
+  uint32_t fp16_ones = 0;
+  if constexpr (QK) {
+    const StreamKeys ku = a.keys[unit];
+    k_row_bytes = (unsigned)a.k_row_elems * (unsigned)bits / 8u;
+    k_base = (const unsigned char*)a.hk + row0 * k_row_bytes + (I4 ? (bits == 4 ? ku.c0 / 2 : ku.c0 / 4) : ku.c0 * 2);
+    k_hi_plane = (unsigned)a.k_row_elems / 4u + (unsigned)ku.c0 / 8u - (unsigned)ku.c0 / 4u;
+    k_sz0 = I4 ? row0 * a.k_blocks_q + (ku.c0 >> 7) : 0;
+    k_cols = ku.ncols;
+    k_blk = (k_cols + 127) >> 7;
+    qk_lds = qk_lds_all + (wave & (upw - 1)) * a.lds_unit_stride;
+    fp16_ones = per_lane_constant(0x3c003c00u);
+  }
+  struct Keys {
+    uint4v h[QK ? 2 : 1][QK ? kKeyLoads : 1];      // [16-token tile][load]
+    uint16_t sz[2];                                // quantized: the lane's share of the set's scales and zero-points
+  };
+  auto issue_keys = [&](Keys& st, int k) {
+    if constexpr (QK) {
+      if constexpr (I4) {
+        const unsigned t = (unsigned)min(k * 32 + (kq >> 1) * 16 + n, last);
+        const uint16_t* arr = (kq & 1) ? a.hk_zero : a.hk_scale;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) st.sz[x] = arr[k_sz0 + (size_t)t * a.k_blocks_q + min(x, k_blk - 1)];
+      }
+#pragma unroll
+      for (int tau = 0; tau < 2; ++tau) {
+        const unsigned t = (unsigned)min(k * 32 + tau * 16 + n, last);
+#pragma unroll
+        for (int x = 0; x < kKeyLoads; ++x) {
+          const unsigned off = I4 ? (unsigned)min(x, k_blk - 1) * 64u + (unsigned)kq * 16u : (unsigned)min(x * 32 + kq * 8, k_cols - 8) * 2u;
+          const unsigned char* p = k_base + (size_t)(t * k_row_bytes);
+          if constexpr (!I4 || bits == 4) {
+            st.h[tau][x] = *reinterpret_cast<const uint4v*>(p + off);
+          } else {
+            const uint2v lo = *reinterpret_cast<const uint2v*>(p + (off >> 1));
+            st.h[tau][x].x = lo.x;
+            st.h[tau][x].y = lo.y;
+            if constexpr (bits == 3) st.h[tau][x].z = *reinterpret_cast<const uint32_t*>(p + k_hi_plane + (off >> 2));
+          }
+        }
+      }
+    }
+  };
+  // the set's scores of all heads to sc_lds [head][token]
+  auto make_scores = [&](const Keys& st) {
+    if constexpr (QK) {
+      const int qrow = min(n, nh - 1) * kStreamPitch * 2;
+      float4v d2[2] = {};
+      if constexpr (!I4) {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const half8 af = *reinterpret_cast<const half8*>(qk_lds + qrow + (x * 32 + kq * 8) * 2);
+          const half8 al = *reinterpret_cast<const half8*>(qk_lds + nh * kStreamPitch * 2 + qrow + (x * 32 + kq * 8) * 2);
+#pragma unroll
+          for (int tau = 0; tau < 2; ++tau) {
+            uint4v hw = st.h[tau][x];
+            if constexpr (kIsBf16) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                hw[e] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__builtin_bit_cast(float, hw[e] << 16),
+                                                                                __builtin_bit_cast(float, hw[e] & 0xffff0000u)));
+            }
+            const half8 bop = __builtin_bit_cast(half8, hw);
+            d2[tau] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, bop, d2[tau], 0, 0, 0);
+            d2[tau] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bop, d2[tau], 0, 0, 0);
+          }
+        }
+      } else {
+        uint32_t szv[4];                           // [2 tau + (0: scales, 1: zero-points)], block x in bits 16 x ..
+        const int own = (int)((uint32_t)st.sz[0] | ((uint32_t)st.sz[1] << 16));
+#pragma unroll
+        for (int k4 = 0; k4 < 4; ++k4) szv[k4] = (uint32_t)__builtin_amdgcn_ds_bpermute((n + 16 * k4) * 4, own);
+        const float* qs_base = reinterpret_cast<const float*>(qk_lds + nh * kStreamPitch * 2);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          half8 af[4];
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) af[jj] = *reinterpret_cast<const half8*>(qk_lds + qrow + (x * 128 + kq * 32 + jj * 8) * 2);
+          float qs[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) qs[r] = qs_base[min(4 * kq + r, nh - 1) * 2 + min(x, k_blk - 1)];
+#pragma unroll
+          for (int tau = 0; tau < 2; ++tau) {
+            float4v d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+              uint32_t w = st.h[tau][x][jj];
+              if constexpr (bits != 4) w = expand_low_bits(st.h[tau][x][jj >> 1] >> (16 * (jj & 1)), st.h[tau][x][2] >> (8 * jj), bits == 3);
+              const NibblePairs np = nibbles_to_fp16_pairs(w, fp16_ones);
+              const uint4v bw = {np.p[0], np.p[1], np.p[2], np.p[3]};
+              d = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[jj], __builtin_bit_cast(half8, bw), d, 0, 0, 0);
+            }
+            const float sc = x < k_blk ? F16::to_float((uint16_t)(szv[2 * tau] >> (16 * x))) : 0.f;
+            const float zp = F16::to_float((uint16_t)(szv[2 * tau + 1] >> (16 * x)));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d2[tau][r] = fmaf(sc, fmaf(-(zp + 64.f), qs[r], 64.f * d[r]), d2[tau][r]);
+          }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (4 * kq + r >= nh) continue;            // accumulator row = head
+#pragma unroll
+        for (int tau = 0; tau < 2; ++tau) sc_lds[wave][(4 * kq + r) * kScPitch + tau * 16 + n] = d2[tau][r] * a.scale;
+      }
+      wave_lds_fence();
+    }
+  };
 
   struct Blk {
     uint32_t h[8][I4 ? (QB == 3 ? 2 : 1) : 4];     // [token j of the lane's quarter][dword]; quantized: codes, third bits (3-bit only)
   };
   struct Set {
     Blk blk[NG];
-    float sc[HS][TWO ? 2 : 1];
+    float sc[QK ? 1 : HS][TWO ? 2 : 1];
+    Keys keys;
     uint16_t sz[NA];                               // quantized: scales (lanes 0 .. 31) or zero-points (32 .. 63) of the lane's softmax token, as loaded
   };
 
@@ -147,6 +300,7 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
   // what a clamped load returns is given zero weight or never stored
   auto issue = [&](Set& st, int k) {
     const int tb = k * 32;
+    issue_keys(st.keys, k);
 #pragma unroll
     for (int ng = 0; ng < (kPair ? 1 : NG); ++ng) {
 #pragma unroll
@@ -179,10 +333,12 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
       }
     }
     const int ts = min(tb + tl, last);
+    if constexpr (!QK) {
 #pragma unroll
-    for (int i = 0; i < HS; ++i) {
-      st.sc[i][0] = sc_ptr[i][ts];
-      if constexpr (TWO) st.sc[i][1] = sc_ptr[i][ts + a.part_stride];
+      for (int i = 0; i < HS; ++i) {
+        st.sc[i][0] = sc_ptr[i][ts];
+        if constexpr (TWO) st.sc[i][1] = sc_ptr[i][ts + a.part_stride];
+      }
     }
     if constexpr (I4) {
       // the two lanes of a token split its scales and zero-points (2-byte requests cost the memory pipeline as much
@@ -216,6 +372,7 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
 
   auto process = [&](Set& st, int k) {
     const bool tok_ok = k * 32 + tl < ntok;
+    make_scores(st.keys);
     // ---- online softmax statistics of the 32 tokens
     float s[HS], bm[HS];
     bool grew = false;
@@ -239,7 +396,9 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
     }
 #pragma unroll
     for (int i = 0; i < HS; ++i) {
-      float v = st.sc[i][0];
+      float v;
+      if constexpr (QK) v = sc_lds[wave][min(hp + 2 * i, nh - 1) * kScPitch + tl];
+      else v = st.sc[i][0];
       if constexpr (TWO) v += two[i] ? st.sc[i][1] : 0.f;
       s[i] = (tok_ok && hp + 2 * i < nh && k * 32 + tl < lim[i]) ? v : -INFINITY;
       bm[i] = half_wave_max(s[i]);
@@ -422,7 +581,26 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(P
   }
 }
 
+template <typename T, int HS, int NG, int QB, bool TWO>
+__global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void pv_kernel(PvArgs a) {
+  pv_body<T, HS, NG, QB, TWO, false>(a);
+}
+template <typename T, int HS, int NG, int QB>
+__global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void stream_kernel(StreamArgs a) {
+  pv_body<T, HS, NG, QB, false, true>(a);
+}
+
 namespace {
+
+template <typename T, int QB>
+StreamFn stream_fn_t(int cls) {
+  switch (cls) {
+    case 0: return stream_kernel<T, 2, 1, QB>;
+    case 1: return stream_kernel<T, 2, 2, QB>;
+    case 2: return stream_kernel<T, 8, 1, QB>;
+    default: return stream_kernel<T, 8, 2, QB>;
+  }
+}
 
 template <typename T, int QB, bool TWO>
 PvFn pv_fn_t(int cls) {
@@ -444,6 +622,13 @@ PvFn pv_fn_p(int act, int bits, int cls) {
 
 PvFn pv_fn(int act, int bits, int cls, bool two_planes) {
   return two_planes ? pv_fn_p<true>(act, bits, cls) : pv_fn_p<false>(act, bits, cls);
+}
+
+StreamFn stream_fn(int act, int bits, int cls) {
+  if (bits == 4) return stream_fn_t<F16, 4>(cls);
+  if (bits == 3) return stream_fn_t<F16, 3>(cls);
+  if (bits == 2) return stream_fn_t<F16, 2>(cls);
+  return act == PALU_F16 ? stream_fn_t<F16, 0>(cls) : stream_fn_t<BF16, 0>(cls);
 }
 
 int launch_plane_sum(const PlaneSumArgs& a, int batch, hipStream_t s) {
