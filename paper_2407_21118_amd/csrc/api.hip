@@ -1532,17 +1532,20 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       }
       // Scores and values in one launch (attend16_kernel).  A unit's heads have to be whole groups (their value latents are then read by
       // one workgroup of a run only) of one value rank, all in one launch with one pass of query rows, every head in one unit.
-      // Wherever that holds it is the faster form (attend16.hip); with stage events the stages have to be launches.
+      // It is the faster form (attend16.hip) with two exceptions, see pays_* below; with stage events the stages have to be launches.
       bool attend = use16 && !use8 && (shared16 || m.qpk == 1) && m.qpk <= kShared16Rows && !v_i4 && !stage_events && g_opt_value_split == 0 &&
                     plan.total_units <= kMaxAttendUnits && plan.max_slices == 1 && w.lpad <= (1 << 24) &&
                     (plan.n_cls == 1 ? rank_class_16(plan.cls_id[0] / 3) : mixed && use_one_round);
       static thread_local AttendArgs t;
+      int cols = PALU_MAX_RANK, rows = 0;                        // fewest value columns and most query rows of a unit
       for (int i = 0; i < plan.total_units && attend; ++i) {
         const ScoreUnit& x = t.units.u[i] = unit16(mk, plan.units[i]);
         const int j = mk.group_of_head[x.h0], rv = m.v_off[j + 1] - m.v_off[j], groups = 1 << plan.cls_id[plan.unit_cls[i]] % 3;
         attend = x.h0 == mk.head_off[j] && x.h0 + x.nh == mk.head_off[j + groups];
         for (int g = 1; g < groups && attend; ++g) attend = m.v_off[j + g + 1] - m.v_off[j + g] == rv;
         t.val[i] = AttendValue{m.v_off[j], rv, m.bv_off[j] / PALU_D_HEAD};
+        cols = std::min(cols, groups * rv);
+        rows = std::max(rows, x.nh * m.qpk);
       }
       if (attend) {
         const bool flat = plan.n_cls == 1 ? flat16(plan.total_units) : mix_flat;
@@ -1585,7 +1588,17 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         // the partial results, one per workgroup and sequence it works on, fit where the value kernel's go; runs through all sequences, and units
         // of different ranks, note which they are per head in the region of B_k's layout, which this path leaves alone
         const bool noted = flat || plan.n_cls > 1;
-        attend = (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
+        // A change of segment costs about 3 us of a workgroup, which the values of short segments of few columns do not repay.  us a step, two launches
+        // -> one, average tiles a segment x columns: 40 x 600 tokens rank 64 (10 x 64) 52.9 -> 57.3, rank 96 (10 x 96) 60.0 -> 61.5, rank 128 (10 x
+        // 128) 66.5 -> 66.5, 40 x 1200 rank 64 (21 x 64) 76.9 -> 80.1, rank 96 (21 x 96) 88.0 -> 85.8, 20 x 3000 rank 64 (36 x 64) 86.6 -> 85.6; 256
+        // columns: 100 x 200 (5) 101.2 -> 95.3, 40 x 300 (5) 75.3 -> 72.2.
+        const long long seg_tiles = flat ? (long long)batch * tiles / (n_wg + batch) : run;
+        const bool pays_segment = !flat || cols >= 192 || seg_tiles * cols >= 1900;
+        // Rows go 16 at a time, each time over all values of the run; the value kernel has the blocks of 32 rows side by side.  Two blocks pay
+        // where the second is not full (a launch of its own there) or the run is short: 8 queries over 2 x 8000 tokens, rank 128 (16 tiles) 59.3
+        // -> 61.9, 1 x 4000, rank 256 (4 tiles) 44.0 -> 37.7; 5 over 1 x 16000 91.8 -> 75.7.
+        const bool pays_rows = rows <= 16 || rows % 16 != 0 || run <= 8;
+        attend = pays_segment && pays_rows && (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
                  (!noted || (size_t)batch * m.n_heads * 8 <= (size_t)w.mfold_bstride * 2) && n_wg <= kMaxSplits;
         if (attend) {
           const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3;

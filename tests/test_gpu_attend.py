@@ -110,7 +110,7 @@ def test_more_runs_than_value_splits():
     """Many sequences of one unit: more partial results per sequence, and in all, than the value kernel's splits would make."""
     from gpu_util import TOL_FP, rel_err, run_hip, run_oracle
     lens = [(37 * i) % 301 for i in range(140)] + [2500]
-    case = synth.make_case_orthonormal(_layer(4, 4, 64, 64), len(lens), max(lens), seed=5)
+    case = synth.make_case_orthonormal(_layer(4, 4, 64, 256), len(lens), max(lens), seed=5)
     case.seq_lens = np.array(lens, np.int32)
     case.q_pos = np.maximum(case.seq_lens - 1, 0)
     some = case.seq_lens > 0
