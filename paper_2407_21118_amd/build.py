@@ -36,7 +36,7 @@ def sources():
     units = [(f, VGPR_FORM, "") for f in vgpr]
     units += [(f, VGPR_FORM + FLAT, "_flat") for f in ("score16_shared_forms.hip", "score16_forms.hip")]
     units += [("attend16_forms.hip", VGPR_FORM, ""), ("attend16_forms.hip", VGPR_FORM + FLAT, "_flat"), ("attend16_forms.hip", VGPR_FORM + ["-DPALU_ATTEND_SHARED=1"], "_shared")]
-    units += [("attend16_mixed_forms.hip", VGPR_FORM, ""), ("attend16_mixed_forms.hip", VGPR_FORM + FLAT, "_flat")]
+    units += [("attend16_mixed_forms.hip", VGPR_FORM, "")]
     units += [("encode_gemm.hip", [], "")]
     return [(os.path.join(CSRC, f), extra, os.path.splitext(f)[0] + suffix + ".o") for f, extra, suffix in units]
 

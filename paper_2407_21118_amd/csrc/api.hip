@@ -1535,7 +1535,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       // It is the faster form (attend16.hip) with two exceptions, see pays_* below; with stage events the stages have to be launches.
       bool attend = use16 && !use8 && (shared16 || m.qpk == 1) && m.qpk <= kShared16Rows && !v_i4 && !stage_events && g_opt_value_split == 0 &&
                     plan.total_units <= kMaxAttendUnits && plan.max_slices == 1 && w.lpad <= (1 << 24) &&
-                    (plan.n_cls == 1 ? rank_class_16(plan.cls_id[0] / 3) : mixed && use_one_round);
+                    (plan.n_cls == 1 ? rank_class_16(plan.cls_id[0] / 3) : mixed && use_one_round && !mix_flat);
       static thread_local AttendArgs t;
       int cols = PALU_MAX_RANK, rows = 0;                        // fewest value columns and most query rows of a unit
       for (int i = 0; i < plan.total_units && attend; ++i) {
@@ -1548,7 +1548,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         rows = std::max(rows, x.nh * m.qpk);
       }
       if (attend) {
-        const bool flat = plan.n_cls == 1 ? flat16(plan.total_units) : mix_flat;
+        const bool flat = plan.n_cls == 1 && flat16(plan.total_units);
         dim3 grid(1);
         int n_wg = 0, run = 0;                                   // most workgroups of a unit (and sequence); longest run
         if (plan.n_cls == 1) {
@@ -1558,7 +1558,6 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         } else {
           // Workgroups go, one at a time, to the unit whose workgroups would run longest, by the cost of its keys (above) and its
           // values (256 columns: 16 us per 1000 tokens of one workgroup, while others multiply)
-          const long long seqs = mix_seqs;
           int n[kMaxAttendUnits];
           long long total = 0;
           auto us = [&](int i) {
@@ -1568,7 +1567,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           for (;;) {
             int worst = 0;
             for (int i = 1; i < plan.total_units; ++i) if (us(i) > us(worst)) worst = i;
-            if (n[worst] >= run_tiles || (total + 1) * seqs > device_cu_count()) break;
+            if (n[worst] >= run_tiles || (total + 1) * batch > device_cu_count()) break;
             ++n[worst];
             ++total;
           }
@@ -1578,7 +1577,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
             t.mix.run[i] = (int)(run_tiles / n[i]);
             t.mix.run_more[i] = (int)(run_tiles % n[i]);
             t.mix.nk[i] = (uint8_t)(plan.cls_id[plan.unit_cls[i]] / 3 + 1);
-            first += n[i] * (int)seqs;
+            first += n[i] * batch;
             n_wg = std::max(n_wg, n[i]);
             run = std::max(run, (int)((run_tiles + n[i] - 1) / n[i]));
           }
@@ -1615,7 +1614,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           t.n_split = n_wg;
           t.o_stride = w.o_stride;
           t.units.n_units = plan.total_units;
-          const AttendFn fn = plan.n_cls > 1 ? (flat ? attend16_mixed_fn<true>(act) : attend16_mixed_fn<false>(act))
+          const AttendFn fn = plan.n_cls > 1 ? attend16_mixed_fn(act)
                             : shared16 ? attend16q_fn<false>(act, rc, m.qpk)
                             : (flat ? attend16_fn<true>(act, rc, lg) : attend16_fn<false>(act, rc, lg));
           const size_t lds = (size_t)attend_lds_bytes(plan.n_cls > 1 ? 256 : (32 * (rc + 1)) << lg, m.qpk);

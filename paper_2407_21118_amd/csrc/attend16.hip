@@ -362,30 +362,31 @@ __global__ __launch_bounds__(256) void attend16_kernel(AttendArgs a) {
 #include "score16_body.inc"
 }
 
-// The same body for a launch over units of several key ranks (see score16_mixed_kernel): every unit has its own number of
-// workgroups, chosen by the host so that all end at about the same time.  grid (sum over units of workgroups, and sequences).
-template <typename T, int NK, bool FLAT>
+// The same body for a launch over units of several key ranks (see score16_mixed_kernel), runs inside one sequence: every unit has its own number of
+// workgroups, chosen by the host so that all end at about the same time.  grid (sum over units of workgroups and sequences).
+// Ranks 64 .. 256 by group, 32 heads, us a step, two launches -> this: 1 x 16384 tokens 50.7 -> 46.1, 2 x 5000 37.6 -> 34.8.  (Runs through all sequences, whose
+// weights stay in registers across the values, spill 63 of them in this kernel: 4 x 16384 156.5 -> 168, 8 of 2000 .. 4000 66.8 -> 84.)
+template <typename T, int NK>
 __device__ __forceinline__ void attend16_body(const AttendArgs& a, const int wg, const int n_wg, const int unit, const int seq, const int run, const int run_more) {
   constexpr int G = 1, NQ = 1, QB = 0;
-  constexpr bool kValues = true;
+  constexpr bool FLAT = false, kValues = true;
 #include "score16_body.inc"
 }
-template <typename T, bool FLAT>
+template <typename T>
 __global__ __launch_bounds__(256) void attend16_mixed_kernel(AttendArgs a) {
   int unit = 0;
   for (int i = 1; i < a.units.n_units; ++i)
     if ((int)blockIdx.x >= a.mix.first[i]) unit = i;
-  const int local = (int)blockIdx.x - a.mix.first[unit], all = a.mix.first[unit + 1] - a.mix.first[unit];
-  const int n_wg = FLAT ? all : all / a.batch, seq = FLAT ? 0 : local / n_wg, wg = local - seq * n_wg;
-  const int run = a.mix.run[unit], run_more = a.mix.run_more[unit];
+  const int local = (int)blockIdx.x - a.mix.first[unit], n_wg = (a.mix.first[unit + 1] - a.mix.first[unit]) / a.batch;
+  const int seq = local / n_wg, wg = local - seq * n_wg, run = a.mix.run[unit], run_more = a.mix.run_more[unit];
   switch (a.mix.nk[unit]) {
-    case 2: attend16_body<T, 2, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
-    case 3: attend16_body<T, 3, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
-    case 4: attend16_body<T, 4, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
-    case 5: attend16_body<T, 5, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
-    case 6: attend16_body<T, 6, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
-    case 7: attend16_body<T, 7, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
-    default: attend16_body<T, 8, FLAT>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 2: attend16_body<T, 2>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 3: attend16_body<T, 3>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 4: attend16_body<T, 4>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 5: attend16_body<T, 5>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 6: attend16_body<T, 6>(a, wg, n_wg, unit, seq, run, run_more); break;
+    case 7: attend16_body<T, 7>(a, wg, n_wg, unit, seq, run, run_more); break;
+    default: attend16_body<T, 8>(a, wg, n_wg, unit, seq, run, run_more); break;
   }
 }
 #undef SCORE16_VALUES

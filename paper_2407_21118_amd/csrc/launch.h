@@ -30,7 +30,7 @@ template <bool FLAT> ScoreFn score16q4_fn(int rc, int nq, int lg);
 using AttendFn = void (*)(AttendArgs);
 template <bool FLAT> AttendFn attend16_fn(int act, int rc, int lg);
 template <bool FLAT> AttendFn attend16q_fn(int act, int rc, int nq);
-template <bool FLAT> AttendFn attend16_mixed_fn(int act);
+AttendFn attend16_mixed_fn(int act);
 // option score_fp8
 ScoreFn score8_fn(int rc, int lg);
 struct Fold8Args {
