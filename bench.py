@@ -279,13 +279,13 @@ def main() -> int:
     if transposed:                                             # the projection weights column by column: made once, like the decomposition
         Akt, Avt = case.Ak.t().contiguous(), case.Av.t().contiguous()
 
-    def step(i: int, events=None, decode_events=None):
+    def step(i: int, events=None):
         s = i % n_sets
-        if transposed and events is None and decode_events is None:
+        if transposed and events is None:
             P.palu_decode_step_t(desc, batch, seq, seq, case.x_new, Akt, Avt, dst_row, case.q, case.q_pos,
                                  case.Hk[s], case.Hv[s], case.Bk, case.Bv, table, seq, out=out, workspace=ws)
             return
-        if fused and events is None and decode_events is None:
+        if fused and events is None:
             P.palu_decode_step(desc, batch, seq, seq, case.x_new, case.Ak, case.Av, dst_row, case.q, case.q_pos,
                                case.Hk[s], case.Hv[s], case.Bk, case.Bv, table, seq, out=out, workspace=ws,
                                encode_workspace=ws_e)
@@ -307,12 +307,8 @@ def main() -> int:
             codes, sc, zp = qv[s]
             P.palu_quant_latent(desc, 1, new_v, layer.R_v, batch, codes, sc, zp, dst_row)
             hv, vq = codes, dict(hv_scale=sc, hv_zero=zp)
-        if decode_events:
-            decode_events[0].record()
         P.palu_attn_decode(desc, batch, seq, seq, case.q, case.q_pos, hk, hv, case.Bk, case.Bv, table, seq,
                            out=out, workspace=ws, stage_events=events, **kq, **vq)
-        if decode_events:
-            decode_events[1].record()
 
     # ---- timed region ------------------------------------------------------
     for i in range(args.warmup):
@@ -367,19 +363,27 @@ def main() -> int:
     stage_ms = np.array([[row[k].elapsed_time(row[k + 1]) for k in range(P.PALU_DECODE_STAGES)] for row in evs])
     names = ["fold", "score", "value", "combine"]
     bracket_us = {n: float(np.mean(stage_ms[:, k]) * 1e3) for k, n in enumerate(names)}
-    # An event between two kernels costs marker time that the kernels do not have without it.  Measure it
-    # live: the same decode calls with one event pair around the whole call hold one marker gap, the staged
-    # ones four, so (sum of stage brackets - whole-call bracket) / 3 is the gap of one interior event.
-    dec = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n_prof)]
+    # An event between two kernels costs marker time that the kernels do not have without it.  Measure it live, on launches of next to
+    # no work: with an event after each of the first three of four, and with none in between.  (Not on the call itself: without
+    # hooks it may run its scores and values as one launch.)
+    marks = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
+    dec = {True: [], False: []}
     for i in range(n_prof):
-        step(args.warmup + i, None, dec[i])
+        for marked, pairs in dec.items():
+            pairs.append((torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)))
+            pairs[-1][0].record()
+            for k in range(P.PALU_DECODE_STAGES):
+                out.zero_()
+                if marked and k < P.PALU_DECODE_STAGES - 1:
+                    marks[k].record()
+            pairs[-1][1].record()
     torch.cuda.synchronize()
-    whole_us = float(np.mean([a.elapsed_time(b) for a, b in dec]) * 1e3)
-    gap_us = max(0.0, (sum(bracket_us.values()) - whole_us) / (P.PALU_DECODE_STAGES - 1))
+    marked_us, plain_us = (float(np.median([a.elapsed_time(b) for a, b in dec[m]]) * 1e3) for m in (True, False))
+    gap_us = max(0.0, (marked_us - plain_us) / (P.PALU_DECODE_STAGES - 1))
     gap_us = min(gap_us, min(bracket_us.values()))         # no stage is shorter than nothing (a near-empty first stage)
     stage_us = {n: bracket_us[n] - gap_us for n in names}
     stage_us_med = {n: float(np.median(stage_ms[:, k]) * 1e3) - gap_us for k, n in enumerate(names)}
-    log(f"[bench] stage brackets us: {bracket_us}; whole decode call {whole_us:.2f} us; marker gap {gap_us:.2f} us")
+    log(f"[bench] stage brackets us: {bracket_us}; marker gap {gap_us:.2f} us")
     log(f"[bench] stage us (bracket - gap): {stage_us}")
 
     score_tflops = work["score_flops"] / (stage_us["score"] * 1e-6) / 1e12

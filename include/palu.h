@@ -432,8 +432,11 @@ int palu_attn_decode_multi(const palu_layer_desc* desc, int32_t batch, int32_t n
  * PALU_DECODE_STAGES + 1 hipEvent_t handles created by the caller (each passed
  * as void*): event i is recorded on `stream` before stage i is enqueued, the
  * last one after the final stage.  NULL disables the hooks (then identical to
- * palu_attn_decode).  Recording events between the stages inserts queue
- * barriers, so a step timed this way is slower than an unhooked one.
+ * palu_attn_decode).  With hooks every stage is launched by itself, where
+ * palu_attn_decode may take the scores and the values in one launch (the same
+ * arithmetic over other splits of the sequence: results agree to the rounding of
+ * the split sums), and recording events between the stages inserts queue barriers,
+ * so a step timed this way is slower than an unhooked one.
  */
 enum { PALU_DECODE_STAGES = 4 };
 int palu_attn_decode_staged(const palu_layer_desc* desc, int32_t batch, int32_t seq_len, int32_t max_seq,

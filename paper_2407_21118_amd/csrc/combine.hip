@@ -47,6 +47,9 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   __shared__ __attribute__((aligned(16))) float olat[PALU_MAX_RANK];
   __shared__ __attribute__((aligned(16))) float part[1024];              // phase 2: [4 split groups][64 k-quads][4]; phase 3: [8 k parts][32 column quads][4]
   __shared__ float red[4];
+  asm volatile("" :: "s"(a.o_part), "s"(a.ml_part), "s"(a.Bv), "s"(a.seq_lens), "s"(a.slots), "s"(a.n_split), "s"(a.split_tokens), "s"(a.run),
+               "s"(a.run_more), "s"(a.seq_len), "s"(a.o_stride), "s"(a.meta.n_heads), "s"(a.meta.qpk));      // all in registers here: one round trip (on
+  // demand, branch by branch: 0.4 .. 0.7 us a step more)
   const int tid = threadIdx.x;
   const Meta& m = a.meta;
   const int h = blockIdx.x >> 2, quarter = blockIdx.x & 3, b = blockIdx.y;
@@ -167,6 +170,8 @@ __global__ __launch_bounds__(64 * WAVES) void combine_rows_kernel(CombineArgs a,
   extern __shared__ __attribute__((aligned(16))) float comb_lds[];
   __shared__ float total[NB];
   constexpr int W = WAVES / NB, KP = 2 * WAVES, kThreads = 64 * WAVES;      // wavefronts per row; k parts of the product
+  asm volatile("" :: "s"(a.o_part), "s"(a.ml_part), "s"(a.Bv), "s"(a.seq_lens), "s"(a.slots), "s"(a.n_split), "s"(a.split_tokens), "s"(a.run),
+               "s"(a.run_more), "s"(a.seq_len), "s"(a.o_stride), "s"(a.meta.n_heads), "s"(a.meta.qpk));      // all in registers here: one round trip
   const Meta& m = a.meta;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int rows = a.batch * m.qpk, row0 = blockIdx.y * NB;
