@@ -173,6 +173,8 @@ __global__ __launch_bounds__(256) void encode_finish_kernel(EncodeArgs a) {
   const int tid = threadIdx.x;
   const int c = blockIdx.x * 256 + (tid & 63) * 4, t = blockIdx.y, sub = tid >> 6;
   const int per = (a.k_splits + 3) / 4;
+  asm volatile("" :: "s"(sd.partial), "s"(sd.latent), "s"(sd.row_stride), "s"(sd.R), "s"(a.dst_row), "s"(a.n_tok), "s"(a.k_splits));      // one round trip
+  const long long row = a.dst_row ? a.dst_row[t] : t;      // ... and this beside the sums, not behind them
   float4v s = {0.f, 0.f, 0.f, 0.f};
   if (c < sd.R) {
     const float* p = sd.partial + (size_t)t * sd.R + c;
@@ -186,7 +188,6 @@ __global__ __launch_bounds__(256) void encode_finish_kernel(EncodeArgs a) {
   if (tid < 128 && (int)blockIdx.x * 256 + cc < sd.R) {
     const float s0 = (part[0][cc] + part[1][cc]) + (part[2][cc] + part[3][cc]);
     const float s1 = (part[0][cc + 1] + part[1][cc + 1]) + (part[2][cc + 1] + part[3][cc + 1]);
-    const long long row = a.dst_row ? a.dst_row[t] : t;
     uint32_t* dst = reinterpret_cast<uint32_t*>(sd.latent + row * sd.row_stride + blockIdx.x * 256 + cc);
     *dst = (uint32_t)T::from_float(s0) | ((uint32_t)T::from_float(s1) << 16);
   }
@@ -241,6 +242,9 @@ __device__ __forceinline__ void encode_t_body(const EncodeTArgs& a, int wg_id, E
   const bool cols_ok = c0 < R;
   const uint16_t* At = a.At[side] + (size_t)min(c0, R - kTCols) * a.d;
   for (int tb = 0; tb < a.n_tok; tb += TOK) {
+    int dst[TOK];                                                // where the rows go, known before the sums are
+#pragma unroll
+    for (int t = 0; t < TOK; ++t) dst[t] = a.dst_row ? a.dst_row[min(tb + t, a.n_tok - 1)] : tb + t;
     float acc[kTCols][TOK];
 #pragma unroll
     for (int c = 0; c < kTCols; ++c)
@@ -303,8 +307,7 @@ __device__ __forceinline__ void encode_t_body(const EncodeTArgs& a, int wg_id, E
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
         if (lane == 0 && cols_ok && tb + t < a.n_tok) {
-          const long long row = a.dst_row ? a.dst_row[tb + t] : tb + t;
-          a.latent[side][row * a.row_stride[side] + c0 + c] = T::from_float(v);
+          a.latent[side][(long long)dst[t] * a.row_stride[side] + c0 + c] = T::from_float(v);
         }
       }
   }
@@ -357,10 +360,20 @@ struct QuantArgs {
 // One wavefront per (token, 128-channel block); lane l owns channels 2l, 2l+1.
 template <typename T>
 __global__ __launch_bounds__(256) void quant_kernel(QuantArgs a) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  asm volatile("" :: "s"(a.latent), "s"(a.codes), "s"(a.scale), "s"(a.zero), "s"(a.dst_row), "s"(a.row_stride), "s"(a.n_tok), "s"(a.R), "s"(a.n_blocks),
+               "s"(a.bits));                      // one round trip
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const long long item = (long long)blockIdx.x * 4 + wave;
   if (item >= (long long)a.n_tok * a.n_blocks) return;
-  const int t = (int)(item / a.n_blocks), blk = (int)(item - (long long)t * a.n_blocks);
+  int t, blk;                                     // items beyond 32 bits take the long division
+  if ((long long)a.n_tok * a.n_blocks < (1LL << 31)) {
+    t = (int)((unsigned)item / (unsigned)a.n_blocks);
+    blk = (int)item - t * a.n_blocks;
+  } else {
+    t = (int)(item / a.n_blocks);
+    blk = (int)(item - (long long)t * a.n_blocks);
+  }
+  const size_t orow = a.dst_row ? (size_t)a.dst_row[t] : (size_t)t;      // beside the latents, not behind their block's parameters
   const uint32_t raw = *reinterpret_cast<const uint32_t*>(a.latent + (size_t)t * a.row_stride + blk * 128 + lane * 2);
   const float x0 = T::to_float((uint16_t)(raw & 0xffffu));
   const float x1 = T::to_float((uint16_t)(raw >> 16));
@@ -371,7 +384,6 @@ __global__ __launch_bounds__(256) void quant_kernel(QuantArgs a) {
     mx = fmaxf(mx, __shfl_xor(mx, off, 64));
   }
   const QuantParams qp = quant_params(mn, mx, (float)((1 << a.bits) - 1));
-  const size_t orow = a.dst_row ? (size_t)a.dst_row[t] : (size_t)t;
   const uint32_t c0 = quant_code(x0, qp), c1 = quant_code(x1, qp);
   if (a.bits == 4) {
     a.codes[orow * (a.R / 2) + blk * 64 + lane] = (uint8_t)(c0 | (c1 << 4));
