@@ -329,7 +329,7 @@ __device__ __forceinline__ void value_block(const AttendArgs& a, const ValueSegm
 // pipes of some work while others read values.
 // grid as score16_kernel's, 256 threads, attend_lds_bytes of LDS.
 #undef SCORE16_DRAIN
-#define SCORE16_DRAIN values_of_segment()                        // value_of_run waits for them
+#define SCORE16_DRAIN values_of_segment()                        // value_block waits for them
 #define SCORE16_VALUES                                                                                                              \
   constexpr int HS = attend_hs(NQ), kHalves = kAheadTiles * kDmaIssues / 8;                                                         \
   static_assert(attend_partials_lds(HS, 2) <= (size_t)score16_lds_bytes(kWidth), "the partial results live in the score phase's ring"); \
