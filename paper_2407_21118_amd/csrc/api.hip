@@ -459,8 +459,8 @@ inline bool rank_class_16(int rc) { return rc >= 1 && rc <= 7; }
 // rows; the kernel is compiled for 2, 4 and 8 rows
 inline bool shared16_ok(int rc) { return rc >= 1 && rc <= 7; }
 constexpr int kShared16Rows = 8;
-// Longest run of tiles whose values follow in the score launch: 512 tokens to a wavefront, the value kernel's longest split (one
-// running maximum per split; longer ones would make more of its 16-bit probabilities subnormal).
+// Longest run of tiles whose values follow in the score launch: 512 tokens to a wavefront, the longest split of the value kernel's units of
+// up to four heads (one running maximum per split; longer ones would make more of its 16-bit probabilities subnormal).
 constexpr int kMaxAttendTiles = 64;
 constexpr int score16q4_lds_bytes(int width) { return 3 * score_tile_bytes(width) + 3 * kRopeTileBytes; }
 
@@ -1536,6 +1536,12 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       bool attend = use16 && !use8 && (shared16 || m.qpk == 1) && m.qpk <= kShared16Rows && !v_i4 && !stage_events && g_opt_value_split == 0 &&
                     plan.total_units <= kMaxAttendUnits && plan.max_slices == 1 && w.lpad <= (1 << 24) &&
                     (plan.n_cls == 1 ? rank_class_16(plan.cls_id[0] / 3) : mixed && use_one_round && !mix_flat);
+      // The longest run whose values are as precise as the value kernel's: a probability is a 16-bit float against the running maximum of its
+      // wavefront's share, a quarter of the run, and the longer the share, the more of them are subnormal.  Shares longer than the value
+      // kernel's splits (one head of key rank 256 and value rank 64 per group: a value unit is four score units) measured 1.03 .. 1.10 of its
+      // error against 64 bits at N(0, 1) queries, 1.2 .. 1.8 at four times these; as long ones are level, shorter ones better.
+      // (With option score_chunks the caller has chosen the runs.)
+      const int share_tiles = g_opt_score_chunks > 0 ? kMaxAttendTiles : std::min(4 * split_tokens / kTile, kMaxAttendTiles);
       static thread_local AttendArgs t;
       int cols = PALU_MAX_RANK, rows = 0;                        // fewest value columns and most query rows of a unit
       for (int i = 0; i < plan.total_units && attend; ++i) {
@@ -1563,8 +1569,9 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           auto us = [&](int i) {
             return (double)((run_tiles + n[i] - 1) / n[i]) * (weight(plan.cls_id[plan.unit_cls[i]] / 3 + 1) + 16.0 * t.val[i].rv / 256.0);
           };
-          for (int i = 0; i < plan.total_units; ++i) total += n[i] = 1;
-          for (;;) {
+          for (int i = 0; i < plan.total_units; ++i) total += n[i] = ceil_div((int)run_tiles, std::min((int)run_tiles, share_tiles));
+          attend = total * batch <= device_cu_count();
+          while (attend) {
             int worst = 0;
             for (int i = 1; i < plan.total_units; ++i) if (us(i) > us(worst)) worst = i;
             if (n[worst] >= run_tiles || (total + 1) * batch > device_cu_count()) break;
@@ -1597,7 +1604,9 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         // where the second is not full (a launch of its own there) or the run is short: 8 queries over 2 x 8000 tokens, rank 128 (16 tiles) 59.3
         // -> 61.9, 1 x 4000, rank 256 (4 tiles) 44.0 -> 37.7; 5 over 1 x 16000 91.8 -> 75.7.
         const bool pays_rows = rows <= 16 || rows % 16 != 0 || run <= 8;
-        attend = pays_segment && pays_rows && (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
+        const int longest = flat ? std::min({run, tiles, kMaxAttendTiles}) : run;      // tiles whose values follow in one go
+        attend = attend && pays_segment && pays_rows && longest <= share_tiles &&
+                 (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap) &&
                  (!noted || (size_t)batch * m.n_heads * 8 <= (size_t)w.mfold_bstride * 2) && n_wg <= kMaxSplits;
         if (attend) {
           const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3;

@@ -46,8 +46,9 @@ def rel_err(got: np.ndarray, ref: np.ndarray):
     return float(whole), float(rows)
 
 
-def run_hip(case, k_i4=False, v_i4=False, quant=None, rope_len=None, bits=4):
-    """HIP path on the case; `quant` = dict(k=(packed, scale, zero), v=(...)) of numpy arrays."""
+def run_hip(case, k_i4=False, v_i4=False, quant=None, rope_len=None, bits=4, staged=False):
+    """HIP path on the case; `quant` = dict(k=(packed, scale, zero), v=(...)) of numpy arrays; staged: with
+    events between the stages, which makes every stage a launch of its own."""
     layer = case.layer
     desc = make_desc(layer, case.dtype, k_i4, v_i4, bits)
     B, L = case.batch, case.seq
@@ -78,6 +79,10 @@ def run_hip(case, k_i4=False, v_i4=False, quant=None, rope_len=None, bits=4):
         kw["seq_lens"] = torch.from_numpy(np.asarray(case.seq_lens, np.int32)).cuda()
     n_pos = n_pos if rope_len is None else rope_len
     table = P.palu_rope_table_init(layer.rope_theta, layer.d_head, n_pos)
+    if staged:
+        kw["stage_events"] = [torch.cuda.Event(enable_timing=True) for _ in range(P.PALU_DECODE_STAGES + 1)]
+        for e in kw["stage_events"]:
+            e.record()              # creates the HIP event handle
     out = P.palu_attn_decode(desc, B, L, L, q, q_pos, hk, hv, Bk, Bv, table, n_pos, **kw)
     torch.cuda.synchronize()
     return out.cpu().numpy()
