@@ -134,3 +134,19 @@ def test_as_precise_as_scores_and_values_apart(layer, dtype, seq, scale):
     one, apart = (np.sqrt(np.mean((run_hip(case, staged=s).astype(np.float64) - ref) ** 2)) for s in (False, True))
     say(f"[attend] {layer.R_k} / {layer.R_v} {dtype} {seq} q x{scale:g}: rms error {one:.3e}, stages apart {apart:.3e}")
     assert one <= 1.1 * apart
+
+
+def test_units_of_fewer_heads_keep_the_exact_maximum():
+    """Two heads to a unit, shares and splits of 64 tokens both: the value kernel, four heads to a unit, lets them all catch up with
+    their running maxima where one of them rises, and a unit of two must not round more for catching up less often (errors
+    of six draws together: its exact maximum can only be closer)."""
+    from gpu_util import run_hip, run_oracle, say
+    sums = np.zeros(2)
+    for seed in range(6):
+        case = synth.make_case_orthonormal(_layer(8, 1, 96, 64), 1, 16384, seed=seed)
+        case.q = synth.round_to(case.q * 4.0, "f16")
+        ref = run_oracle(case)
+        sums += [np.sum((run_hip(case, staged=s).astype(np.float64) - ref) ** 2) for s in (False, True)]
+    one, apart = np.sqrt(sums)
+    say(f"[attend] two heads to a unit: error {one:.3e}, stages apart {apart:.3e}")
+    assert one <= apart
