@@ -7,6 +7,7 @@
 #include "score.hip"
 #include "score16.hip"
 #include "attend16.hip"
+#include "deal.h"
 #include "score8.hip"
 #include "combine.hip"
 #include "qk.hip"
@@ -1562,31 +1563,25 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           n_wg = a.n_wg;
           run = a.run + (a.run_more ? 1 : 0);
         } else {
-          // Workgroups go, one at a time, to the unit whose workgroups would run longest, by the cost of its keys (above) and its
-          // values (256 columns: 16 us per 1000 tokens of one workgroup, while others multiply)
-          int n[kMaxAttendUnits];
-          long long total = 0;
-          auto us = [&](int i) {
-            return (double)((run_tiles + n[i] - 1) / n[i]) * (weight(plan.cls_id[plan.unit_cls[i]] / 3 + 1) + 16.0 * t.val[i].rv / 256.0);
-          };
-          for (int i = 0; i < plan.total_units; ++i) total += n[i] = ceil_div((int)run_tiles, std::min((int)run_tiles, share_tiles));
-          attend = total * batch <= device_cu_count();
-          while (attend) {
-            int worst = 0;
-            for (int i = 1; i < plan.total_units; ++i) if (us(i) > us(worst)) worst = i;
-            if (n[worst] >= run_tiles || (total + 1) * batch > device_cu_count()) break;
-            ++n[worst];
-            ++total;
+          // Workgroups go to the unit whose workgroups would run longest, by the cost of its keys (above) and its values (256 columns: 16 us
+          // per 1000 tokens of one workgroup, while others multiply)
+          static_assert(kMaxAttendUnits <= kMaxDealUnits, "deal_workgroups");
+          int n[kMaxAttendUnits], least[kMaxAttendUnits];
+          double cost[kMaxAttendUnits];
+          for (int i = 0; i < plan.total_units; ++i) {
+            least[i] = ceil_div(tiles, std::min(tiles, share_tiles));
+            cost[i] = weight(plan.cls_id[plan.unit_cls[i]] / 3 + 1) + 16.0 * t.val[i].rv / 256.0;
           }
+          attend = deal_workgroups(plan.total_units, tiles, device_cu_count() / batch, cost, least, n) > 0;
           int first = 0;
           for (int i = 0; i < plan.total_units; ++i) {
             t.mix.first[i] = first;
-            t.mix.run[i] = (int)(run_tiles / n[i]);
-            t.mix.run_more[i] = (int)(run_tiles % n[i]);
+            t.mix.run[i] = tiles / n[i];
+            t.mix.run_more[i] = tiles % n[i];
             t.mix.nk[i] = (uint8_t)(plan.cls_id[plan.unit_cls[i]] / 3 + 1);
             first += n[i] * batch;
             n_wg = std::max(n_wg, n[i]);
-            run = std::max(run, (int)((run_tiles + n[i] - 1) / n[i]));
+            run = std::max(run, ceil_div(tiles, n[i]));
           }
           t.mix.first[plan.total_units] = first;
           grid = dim3((unsigned)first);
