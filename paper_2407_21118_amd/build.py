@@ -35,7 +35,8 @@ def sources():
     vgpr = ["score16_shared_forms.hip", "score_forms.hip", "score_forms_lowbit.hip", "score16_forms.hip", "pv.hip", "api.hip"]
     units = [(f, VGPR_FORM, "") for f in vgpr]
     units += [(f, VGPR_FORM + FLAT, "_flat") for f in ("score16_shared_forms.hip", "score16_forms.hip")]
-    units += [("attend16_forms.hip", VGPR_FORM, ""), ("attend16_forms.hip", VGPR_FORM + FLAT, "_flat"), ("attend16_forms.hip", VGPR_FORM + ["-DPALU_ATTEND_SHARED=1"], "_shared")]
+    units += [("attend16_forms.hip", VGPR_FORM, ""), ("attend16_forms.hip", VGPR_FORM + FLAT, "_flat"), ("attend16_forms.hip", VGPR_FORM + ["-DPALU_ATTEND_SHARED=1"], "_shared"),
+              ("attend16_forms.hip", VGPR_FORM + ["-DPALU_ATTEND_SHARED=2"], "_shared_few")]
     units += [("attend16_mixed_forms.hip", VGPR_FORM, "")]
     units += [("encode_gemm.hip", [], "")]
     return [(os.path.join(CSRC, f), extra, os.path.splitext(f)[0] + suffix + ".o") for f, extra, suffix in units]

@@ -1604,7 +1604,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
                  (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap) &&
                  (!noted || (size_t)batch * m.n_heads * 8 <= (size_t)w.mfold_bstride * 2) && n_wg <= kMaxSplits;
         if (attend) {
-          const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3;
+          const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3, hs = attend_hs(m.qpk, rows);
           a.sk_row0 = 0;
           a.sk_rows = m.qpk;
           static_cast<ScoreCommon&>(t) = a;
@@ -1619,9 +1619,9 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
           t.o_stride = w.o_stride;
           t.units.n_units = plan.total_units;
           const AttendFn fn = plan.n_cls > 1 ? attend16_mixed_fn(act)
-                            : shared16 ? attend16q_fn<false>(act, rc, m.qpk)
+                            : shared16 ? (hs == 2 ? attend16q_fn<true>(act, rc, m.qpk) : attend16q_fn<false>(act, rc, m.qpk))
                             : (flat ? attend16_fn<true>(act, rc, lg) : attend16_fn<false>(act, rc, lg));
-          const size_t lds = (size_t)attend_lds_bytes(plan.n_cls > 1 ? 256 : (32 * (rc + 1)) << lg, m.qpk);
+          const size_t lds = (size_t)attend_lds_bytes(plan.n_cls > 1 ? 256 : (32 * (rc + 1)) << lg, hs);
           if (!fn) return PALU_ERR_UNSUPPORTED;
           if ((st = allow_lds(fn, lds)) != PALU_OK) return st;
           hipLaunchKernelGGL(fn, grid, dim3(256), lds, s, t);

@@ -35,8 +35,11 @@ constexpr int kAttLim = kAttMl + 4 * 16 * 2 * 4;                // row limits of
 constexpr int kAttRun = kAttLim + 32 * 4;                       // (max, sum) so far of up to 32 query rows, and the factors of what they had
 constexpr int kAttSc = kAttRun + 32 * 2 * 4 + 16 * 4;           // scores of two sets of every wavefront
 constexpr int attend_scratch_bytes(int hs) { return kAttSc + 4 * 2 * hs * 256; }
-constexpr int attend_hs(int nq) { return nq == 1 ? 2 : (nq == 2 ? 4 : 8); }      // at most 4 heads with a query each, else 4 nq query rows, 16 at a time
-constexpr int attend_lds_bytes(int width, int nq) { return score16_lds_bytes(width) + attend_scratch_bytes(attend_hs(nq)); }
+// Score slots per lane: 2 HS query rows at a time.  Units of one head, or two with two queries, have no more than 4 rows, as many as four heads with a query
+// each, and the slots decide what the softmax costs (eight for 4 rows: 11 us over 64 tiles): 4 queries over 64 tiles, one head of rank 64 to
+// a unit, 64 / 96 / 160 value columns 112 / 112 / 121 -> 98 / 99 / 109 us a step (two launches 101 / 104 / 117), rank 256 178 / 177 / 188 -> 169 / 168 / 178.
+constexpr int attend_hs(int nq, int rows) { return nq == 1 || rows <= 4 ? 2 : (nq == 2 ? 4 : 8); }
+constexpr int attend_lds_bytes(int width, int hs) { return score16_lds_bytes(width) + attend_scratch_bytes(hs); }
 constexpr size_t attend_partials_lds(int hs, int ng) { return (size_t)4 * 2 * hs * ng * 128 * 4; }
 
 // A segment (tiles of one sequence) and the unit whose values it is about
@@ -327,14 +330,14 @@ __device__ __forceinline__ void value_block(const AttendArgs& a, const ValueSegm
   __syncthreads();                                          // LDS is the next block's
 }
 
-// T, NK, G, NQ, FLAT: as in score16_kernel.  FLAT: a workgroup's run goes through the tiles of all sequences; the values of a segment follow
+// T, NK, G, NQ, FLAT: as in score16_kernel; HS: attend_hs.  FLAT: a workgroup's run goes through the tiles of all sequences; the values of a segment follow
 // its scores, up to a.seg_tiles tiles at a time.  Workgroups then are at different places of their segments at any time: the matrix
 // pipes of some work while others read values.
 // grid as score16_kernel's, 256 threads, attend_lds_bytes of LDS.
 #undef SCORE16_DRAIN
 #define SCORE16_DRAIN values_of_segment()                        // value_block waits for them
 #define SCORE16_VALUES                                                                                                              \
-  constexpr int HS = attend_hs(NQ), kHalves = kAheadTiles * kDmaIssues / 8;                                                         \
+  constexpr int kHalves = kAheadTiles * kDmaIssues / 8;                                                                             \
   static_assert(attend_partials_lds(HS, 2) <= (size_t)score16_lds_bytes(kWidth), "the partial results live in the score phase's ring"); \
   int sequence_before = -1;                                                                                                         \
   auto values_of_segment = [&]() __attribute__((always_inline)) {                                                                   \
@@ -357,7 +360,7 @@ __device__ __forceinline__ void value_block(const AttendArgs& a, const ValueSegm
         else value_block<T, HS, 1, kHalves>(a, v, r0, cb, lds, scratch, ring);                                                      \
       }                                                                                                                             \
   };
-template <typename T, int NK, int G, int NQ, bool FLAT>
+template <typename T, int NK, int G, int NQ, bool FLAT, int HS>
 __global__ __launch_bounds__(256) void attend16_kernel(AttendArgs a) {
   constexpr int QB = 0;
   constexpr bool kValues = true;
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(256) void attend16_kernel(AttendArgs a) {
 // weights stay in registers across the values, spill 63 of them in this kernel: 4 x 16384 156.5 -> 168, 8 of 2000 .. 4000 66.8 -> 84.)
 template <typename T, int NK>
 __device__ __forceinline__ void attend16_body(const AttendArgs& a, const int wg, const int n_wg, const int unit, const int seq, const int run, const int run_more) {
-  constexpr int G = 1, NQ = 1, QB = 0;
+  constexpr int G = 1, NQ = 1, QB = 0, HS = 2;
   constexpr bool FLAT = false, kValues = true;
 #include "score16_body.inc"
 }

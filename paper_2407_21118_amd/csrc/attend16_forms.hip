@@ -1,5 +1,5 @@
 // Instantiations of the attention kernel (attend16.hip): one query per head, runs in one sequence or (PALU_SCORE_FLAT) through all; or (PALU_ATTEND_SHARED) several
-// queries per key/value head.
+// queries per key/value head (2: units of at most four query rows).
 #include "launch.h"
 #include "attend16.hip"
 
@@ -20,9 +20,9 @@ constexpr bool kFlat = PALU_SCORE_FLAT != 0;
 namespace {
 template <typename T, int NK>
 AttendFn attend16_fn_g(int lg) {
-  if constexpr (NK <= 2) { if (lg == 2) return attend16_kernel<T, NK, 4, 1, kFlat>; }
-  if constexpr (NK <= 4) { if (lg == 1) return attend16_kernel<T, NK, 2, 1, kFlat>; }
-  return lg == 0 ? attend16_kernel<T, NK, 1, 1, kFlat> : nullptr;
+  if constexpr (NK <= 2) { if (lg == 2) return attend16_kernel<T, NK, 4, 1, kFlat, 2>; }
+  if constexpr (NK <= 4) { if (lg == 1) return attend16_kernel<T, NK, 2, 1, kFlat, 2>; }
+  return lg == 0 ? attend16_kernel<T, NK, 1, 1, kFlat, 2> : nullptr;
 }
 template <typename T>
 AttendFn attend16_fn_t(int rc, int lg) {
@@ -43,11 +43,13 @@ template <>
 AttendFn attend16_fn<kFlat>(int act, int rc, int lg) { return act == PALU_F16 ? attend16_fn_t<F16>(rc, lg) : attend16_fn_t<BF16>(rc, lg); }
 #else
 namespace {
+constexpr bool kFew = PALU_ATTEND_SHARED == 2;
 template <typename T, int NK>
 AttendFn attend16q_fn_n(int nq) {
-  if (nq <= 2) return attend16_kernel<T, NK, 1, 2, kFlat>;
-  if (nq <= 4) return attend16_kernel<T, NK, 1, 4, kFlat>;
-  return attend16_kernel<T, NK, 1, 8, kFlat>;
+  if (nq <= 2) return attend16_kernel<T, NK, 1, 2, kFlat, kFew ? 2 : 4>;
+  if (nq <= 4) return attend16_kernel<T, NK, 1, 4, kFlat, kFew ? 2 : 8>;
+  if constexpr (!kFew) return attend16_kernel<T, NK, 1, 8, kFlat, 8>;
+  return nullptr;
 }
 template <typename T>
 AttendFn attend16q_fn_t(int rc, int nq) {
@@ -65,7 +67,7 @@ AttendFn attend16q_fn_t(int rc, int nq) {
 }  // namespace
 
 template <>
-AttendFn attend16q_fn<kFlat>(int act, int rc, int nq) { return act == PALU_F16 ? attend16q_fn_t<F16>(rc, nq) : attend16q_fn_t<BF16>(rc, nq); }
+AttendFn attend16q_fn<kFew>(int act, int rc, int nq) { return act == PALU_F16 ? attend16q_fn_t<F16>(rc, nq) : attend16q_fn_t<BF16>(rc, nq); }
 #endif
 
 }  // namespace palu

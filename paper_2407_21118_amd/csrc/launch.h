@@ -26,10 +26,10 @@ template <bool FLAT> ScoreFn score16q_fn(int act, int rc, int nq);
 // groups per workgroup (lg)
 template <bool FLAT> ScoreFn score16q4_fn(int rc, int nq, int lg);
 // score16_kernel's runs of tiles with the value contraction behind them, one launch for both (attend16.hip); nq: query rows per
-// key/value head (1, or up to 8)
+// key/value head (1, or up to 8); FEW: at most four rows to a unit
 using AttendFn = void (*)(AttendArgs);
 template <bool FLAT> AttendFn attend16_fn(int act, int rc, int lg);
-template <bool FLAT> AttendFn attend16q_fn(int act, int rc, int nq);
+template <bool FEW> AttendFn attend16q_fn(int act, int rc, int nq);
 AttendFn attend16_mixed_fn(int act);
 // option score_fp8
 ScoreFn score8_fn(int rc, int lg);

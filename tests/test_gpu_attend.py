@@ -23,6 +23,9 @@ CASES = [
     (4, 2, 96, 192, 1, "f16", [300, 40], 2), (6, 3, 192, 256, 1, "f16", [70], 1), (4, 4, 256, 256, 1, "f16", [511, 0, 96], 2),
     (4, 4, 256, 256, 4, "f16", [161, 33], 1), (4, 4, 128, 384, 2, "f16", [129], 1), (4, 4, 64, 128, 8, "f16", [200, 64], 2),
     (4, 2, 256, 160, 8, "bf16", [97], 1), (3, 3, 96, 96, 3, "f16", [333], 3), (4, 4, 160, 256, 5, "f16", [64, 0], 0),
+    # at most four query rows to a unit
+    (2, 1, 128, 96, 4, "f16", [300, 33], 1), (3, 1, 64, 64, 3, "bf16", [2047], 1), (2, 2, 256, 160, 2, "f16", [97, 0, 513], 2), (2, 1, 96, 128, 2, "f16", [161], 1),
+    (4, 2, 224, 256, 2, "bf16", [700], 3), (3, 1, 128, 128, 1, "f16", [640, 31], 1),
 ]
 
 
