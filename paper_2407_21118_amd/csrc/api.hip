@@ -1170,6 +1170,14 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
     for (int i = 0; i < pp.total_units && streamed; ++i)
       streamed = qp.units[i].h0 == pp.units[i].h0 && qp.units[i].nh == pp.units[i].nh && qp.units[i].wpad == 256 && pp.unit_cls[i] == pp.unit_cls[0] &&
                  (!k_i4 || pp.units[i].nh <= 4);
+    const int stream_upw = pp.total_units >= 4 ? 4 : (pp.total_units >= 2 ? 2 : 1);
+    const dim3 stream_grid((unsigned)ceil_div(pp.total_units, stream_upw), (unsigned)ceil_div(n_split, 4 / stream_upw), (unsigned)batch);
+    // Unquantized, a compute unit holds one of its workgroups (two of each of the two kernels): more than one round of them pays only for splits that
+    // outweigh another start, and enough of them.  Speed of one launch over two, 32 heads, rank 256 / 64: 25 x 400 tokens (0.98 rounds, 80 tokens a
+    // split) 1.16, 33 x 400 (1.03, 100) 0.93, 44 x 900 (1.03, 300) 0.91, 75 x 400 (1.17, 200) 0.89, 17 x 2500 (1.06, 312) 1.00, 21 x 2500 (1.15,
+    // 357) 1.09, 60 x 2500 (2.3, 500) 1.18; 128 / 128 the same way 1.20, 0.98, 0.99, 0.94, 1.10, 1.11, 1.29; 16 units of rank 128 / 128 33 x 900
+    // (1.03, 450, two splits to a sequence) 0.96; four queries to a head of rank 64 / 64 77 x 653 (1.2, 327, two) 0.76.
+    streamed = streamed && (k_i4 || (long long)stream_grid.x * stream_grid.y * stream_grid.z <= device_cu_count() || (n_split >= 5 && seq_len >= 310 * n_split));
     if (streamed) {
       static thread_local StreamArgs t;
       t.hv = hv;
@@ -1208,13 +1216,12 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         t.keys[i] = StreamKeys{qp.units[i].c0, qp.units[i].q_off, qp.units[i].qs_off, qp.units[i].ncols};
         max_nh = std::max(max_nh, (int)pp.units[i].nh);
       }
-      t.units_per_wg = pp.total_units >= 4 ? 4 : (pp.total_units >= 2 ? 2 : 1);
+      t.units_per_wg = stream_upw;
       t.lds_unit_stride = (int)align_up(stream_unit_lds(k_i4, max_nh), 16);
       const size_t lds = (size_t)t.lds_unit_stride * t.units_per_wg;
       const StreamFn fn = stream_fn(act, k_bits, pp.unit_cls[0]);
       if ((st = allow_dynamic_lds(fn, lds + kStaticLdsMax)) != PALU_OK) return st;
-      const dim3 grid((unsigned)ceil_div(pp.total_units, t.units_per_wg), (unsigned)ceil_div(n_split, 4 / t.units_per_wg), (unsigned)batch);
-      hipLaunchKernelGGL(fn, grid, dim3(256), lds, s, t);
+      hipLaunchKernelGGL(fn, stream_grid, dim3(256), lds, s, t);
       if ((st = launch_ok()) != PALU_OK) return st;
     }
     for (int cls = 0; cls < 2 && !streamed; ++cls) {              // 0: up to 16 heads per unit, 1: up to 32

@@ -4,6 +4,7 @@ bits, and measure the error the way the tolerance is stated."""
 
 from __future__ import annotations
 
+import ctypes
 import sys
 
 import numpy as np
@@ -46,9 +47,21 @@ def rel_err(got: np.ndarray, ref: np.ndarray):
     return float(whole), float(rows)
 
 
-def run_hip(case, k_i4=False, v_i4=False, quant=None, rope_len=None, bits=4, staged=False):
+def launches(call) -> int:
+    """Kernels that call() enqueues on the current stream: the nodes of a capture of it that is never run."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+        call()
+    n = ctypes.c_size_t()
+    status = P.load_library().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n))     # (of the runtime the library is linked to)
+    assert status == 0, status
+    return n.value
+
+
+def run_hip(case, k_i4=False, v_i4=False, quant=None, rope_len=None, bits=4, staged=False, n_launches=None):
     """HIP path on the case; `quant` = dict(k=(packed, scale, zero), v=(...)) of numpy arrays; staged: with
-    events between the stages, which makes every stage a launch of its own."""
+    events between the stages, which makes every stage a launch of its own; n_launches: list that
+    receives the number of kernels the call enqueues."""
     layer = case.layer
     desc = make_desc(layer, case.dtype, k_i4, v_i4, bits)
     B, L = case.batch, case.seq
@@ -85,6 +98,8 @@ def run_hip(case, k_i4=False, v_i4=False, quant=None, rope_len=None, bits=4, sta
             e.record()              # creates the HIP event handle
     out = P.palu_attn_decode(desc, B, L, L, q, q_pos, hk, hv, Bk, Bv, table, n_pos, **kw)
     torch.cuda.synchronize()
+    if n_launches is not None:
+        n_launches.append(launches(lambda: P.palu_attn_decode(desc, B, L, L, q, q_pos, hk, hv, Bk, Bv, table, n_pos, out=out, **kw)))
     return out.cpu().numpy()
 
 
