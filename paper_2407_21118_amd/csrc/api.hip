@@ -1564,11 +1564,12 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       if (attend) {
         const bool flat = plan.n_cls == 1 && flat16(plan.total_units);
         dim3 grid(1);
-        int n_wg = 0, run = 0;                                   // most workgroups of a unit (and sequence); longest run
+        int n_wg = 0, run = 0, whole_run = 0;                    // most workgroups of a unit (and sequence); longest run, and that without the tile some have more
         if (plan.n_cls == 1) {
           grid = grid16(plan.total_units, flat);
           n_wg = a.n_wg;
           run = a.run + (a.run_more ? 1 : 0);
+          whole_run = a.run;
         } else {
           // Workgroups go to the unit whose workgroups would run longest, by the cost of its keys (above) and its values (256 columns: 16 us
           // per 1000 tokens of one workgroup, while others multiply)
@@ -1589,6 +1590,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
             first += n[i] * batch;
             n_wg = std::max(n_wg, n[i]);
             run = std::max(run, ceil_div(tiles, n[i]));
+            whole_run = std::max(whole_run, tiles / n[i]);
           }
           t.mix.first[plan.total_units] = first;
           grid = dim3((unsigned)first);
@@ -1596,19 +1598,24 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         // the partial results, one per workgroup and sequence it works on, fit where the value kernel's go; runs through all sequences, and units
         // of different ranks, note which they are per head in the region of B_k's layout, which this path leaves alone
         const bool noted = flat || plan.n_cls > 1;
-        // A change of segment costs about 3 us of a workgroup, which the values of short segments of few columns do not repay.  us a step, two launches
-        // -> one, average tiles a segment x columns: 40 x 600 tokens rank 64 (10 x 64) 52.9 -> 57.3, rank 96 (10 x 96) 60.0 -> 61.5, rank 128 (10 x
-        // 128) 66.5 -> 66.5, 40 x 1200 rank 64 (21 x 64) 76.9 -> 80.1, rank 96 (21 x 96) 88.0 -> 85.8, 20 x 3000 rank 64 (36 x 64) 86.6 -> 85.6; 256
-        // columns: 100 x 200 (5) 101.2 -> 95.3, 40 x 300 (5) 75.3 -> 72.2.
+        // Runs through all sequences: a change of segment costs a workgroup 3 us and more, about 5 for each further 256 columns, and the one with the
+        // most changes is waited for, which lengths that differ make worse; what pays for it are value bytes read while others multiply.  Of less than
+        // 128 columns in the last block part of every request is idle as well.  Tiles a segment has on average (of the longest length), from which on it is faster,
+        // us a step, two launches -> one, 8 units.  One length: 128 columns, rank 128 9 x 2500 (17) 73.5 -> 74.5, 20 x 2000 (24) 85.7 -> 80.0;
+        // 192 64 / 48 x 250 (4) 52.4 -> 48.4; 384 120 x 300 (7) 130 -> 145, 9 x 1200 (8) 50.9 -> 54.1, 48 x 600 (11) 107 -> 94.  Lengths between half
+        // and all of: 192 48 x 1000 (19) 79.2 -> 84.6, 24 x 1500 (20) 1.03 times as fast, 17 x 3000 (32) 1.22; 256 48 x 500 (9) 61.7 -> 64.1, 16 x 1000
+        // (10) 1.04, 48 x 1000 (19) 0.99, 48 x 2043 (38) 1.14; 384 24 x 700 (9) 57.8 -> 61.8, 16 x 1000 (10) 53.6 -> 55.9, 12 x 1500 (12)
+        // 59.8 -> 60.6, 100 x 600 (14) 1.20; 96 100 x 1200 (28) 150 -> 153, 32 x 1500 (23) 69.2 -> 71.5; 64 20 x 4000 (48) 106 -> 111; 320 17 x 5585 (20, 2 units) 61 -> 65.
         const long long seg_tiles = flat ? (long long)batch * tiles / (n_wg + batch) : run;
-        const bool pays_segment = !flat || cols >= 192 || seg_tiles * cols >= 1900;
+        const int least_tiles = cols > 256 ? (seq_lens ? 13 : 10) : (seq_lens ? (cols < 256 ? 20 : 10) : (cols < 192 ? 15 : 0));
+        const bool chosen = g_opt_score_chunks > 0;              // ... by the caller
+        const bool pays_segment = !flat || chosen || ((cols % 256 == 0 || cols % 256 >= 128) && seg_tiles >= least_tiles);
         // Rows go 16 at a time, each time over all values of the run; the value kernel has the blocks of 32 rows side by side.  Two blocks pay
         // where the second is not full (a launch of its own there) or the run is short: 8 queries over 2 x 8000 tokens, rank 128 (16 tiles) 59.3
         // -> 61.9, 1 x 4000, rank 256 (4 tiles) 44.0 -> 37.7; 5 over 1 x 16000 91.8 -> 75.7.
-        const bool pays_rows = rows <= 16 || rows % 16 != 0 || run <= 8;
-        const int longest = flat ? std::min({run, tiles, kMaxAttendTiles}) : run;      // tiles whose values follow in one go
-        attend = attend && pays_segment && pays_rows && longest <= share_tiles &&
-                 (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap) &&
+        const bool pays_rows = chosen || rows <= 16 || rows % 16 != 0 || run <= 8;
+        attend = attend && pays_segment && pays_rows && (flat ? std::min({whole_run, tiles, kMaxAttendTiles}) : whole_run) <= share_tiles &&
+                 (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
                  (!noted || (size_t)batch * m.n_heads * 8 <= (size_t)w.mfold_bstride * 2) && n_wg <= kMaxSplits;
         if (attend) {
           const int rc = plan.cls_id[0] / 3, lg = plan.cls_id[0] % 3, hs = attend_hs(m.qpk, rows);

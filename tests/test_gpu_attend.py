@@ -1,6 +1,7 @@
 """Scores and values of a run of tiles in one workgroup (csrc/attend16.hip) against the float64 oracle: runs shorter and longer than
 the ring of tiles, shares of a run that are empty for some wavefronts, value ranks of part of a 128-column block, of one, two and
-several, units over several groups, every number of query rows, row limits inside a run and before it."""
+several, units over several groups, every number of query rows, row limits inside a run and before it; and which calls take it (two
+kernels instead of three)."""
 
 import numpy as np
 import pytest
@@ -25,7 +26,7 @@ CASES = [
     (4, 2, 256, 160, 8, "bf16", [97], 1), (3, 3, 96, 96, 3, "f16", [333], 3), (4, 4, 160, 256, 5, "f16", [64, 0], 0),
     # at most four query rows to a unit
     (2, 1, 128, 96, 4, "f16", [300, 33], 1), (3, 1, 64, 64, 3, "bf16", [2047], 1), (2, 2, 256, 160, 2, "f16", [97, 0, 513], 2), (2, 1, 96, 128, 2, "f16", [161], 1),
-    (4, 2, 224, 256, 2, "bf16", [700], 3), (3, 1, 128, 128, 1, "f16", [640, 31], 1),
+    (4, 2, 224, 256, 2, "bf16", [700], 3), (2, 1, 128, 128, 1, "f16", [640, 31], 1),
 ]
 
 
@@ -45,36 +46,62 @@ def test_run_of_tiles(heads, group, rk, rv, qpk, dtype, lens, chunks, flat):
     case = synth.make_case_orthonormal(_layer(heads, group, rk, rv, qpk), len(lens), max(lens), seed=heads + rk + rv + qpk, dtype=dtype)
     case.seq_lens = np.array(lens, np.int32) if len(lens) > 1 else None
     case.q_pos = np.maximum(np.array(lens, np.int32) - 1, 0)
+    n = []
     P.palu_set_option("score_chunks", chunks if flat or case.seq_lens is None else 0)     # (with lengths the option means runs through all sequences)
     try:
-        got = run_hip(case)
+        got = run_hip(case, n_launches=n)
     finally:
         P.palu_set_option("score_chunks", 0)
     ref = run_oracle(case)
-    err = rel_err(got, ref)[0]
+    some = np.array(lens) > 0
+    err = max(rel_err(got[some], ref[some]))               # of every sequence and head by itself
     say(f"[attend] {heads}/{group} heads rank {rk}/{rv} x{qpk} {dtype} {lens[:8]} chunks {chunks}: {err:.2e}")
-    assert err <= TOL_FP
-    for b, n in enumerate(lens):
-        if n == 0:
-            assert not got[b].any()
+    assert err <= TOL_FP and not got[~some].any()
+    assert n == [2]
 
 
-@pytest.mark.parametrize("kr,vr,dtype,lens", [([64, 256, 96], [384, 32, 160], "f16", [1]), ([256, 128, 224, 160], [96, 256, 128, 416], "bf16", [333, 0]),
-                                              ([192, 64, 256], [256, 160, 64], "f16", [129, 700, 0, 31, 65]), ([128, 96], [160, 512], "f16", [6000, 64, 5000])])
-def test_units_of_several_ranks(kr, vr, dtype, lens):
-    """One launch over groups of different key and value ranks: one sequence, two (runs inside one) and several (runs through all)."""
+RANKS = ([256, 64, 128, 224, 96, 160, 192, 256], [256, 160, 64, 128, 384, 32, 256, 192])
+
+
+@pytest.mark.parametrize("kr,vr,dtype,lens,n_launches", [
+    ([64, 256, 96], [384, 32, 160], "f16", [1], 2), ([256, 128, 224, 160], [96, 256, 128, 416], "bf16", [333, 0], 2),
+    # more tiles than the compute units have workgroups: runs of several tiles, of other lengths from unit to unit
+    (*RANKS, "f16", [9000], 2), (*RANKS, "bf16", [5000, 1700], 2), ([64, 256, 128, 192], [256, 256, 64, 128], "f16", [15000], 2),
+    ([96, 64], [256, 128], "bf16", [16383, 7001], 2),
+    # through all sequences, or where a cheap unit's run would be longer than a split of its values: two launches
+    ([192, 64, 256], [256, 160, 64], "f16", [129, 700, 0, 31, 65], 3), ([128, 96], [160, 512], "f16", [6000, 64, 5000], 3)])
+def test_units_of_several_ranks(kr, vr, dtype, lens, n_launches):
+    """Groups of different key and value ranks: for one and two sequences one launch, each unit with a number of workgroups of its own (sizes
+    for 256 compute units)."""
     from gpu_util import TOL_FP, rel_err, run_hip, run_oracle, say
     layer = synth.ragged_layer(4 * len(kr), 4, kr, vr)
     case = synth.make_case_orthonormal(layer, len(lens), max(lens), seed=sum(kr) + len(lens), dtype=dtype)
     case.seq_lens = np.array(lens, np.int32) if len(lens) > 1 else None
     case.q_pos = np.maximum(np.array(lens, np.int32) - 1, 0)
-    got, ref = run_hip(case), run_oracle(case)
-    err = rel_err(got, ref)[0]
+    n = []
+    got, ref = run_hip(case, n_launches=n), run_oracle(case)
+    some = np.array(lens) > 0
+    err = max(rel_err(got[some], ref[some]))
     say(f"[attend] ranks {kr} / {vr} {dtype} {lens}: {err:.2e}")
-    assert err <= TOL_FP
-    for b, n in enumerate(lens):
-        if n == 0:
-            assert not got[b].any()
+    assert err <= TOL_FP and not got[~some].any()
+    assert n == [n_launches]
+
+
+@pytest.mark.parametrize("heads,group,rk,rv,lens,n_launches", [
+    (8, 4, 64, 64, [4000] * 80, 3), (8, 4, 64, 256, [1000] * 130, 2), (32, 4, 64, 192, [500 - 5 * i for i in range(48)], 3), (32, 4, 64, 256, [2043 - 20 * i for i in range(48)], 2),
+    (32, 4, 64, 384, [300 - i for i in range(100)], 3), (32, 4, 64, 384, [600 - i for i in range(100)], 2), (8, 4, 128, 320, [2500 - 9 * i for i in range(34)], 3),
+    (8, 1, 128, 32, [30000], 3), (8, 1, 96, 64, [16384], 2)])
+def test_which_calls_take_one_launch(heads, group, rk, rv, lens, n_launches):
+    """The rules' both sides, with the other way's result: runs through all sequences by their segments and value columns, one sequence
+    whose runs would be longer than the value kernel's splits (sizes for 256 compute units)."""
+    from gpu_util import TOL_FP, rel_err, run_hip
+    case = synth.make_case_orthonormal(_layer(heads, group, rk, rv), len(lens), max(lens), seed=len(lens) + rv)
+    case.seq_lens = np.array(lens, np.int32) if len(set(lens)) > 1 else None
+    case.q_pos = np.array(lens, np.int32) - 1
+    n = []
+    got, apart = run_hip(case, n_launches=n), run_hip(case, staged=True).astype(np.float64)
+    assert n == [n_launches]
+    assert max(rel_err(got, apart)) <= TOL_FP
 
 
 @pytest.mark.parametrize("n_q,qpk,rk,rv", [(1, 1, 256, 256), (2, 1, 128, 384), (4, 1, 256, 256), (3, 2, 64, 128), (8, 1, 160, 256)])
@@ -103,10 +130,40 @@ def test_row_limits_inside_a_run(n_q, qpk, rk, rv):
     got = got.cpu().numpy()
     ref = O.attn_decode_multi(q, q_pos, q_len, case.Hk, case.Hv, case.Bk, case.Bv, layer.group_head_off, layer.k_rank_off, layer.v_rank_off,
                               128, layer.rope_theta, q_per_kv=qpk)
-    err = rel_err(got.reshape(batch * n_q, -1, 128), np.asarray(ref).reshape(batch * n_q, -1, 128))[0] if np.abs(ref).max() > 0 else 0.0
+    some = q_len > 0
+    err = max(rel_err(got[some], np.asarray(ref)[some]))
     say(f"[attend] {n_q} queries x{qpk} rank {rk}/{rv}: {err:.2e}")
     assert err <= TOL_FP
-    assert not got[q_len == 0].any()
+    assert not got[~some].any()
+
+
+@pytest.mark.parametrize("rk,rv,lens,q_len,chunks", [(256, 256, [511, 0, 96, 33, 700], [37, 0, 96, 500, 512], 2), (64, 384, [300, 290, 64, 1, 150], [0, 289, 32, 1, 151], 1),
+                                                     (128, 192, [4200, 300, 1000], [2100, 300, 999], 1)])
+def test_row_limits_in_runs_through_all_sequences(rk, rv, lens, q_len, chunks):
+    """Row limits beside sequence lengths: none attended, in a run's first segment and before its others, past the sequence's end."""
+    import torch
+    import paper_2407_21118_amd as P
+    from gpu_util import TOL_FP, launches, make_desc, rel_err, to_dev
+    layer, batch, seq = _layer(4, 4, rk, rv), len(lens), max(lens)
+    case = synth.make_case_orthonormal(layer, batch, seq, seed=rk + rv)
+    limits = np.minimum(lens, q_len).astype(np.int32)
+    dv = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()
+    out = torch.empty((batch, 1, 4, 128), dtype=torch.float32, device="cuda")
+    args = (make_desc(layer, "f16"), batch, 1, seq, seq, to_dev(case.q[:, None], "f16"), dv(np.maximum(limits - 1, 0)[:, None]), to_dev(case.Hk, "f16"),
+            to_dev(case.Hv, "f16"), to_dev(case.Bk, "f16"), to_dev(case.Bv, "f16"), P.palu_rope_table_init(layer.rope_theta, 128, seq), seq)
+    kw = dict(q_len=dv(np.array(q_len)[:, None]), seq_lens=dv(lens), out=out)
+    P.palu_set_option("score_chunks", chunks)
+    try:
+        P.palu_attn_decode_multi(*args, **kw)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()[:, 0]
+        assert launches(lambda: P.palu_attn_decode_multi(*args, **kw)) == 2
+    finally:
+        P.palu_set_option("score_chunks", 0)
+    ref = O.attn_decode(case.q, np.maximum(limits - 1, 0), case.Hk, case.Hv, case.Bk, case.Bv, layer.group_head_off, layer.k_rank_off, layer.v_rank_off, 128,
+                        layer.rope_theta, None, limits)
+    some = limits > 0
+    assert max(rel_err(got[some], ref[some])) <= TOL_FP and not got[~some].any()
 
 
 def test_more_runs_than_value_splits():
