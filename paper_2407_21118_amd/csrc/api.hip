@@ -1610,10 +1610,14 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         const int least_tiles = cols > 256 ? (seq_lens ? 13 : 10) : (seq_lens ? (cols < 256 ? 20 : 10) : (cols < 192 ? 15 : 0));
         const bool chosen = g_opt_score_chunks > 0;              // ... by the caller
         const bool pays_segment = !flat || chosen || ((cols % 256 == 0 || cols % 256 >= 128) && seg_tiles >= least_tiles);
-        // Rows go 16 at a time, each time over all values of the run; the value kernel has the blocks of 32 rows side by side.  Two blocks pay
-        // where the second is not full (a launch of its own there) or the run is short: 8 queries over 2 x 8000 tokens, rank 128 (16 tiles) 59.3
-        // -> 61.9, 1 x 4000, rank 256 (4 tiles) 44.0 -> 37.7; 5 over 1 x 16000 91.8 -> 75.7.
-        const bool pays_rows = chosen || rows <= 16 || rows % 16 != 0 || run <= 8;
+        // Rows go 16 at a time and columns 256 at a time, every block over all values of the run behind a merge of the last; the value kernel has
+        // such blocks side by side.  More than 16 rows pay where the second block has at most 4 (a launch of its own there), or for 256 columns
+        // and runs of at most 8 tiles.  Speed of one launch over two, 8 units of rank 128, 1 x 1000 n tokens, n = tiles a run: 5 queries
+        // (20 rows), 256 columns, n = 1 .. 32 1.24 .. 1.15, 512 n = 1 / 2 / 4 / 32 0.95 / 1.00 / 1.11 / 1.15; 6 (24), 256 n = 2 / 4 / 8 / 16 / 32 1.04 / 1.14 / 1.04 /
+        // 0.96 / 0.94, 384 n = 1 .. 32 0.79 .. 0.93; 8 (32), 256 n = 4 / 8 1.14 / 1.05, 384 n = 1 / 2 / 4 / 8 0.80 / 0.84 / 0.91 / 0.88.
+        // Eight rows of few columns pay for shorter runs than others: one head, rank 64 / 64, n = 24 / 32 / 48 1.01 / 0.99 / 0.97.
+        const bool pays_rows = chosen || (rows <= 16 ? m.qpk <= 4 || cols >= 128 || run <= 24
+                                          : (rows - 1) % 16 < 4 ? cols <= 256 || run > 2 : cols <= 256 && run <= 8);
         attend = attend && pays_segment && pays_rows && (flat ? std::min({whole_run, tiles, kMaxAttendTiles}) : whole_run) <= share_tiles &&
                  (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
                  (!noted || (size_t)batch * m.n_heads * 8 <= (size_t)w.mfold_bstride * 2) && n_wg <= kMaxSplits;

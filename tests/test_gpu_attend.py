@@ -64,11 +64,12 @@ RANKS = ([256, 64, 128, 224, 96, 160, 192, 256], [256, 160, 64, 128, 384, 32, 25
 
 
 @pytest.mark.parametrize("kr,vr,dtype,lens,n_launches", [
-    ([64, 256, 96], [384, 32, 160], "f16", [1], 2), ([256, 128, 224, 160], [96, 256, 128, 416], "bf16", [333, 0], 2),
+    ([64, 256, 96], [256, 32, 160], "f16", [1], 2), ([256, 128, 224, 160], [96, 256, 128, 192], "bf16", [333, 0], 2),
     # more tiles than the compute units have workgroups: runs of several tiles, of other lengths from unit to unit
     (*RANKS, "f16", [9000], 2), (*RANKS, "bf16", [5000, 1700], 2), ([64, 256, 128, 192], [256, 256, 64, 128], "f16", [15000], 2),
     ([96, 64], [256, 128], "bf16", [16383, 7001], 2),
-    # through all sequences, or where a cheap unit's run would be longer than a split of its values: two launches
+    # through all sequences, two launches; and more than 256 columns behind a run of one or two tiles
+    ([64, 256, 96], [384, 32, 160], "f16", [1], 2), ([256, 128, 224, 160], [96, 256, 128, 416], "bf16", [333, 0], 2),
     ([192, 64, 256], [256, 160, 64], "f16", [129, 700, 0, 31, 65], 3), ([128, 96], [160, 512], "f16", [6000, 64, 5000], 3)])
 def test_units_of_several_ranks(kr, vr, dtype, lens, n_launches):
     """Groups of different key and value ranks: for one and two sequences one launch, each unit with a number of workgroups of its own (sizes
@@ -87,15 +88,17 @@ def test_units_of_several_ranks(kr, vr, dtype, lens, n_launches):
     assert n == [n_launches]
 
 
-@pytest.mark.parametrize("heads,group,rk,rv,lens,n_launches", [
-    (8, 4, 64, 64, [4000] * 80, 3), (8, 4, 64, 256, [1000] * 130, 2), (32, 4, 64, 192, [500 - 5 * i for i in range(48)], 3), (32, 4, 64, 256, [2043 - 20 * i for i in range(48)], 2),
-    (32, 4, 64, 384, [300 - i for i in range(100)], 3), (32, 4, 64, 384, [600 - i for i in range(100)], 2), (8, 4, 128, 320, [2500 - 9 * i for i in range(34)], 3),
-    (8, 1, 128, 32, [30000], 3), (8, 1, 96, 64, [16384], 2)])
-def test_which_calls_take_one_launch(heads, group, rk, rv, lens, n_launches):
+@pytest.mark.parametrize("heads,group,rk,rv,qpk,lens,n_launches", [
+    (8, 4, 64, 64, 1, [4000] * 80, 3), (8, 4, 64, 256, 1, [1000] * 130, 2), (32, 4, 64, 192, 1, [500 - 5 * i for i in range(48)], 3),
+    (32, 4, 64, 256, 1, [2043 - 20 * i for i in range(48)], 2), (32, 4, 64, 384, 1, [300 - i for i in range(100)], 3), (32, 4, 64, 384, 1, [600 - i for i in range(100)], 2),
+    (8, 4, 128, 320, 1, [2500 - 9 * i for i in range(34)], 3), (8, 1, 128, 32, 1, [30000], 3), (8, 1, 96, 64, 1, [16384], 2),
+    (8, 4, 64, 256, 6, [4000], 2), (8, 4, 64, 384, 6, [4000], 3), (4, 4, 64, 256, 6, [90000], 3), (4, 4, 64, 256, 5, [90000], 2), (4, 4, 64, 384, 5, [8000], 4),
+    (8, 4, 64, 384, 8, [4000], 3), (8, 4, 128, 384, 4, [4000], 2), (4, 1, 64, 64, 8, [90000], 3), (4, 1, 64, 64, 8, [20000], 2)])
+def test_which_calls_take_one_launch(heads, group, rk, rv, qpk, lens, n_launches):
     """The rules' both sides, with the other way's result: runs through all sequences by their segments and value columns, one sequence
-    whose runs would be longer than the value kernel's splits (sizes for 256 compute units)."""
+    whose runs would be longer than the value kernel's splits, blocks of rows and columns (sizes for 256 compute units)."""
     from gpu_util import TOL_FP, rel_err, run_hip
-    case = synth.make_case_orthonormal(_layer(heads, group, rk, rv), len(lens), max(lens), seed=len(lens) + rv)
+    case = synth.make_case_orthonormal(_layer(heads, group, rk, rv, qpk), len(lens), max(lens), seed=len(lens) + rv)
     case.seq_lens = np.array(lens, np.int32) if len(set(lens)) > 1 else None
     case.q_pos = np.array(lens, np.int32) - 1
     n = []
