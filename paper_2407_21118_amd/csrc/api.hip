@@ -1551,7 +1551,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       // (With option score_chunks the caller has chosen the runs.)
       const int share_tiles = g_opt_score_chunks > 0 ? kMaxAttendTiles : std::min(4 * split_tokens / kTile, kMaxAttendTiles);
       static thread_local AttendArgs t;
-      int cols = PALU_MAX_RANK, rows = 0;                        // fewest value columns and most query rows of a unit
+      int cols = PALU_MAX_RANK, most_cols = 0, rows = 0;         // fewest and most value columns, most query rows of a unit
       for (int i = 0; i < plan.total_units && attend; ++i) {
         const ScoreUnit& x = t.units.u[i] = unit16(mk, plan.units[i]);
         const int j = mk.group_of_head[x.h0], rv = m.v_off[j + 1] - m.v_off[j], groups = 1 << plan.cls_id[plan.unit_cls[i]] % 3;
@@ -1559,6 +1559,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         for (int g = 1; g < groups && attend; ++g) attend = m.v_off[j + g + 1] - m.v_off[j + g] == rv;
         t.val[i] = AttendValue{m.v_off[j], rv, m.bv_off[j] / PALU_D_HEAD};
         cols = std::min(cols, groups * rv);
+        most_cols = std::max(most_cols, groups * rv);
         rows = std::max(rows, x.nh * m.qpk);
       }
       if (attend) {
@@ -1618,7 +1619,11 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         // Eight rows of few columns pay for shorter runs than others: one head, rank 64 / 64, n = 24 / 32 / 48 1.01 / 0.99 / 0.97.
         const bool pays_rows = chosen || (rows <= 16 ? m.qpk <= 4 || cols >= 128 || run <= 24
                                           : (rows - 1) % 16 < 4 ? cols <= 256 || run > 2 : cols <= 256 && run <= 8);
-        attend = attend && pays_segment && pays_rows && (flat ? std::min({whole_run, tiles, kMaxAttendTiles}) : whole_run) <= share_tiles &&
+        // Units of several ranks: not with a second block of columns behind the one or two tiles of a run (32 heads of searched ranks, 1 x 689 tokens
+        // 31.3 us a step as two launches, 32.3 as one, 1 x 1292 33.2 / 34.2, 2 x 654 34.1 / 35.1; 1 x 3021 38.3 / 37.6, and without it 1 x 1430
+        // of 8 heads 27.0 / 22.8).
+        const bool pays_classes = plan.n_cls == 1 || most_cols <= 256 || run > 2;
+        attend = attend && pays_segment && pays_rows && pays_classes && (flat ? std::min({whole_run, tiles, kMaxAttendTiles}) : whole_run) <= share_tiles &&
                  (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
                  (!noted || (size_t)batch * m.n_heads * 8 <= (size_t)w.mfold_bstride * 2) && n_wg <= kMaxSplits;
         if (attend) {

@@ -68,8 +68,8 @@ RANKS = ([256, 64, 128, 224, 96, 160, 192, 256], [256, 160, 64, 128, 384, 32, 25
     # more tiles than the compute units have workgroups: runs of several tiles, of other lengths from unit to unit
     (*RANKS, "f16", [9000], 2), (*RANKS, "bf16", [5000, 1700], 2), ([64, 256, 128, 192], [256, 256, 64, 128], "f16", [15000], 2),
     ([96, 64], [256, 128], "bf16", [16383, 7001], 2),
-    # through all sequences, two launches; and more than 256 columns behind a run of one or two tiles
-    ([64, 256, 96], [384, 32, 160], "f16", [1], 2), ([256, 128, 224, 160], [96, 256, 128, 416], "bf16", [333, 0], 2),
+    # through all sequences, or more than 256 columns behind a run of one or two tiles: two launches
+    ([64, 256, 96], [384, 32, 160], "f16", [1], 3), ([256, 128, 224, 160], [96, 256, 128, 416], "bf16", [333, 0], 3),
     ([192, 64, 256], [256, 160, 64], "f16", [129, 700, 0, 31, 65], 3), ([128, 96], [160, 512], "f16", [6000, 64, 5000], 3)])
 def test_units_of_several_ranks(kr, vr, dtype, lens, n_launches):
     """Groups of different key and value ranks: for one and two sequences one launch, each unit with a number of workgroups of its own (sizes
