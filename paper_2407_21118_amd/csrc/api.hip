@@ -1220,6 +1220,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       t.lds_unit_stride = (int)align_up(stream_unit_lds(k_i4, max_nh), 16);
       const size_t lds = (size_t)t.lds_unit_stride * t.units_per_wg;
       const StreamFn fn = stream_fn(act, k_bits, pp.unit_cls[0]);
+      if (!fn) return PALU_ERR_UNSUPPORTED;
       if ((st = allow_dynamic_lds(fn, lds + kStaticLdsMax)) != PALU_OK) return st;
       hipLaunchKernelGGL(fn, stream_grid, dim3(256), lds, s, t);
       if ((st = launch_ok()) != PALU_OK) return st;
@@ -1540,7 +1541,7 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
       }
       // Scores and values in one launch (attend16_kernel).  A unit's heads have to be whole groups (their value latents are then read by
       // one workgroup of a run only) of one value rank, all in one launch with one pass of query rows, every head in one unit.
-      // It is the faster form (attend16.hip) with two exceptions, see pays_* below; with stage events the stages have to be launches.
+      // It is the faster form (attend16.hip) but for some sizes, see pays_* below; with stage events the stages have to be launches.
       bool attend = use16 && !use8 && (shared16 || m.qpk == 1) && m.qpk <= kShared16Rows && !v_i4 && !stage_events && g_opt_value_split == 0 &&
                     plan.total_units <= kMaxAttendUnits && plan.max_slices == 1 && w.lpad <= (1 << 24) &&
                     (plan.n_cls == 1 ? rank_class_16(plan.cls_id[0] / 3) : mixed && use_one_round && !mix_flat);

@@ -592,14 +592,13 @@ __global__ __launch_bounds__(256, (QB != 0 && HS <= 2) ? 2 : 1) void stream_kern
 
 namespace {
 
+// units of more than 4 heads: unquantized only (nullptr otherwise)
 template <typename T, int QB>
 StreamFn stream_fn_t(int cls) {
-  switch (cls) {
-    case 0: return stream_kernel<T, 2, 1, QB>;
-    case 1: return stream_kernel<T, 2, 2, QB>;
-    case 2: return stream_kernel<T, 8, 1, QB>;
-    default: return stream_kernel<T, 8, 2, QB>;
-  }
+  if (cls == 0) return stream_kernel<T, 2, 1, QB>;
+  if (cls == 1) return stream_kernel<T, 2, 2, QB>;
+  if constexpr (QB == 0) return cls == 2 ? stream_kernel<T, 8, 1, QB> : stream_kernel<T, 8, 2, QB>;
+  return nullptr;
 }
 
 template <typename T, int QB, bool TWO>
