@@ -11,19 +11,24 @@ distinct latent caches larger than the 256 MB last-level cache so that every
 step streams its latents from HBM.
 
 Prints ONE JSON line: the step time (metric/value/unit/ms_per_step), the
-workload (config), the roofline of the dominant kernel (roofline: algorithmic
-FLOPs or bytes per launch over its measured duration, against the MI355X peak),
-the same for the value kernel (roofline_value), per-stage times (stage_us) and
-the CPU oracle timed beside it (cpu_baseline).
+workload (config), the roofline of the dominant launch of the timed step (roofline:
+algorithmic FLOPs or bytes per launch over its measured duration, against the
+MI355X peak), that of the value kernel where it is a launch of its own
+(roofline_value), medians of the stages launched apart (stage_us; with their
+rooflines under stages_apart where the step runs scores and values as one
+launch) and the CPU oracle timed beside it (cpu_baseline).
 """
 
 from __future__ import annotations
 
 import argparse
+import ctypes
 import json
 import os
 import sys
 import time
+
+import numpy as np
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
@@ -60,6 +65,24 @@ def algorithmic_work(layer, batch, seq, k_i4, v_i4, bits=4):
         "b_bytes": 2 * (layer.b_elems("k") + layer.b_elems("v")),
         "a_bytes": 2 * layer.n_q_heads * d_h * (layer.R_k + layer.R_v),
     }
+
+
+def stage_medians(stage_ms, names):
+    """Median microseconds of every stage over the profiled calls (rows): a single slow call, the first launch of a
+    kernel among them, does not move them."""
+    return {n: float(np.median(np.asarray(stage_ms)[:, k]) * 1e3) for k, n in enumerate(names)}
+
+
+def kernels_enqueued(call, P, torch) -> int:
+    """Kernels that call() enqueues, counted in a stream capture that is never run."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+        call()
+    n = ctypes.c_size_t()
+    status = P.load_library().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n))
+    if status != 0:
+        raise RuntimeError(f"hipGraphGetNodes: {status}")
+    return n.value
 
 
 def prompt_encode(args, P, torch) -> int:
@@ -106,7 +129,6 @@ def prompt_encode(args, P, torch) -> int:
 def multi_query_decode(args, P, torch) -> int:
     """palu_attn_decode_multi: N query tokens per sequence (a speculative-decoding check, a chunk of a prompt)
     over the cache of the chosen configuration; attention only, timed with events around `steps` calls."""
-    import numpy as np
     from workloads import device as wd, synth
     cfg = args.config
     layer = synth.config_layer(cfg.split("-")[0])
@@ -200,7 +222,6 @@ def main() -> int:
         print("bench.py measures one GPU: this build has no multi-GPU path (run with --gpus 1)", file=sys.stderr)
         return 2
 
-    import numpy as np
     import torch
 
     import paper_2407_21118_amd as P
@@ -279,13 +300,20 @@ def main() -> int:
     if transposed:                                             # the projection weights column by column: made once, like the decomposition
         Akt, Avt = case.Ak.t().contiguous(), case.Av.t().contiguous()
 
-    def step(i: int, events=None):
+    def decode(s: int, events=None):
+        hk, kq = (qk[s][0], dict(hk_scale=qk[s][1], hk_zero=qk[s][2])) if k_i4 else (case.Hk[s], {})
+        hv, vq = (qv[s][0], dict(hv_scale=qv[s][1], hv_zero=qv[s][2])) if v_i4 else (case.Hv[s], {})
+        P.palu_attn_decode(desc, batch, seq, seq, case.q, case.q_pos, hk, hv, case.Bk, case.Bv, table, seq,
+                           out=out, workspace=ws, stage_events=events, **kq, **vq)
+
+    def step(i: int, events=None, around=None):          # around: a pair of events around the decode call
         s = i % n_sets
-        if transposed and events is None:
+        apart = events is not None or around is not None
+        if transposed and not apart:
             P.palu_decode_step_t(desc, batch, seq, seq, case.x_new, Akt, Avt, dst_row, case.q, case.q_pos,
                                  case.Hk[s], case.Hv[s], case.Bk, case.Bv, table, seq, out=out, workspace=ws)
             return
-        if fused and events is None:
+        if fused and not apart:
             P.palu_decode_step(desc, batch, seq, seq, case.x_new, case.Ak, case.Av, dst_row, case.q, case.q_pos,
                                case.Hk[s], case.Hv[s], case.Bk, case.Bv, table, seq, out=out, workspace=ws,
                                encode_workspace=ws_e)
@@ -298,17 +326,15 @@ def main() -> int:
         else:
             P.palu_encode(desc, 0, case.x_new, case.Ak, k_dst, k_stride, k_rows, ws_e)
             P.palu_encode(desc, 1, case.x_new, case.Av, v_dst, v_stride, v_rows, ws_e)
-        hk, kq, hv, vq = case.Hk[s], {}, case.Hv[s], {}
         if k_i4:
-            codes, sc, zp = qk[s]
-            P.palu_quant_latent(desc, 0, new_k, layer.R_k, batch, codes, sc, zp, dst_row)
-            hk, kq = codes, dict(hk_scale=sc, hk_zero=zp)
+            P.palu_quant_latent(desc, 0, new_k, layer.R_k, batch, *qk[s], dst_row)
         if v_i4:
-            codes, sc, zp = qv[s]
-            P.palu_quant_latent(desc, 1, new_v, layer.R_v, batch, codes, sc, zp, dst_row)
-            hv, vq = codes, dict(hv_scale=sc, hv_zero=zp)
-        P.palu_attn_decode(desc, batch, seq, seq, case.q, case.q_pos, hk, hv, case.Bk, case.Bv, table, seq,
-                           out=out, workspace=ws, stage_events=events, **kq, **vq)
+            P.palu_quant_latent(desc, 1, new_v, layer.R_v, batch, *qv[s], dst_row)
+        if around:
+            around[0].record()
+        decode(s, events)
+        if around:
+            around[1].record()
 
     # ---- timed region ------------------------------------------------------
     for i in range(args.warmup):
@@ -350,19 +376,22 @@ def main() -> int:
     log(f"[bench] per step over {n_groups} groups of {kGroup}: median {step_us_median:.2f} us, min {step_us_min:.2f} us, "
         f"mean of the {args.steps} bracketed steps {ms_per_step * 1e3:.2f} us")
 
-    # ---- per-stage durations: same steps again with event hooks between the stages
-    n_prof = min(args.steps, 100)
+    # ---- per-stage durations: same steps again with event hooks between the stages, which makes every stage a launch of its own
+    # (kernels that the timed steps may not have run: a few calls first that are not counted)
+    n_prof, n_first = 100, 10
     evs = [[torch.cuda.Event(enable_timing=True) for _ in range(P.PALU_DECODE_STAGES + 1)] for _ in range(n_prof)]
     for row in evs:
         for e in row:
             e.record()              # creates the HIP event handles
     torch.cuda.synchronize()
+    for i in range(n_first):
+        step(args.warmup + i, evs[0])
+    torch.cuda.synchronize()
     for i in range(n_prof):
         step(args.warmup + i, evs[i])
     torch.cuda.synchronize()
-    stage_ms = np.array([[row[k].elapsed_time(row[k + 1]) for k in range(P.PALU_DECODE_STAGES)] for row in evs])
     names = ["fold", "score", "value", "combine"]
-    bracket_us = {n: float(np.mean(stage_ms[:, k]) * 1e3) for k, n in enumerate(names)}
+    bracket_us = stage_medians([[row[k].elapsed_time(row[k + 1]) for k in range(P.PALU_DECODE_STAGES)] for row in evs], names)
     # An event between two kernels costs marker time that the kernels do not have without it.  Measure it live, on launches of next to
     # no work: with an event after each of the first three of four, and with none in between.  (Not on the call itself: without
     # hooks it may run its scores and values as one launch.)
@@ -382,9 +411,24 @@ def main() -> int:
     gap_us = max(0.0, (marked_us - plain_us) / (P.PALU_DECODE_STAGES - 1))
     gap_us = min(gap_us, min(bracket_us.values()))         # no stage is shorter than nothing (a near-empty first stage)
     stage_us = {n: bracket_us[n] - gap_us for n in names}
-    stage_us_med = {n: float(np.median(stage_ms[:, k]) * 1e3) - gap_us for k, n in enumerate(names)}
     log(f"[bench] stage brackets us: {bracket_us}; marker gap {gap_us:.2f} us")
     log(f"[bench] stage us (bracket - gap): {stage_us}")
+
+    # ---- scores and values as one launch?  Then that launch: the decode call of a step between two events (as a stage above is), less the
+    # launches beside it
+    decode(0)
+    one_launch = kernels_enqueued(lambda: decode(0), P, torch) == (3 if args.no_rope else 2)
+    attend_us = None
+    if one_launch:
+        pairs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n_prof)]
+        for i in range(n_first):
+            step(args.warmup + i, around=pairs[0])
+        for i in range(n_prof):
+            step(args.warmup + i, around=pairs[i])
+        torch.cuda.synchronize()
+        call_us = float(np.median([a.elapsed_time(b) for a, b in pairs])) * 1e3 - gap_us
+        attend_us = call_us - stage_us["combine"] - (stage_us["fold"] if args.no_rope else 0.0)
+        log(f"[bench] scores and values in one launch: {attend_us:.2f} us of {call_us:.2f} us a decode call")
 
     score_tflops = work["score_flops"] / (stage_us["score"] * 1e-6) / 1e12
     k_gbs = work["k_latent_bytes"] / (stage_us["score"] * 1e-6) / 1e9
@@ -429,7 +473,6 @@ def main() -> int:
             "traffic": None, "launch_us": stage_us["value"], "bytes_per_launch": work["v_latent_bytes"],
         },
         "stage_us": stage_us,
-        "stage_us_median": stage_us_med,
         "stage_us_bracketed": bracket_us,
         "event_gap_us": gap_us,
         "step_GBps_algorithmic": total_gbs,
@@ -499,16 +542,34 @@ def main() -> int:
             "bytes_per_launch": work["k_latent_bytes"],
         }
 
+    if one_launch:          # the timed step does not run the two kernels above
+        result["stages_apart"] = {"note": "the same call with events between its stages, which launches scores and values apart",
+                                  "score": result["roofline"], "value": result.pop("roofline_value")}
+        latent_bytes = work["k_latent_bytes"] + work["v_latent_bytes"]
+        flops = work["score_flops"] + work["pv_flops"]
+        gbs, tflops = latent_bytes / (attend_us * 1e-6) / 1e9, flops / (attend_us * 1e-6) / 1e12
+        result["roofline"] = {"kernel": "stream_kernel (folded query x key latents, softmax, P.H_v in one pass)", "bound": "hbm", "achieved": gbs,
+                              "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS} if args.no_rope else {
+                              "kernel": "attend16_kernel (key reconstruction on MFMA + RoPE + q.K in float32, then softmax and P.H_v of the same run)",
+                              "bound": "mfma", "achieved": tflops, "peak": MFMA_F16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tflops / MFMA_F16_PEAK_TFLOPS}
+        result["roofline"].update(traffic=None, launch_us=attend_us, flops_per_launch=flops, bytes_per_launch=latent_bytes, latent_read_GBps=gbs,
+                                  launch_us_is="median of the decode call between two events, less the event gap and the other launches' stage_us")
+        if "measured_peaks" in result:
+            result["roofline"]["frac_of_measured"] = (gbs / result["measured_peaks"]["hbm_read_GBps_2GiB"] if args.no_rope
+                                                      else tflops / result["measured_peaks"]["mfma_f16_TFLOPs"])
+
     # measured HBM traffic per launch of the dominant kernel, from counter runs kept under profiles/
     try:
         with open(os.path.join(ROOT, "profiles", "hbm_traffic.json")) as f:
             tr = json.load(f).get(cfg + (":no-rope" if args.no_rope else ""))
         if tr and args.latent_bits == 4 and not args.opt:
-            result["roofline"]["traffic"] = tr["score_kernel_bytes"]
-            result["roofline_value"]["traffic"] = tr["value_kernel_bytes"]
             # not measured in this run: rocprofv3 counter runs of this same command, kept under profiles/
-            result["roofline"]["traffic_source"] = result["roofline_value"]["traffic_source"] = tr.get(
-                "source", "profiles/hbm_traffic.json")
+            apart = result.get("stages_apart")
+            parts = [(apart["score"], "score"), (apart["value"], "value"), (result["roofline"], "attention")] if apart else [
+                (result["roofline"], "score"), (result["roofline_value"], "value")]
+            for entry, kernel in parts:
+                entry["traffic"] = tr.get(f"{kernel}_kernel_bytes")
+                entry["traffic_source"] = tr.get("source", "profiles/hbm_traffic.json")
     except OSError:
         pass
 
