@@ -99,11 +99,15 @@ int palu_version(void);
  * choose.  Not thread-safe against concurrent decode calls.
  *   "score_waves"         4 or 8 wavefronts per score workgroup for ranks <= 256
  *   "score_chunks"        sequence chunks per (sequence, head block) in the score kernel (with seq_lens: that many
- *                         workgroups per sequence and head block, with equal shares of all sequences' tiles)
+ *                         workgroups per sequence and head block, with equal shares of all sequences' tiles).
+ *                         Where these take the values as well (runs of up to 64 tiles of 32 tokens), a quarter of a run
+ *                         is also what the 16-bit probabilities are rounded against: the library's own choice keeps that
+ *                         within the value kernel's splits, this option does not
  *   "score_mixed"         default 1: a layer whose groups have different ranks (all 64 .. 256 after slicing, fp16 or
  *                         bf16 latents, one query per head) gets ONE score launch over all rank classes; 0: one
  *                         launch per rank class
- *   "value_split_tokens"  tokens per sequence split in the value kernel (multiple of 32, <= 4096)
+ *   "value_split_tokens"  tokens per sequence split in the value kernel (multiple of 32, <= 4096); scores and values
+ *                         are then two launches
  *   "score_fp8"           1: low-precision key reconstruction (Sec. 4.5.2, last paragraph), for fp16 layers with RoPE,
  *                         unquantized key latents and ranks 64 .. 256: B_k is rounded to 8-bit floats (OCP E4M3)
  *                         with one power-of-two scale per feature column, the key latents are rounded to E4M3
