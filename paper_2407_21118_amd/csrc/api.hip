@@ -1607,9 +1607,12 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         // 192 64 / 48 x 250 (4) 52.4 -> 48.4; 384 120 x 300 (7) 130 -> 145, 9 x 1200 (8) 50.9 -> 54.1, 48 x 600 (11) 107 -> 94.  Lengths between half
         // and all of: 192 48 x 1000 (19) 79.2 -> 84.6, 24 x 1500 (20) 1.03 times as fast, 17 x 3000 (32) 1.22; 256 48 x 500 (9) 61.7 -> 64.1, 16 x 1000
         // (10) 1.04, 48 x 1000 (19) 0.99, 48 x 2043 (38) 1.14; 384 24 x 700 (9) 57.8 -> 61.8, 16 x 1000 (10) 53.6 -> 55.9, 12 x 1500 (12)
-        // 59.8 -> 60.6, 100 x 600 (14) 1.20; 96 100 x 1200 (28) 150 -> 153, 32 x 1500 (23) 69.2 -> 71.5; 64 20 x 4000 (48) 106 -> 111; 320 17 x 5585 (20, 2 units) 61 -> 65.
+        // 59.8 -> 60.6, 100 x 600 (14) 1.20; 96 100 x 1200 (28) 150 -> 153, 32 x 1500 (23) 69.2 -> 71.5; 64 20 x 4000
+        // (48) 106 -> 111; 320 17 x 5585 (20, 2 units) 61 -> 65.
+        // Lengths between a 32nd and all of: 128 100 x 2048 (28, 2 units) 51.6 -> 58.3, 48 x 2048 (38) 88.6 -> 93.0, 16 x 4096 (42) 51.4 -> 53.5,
+        // 100 x 2048 (48) level, 48 x 8192 (153) 234 -> 209; 256 48 x 2048 132 -> 117, 8 x 4096 (25) 51.7 -> 49.1.
         const long long seg_tiles = flat ? (long long)batch * tiles / (n_wg + batch) : run;
-        const int least_tiles = cols > 256 ? (seq_lens ? 13 : 10) : (seq_lens ? (cols < 256 ? 20 : 10) : (cols < 192 ? 15 : 0));
+        const int least_tiles = cols > 256 ? (seq_lens ? 13 : 10) : (seq_lens ? (cols < 192 ? 50 : (cols < 256 ? 20 : 10)) : (cols < 192 ? 15 : 0));
         const bool chosen = g_opt_score_chunks > 0;              // ... by the caller
         const bool pays_segment = !flat || chosen || ((cols % 256 == 0 || cols % 256 >= 128) && seg_tiles >= least_tiles);
         // Rows go 16 at a time and columns 256 at a time, every block over all values of the run behind a merge of the last; the value kernel has
