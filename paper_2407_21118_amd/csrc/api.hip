@@ -1602,10 +1602,11 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         const bool noted = flat || plan.n_cls > 1;
         // Runs through all sequences: a change of segment costs a workgroup 3 us and more, about 5 for each further 256 columns, and the one with the
         // most changes is waited for, which lengths that differ make worse; what pays for it are value bytes read while others multiply.  Of less than
-        // 128 columns in the last block part of every request is idle as well.  Tiles a segment has on average (of the longest length), from which on it is faster,
-        // us a step, two launches -> one, 8 units.  One length: 128 columns, rank 128 9 x 2500 (17) 73.5 -> 74.5, 20 x 2000 (24) 85.7 -> 80.0;
-        // 256 7 x 700 (3, runs of 5 tiles) 0.96 times as fast, 12 x 782 (6, runs of 9) 0.99, 9 x 1200 (8, 11) 1.05; 192 64 / 48 x 250 (4, 12) 52.4 -> 48.4; 384 120 x 300 (7) 130 -> 145, 9 x 1200 (8) 50.9 -> 54.1, 48 x 600 (11) 107 -> 94.  Lengths between half
-        // and all of: 192 48 x 1000 (19) 79.2 -> 84.6, 24 x 1500 (20) 1.03 times as fast, 17 x 3000 (32) 1.22; 256 48 x 500 (9) 61.7 -> 64.1, 16 x 1000
+        // 128 columns in the last block part of every request is idle as well.  Tiles a segment has on average (of the longest length), from which
+        // on it is faster, us a step, two launches -> one, 8 units.  One length: 128 columns, rank 128 9 x 2500 (17) 73.5 -> 74.5, 20 x 2000 (24)
+        // 85.7 -> 80.0; 256 7 x 700 (3, runs of 5 tiles) 0.96 times as fast, 12 x 782 (6, runs of 9) 0.99, 9 x 1200 (8, 11) 1.05; 192 rank 64 48 x 250
+        // (4, 12) 52.4 -> 48.4; 384 120 x 300 (7) 130 -> 145, 9 x 1200 (8) 50.9 -> 54.1, 48 x 600 (11) 107 -> 94.  Lengths between half and all of:
+        // 192 48 x 1000 (19) 79.2 -> 84.6, 24 x 1500 (20) 1.03 times as fast, 17 x 3000 (32) 1.22; 256 48 x 500 (9) 61.7 -> 64.1, 16 x 1000
         // (10) 1.04, 48 x 1000 (19) 0.99, 48 x 2043 (38) 1.14; 384 24 x 700 (9) 57.8 -> 61.8, 16 x 1000 (10) 53.6 -> 55.9, 12 x 1500 (12)
         // 59.8 -> 60.6, 100 x 600 (14) 1.20; 96 100 x 1200 (28) 150 -> 153, 32 x 1500 (23) 69.2 -> 71.5; 64 20 x 4000
         // (48) 106 -> 111; 320 17 x 5585 (20, 2 units) 61 -> 65.
@@ -1623,10 +1624,11 @@ static int decode_impl(const palu_layer_desc* desc, int32_t batch, int32_t n_q, 
         // Eight rows of few columns pay for shorter runs than others: one head, rank 64 / 64, n = 24 / 32 / 48 1.01 / 0.99 / 0.97.
         const bool pays_rows = chosen || (rows <= 16 ? m.qpk <= 4 || cols >= 128 || run <= 24
                                           : (rows - 1) % 16 < 4 ? cols <= 256 || run > 2 : cols <= 256 && run <= 8);
-        // A second block of columns behind the one or two tiles of a run costs more than the launch.  Speed of one launch over two, one sequence, rank 128, runs
-        // of 1 / 2 / 3 / 4 tiles: 8 heads, 384 columns 0.89 / 0.98 / 1.06 / 1.12, 512 0.87 / 0.97 / 1.04 / 1.10 (256 1.06 / 1.12 / 1.14 / 1.19); 32 heads, 384
-        // 1.00 / 0.98 / 1.01 / 1.04; 8 heads, 7 x 700 tokens (2), 384 0.92; 32 heads of searched ranks, 1 x 689 tokens 31.3 us a step -> 32.3, 1 x 3021 38.3 -> 37.6.
-        // (Of units of several ranks, whose longest runs are not those of the most columns, one tile more: 2 x 1296 of 16 heads 26.1 -> 27.4, 2 x 2291 28.4 -> 29.9.)
+        // A second block of columns behind the one or two tiles of a run costs more than the launch.  Speed of one launch over two, one sequence, rank
+        // 128, runs of 1 / 2 / 3 / 4 tiles: 8 heads, 384 columns 0.89 / 0.98 / 1.06 / 1.12, 512 0.87 / 0.97 / 1.04 / 1.10 (256 1.06 / 1.12 / 1.14 /
+        // 1.19); 32 heads, 384 1.00 / 0.98 / 1.01 / 1.04; 8 heads, 7 x 700 tokens (2), 384 0.92; 32 heads of searched ranks, 1 x 689 tokens 31.3 us a
+        // step -> 32.3, 1 x 3021 38.3 -> 37.6.  (Of units of several ranks, whose longest runs are not those of the most columns, one tile more: 2 x
+        // 1296 of 16 heads 26.1 -> 27.4, 2 x 2291 28.4 -> 29.9.)
         const bool pays_columns = flat || chosen || most_cols <= 256 || run > (plan.n_cls > 1 ? 3 : 2);
         attend = attend && pays_segment && pays_rows && pays_columns && (flat ? std::min({whole_run, tiles, kMaxAttendTiles}) : whole_run) <= share_tiles &&
                  (flat ? n_wg + batch <= (long long)batch * n_split_cap && m.qpk == 1 : n_wg <= n_split_cap && run <= kMaxAttendTiles) &&
